@@ -32,6 +32,10 @@ constexpr uint32_t STATUS_NEEDS_CARRY = 1u << 17;
 // starts more than LOOK entries into a row: the look-behind of this matrix reads
 // the far part of the records too (see below).
 constexpr uint32_t STATUS_FAR_HEADS = 1u << 18;
+// Internal status bit: at least one in ORDER_MIN_SHARE complete tiles lies inside
+// a single row (the tile order by columns may pay, see tile_order).
+constexpr uint32_t STATUS_LONG_ROWS = 1u << 19;
+constexpr int ORDER_MIN_SHARE = 2;
 // A tile whose first segment continues a row of the previous tile completes
 // that row itself when it can get at the row's head.  The tiles of one
 // workgroup of the tile kernel are neighbours and hand the finished head over
@@ -241,6 +245,17 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t w, uint32_t nb, uint32_t 
     return (k / chunk) * (NUM_XCD * chunk) + xcd * chunk + (k % chunk);
 }
 
+// Place in the list of tile_order that workgroup w of nb takes (nb and the first
+// `ends` places, in workgroups, are multiples of NUM_XCD).  The list's first part
+// is dealt out evenly among its second: the one waits for lines from memory, the
+// other for the L2.  First part: plain; second part: XCD k takes the k-th eighth.
+__device__ __forceinline__ uint32_t order_place(uint32_t w, uint32_t nb, uint32_t ends) {
+    const uint32_t xcd = w % NUM_XCD, o = w / NUM_XCD, no = nb / NUM_XCD, ne = ends / NUM_XCD;
+    const uint32_t before = uint32_t(uint64_t(o) * ne / no), after = uint32_t(uint64_t(o + 1) * ne / no);
+    if (after > before) return before * NUM_XCD + xcd;
+    return ends + xcd * (no - ne) + (o - before);
+}
+
 // ----------------------------------------------------------------------------
 // Conversion step 2a: tile_ptr (Algorithm 4, first loop).  One thread per
 // tile boundary.  The same launch clears the flag words the next kernel ORs
@@ -264,8 +279,8 @@ k_tile_ptr(int m, const IT* __restrict__ row_ptr, int T, int p, int pc, int grou
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
-    if (gid == 0) *status = 0u;
-    int far = 0, far_heads = 0;
+    if (gid < 3) status[gid] = 0u;        // and the plan of the tile order
+    int far = 0, far_heads = 0, inside = 0;
     for (size_t t = gid; t <= size_t(p); t += stride) {
         int64_t bnd = int64_t(t) * T;
         const int row = count_le(row_ptr, m + 1, bnd) - 1;
@@ -276,6 +291,7 @@ k_tile_ptr(int m, const IT* __restrict__ row_ptr, int T, int p, int pc, int grou
         int64_t head = 0;
         if (t < size_t(p) && row >= 0 && row < m) head = bnd - int64_t(row_ptr[row]);
         tile_head[t] = uint32_t(head < 0 ? 0 : (head > int64_t(0xffffffffu) ? int64_t(0xffffffffu) : head));
+        inside += int(t < size_t(pc) && row >= 0 && row < m && int64_t(row_ptr[row + 1]) >= bnd + T);
         // for the one-launch SpMV: the groups of tiles that row touches (first, how many)
         if (slots > 0) {
             uint2 sp = {0u, 1u};
@@ -304,23 +320,32 @@ k_tile_ptr(int m, const IT* __restrict__ row_ptr, int T, int p, int pc, int grou
     // but into one word per workgroup, which the scan kernel collects.
     far = __syncthreads_or(far);
     far_heads = __syncthreads_or(far_heads);
-    if (threadIdx.x == 0) wg_far[blockIdx.x] = uint32_t(far != 0) | (uint32_t(far_heads != 0) << 1);   // bit 0, bit 1
+    // tiles that lie inside one row: how many (two or more of a thread count as one)
+    inside = __syncthreads_count(inside);
+    if (threadIdx.x == 0) wg_far[blockIdx.x] = uint32_t(far != 0) | (uint32_t(far_heads != 0) << 1) | (uint32_t(inside) << 2);   // bit 0, bit 1, count
 }
 
 // What the workgroups of k_tile_ptr (nwg of them) found about the tiles' heads
 // (bit 0: some tile starts too far into a row for the tile kernel alone; bit 1:
 // some workgroup's first tile starts more than LOOK entries into a row) goes to
 // the status word, once.  Every thread of the workgroup must call this.
-__device__ __forceinline__ uint32_t any_tile_far(const uint32_t* __restrict__ wg_far, int nwg, uint32_t* status) {
+__device__ __forceinline__ uint32_t any_tile_far(const uint32_t* __restrict__ wg_far, int nwg, int pc, uint32_t* status) {
+    __shared__ uint32_t inside_rows;
+    if (threadIdx.x == 0) inside_rows = 0;
     int far = 0, far_heads = 0;
+    uint32_t inside = 0;
     for (int w = threadIdx.x; w < nwg; w += blockDim.x) {
         const uint32_t bits = wg_far[w];
         far |= int(bits & 1u);
         far_heads |= int(bits & 2u);
+        inside += bits >> 2;
     }
     far = __syncthreads_or(far);
     far_heads = __syncthreads_or(far_heads);
-    const uint32_t raise = (far ? STATUS_NEEDS_CARRY : 0u) | (far_heads ? STATUS_FAR_HEADS : 0u);
+    if (inside) atomicAdd(&inside_rows, inside);
+    __syncthreads();
+    const bool long_rows = pc > 0 && inside_rows >= uint32_t(pc / ORDER_MIN_SHARE + 1);
+    const uint32_t raise = (far ? STATUS_NEEDS_CARRY : 0u) | (far_heads ? STATUS_FAR_HEADS : 0u) | (long_rows ? STATUS_LONG_ROWS : 0u);
     if (raise && threadIdx.x == 0) atomicOr(status, raise);
     return raise;
 }
@@ -348,7 +373,7 @@ k_rows(int m, IT nnz, const IT* __restrict__ row_ptr, int sigma, int T, int W, i
     using tp_t = typename Index<IT>::tp_t;
     constexpr tp_t DIRTY = Index<IT>::DIRTY;
     // what k_tile_ptr found about the tiles' heads, for the transposition that follows
-    if (blockIdx.x == 0) any_tile_far(wg_far, nwg, status);
+    if (blockIdx.x == 0) any_tile_far(wg_far, nwg, pc, status);
     const int lane = lane_id();
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const bool in = g < int64_t(m);                       // every lane stays for the shuffles below
@@ -471,10 +496,95 @@ __device__ __forceinline__ void scan_epilogue(int pc, int p, IT total, IT* __res
         atomicOr(status, CSR5_STATUS_HAS_DIRTY | CSR5_STATUS_HAS_EMPTY_ROWS);
 }
 
+// ----------------------------------------------------------------------------
+// Order in which the tile kernel takes the tiles of a matrix with long rows and a
+// large x.  A tile inside one row gathers from a narrow stretch of x (the row's
+// columns ascend), but the tiles in flight at a time, neighbours in the matrix,
+// belong to all parts of a few rows: together they touch all of x, and an x larger
+// than an XCD's L2 is fetched again for every few rows, a 128-byte line per
+// gather.  Taken by first column instead, with the k-th eighth of the list going
+// to XCD k, the tiles in flight on an XCD share about (1/64 of x + a tile's
+// stretch), which its L2 holds: 1500 rows of 20 000 entries among 1.5 M short
+// ones, x of 32 MB, 600 -> 227 us (10 -> 26 % of the HBM peak on the bytes the
+// product cannot do without); x of 8 MB, 1000 such rows, 233 -> 134 us; x of
+// 4.8 MB, 200 of them, 40.3 -> 35.2 us.
+// Where the line lies (measured with such matrices and with power-law ones):
+// ORDER_MIN_X_BYTES is the L2 of one XCD, which holds any smaller x whole;
+// ORDER_MIN_SHARE: with half of the tiles inside one row and more the order wins,
+// with a third (power-law, whose long rows all gather from the same low columns)
+// it loses 15-20 %; below ORDER_MIN_TILES the chip takes all tiles at once.
+// The list: the tiles that hold row ends, in (nearly) their own order, then, from
+// a multiple of `align` on, the tiles inside one row by first column.  A counting
+// sort over 2 * ORDER_BUCKETS keys by one workgroup of SCAN_THREADS, next to the
+// scan of empty_offset_ptr; within a bucket any order will do.  plan[0]: where the
+// second part begins, plan[1]: entries in all (those between the parts hold no
+// tile: 0xffffffff); both 0: no order.  first_col: from the transposition.
+// ----------------------------------------------------------------------------
+constexpr size_t ORDER_MIN_X_BYTES = 4u << 20;
+constexpr int ORDER_BUCKETS = SCAN_THREADS, ORDER_MIN_TILES = 2048;
+
+struct OrderJob {
+    int32_t n, align;                // align = 0: nothing to do
+    const int32_t* first_col;
+    uint32_t *order, *plan;
+};
+
+template <typename IT>
+__device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
+                           const uint32_t* __restrict__ status) {
+    if (!(*status & STATUS_LONG_ROWS) || !(*status & STATUS_NEEDS_CARRY)) return;     // (plan was cleared with the status word)
+    __shared__ uint32_t at[2 * ORDER_BUCKETS];
+    __shared__ uint32_t wave_total[SCAN_THREADS / OMEGA];
+    __shared__ uint32_t row_end_tiles;
+    constexpr auto ROWMASK = Index<IT>::ROWMASK;
+    const int32_t* __restrict__ const first_col = job.first_col;
+    uint32_t* __restrict__ const order = job.order;
+    const int64_t n = job.n;
+    auto bucket = [&](int t) -> int {
+        int64_t c = first_col[t];
+        c = c < 0 ? 0 : (c >= n ? n - 1 : c);
+        const bool inside = (tile_ptr[t] & ROWMASK) == (tile_ptr[t + 1] & ROWMASK);
+        return inside ? ORDER_BUCKETS + int(c * ORDER_BUCKETS / n) : int(int64_t(t) * ORDER_BUCKETS / pc);
+    };
+    for (int k = threadIdx.x; k < 2 * ORDER_BUCKETS; k += SCAN_THREADS) at[k] = 0;
+    __syncthreads();
+#pragma unroll 4
+    for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) atomicAdd(&at[bucket(t)], 1u);
+    __syncthreads();
+    // exclusive scan, two buckets per thread
+    const int lane = lane_id(), wave = threadIdx.x / OMEGA;
+    const uint32_t a = at[2 * threadIdx.x], b = at[2 * threadIdx.x + 1];
+    uint32_t incl = a + b;
+#pragma unroll
+    for (int d = 1; d < OMEGA; d <<= 1) {
+        const uint32_t up = __shfl_up(incl, d, OMEGA);
+        if (lane >= d) incl += up;
+    }
+    if (lane == OMEGA - 1) wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - a - b;
+    for (int w = 0; w < wave; w++) before += wave_total[w];
+    if (2 * threadIdx.x == ORDER_BUCKETS) row_end_tiles = before;
+    __syncthreads();
+    const uint32_t align = uint32_t(job.align), ends = row_end_tiles, second = (ends + align - 1) / align * align;
+    if (2 * threadIdx.x >= ORDER_BUCKETS) before += second - ends;
+    at[2 * threadIdx.x] = before;
+    at[2 * threadIdx.x + 1] = before + a;
+    for (uint32_t q = ends + threadIdx.x; q < second; q += SCAN_THREADS) order[q] = 0xffffffffu;
+    __syncthreads();
+#pragma unroll 4
+    for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) order[atomicAdd(&at[bucket(t)], 1u)] = uint32_t(t);
+    if (threadIdx.x == 0) {
+        job.plan[0] = second;
+        job.plan[1] = uint32_t(pc) + second - ends;
+    }
+}
+
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-           uint32_t* __restrict__ status) {
+           uint32_t* __restrict__ status, const OrderJob job) {
+    if (blockIdx.x == 1) return tile_order<IT>(pc, job, tile_ptr, status);
     IT total = 0;
     if (*status & STATUS_SCAN_NEEDED)
         for (int64_t base = 0; base < pc; base += SCAN_CHUNK) total += scan_chunk(eop, base, int64_t(pc), total);
@@ -484,10 +594,13 @@ k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* 
 // more than SCAN_SINGLE tiles, step 1: workgroup b scans chunk b on its own
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
-k_scan_chunks(int pc, IT* __restrict__ eop, IT* __restrict__ chunk_sum, const uint32_t* __restrict__ status) {
+k_scan_chunks(int pc, IT* __restrict__ eop, IT* __restrict__ chunk_sum, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
+              const uint32_t* __restrict__ status, const OrderJob job) {
+    int chunk = blockIdx.x;
+    if (job.align && chunk-- == 0) return tile_order<IT>(pc, job, tile_ptr, status);       // the longest first
     if (!(*status & STATUS_SCAN_NEEDED)) return;
-    const IT total = scan_chunk(eop, int64_t(blockIdx.x) * SCAN_CHUNK, int64_t(pc), IT(0));
-    if (threadIdx.x == 0) chunk_sum[blockIdx.x] = total;
+    const IT total = scan_chunk(eop, int64_t(chunk) * SCAN_CHUNK, int64_t(pc), IT(0));
+    if (threadIdx.x == 0) chunk_sum[chunk] = total;
 }
 
 // step 2: workgroup b sums the totals of the chunks before its own (at most
@@ -695,6 +808,9 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
             bad |= (c[k] < 0) | (c[k] >= n);
         }
         if constexpr (!BACK && look_sigma(SIGMA)) {
+            // (a matrix that never reads the records keeps every tile's first column in their place, for tile_order)
+            if (last_val && (st_heads & (STATUS_NEEDS_CARRY | STATUS_LONG_ROWS)) == (STATUS_NEEDS_CARRY | STATUS_LONG_ROWS) && lane == 0)
+                reinterpret_cast<int32_t*>(last_val)[tile] = c[0];
             if (keep_last) {
                 int32_t* const near_c = last_col + rec * size_t(rec_bytes / 4);
                 int32_t* const far_c = near_c + FAR_COL_AT;
@@ -1071,7 +1187,8 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
        const VT* __restrict__ val, const VT* __restrict__ x, VT* __restrict__ y,
        VT* __restrict__ carry, uint64_t* __restrict__ meet, uint32_t* __restrict__ arrived,
        const uint2* __restrict__ span, const uint32_t* __restrict__ status, const uint32_t* __restrict__ tile_head,
-       const int32_t* __restrict__ last_col, const VT* __restrict__ last_val) {
+       const int32_t* __restrict__ last_col, const VT* __restrict__ last_val,
+       const uint32_t* __restrict__ order, uint32_t order_second, uint32_t order_len) {
     constexpr bool CAN_LOOK = MODE == MODE_LOOK;
     constexpr bool ONE = MODE == MODE_ONE;
     constexpr bool MEET = CAN_LOOK || ONE;      // the wavefronts of a workgroup meet at one barrier
@@ -1115,7 +1232,14 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
     }
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
-    const int tile = int(xcd_order(blockIdx.x - has_tail, nb_tiles, xcd_chunk)) * WAVES + wave;
+    int tile;
+    if (MODE == MODE_CARRY && order) {      // the list of tile_order
+        const uint32_t k = order_place(blockIdx.x - has_tail, nb_tiles, order_second / WAVES) * WAVES + wave;
+        const uint32_t t = k < order_len ? order[k] : 0xffffffffu;
+        tile = t < uint32_t(pc) ? int(t) : pc;
+    } else {
+        tile = int(xcd_order(blockIdx.x - has_tail, nb_tiles, xcd_chunk)) * WAVES + wave;
+    }
     // (every wavefront of a tile workgroup passes exactly one barrier, see below)
     if (tile >= pc) {
         if constexpr (MEET) __syncthreads();
@@ -1603,9 +1727,11 @@ hipError_t launch_spmv(const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
                        const uint32_t* tile_desc, const IT* eop, const int32_t* eo,
                        const int32_t* col_idx, const VT* val, const VT* x, VT* y,
                        VT* carry, uint64_t* meet, uint32_t* arrived, const uint2* span, const uint32_t* status, const uint32_t* tile_head, const int32_t* last_col,
-                       const VT* last_val, bool zero_rows, uint32_t far_mode, hipStream_t s) {
+                       const VT* last_val, bool zero_rows, uint32_t far_mode,
+                       const uint32_t* order, uint32_t order_second, uint32_t order_len, hipStream_t s) {
     constexpr int WAVES = TransposeShape<SIGMA>::WAVES;
     uint32_t nb_tiles = uint32_t((g.pc + WAVES - 1) / WAVES);
+    if (MODE == MODE_CARRY && order) nb_tiles = (order_len + NUM_XCD * WAVES - 1) / (NUM_XCD * WAVES) * NUM_XCD;
     uint32_t has_tail = (int64_t(g.pc) * g.T < nnz) ? 1u : 0u;
     // rows without nonzeros: up to 512 workgroups stride over the rows
     size_t nb_zero = zero_rows ? (size_t(m) + WAVES * OMEGA - 1) / (WAVES * OMEGA) : 0;
@@ -1620,7 +1746,7 @@ hipError_t launch_spmv(const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
         xcd_chunk = XCD_CHUNK;
     hipLaunchKernelGGL((k_spmv<SIGMA, VT, IT, MODE>), dim3(nb), dim3(WAVES * OMEGA), 0, s, m, nnz, g.pc, g.p, nb_tiles, has_tail,
                        xcd_chunk, far_mode, record_bytes(int64_t(nnz)), row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry,
-                       meet, arrived, span, status, tile_head, last_col, last_val);
+                       meet, arrived, span, status, tile_head, last_col, last_val, order, order_second, order_len);
     return hipGetLastError();
 }
 
@@ -1742,6 +1868,9 @@ struct csr5_handle_s {
     // small and for large sigma): two views of one array of LAST_REC_BYTES-byte records
     int32_t* last_col;
     void* last_val;
+    // The tile kernel's order of the tiles (tile_order), in the place of the records; NULL: by number
+    uint32_t* order;
+    uint32_t order_second, order_len;
     void* owned;           // hipMalloc'ed block, or NULL when a workspace was given
     hipStream_t conv_stream;
     int device;            // HIP device that was current at conversion
@@ -1839,6 +1968,14 @@ size_t csr5l_workspace_bytes(int32_t m, int64_t nnz, int32_t sigma) {
 
 }  // extern "C"
 
+// The first `words` words at the handle's status word; notes the status for later calls.
+static int read_status(csr5_handle_t h, uint32_t* got, int words) {
+    if (hipMemcpyAsync(got, h->status, size_t(words) * 4, hipMemcpyDeviceToHost, h->conv_stream) != hipSuccess) return CSR5_EHIP;
+    if (hipStreamSynchronize(h->conv_stream) != hipSuccess) return CSR5_EHIP;
+    h->status_host.store(int32_t(got[0] & 0x7fffffffu), std::memory_order_relaxed);
+    return CSR5_OK;
+}
+
 template <typename VT, typename IT>
 static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t* col_idx,
                         VT* val, int32_t sigma, void* workspace, size_t workspace_bytes,
@@ -1899,6 +2036,8 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     h->last_val = L.has_last ? basep + L.off_last : nullptr;                               // record + 0
     h->last_col = L.has_last ? reinterpret_cast<int32_t*>(basep + L.off_last + LOOK * 8) : nullptr;
     h->status = reinterpret_cast<uint32_t*>(basep + L.off_status);
+    h->order = nullptr;
+    h->order_second = h->order_len = 0;
     h->conv_stream = s;
     if (hipGetDevice(&h->device) != hipSuccess) {
         if (h->owned) (void)hipFree(h->owned);
@@ -1947,13 +2086,22 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
             default: e = hipErrorInvalidValue;
         }
     }
+    // The tile order goes along with the scan where it may pay and the host will know of it (see below)
+    OrderJob order = {n, 0, nullptr, nullptr, h->status + 1};
+    if (!(flags & CSR5_FLAG_NO_HOST_CHECK) && h->last_val && h->aux_form == 0 && g.pc >= ORDER_MIN_TILES &&
+        size_t(n) * sizeof(VT) >= ORDER_MIN_X_BYTES) {
+        order.align = NUM_XCD * tile_group_waves(g.sigma);
+        order.first_col = static_cast<const int32_t*>(h->last_val);
+        order.order = static_cast<uint32_t*>(h->last_val) + g.pc;      // pc + align words: the records have 96 bytes and more per tile
+    }
     if (e == hipSuccess && g.pc <= SCAN_SINGLE) {
-        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr, h->status);
+        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(order.align ? 2 : 1), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr, h->status, order);
         e = hipGetLastError();
     } else if (e == hipSuccess) {
         IT* chunk_sum = reinterpret_cast<IT*>(basep + L.off_scan);
         const int nchunks = (g.pc + SCAN_CHUNK - 1) / SCAN_CHUNK;      // <= 2^26 / 2^13 = SCAN_CHUNK
-        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum, h->status);
+        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + (order.align ? 1 : 0)), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
+                           tile_ptr, h->status, order);
         e = hipGetLastError();
         if (e == hipSuccess) {
             hipLaunchKernelGGL(k_scan_finish<IT>, dim3(nchunks), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, chunk_sum,
@@ -1977,9 +2125,14 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK)) {
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
-        uint32_t st = 0;
-        int rc = csr5_status(h, &st);
-        if (rc == CSR5_OK && (st & BAD_BITS)) {
+        uint32_t got[3] = {0, 0, 0};      // the status word and the plan of the tile order behind it
+        int rc = read_status(h, got, order.align ? 3 : 1);
+        if (rc == CSR5_OK && got[2]) {
+            h->order = order.order;
+            h->order_second = got[1];
+            h->order_len = got[2];
+        }
+        if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);
             (void)hipStreamSynchronize(s);
             rc = CSR5_EINVAL;
@@ -2053,13 +2206,13 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     // path, is small enough for it to pay, and the call uses the handle's own slot
     // (whose counters the conversion cleared).
     const bool one_pays = h->g.p <= ONE_LAUNCH_ANY_TILES || h->nnz / (h->m > 0 ? h->m : 1) < ONE_LAUNCH_SHORT_ROWS;
-    const bool one = !carry_mem && known >= 0 && !can_look && h->span &&
+    const bool one = !carry_mem && known >= 0 && !can_look && h->span && !h->order &&
                      (h->aux_form == 2 || (h->aux_form == 0 && one_pays));
     uint64_t* const meet = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(carry) + slot_off_meet(h->g));
     uint32_t* const arrived = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(carry) + slot_off_arrived(h->g, tile_group_waves(h->g.sigma)));
 #define ARGS h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
              static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->span, h->status, h->tile_head, h->last_col, \
-             static_cast<const VT*>(h->last_val), zero_rows, far_mode, s
+             static_cast<const VT*>(h->last_val), zero_rows, far_mode, h->order, h->order_second, h->order_len, s
     if (which & LAUNCH_TILES) {
 #define X(S) case S:                                                                                  \
         if (look_sigma(S) && can_look) e = launch_spmv<S, VT, IT, look_sigma(S) ? MODE_LOOK : MODE_CARRY>(ARGS); \
@@ -2255,11 +2408,9 @@ int csr5_free(csr5_handle_t h) {
 
 int csr5_status(csr5_handle_t h, uint32_t* status) {
     if (!h || !status) return CSR5_EINVAL;
-    if (hipMemcpyAsync(status, h->status, 4, hipMemcpyDeviceToHost, h->conv_stream) != hipSuccess) return CSR5_EHIP;
-    if (hipStreamSynchronize(h->conv_stream) != hipSuccess) return CSR5_EHIP;
-    h->status_host.store(int32_t(*status & 0x7fffffffu), std::memory_order_relaxed);
-    *status &= STATUS_PUBLIC;
-    return CSR5_OK;
+    const int rc = read_status(h, status, 1);
+    if (rc == CSR5_OK) *status &= STATUS_PUBLIC;
+    return rc;
 }
 
 int csr5_get_info(csr5_handle_t h, int32_t* omega, int32_t* sigma, int32_t* p, int32_t* p_complete,

@@ -1,0 +1,67 @@
+"""GPU parity of the tile order by columns: matrices most of whose tiles lie inside one
+long row, with x larger than the L2 of one accelerator die, at the sizes where the order
+begins (2048 complete tiles; x of 4 MiB) and at workgroups of four and of two tiles."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1503_05032_amd import binding as B
+from paper_1503_05032_amd import workloads as wl
+
+from gpu_util import DeviceCsr, check_format, check_spmv, convert
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(sigma, tiles, ragged, n, seed):
+    """`tiles` complete tiles and `ragged` further entries: rows of 5 to 20 tiles, a fifth
+    of the entries in short and empty rows between them."""
+    rng = np.random.default_rng(seed)
+    T = 64 * sigma
+    total, lens = tiles * T + ragged, []
+    while total > 0:
+        for k in [int(rng.integers(5 * T, 20 * T))] + rng.integers(0, 9, size=600).tolist():
+            k = min(k, total)
+            lens.append(k)
+            total -= k
+    return wl.from_row_lengths(np.array(lens), n, seed=seed, name=f"long{sigma}_{tiles}")
+
+
+@pytest.mark.parametrize("sigma,tiles,ragged,wide", [(8, 2048, 0, False), (8, 2047, 511, False), (8, 2049, 1, True), (8, 3001, 77, False),
+                                                     (16, 2050, 3, False), (17, 2051, 500, True), (32, 2048, 9, False)])
+def test_long_rows_with_a_large_x(sigma, tiles, ragged, wide):
+    for n in (524_287, 524_288, 700_001):
+        a = _matrix(sigma, tiles, ragged, n, seed=sigma + tiles)
+        print("order", sigma, tiles, ragged, wide, n, a.m, a.nnz, flush=True)
+        d = DeviceCsr(a, wide=wide)
+        h = convert(d, sigma=sigma)
+        if n == 700_001:
+            check_format(d, h, (a.name, n))
+        for call in range(2):
+            check_spmv(d, h, (a.name, n, call), x=np.random.default_rng(call).standard_normal(n))
+        if not wide:                                     # the entry point with its own cross-tile array takes the same order
+            y = d.y.clone()
+            d.y.fill_(float("nan"))
+            B.csr5_spmv_static(h, d.x, d.y)
+            torch.cuda.synchronize()
+            _, s = oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val, d.x.cpu().numpy())
+            assert np.all(np.abs((y - d.y).cpu().numpy()) <= 2e-12 * s + 1e-300)
+        B.csr5_to_csr(h)
+        torch.cuda.synchronize()
+        assert np.array_equal(d.col_idx.cpu().numpy(), a.col_idx)
+        B.csr5_free(h)
+
+
+def test_long_rows_single_precision():
+    a = _matrix(16, 2100, 5, 1_100_000, seed=3)
+    d = DeviceCsr(a)
+    val, x = d.val.float(), d.x.float()
+    y = torch.full((a.m,), float("nan"), dtype=torch.float32, device="cuda:0")
+    h = B.csr5s_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val, sigma=16)
+    B.csr5s_spmv_ex(h, x, y)
+    torch.cuda.synchronize()
+    ref, s = oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val.astype(np.float32).astype(np.float64), x.cpu().numpy().astype(np.float64))
+    # a term passes through the walk, the tile's scan and the sum over a row's 20 tiles at most: fewer than 64 additions of 2^-24 each
+    assert np.all(np.abs(y.cpu().numpy() - ref) <= 1e-5 * s + 1e-30)
+    B.csr5_free(h)
