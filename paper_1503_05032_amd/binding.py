@@ -139,11 +139,13 @@ def _arr(t, dtypes, min_numel, name):
         import torch
         _DTYPES.update({"i32": torch.int32, "i64": torch.int64, "f64": torch.float64, "f32": torch.float32,
                         "u8": torch.uint8})
-    if not any(t.dtype is _DTYPES[d] for d in dtypes):
+    if t.dtype is not _DTYPES[dtypes[0]] and not any(t.dtype is _DTYPES[d] for d in dtypes):
         raise ValueError(f"{name}: expected dtype {' or '.join(dtypes)}, got {t.dtype}")
     if t.numel() < min_numel:
         raise ValueError(f"{name}: needs at least {min_numel} elements, has {t.numel()}")
-    return _ptr(t)
+    if not t.is_cuda or not t.is_contiguous():
+        raise ValueError("expected a contiguous GPU tensor")
+    return t.data_ptr() or None
 
 
 def _csr_args(m, n, nnz, row_ptr, col_idx, val, index, value):
@@ -151,10 +153,26 @@ def _csr_args(m, n, nnz, row_ptr, col_idx, val, index, value):
             _arr(val, [value], nnz, "val"))
 
 
+_current_stream = None      # returns torch's current stream on the current device, as an address
+
+
+def _find_current_stream():
+    """torch.cuda.current_stream() builds a Stream object, 2.9 us a call, as long as a small SpMV's kernel; torch's
+    own launch code asks for the address only (0.3 us), and so does this where torch has that call."""
+    import torch
+    torch.cuda.current_stream()                          # initialises the device as before
+    raw, device = (getattr(torch._C, f, None) for f in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
 def _stream(s):
     if s is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        global _current_stream
+        if _current_stream is None:
+            _current_stream = _find_current_stream()
+        return _current_stream() or None
     if isinstance(s, int):
         return s or None
     return s.cuda_stream or None
@@ -270,7 +288,8 @@ def csr5_spmv(h, x, y, check=True):
 
 
 def csr5_spmv_ex(h, x, y, stream=None, check=True):
-    return _chk(load().csr5_spmv_ex(h, *_xy(h, x, y, "f64"), _stream(stream)), "csr5_spmv_ex", check)
+    px, py = _xy(h, x, y, "f64")
+    return _chk(load().csr5_spmv_ex(h, px, py, _stream(stream)), "csr5_spmv_ex", check)
 
 
 def csr5_spmv_bound(h, x, y, stream=None):
