@@ -26,7 +26,7 @@ constexpr uint32_t BAD_BITS = CSR5_STATUS_BAD_ROW_PTR | CSR5_STATUS_BAD_COL_IDX;
 constexpr uint32_t STATUS_SCAN_NEEDED = 1u << 16;
 // Internal status bit: some tile (the incomplete one included) starts further
 // into a row than the look-behind can make up for, so the SpMV sends its
-// cross-tile sums through the auxiliary array (see k_spmv and k_tile_ptr).
+// cross-tile sums through the auxiliary array (see k_spmv and k_prepare).
 constexpr uint32_t STATUS_NEEDS_CARRY = 1u << 17;
 // Internal status bit: some first tile of a workgroup (or the incomplete tile)
 // starts more than LOOK entries into a row: the look-behind of this matrix reads
@@ -257,50 +257,121 @@ __device__ __forceinline__ uint32_t order_place(uint32_t w, uint32_t nb, uint32_
 }
 
 // ----------------------------------------------------------------------------
-// Conversion step 2a: tile_ptr (Algorithm 4, first loop).  One thread per
-// tile boundary.  The same launch clears the flag words the next kernel ORs
-// into, and the status word, and notes for every tile how many entries of its
-// first row lie before it (tile_head, an auxiliary array of the SpMV).
+// Conversion step 2a: tile_ptr (Algorithm 4, first loop), and everything else that
+// only row_ptr is needed for.
+// The first `nb_tiles` workgroups (at most PREP_TILE_WG): one thread per tile
+// boundary searches its row, notes how many entries of the tile's first row lie
+// before it (tile_head, an auxiliary array of the SpMV) and, where the one-launch
+// SpMV may run, which groups of tiles that row touches.  The others (at most
+// PREP_ROW_WG) check row_ptr and look for empty rows in the incomplete tile.  All
+// of them put the words of the one-launch SpMV at rest.
+// What they find goes into a word per workgroup, not to the status word: this
+// launch clears that word, and many workgroups aiming at one word queue up.  The
+// transposition that follows collects them.
+// Bound by the latency of the search, a chain of dependent loads: seven probes a
+// round, 7 rounds at 1 M rows instead of 20 (count_le_wide).  With more tiles than
+// SEARCH_WIDE_MAX_TILES the lines touched count and the binary search is better.
+// (The flags of the rows' first nonzeros, one atomic OR per descriptor word into
+// words cleared here, were a launch of their own between this one and the
+// transposition, which now forms them where it forms the descriptors: 100^3 stencil
+// 18.0 -> 8.8 us for what is left of the two launches, the transposition the same;
+// 1.5 M rows of which a third are empty 47 -> 9.3 us, the transposition 133 -> 140.)
 // ----------------------------------------------------------------------------
+constexpr int PREP_TILE_WG = 256, PREP_ROW_WG = 1024, PREP_THREADS = 256, PREP_UNROLL = 4;
+constexpr int SEARCH_WIDE_MAX_TILES = 1 << 17;
+// the words of the row part
+constexpr uint32_t ROWS_BAD = 1u, ROWS_FIRST_EMPTY = 2u, ROWS_TAIL_EMPTY = 4u;
+// the words of the tile part: two bits, and above them how many tiles lie inside one row
+constexpr uint32_t TILES_FAR = 1u, TILES_FAR_HEADS = 2u;
+constexpr int TILES_INSIDE_SHIFT = 2;
+
+// count_le with seven probes of eight parts a round, in flight together.
 template <typename IT>
-__global__ void __launch_bounds__(256)
-k_tile_ptr(int m, const IT* __restrict__ row_ptr, int T, int p, int pc, int group, int record_reach,
-           typename Index<IT>::tp_t* __restrict__ tile_ptr, uint32_t* __restrict__ tile_head,
-           uint32_t* __restrict__ wg_far, uint32_t* __restrict__ desc, size_t ndesc,
-           uint32_t* __restrict__ arrived, uint64_t* __restrict__ meet, size_t slot_bytes, int slots,
-           uint2* __restrict__ span, uint32_t* __restrict__ status) {
+__device__ __forceinline__ int count_le_wide(const IT* __restrict__ a, int len, int64_t key) {
+    int lo = 0;
+    while (len > 8) {
+        const int step = len >> 3;
+        int found = 0;
+#pragma unroll
+        for (int i = 1; i < 8; i++) found += int(int64_t(a[lo + i * step - 1]) <= key);
+        lo += found * step;
+        len = found == 7 ? len - 7 * step : step - 1;
+    }
+    int found = 0;
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+        if (i < len) found += int(int64_t(a[lo + i]) <= key);
+    return lo + found;
+}
+
+template <typename IT>
+__global__ void __launch_bounds__(PREP_THREADS)
+k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, int group, int record_reach, uint32_t nb_tiles,
+          typename Index<IT>::tp_t* __restrict__ tile_ptr, uint32_t* __restrict__ tile_head, uint32_t* __restrict__ words,
+          uint32_t* __restrict__ arrived, uint64_t* __restrict__ meet, size_t slot_bytes, int slots,
+          uint2* __restrict__ span, uint32_t* __restrict__ status) {
     using tp_t = typename Index<IT>::tp_t;
-    size_t gid = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    size_t stride = size_t(gridDim.x) * blockDim.x;
-    for (size_t k = gid; k < ndesc; k += stride) desc[k] = 0u;
+    const size_t gid = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
     // the one-launch SpMV finds its counters at zero and its meeting places empty, and leaves them so
     const size_t groups = (size_t(pc) + group - 1) / group + 1;         // one word of each per group of tiles
     for (int slot = 0; slot < slots; slot++) {
+        const size_t stride = size_t(gridDim.x) * blockDim.x;
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
     if (gid < 3) status[gid] = 0u;        // and the plan of the tile order
-    int far = 0, far_heads = 0, inside = 0;
+    uint32_t found = 0;
+    if (blockIdx.x >= nb_tiles) {         // ---- rows
+        const int64_t stride = int64_t(gridDim.x - nb_tiles) * PREP_THREADS;
+        for (int64_t r0 = int64_t(blockIdx.x - nb_tiles) * PREP_THREADS + threadIdx.x; r0 < m; r0 += stride * PREP_UNROLL) {
+            IT a[PREP_UNROLL], b[PREP_UNROLL];
+#pragma unroll
+            for (int q = 0; q < PREP_UNROLL; q++) {
+                const int64_t r = r0 + q * stride < m ? r0 + q * stride : r0;
+                a[q] = row_ptr[r];
+                b[q] = row_ptr[r + 1];
+            }
+#pragma unroll
+            for (int q = 0; q < PREP_UNROLL; q++) {
+                const int64_t r = r0 + q * stride < m ? r0 + q * stride : r0;
+                const bool bad = a[q] < 0 || b[q] < a[q] || b[q] > nnz || (r == 0 && a[q] != 0) || (r == m - 1 && b[q] != nnz);
+                const bool empty = !bad && a[q] == b[q];
+                found |= (bad ? ROWS_BAD : 0u) | (empty && r == 0 ? ROWS_FIRST_EMPTY : 0u) |
+                         (empty && p > pc && int64_t(a[q]) > int64_t(pc) * T ? ROWS_TAIL_EMPTY : 0u);
+            }
+        }
+        found = (__syncthreads_or(found & ROWS_BAD) ? ROWS_BAD : 0u) | (__syncthreads_or(found & ROWS_FIRST_EMPTY) ? ROWS_FIRST_EMPTY : 0u) |
+                (__syncthreads_or(found & ROWS_TAIL_EMPTY) ? ROWS_TAIL_EMPTY : 0u);
+        if (threadIdx.x == 0) words[PREP_TILE_WG + blockIdx.x - nb_tiles] = found;
+        return;
+    }
+    // ---- tile boundaries
+    __shared__ uint32_t inside_rows;
+    if (threadIdx.x == 0) inside_rows = 0;
+    __syncthreads();
+    uint32_t inside = 0;
+    const size_t stride = size_t(nb_tiles) * PREP_THREADS;
     for (size_t t = gid; t <= size_t(p); t += stride) {
-        int64_t bnd = int64_t(t) * T;
-        const int row = count_le(row_ptr, m + 1, bnd) - 1;
+        const int64_t bnd = int64_t(t) * T;
+        const int row = (p <= SEARCH_WIDE_MAX_TILES ? count_le_wide(row_ptr, m + 1, bnd) : count_le(row_ptr, m + 1, bnd)) - 1;
         tile_ptr[t] = tp_t(row) & Index<IT>::ROWMASK;
         // how far into its first row the tile starts (0: the row starts with the
         // tile), saturated at 32 bits: what the SpMV needs to know about the
         // boundary, so that it does not have to look into row_ptr itself
-        int64_t head = 0;
-        if (t < size_t(p) && row >= 0 && row < m) head = bnd - int64_t(row_ptr[row]);
+        int64_t head = 0, rs = 0, re = 0;
+        if (row >= 0 && row < m) {
+            rs = int64_t(row_ptr[row]);
+            re = int64_t(row_ptr[row + 1]);
+            if (t < size_t(p)) head = bnd - rs;
+        }
         tile_head[t] = uint32_t(head < 0 ? 0 : (head > int64_t(0xffffffffu) ? int64_t(0xffffffffu) : head));
-        inside += int(t < size_t(pc) && row >= 0 && row < m && int64_t(row_ptr[row + 1]) >= bnd + T);
+        inside += uint32_t(t < size_t(pc) && re >= bnd + T);
         // for the one-launch SpMV: the groups of tiles that row touches (first, how many)
         if (slots > 0) {
             uint2 sp = {0u, 1u};
-            if (row >= 0 && row < m) {
-                const int64_t rs = int64_t(row_ptr[row]), re = int64_t(row_ptr[row + 1]);
-                if (re > rs && rs >= 0) {
-                    const int g0 = tile_group_of(rs, T, pc, group), g1 = tile_group_of(re - 1, T, pc, group);
-                    if (g1 >= g0) sp = uint2{uint32_t(g0), uint32_t(g1 - g0 + 1)};
-                }
+            if (re > rs && rs >= 0) {
+                const int g0 = tile_group_of(rs, T, pc, group), g1 = tile_group_of(re - 1, T, pc, group);
+                if (g1 >= g0) sp = uint2{uint32_t(g0), uint32_t(g1 - g0 + 1)};
             }
             span[t] = sp;
         }
@@ -311,119 +382,42 @@ k_tile_ptr(int m, const IT* __restrict__ row_ptr, int T, int p, int pc, int grou
         // tiles are handed their neighbour's last segment, which is the whole
         // head if the row began inside (or with) that neighbour: at most T entries.
         const bool from_record = (t % size_t(group)) == 0 || t >= size_t(pc);
-        far |= int(head > (from_record ? int64_t(record_reach) : int64_t(T)));
-        far_heads |= int(from_record && head > int64_t(LOOK));
+        if (head > (from_record ? int64_t(record_reach) : int64_t(T))) found |= TILES_FAR;
+        if (from_record && head > int64_t(LOOK)) found |= TILES_FAR_HEADS;
     }
-    // "Some tile starts too far into a row" (the SpMV then needs its
-    // carry array) does not go to the status word from here -- this launch also
-    // clears that word, and thousands of workgroups saying so would queue at it --
-    // but into one word per workgroup, which the scan kernel collects.
-    far = __syncthreads_or(far);
-    far_heads = __syncthreads_or(far_heads);
-    // tiles that lie inside one row: how many (two or more of a thread count as one)
-    inside = __syncthreads_count(inside);
-    if (threadIdx.x == 0) wg_far[blockIdx.x] = uint32_t(far != 0) | (uint32_t(far_heads != 0) << 1) | (uint32_t(inside) << 2);   // bit 0, bit 1, count
+    if (inside) atomicAdd(&inside_rows, inside);
+    found = (__syncthreads_or(found & TILES_FAR) ? TILES_FAR : 0u) | (__syncthreads_or(found & TILES_FAR_HEADS) ? TILES_FAR_HEADS : 0u);
+    if (threadIdx.x == 0) words[blockIdx.x] = found | (inside_rows << TILES_INSIDE_SHIFT);
 }
 
-// What the workgroups of k_tile_ptr (nwg of them) found about the tiles' heads
-// (bit 0: some tile starts too far into a row for the tile kernel alone; bit 1:
-// some workgroup's first tile starts more than LOOK entries into a row) goes to
-// the status word, once.  Every thread of the workgroup must call this.
-__device__ __forceinline__ uint32_t any_tile_far(const uint32_t* __restrict__ wg_far, int nwg, int pc, uint32_t* status) {
+// What the workgroups of k_prepare found goes to the status word (and the mark of
+// the incomplete tile, which has no wavefront of its own, to tile_ptr[pc]).  One
+// workgroup; every thread of it must call this.
+template <typename IT>
+__device__ __forceinline__ void collect_words(const uint32_t* __restrict__ words, int nb_tiles, int nb_rows, int pc,
+                                              typename Index<IT>::tp_t* tile_ptr, uint32_t* status) {
     __shared__ uint32_t inside_rows;
     if (threadIdx.x == 0) inside_rows = 0;
-    int far = 0, far_heads = 0;
-    uint32_t inside = 0;
-    for (int w = threadIdx.x; w < nwg; w += blockDim.x) {
-        const uint32_t bits = wg_far[w];
-        far |= int(bits & 1u);
-        far_heads |= int(bits & 2u);
-        inside += bits >> 2;
-    }
-    far = __syncthreads_or(far);
-    far_heads = __syncthreads_or(far_heads);
-    if (inside) atomicAdd(&inside_rows, inside);
     __syncthreads();
-    const bool long_rows = pc > 0 && inside_rows >= uint32_t(pc / ORDER_MIN_SHARE + 1);
-    const uint32_t raise = (far ? STATUS_NEEDS_CARRY : 0u) | (far_heads ? STATUS_FAR_HEADS : 0u) | (long_rows ? STATUS_LONG_ROWS : 0u);
-    if (raise && threadIdx.x == 0) atomicOr(status, raise);
-    return raise;
-}
-
-// ----------------------------------------------------------------------------
-// Conversion steps 2b + 3a, one thread per matrix row (the first workgroup also
-// passes on what k_tile_ptr noted about the tiles' heads).
-//  * empty row   -> mark the tile whose row range holds it (Algorithm 4, second
-//    loop, turned inside out: the printed loop walks each tile's rows, which
-//    serialises on a tile that spans millions of empty rows).  An empty row
-//    sitting at entry position a lies in the inclusive range
-//    [tile_ptr[t], tile_ptr[t+1]] of exactly one tile, the one that holds entry
-//    a - 1: tiles that start at or after a begin with a later row, tiles that
-//    end before a - 1 end with an earlier one.  Rows before the first nonzero
-//    (a = 0) lie in no tile's range.
-//  * other rows  -> set the bit_flag of the row's first nonzero (Section 3.4;
-//    the scatter of Algorithm 3 step 1) directly inside the packed descriptor.
-// Also validates row_ptr.
-// ----------------------------------------------------------------------------
-template <typename IT>
-__global__ void __launch_bounds__(256)
-k_rows(int m, IT nnz, const IT* __restrict__ row_ptr, int sigma, int T, int W, int p, int pc,
-       typename Index<IT>::tp_t* tile_ptr, uint32_t* desc, const uint32_t* __restrict__ wg_far, int nwg,
-       uint32_t* status) {
-    using tp_t = typename Index<IT>::tp_t;
-    constexpr tp_t DIRTY = Index<IT>::DIRTY;
-    // what k_tile_ptr found about the tiles' heads, for the transposition that follows
-    if (blockIdx.x == 0) any_tile_far(wg_far, nwg, pc, status);
-    const int lane = lane_id();
-    const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const bool in = g < int64_t(m);                       // every lane stays for the shuffles below
-    const int r = in ? int(g) : 0;
-    IT a = 0, b = 0;
-    if (in) { a = row_ptr[r]; b = row_ptr[r + 1]; }
-    const bool bad = in && ((a < 0) || (b < a) || (b > nnz) || (r == 0 && a != 0) || (r == m - 1 && b != nnz));
-    if (bad) raise_status(status, CSR5_STATUS_BAD_ROW_PTR);
-    // Empty row: mark its tile.  Neighbouring empty rows aim at the same tile, so
-    // only the first lane of such a run goes on, and it looks before the atomic (a
-    // tile whose range holds millions of empty rows would otherwise receive
-    // millions of atomics on one word).  The status bits that say "some tile is
-    // marked" are set once, by the scan that follows; only rows before the first
-    // nonzero mark no tile, and row 0 speaks for them.
-    const bool empty = in && !bad && a == b;
-    if (empty && r == 0) raise_status(status, CSR5_STATUS_HAS_EMPTY_ROWS);
-    const bool nonempty = in && !bad && a != b;
-    const IT a_tile = nonempty ? IT(a / T) : IT(0);
-    const int a_off = nonempty ? int(a - a_tile * T) : 0;
-    const int t = (empty && a > 0) ? int((a - 1) / T) : -1 - lane;
-    const int tprev = __shfl_up(t, 1, OMEGA);
-    if (t >= 0 && t < p && (lane == 0 || tprev != t) &&
-        !(__hip_atomic_load(&tile_ptr[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & DIRTY))
-        __hip_atomic_fetch_or(&tile_ptr[t], DIRTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // The flag of the row's first nonzero.  Short rows put the flags of several
-    // consecutive rows, i.e. lanes, into one descriptor word, and atomics on one
-    // word are served one after the other (2 M rows of a power-law matrix: 75 us).
-    // So the lanes that aim at the same word merge their bits first (the rows are
-    // in order, hence those lanes are neighbours) and the last of them issues one OR.
-    const bool sets = in && !bad && a != b && int64_t(a) < int64_t(pc) * T;
-    uint64_t word = ~uint64_t(lane);                      // no real word index, different in every lane
-    uint32_t bits = 0;
-    if (sets) {
-        const int tile = int(a_tile);
-        const int w = a_off;
-        const int i = w / sigma;
-        const int j = w - i * sigma;
-        word = (uint64_t(tile) * W + (j >> 5)) * OMEGA + i;
-        bits = 1u << (j & 31);
+    uint32_t tiles = 0, rows = 0, inside = 0;
+    for (int w = threadIdx.x; w < nb_tiles; w += blockDim.x) {
+        const uint32_t word = words[w];
+        tiles |= word;
+        inside += word >> TILES_INSIDE_SHIFT;
     }
-#pragma unroll
-    for (int d = 1; d < OMEGA; d <<= 1) {
-        const uint32_t up = __shfl_up(bits, d, OMEGA);
-        const uint64_t wup = __shfl_up(word, d, OMEGA);
-        if (lane >= d && wup == word) bits |= up;
+    for (int w = threadIdx.x; w < nb_rows; w += blockDim.x) rows |= words[PREP_TILE_WG + w];
+    if (inside) atomicAdd(&inside_rows, inside);
+    const int far = __syncthreads_or(tiles & TILES_FAR), far_heads = __syncthreads_or(tiles & TILES_FAR_HEADS);
+    const int bad = __syncthreads_or(rows & ROWS_BAD), first = __syncthreads_or(rows & ROWS_FIRST_EMPTY);
+    const int tail = __syncthreads_or(rows & ROWS_TAIL_EMPTY);
+    if (threadIdx.x == 0) {
+        const bool long_rows = pc > 0 && inside_rows >= uint32_t(pc / ORDER_MIN_SHARE + 1);
+        const uint32_t raise = (far ? STATUS_NEEDS_CARRY : 0u) | (far_heads ? STATUS_FAR_HEADS : 0u) | (long_rows ? STATUS_LONG_ROWS : 0u) |
+                               (bad ? CSR5_STATUS_BAD_ROW_PTR : 0u) | (first ? CSR5_STATUS_HAS_EMPTY_ROWS : 0u);
+        if (raise) atomicOr(status, raise);
+        if (tail) tile_ptr[pc] |= Index<IT>::DIRTY;
     }
-    const uint64_t wnext = __shfl_down(word, 1, OMEGA);
-    if (sets && (lane == OMEGA - 1 || wnext != word)) atomicOr(&desc[word], bits);
 }
-
 
 // ----------------------------------------------------------------------------
 // empty_offset layout: exclusive prefix sum of the per-tile segment counts
@@ -433,7 +427,6 @@ k_rows(int m, IT nnz, const IT* __restrict__ row_ptr, int sigma, int T, int W, i
 // every chunk gets a workgroup (local scan + chunk total) and a second launch
 // adds to every chunk the sum of the totals before it.
 // ----------------------------------------------------------------------------
-constexpr uint32_t MAX_TILE_PTR_WG = 8192;     // workgroups of k_tile_ptr
 constexpr uint32_t CARRY_SLOTS = 4;            // carry arrays per handle = SpMVs of one handle that may overlap
 constexpr int SCAN_THREADS = 1024, SCAN_ITEMS = 8, SCAN_CHUNK = SCAN_THREADS * SCAN_ITEMS;
 constexpr int SCAN_SINGLE = 4 * SCAN_CHUNK;
@@ -539,16 +532,16 @@ __device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>:
     constexpr auto ROWMASK = Index<IT>::ROWMASK;
     const int32_t* __restrict__ const first_col = job.first_col;
     uint32_t* __restrict__ const order = job.order;
-    const int64_t n = job.n;
+    const float per_col = float(ORDER_BUCKETS) / float(job.n), per_tile = float(ORDER_BUCKETS) / float(pc);
     auto bucket = [&](int t) -> int {
-        int64_t c = first_col[t];
-        c = c < 0 ? 0 : (c >= n ? n - 1 : c);
+        const int32_t c = first_col[t];
         const bool inside = (tile_ptr[t] & ROWMASK) == (tile_ptr[t + 1] & ROWMASK);
-        return inside ? ORDER_BUCKETS + int(c * ORDER_BUCKETS / n) : int(int64_t(t) * ORDER_BUCKETS / pc);
+        const int k = int(inside ? float(c < 0 ? 0 : c) * per_col : float(t) * per_tile);      // (a column out of range: rejected input)
+        return (inside ? ORDER_BUCKETS : 0) + (k < ORDER_BUCKETS ? k : ORDER_BUCKETS - 1);
     };
     for (int k = threadIdx.x; k < 2 * ORDER_BUCKETS; k += SCAN_THREADS) at[k] = 0;
     __syncthreads();
-#pragma unroll 4
+#pragma unroll 8
     for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) atomicAdd(&at[bucket(t)], 1u);
     __syncthreads();
     // exclusive scan, two buckets per thread
@@ -572,7 +565,7 @@ __device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>:
     at[2 * threadIdx.x + 1] = before + a;
     for (uint32_t q = ends + threadIdx.x; q < second; q += SCAN_THREADS) order[q] = 0xffffffffu;
     __syncthreads();
-#pragma unroll 4
+#pragma unroll 8
     for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) order[atomicAdd(&at[bucket(t)], 1u)] = uint32_t(t);
     if (threadIdx.x == 0) {
         job.plan[0] = second;
@@ -695,7 +688,15 @@ k_empty_offset(int m, const IT* __restrict__ row_ptr, int sigma, int T, int W, i
 // an odd pitch to avoid bank conflicts on the strided LDS read.  BACK = the
 // inverse permutation (CSR5 -> CSR, Section 3.6).  The last block also checks
 // the column indices of the incomplete tile.  The forward pass also keeps, per
-// workgroup, a copy of its last tile's last LOOK entries in CSR order when asked to.
+// workgroup, a copy of its last tile's last LOOK entries in CSR order when asked to,
+// and forms the tile's descriptors (steps 2b, 3a, 3b) from the rows that begin in
+// it: rows tile_ptr[t] + 1 .. tile_ptr[t + 1], 64 at a time, which are asked for
+// behind the tile's entries.  A row with nonzeros sets the bit_flag of its first
+// (Section 3.4; the scatter of Algorithm 3 step 1) in LDS, one without marks the
+// tile (Algorithm 4, second loop: the rows of the inclusive range that begin after
+// the tile does).  A range of more than FLAG_ROWS_MAX rows is nearly all empty
+// rows, perhaps millions: there every lane searches for the row starts in its
+// column instead.
 // ----------------------------------------------------------------------------
 template <int SIGMA>
 struct TransposeShape {
@@ -711,11 +712,24 @@ __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_wave_barrier();
 }
 
+constexpr int FLAG_ROWS_MAX = 4096;
+
+// What the forward pass needs of the conversion beside the entries themselves.
+struct DescJob {
+    int32_t m, wide;                    // wide: 64-bit row_ptr, tile_ptr and eop
+    const void* row_ptr;
+    void* tile_ptr;
+    uint32_t* desc;
+    void* eop;
+    const uint32_t* words;              // of k_prepare
+    int32_t nb_tiles, nb_rows;
+    int32_t* first_col;                 // every tile's first column, for tile_order, or NULL
+};
+
 template <int SIGMA, bool BACK, typename VT>
 __global__ void __launch_bounds__(TransposeShape<SIGMA>::WAVES * OMEGA)
 k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __restrict__ val,
-            uint32_t* __restrict__ status, int32_t* __restrict__ last_col, VT* __restrict__ last_val, int rec_bytes,
-            const void* __restrict__ tile_ptr, uint32_t* __restrict__ desc, void* __restrict__ eop, int wide) {
+            uint32_t* __restrict__ status, int32_t* __restrict__ last_col, VT* __restrict__ last_val, int rec_bytes, const DescJob job) {
     constexpr int T = OMEGA * SIGMA;
     constexpr int YBITS = 32 - __builtin_clz(uint32_t(T - 1));        // ceil(log2(64*sigma))
     constexpr int W = (SIGMA + SBITS + YBITS + 31) / 32;
@@ -733,31 +747,49 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
     // matrix with a tile far into a row never uses (the scan kernel has said so by now).
     // Only a group's last tile is looked at from outside its workgroup; the last
     // complete tile also by the workgroup of the incomplete one.
-    const uint32_t st_heads = *status;
-    const bool keep_last = !BACK && last_val && last_col && !(st_heads & STATUS_NEEDS_CARRY) &&
-                           (wave == WAVES - 1 || tile == pc - 1);
-    const bool keep_far = keep_last && (st_heads & STATUS_FAR_HEADS) && rec_bytes == LAST_REC_BYTES;   // nobody reads the far part otherwise
+    bool keep_last = !BACK && last_val && last_col && active && (wave == WAVES - 1 || tile == pc - 1);
+    bool keep_far = false;
+    if constexpr (!BACK) {
+        if (keep_last) {
+            uint32_t found = 0;
+            for (int w = lane; w < job.nb_tiles; w += OMEGA) found |= job.words[w];
+            keep_last = !__any(found & TILES_FAR);
+            keep_far = keep_last && rec_bytes == LAST_REC_BYTES && __any(found & TILES_FAR_HEADS);   // nobody reads the far part otherwise
+        }
+    }
     const size_t rec = size_t(tile) / WAVES;
 
-    // ---- conversion step 3b rides along (forward pass): the tile's flag words,
-    // as k_rows left them, are asked for now and turned into descriptors below
-    uint64_t flags = 0;
-    bool marked = false;
-    const size_t dbase = size_t(active ? tile : 0) * W * OMEGA + lane;
+    // ---- the row the tile starts in and the next tile's (either may carry its mark
+    // by now: masked).  Clamped: a row_ptr that is not monotone gives anything.
+    const auto row_at = [&](int r) -> int64_t {
+        return job.wide ? static_cast<const int64_t*>(job.row_ptr)[r] : int64_t(static_cast<const int32_t*>(job.row_ptr)[r]);
+    };
+    const auto tile_row = [&](int t) -> int {
+        const uint64_t v = job.wide ? static_cast<const uint64_t*>(job.tile_ptr)[t] & Index<int64_t>::ROWMASK
+                                    : uint64_t(static_cast<const uint32_t*>(job.tile_ptr)[t] & Index<int32_t>::ROWMASK);
+        return v < uint64_t(job.m) ? int(v) : job.m;
+    };
+    int row0 = 0, row1 = 0;              // rows row0 + 1 .. row1 begin in the tile, or are empty rows of its range
     if constexpr (!BACK) {
-        if (active && desc) {
-            flags = desc[dbase];
-            if (SIGMA > 32) flags |= uint64_t(desc[dbase + OMEGA]) << 32;
-            marked = wide ? (static_cast<const uint64_t*>(tile_ptr)[tile] >> 63) != 0
-                          : (static_cast<const uint32_t*>(tile_ptr)[tile] >> 31) != 0;
+        if (active) {
+            row0 = tile_row(tile);
+            row1 = tile_row(tile + 1);
         }
     }
 
     // ---- val: HBM -> registers -> LDS -> registers -> HBM
     VT v[SIGMA];
+    int64_t begins = 0, ends = 0;        // of row row0 + 1 + lane
     if (active) {
 #pragma unroll
         for (int k = 0; k < SIGMA; k++) v[k] = __builtin_nontemporal_load(&val[base + k * OMEGA + lane]);
+        if constexpr (!BACK) {
+            if (row1 >= job.m) row1 = job.m - 1;
+            if (lane < row1 - row0) {
+                begins = row_at(row0 + 1 + lane);
+                ends = row_at(row0 + 2 + lane);
+            }
+        }
         // the tile's last LOOK_MAX entries, still in CSR order (entry k*64 + lane of
         // the tile is v[k] here), for the SpMV's look-behind: near part, far part
         if constexpr (!BACK && look_sigma(SIGMA)) {
@@ -808,9 +840,7 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
             bad |= (c[k] < 0) | (c[k] >= n);
         }
         if constexpr (!BACK && look_sigma(SIGMA)) {
-            // (a matrix that never reads the records keeps every tile's first column in their place, for tile_order)
-            if (last_val && (st_heads & (STATUS_NEEDS_CARRY | STATUS_LONG_ROWS)) == (STATUS_NEEDS_CARRY | STATUS_LONG_ROWS) && lane == 0)
-                reinterpret_cast<int32_t*>(last_val)[tile] = c[0];
+            if (job.first_col && lane == 0) job.first_col[tile] = c[0];
             if (keep_last) {
                 int32_t* const near_c = last_col + rec * size_t(rec_bytes / 4);
                 int32_t* const far_c = near_c + FAR_COL_AT;
@@ -856,14 +886,57 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
     }
     if (!BACK && bad) raise_status(status, CSR5_STATUS_BAD_COL_IDX);
 
-    // ---- conversion step 3b, lane = tile column: forced first flag, y_offset =
-    // exclusive scan of the columns' flag counts, seg_offset = run of flag-less
-    // columns to the right (Algorithm 5; the scan and the run length are wavefront
-    // operations here), packing (Section 3.5), and the tile's segment count for
-    // the empty_offset layout.
+    // ---- conversion steps 2b, 3a and 3b, lane = tile column: the rows' flags, forced
+    // first flag, y_offset = exclusive scan of the columns' flag counts, seg_offset =
+    // run of flag-less columns to the right (Algorithm 5; the scan and the run length
+    // are wavefront operations here), packing (Section 3.5), and the tile's segment
+    // count for the empty_offset layout.
     if constexpr (!BACK) {
-        if (desc) {                                        // uniform over the grid
+        bool marked = false;
+        if (job.desc) {                                    // uniform over the grid
             if (active) {
+                using word_t = typename std::conditional<(SIGMA > 32), unsigned long long, uint32_t>::type;
+                word_t* const fl = reinterpret_cast<word_t*>(lds[wave]);      // one word per column; the entries have left
+                wave_sync_lds();
+                fl[lane] = 0;
+                wave_sync_lds();
+                const int64_t lo_e = int64_t(base);
+                const auto flag_at = [&](int64_t e) {
+                    const int w = int(e - lo_e), i = w / SIGMA;
+                    atomicOr(&fl[i], word_t(1) << (w - i * SIGMA));
+                };
+                if (row1 - row0 <= FLAG_ROWS_MAX) {        // uniform
+                    bool empty = false;
+                    for (int k = lane; k < row1 - row0; k += OMEGA) {      // row row0 + 1 + k
+                        if (k != lane) {
+                            begins = row_at(row0 + 1 + k);
+                            ends = row_at(row0 + 2 + k);
+                        }
+                        if (begins == ends) empty = true;
+                        else if (begins >= lo_e && begins < lo_e + T) flag_at(begins);
+                    }
+                    marked = __any(empty);
+                } else {
+                    marked = true;
+                    int64_t e = lo_e + lane * SIGMA;       // every start in [e, end) is this lane's
+                    const int64_t end = e + SIGMA;
+                    const auto next_start = [&](int64_t key) -> int64_t {      // the first row start above key
+                        int lo = row0, hi = row1 + 1;
+                        while (lo < hi) {
+                            const int mid = lo + ((hi - lo) >> 1);
+                            if (row_at(mid) <= key) lo = mid + 1; else hi = mid;
+                        }
+                        return row_at(lo);
+                    };
+                    for (e = next_start(e - 1); e < end && e >= lo_e;) {
+                        flag_at(e);
+                        const int64_t next = next_start(e);
+                        if (next <= e) break;              // not monotone: rejected input
+                        e = next;
+                    }
+                }
+                wave_sync_lds();
+                uint64_t flags = fl[lane];
                 if (lane == 0) flags |= 1u;
                 const int cnt = __popcll(flags);
                 int incl = cnt;
@@ -882,12 +955,17 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
                 constexpr int YSH = SIGMA + SBITS;  // <= 54
                 const uint64_t lo = flags | (uint64_t(so) << SIGMA) | (uint64_t(yo) << YSH);
                 const uint64_t hi = (YSH + YBITS > 64) ? (uint64_t(yo) >> (64 - YSH)) : 0ull;
-                desc[dbase] = uint32_t(lo);
-                if (W > 1) desc[dbase + OMEGA] = uint32_t(lo >> 32);
-                if (W > 2) desc[dbase + 2 * OMEGA] = uint32_t(hi);
+                uint32_t* const desc = job.desc + size_t(tile) * W * OMEGA + lane;
+                desc[0] = uint32_t(lo);
+                if (W > 1) desc[OMEGA] = uint32_t(lo >> 32);
+                if (W > 2) desc[2 * OMEGA] = uint32_t(hi);
                 if (lane == 0) {
-                    if (wide) static_cast<int64_t*>(eop)[tile] = marked ? total : 0;
-                    else static_cast<int32_t*>(eop)[tile] = marked ? total : 0;
+                    if (job.wide) static_cast<int64_t*>(job.eop)[tile] = marked ? total : 0;
+                    else static_cast<int32_t*>(job.eop)[tile] = marked ? total : 0;
+                    if (marked) {                          // (a neighbour that reads the word masks the bit)
+                        if (job.wide) static_cast<uint64_t*>(job.tile_ptr)[tile] |= Index<int64_t>::DIRTY;
+                        else static_cast<uint32_t*>(job.tile_ptr)[tile] |= Index<int32_t>::DIRTY;
+                    }
                 }
             }
             // "some tile is marked" (and hence "some row is empty"): once per workgroup, not
@@ -899,6 +977,10 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
             __syncthreads();
             if (threadIdx.x == 0 && wg_met_marked)
                 raise_status(status, CSR5_STATUS_HAS_DIRTY | CSR5_STATUS_HAS_EMPTY_ROWS | STATUS_SCAN_NEEDED);
+        }
+        if (blockIdx.x == 0) {
+            if (job.wide) collect_words<int64_t>(job.words, job.nb_tiles, job.nb_rows, pc, static_cast<uint64_t*>(job.tile_ptr), status);
+            else collect_words<int32_t>(job.words, job.nb_tiles, job.nb_rows, pc, static_cast<uint32_t*>(job.tile_ptr), status);
         }
     }
 }
@@ -1752,14 +1834,13 @@ hipError_t launch_spmv(const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
 
 template <int SIGMA, bool BACK, typename VT>
 hipError_t launch_transpose(const Geom& g, int n, int64_t nnz, int32_t* col_idx, VT* val,
-                            uint32_t* status, int32_t* last_col, VT* last_val, const void* tile_ptr,
-                            uint32_t* desc, void* eop, int wide, hipStream_t s) {
+                            uint32_t* status, int32_t* last_col, VT* last_val, const DescJob& job, hipStream_t s) {
     constexpr int WAVES = TransposeShape<SIGMA>::WAVES;
     uint32_t nb = uint32_t((g.pc + WAVES - 1) / WAVES);
-    if (nb == 0) nb = BACK ? 0 : 1;   // forward pass still validates the tail's columns
+    if (nb == 0) nb = BACK ? 0 : 1;   // forward pass still validates the tail's columns and collects the words of k_prepare
     if (nb == 0) return hipSuccess;
     hipLaunchKernelGGL((k_transpose<SIGMA, BACK, VT>), dim3(nb), dim3(WAVES * OMEGA), 0, s, g.pc, n, nnz,
-                       col_idx, val, status, last_col, last_val, record_bytes(nnz), tile_ptr, desc, eop, wide);
+                       col_idx, val, status, last_col, last_val, record_bytes(nnz), job);
     return hipGetLastError();
 }
 
@@ -1882,8 +1963,11 @@ struct csr5_handle_s {
 
 namespace {
 
+constexpr int WORDS_RESERVED = 8192;
+static_assert(PREP_TILE_WG + PREP_ROW_WG <= WORDS_RESERVED, "words of k_prepare");
+
 struct Layout {
-    size_t off_tile_ptr, off_tile_head, off_span, off_desc, off_eop, off_eo, off_carry, off_last, off_scan, off_wg_far, off_status, total;
+    size_t off_tile_ptr, off_tile_head, off_span, off_desc, off_eop, off_eo, off_carry, off_last, off_scan, off_words, off_status, total;
     bool has_last;
     size_t ndesc, eo_cap, carry_slot_bytes;
 };
@@ -1910,7 +1994,7 @@ Layout make_layout(int32_t m, int64_t nnz, const Geom& g, bool wide) {
     const size_t groups = (size_t(g.pc) + tile_group_waves(g.sigma) - 1) / tile_group_waves(g.sigma);
     L.off_last = o;     o += L.has_last ? align256(groups * size_t(record_bytes(nnz))) : 0;
     L.off_scan = o;     o += align256((size_t(g.pc) / SCAN_CHUNK + 1) * isz);   // chunk totals of the scan
-    L.off_wg_far = o;   o += align256(size_t(MAX_TILE_PTR_WG) * 4);              // one word per workgroup of k_tile_ptr
+    L.off_words = o;    o += size_t(WORDS_RESERVED) * 4;                          // one word per workgroup of k_prepare
     L.off_status = o;   o += 256;
     L.total = o;
     return L;
@@ -2055,44 +2139,38 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     IT* const eop = static_cast<IT*>(h->eop);
 
     hipError_t e = hipSuccess;
-    uint32_t* const wg_far = reinterpret_cast<uint32_t*>(basep + L.off_wg_far);
-    int n_far_wg = 0;
-    {   // step 2a (+ clearing)
-        size_t work = L.ndesc > size_t(g.p) + 1 ? L.ndesc : size_t(g.p) + 1;
-        size_t nb = (work + 255) / 256;
-        if (nb > MAX_TILE_PTR_WG) nb = MAX_TILE_PTR_WG;
-        // only the workgroups that hold tile boundaries (thread g of the grid takes tile g first) have anything to say
-        const size_t with_tiles = (size_t(g.p) + 1 + 255) / 256;
-        n_far_wg = int(with_tiles < nb ? with_tiles : nb);
-        hipLaunchKernelGGL(k_tile_ptr<IT>, dim3(uint32_t(nb)), dim3(256), 0, s, m, row_ptr, g.T, g.p, g.pc,
-                           tile_group_waves(g.sigma), int64_t(nnz) <= LOOK_FAR_MAX_NNZ ? LOOK_MAX : LOOK, tile_ptr, h->tile_head, wg_far, h->tile_desc, L.ndesc,
+    uint32_t* const words = reinterpret_cast<uint32_t*>(basep + L.off_words);
+    // The tile order goes along with the scan where it may pay and the host will know of it (see below).  It sorts by
+    // the tiles' first columns, which the transposition leaves in the first carry array, and takes the records' place.
+    OrderJob order = {n, 0, nullptr, nullptr, h->status + 1};
+    if (!(flags & CSR5_FLAG_NO_HOST_CHECK) && h->last_val && h->aux_form == 0 && g.pc >= ORDER_MIN_TILES &&
+        size_t(n) * sizeof(VT) >= ORDER_MIN_X_BYTES) {
+        order.align = NUM_XCD * tile_group_waves(g.sigma);
+        order.first_col = static_cast<const int32_t*>(h->carry);
+        order.order = static_cast<uint32_t*>(h->last_val);             // pc + align words: the records have 96 bytes and more per tile
+    }
+    DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.align ? static_cast<int32_t*>(h->carry) : nullptr};
+    {   // step 2a
+        const size_t nb_tiles = (size_t(g.p) + 1 + PREP_THREADS - 1) / PREP_THREADS;
+        const size_t nb_rows = (size_t(m) + PREP_THREADS * PREP_UNROLL - 1) / (PREP_THREADS * PREP_UNROLL);
+        job.nb_tiles = int(nb_tiles < PREP_TILE_WG ? nb_tiles : PREP_TILE_WG);
+        job.nb_rows = int(nb_rows < PREP_ROW_WG ? nb_rows : PREP_ROW_WG);
+        hipLaunchKernelGGL(k_prepare<IT>, dim3(uint32_t(job.nb_tiles + job.nb_rows)), dim3(PREP_THREADS), 0, s, m, nnz, row_ptr, g.T, g.p, g.pc,
+                           tile_group_waves(g.sigma), int64_t(nnz) <= LOOK_FAR_MAX_NNZ ? LOOK_MAX : LOOK, uint32_t(job.nb_tiles), tile_ptr,
+                           h->tile_head, words,
                            reinterpret_cast<uint32_t*>(basep + L.off_carry + slot_off_arrived(g, tile_group_waves(g.sigma))),
                            reinterpret_cast<uint64_t*>(basep + L.off_carry + slot_off_meet(g)), L.carry_slot_bytes,
                            one_launch_fits(g.sigma, g.p) ? int(CARRY_SLOTS) : 0, reinterpret_cast<uint2*>(basep + L.off_span), h->status);
         e = hipGetLastError();
     }
-    if (e == hipSuccess && m > 0) {   // steps 2b + 3a
-        hipLaunchKernelGGL(k_rows<IT>, dim3(uint32_t((size_t(m) + 255) / 256)), dim3(256), 0, s, m, nnz,
-                           row_ptr, g.sigma, g.T, g.W, g.p, g.pc, tile_ptr, h->tile_desc, wg_far, n_far_wg, h->status);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess && nnz > 0) {   // steps 3b (descriptors, inside the same kernel) + 4
+    if (e == hipSuccess) {            // steps 2b, 3a, 3b (descriptors, inside the same kernel) + 4
         switch (sigma) {
 #define X(S) case S: e = launch_transpose<S, false, VT>(g, n, nnz, col_idx, val, h->status, h->last_col,      \
-                                                        static_cast<VT*>(h->last_val), tile_ptr, h->tile_desc, \
-                                                        eop, wide ? 1 : 0, s); break;
+                                                        static_cast<VT*>(h->last_val), job, s); break;
             CSR5_FOR_SIGMA(X)
 #undef X
             default: e = hipErrorInvalidValue;
         }
-    }
-    // The tile order goes along with the scan where it may pay and the host will know of it (see below)
-    OrderJob order = {n, 0, nullptr, nullptr, h->status + 1};
-    if (!(flags & CSR5_FLAG_NO_HOST_CHECK) && h->last_val && h->aux_form == 0 && g.pc >= ORDER_MIN_TILES &&
-        size_t(n) * sizeof(VT) >= ORDER_MIN_X_BYTES) {
-        order.align = NUM_XCD * tile_group_waves(g.sigma);
-        order.first_col = static_cast<const int32_t*>(h->last_val);
-        order.order = static_cast<uint32_t*>(h->last_val) + g.pc;      // pc + align words: the records have 96 bytes and more per tile
     }
     if (e == hipSuccess && g.pc <= SCAN_SINGLE) {
         hipLaunchKernelGGL(k_scan_eop<IT>, dim3(order.align ? 2 : 1), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr, h->status, order);
@@ -2384,9 +2462,9 @@ int csr5_to_csr(csr5_handle_t h, void* hip_stream) {
         switch (h->g.sigma) {
 #define X(S) case S: e = (h->dtype == CSR5_DTYPE_F32)                                                            \
         ? launch_transpose<S, true, float>(h->g, h->n, h->nnz, h->col_idx, static_cast<float*>(h->val), h->status,     \
-                                           nullptr, nullptr, nullptr, nullptr, nullptr, 0, s)                           \
+                                           nullptr, nullptr, DescJob{}, s)                                             \
         : launch_transpose<S, true, double>(h->g, h->n, h->nnz, h->col_idx, static_cast<double*>(h->val), h->status,   \
-                                            nullptr, nullptr, nullptr, nullptr, nullptr, 0, s);                         \
+                                            nullptr, nullptr, DescJob{}, s);                                            \
         break;
             CSR5_FOR_SIGMA(X)
 #undef X
