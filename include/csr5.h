@@ -109,8 +109,7 @@ size_t csr5_workspace_bytes(int32_t m, int32_t nnz, int32_t sigma);
  *               BORROWED: read now and again by every csr5_spmv (the format
  *               keeps it unchanged, Section 1); must outlive the handle.
  *   col_idx     int32[nnz], values in [0, n).  Any int32-aligned address (a view into a
- *               larger array is fine); a 16-byte aligned one lets the SpMV read it with
- *               wider loads.
+ *               larger array is fine).
  *   val         double[nnz].
  *               Both MODIFIED IN PLACE: inside every complete tile the entries
  *               go from CSR order to tile column-major order (Section 3.1);

@@ -714,6 +714,32 @@ __device__ __forceinline__ void wave_sync_lds() {
 
 constexpr int FLAG_ROWS_MAX = 4096;
 
+// A tile's arrays through buffer descriptors: the address of a load is the
+// descriptor, a lane offset that all loads of the tile share and a constant, so the
+// loads of a tile leave back to back with a quarter of the address arithmetic; any
+// dword-aligned base will do for 16-byte loads (a col_idx that is a view at an odd
+// offset took four loads each); nothing outside the tile is read.  Measured on the
+// tile kernel (plain 64-bit addresses before): 100 000 rows of 100 random columns
+// 65.4 -> 58.4 us, 30 000 rows of 201 38.2 -> 36.3, dense rows with the tile order
+// 226 -> 200, 60 000 short rows 11.8 -> 10.9, 100^3 stencil 61.6 -> 61.0, single
+// precision 44.7 -> 44.1.
+// Non-temporal: without it the streams stay in the 256 MB memory-side cache as far
+// as they fit, and one matrix multiplied again and again gains (90^3 stencil 43.2 ->
+// 37.7 us, 100^3 with half of its tiles 61.0 -> 51.5), but matrices used in turn,
+// and the first product of any, lose (44.8 -> 52.1, 61.2 -> 67.5): not known here
+// which it is.
+constexpr int POLICY_STREAM = 2;                          // nt
+template <typename P>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_buffer(P* first, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<typename std::remove_const<P>::type*>(first), 0, bytes, 0x00020000);
+}
+template <typename P>
+__device__ __forceinline__ P stream_from(__amdgpu_buffer_rsrc_t r, int offset) {
+    if constexpr (sizeof(P) == 16) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, POLICY_STREAM));
+    else if constexpr (sizeof(P) == 8) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b64(r, offset, 0, POLICY_STREAM));
+    else return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, POLICY_STREAM));
+}
+
 // What the forward pass needs of the conversion beside the entries themselves.
 struct DescJob {
     int32_t m, wide;                    // wide: 64-bit row_ptr, tile_ptr and eop
@@ -1374,44 +1400,32 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
     // its owner lane at all (see the gather below), so it is read with 16-byte
     // loads in plain memory order: 4 steps of the tile per instruction.
     const size_t tile_base = size_t(tile) * T;
-    constexpr int NC4 = (SIGMA + 3) / 4;                  // 16-byte col loads per lane
+    constexpr int NC4 = (SIGMA + 3) / 4;                  // 16-byte col loads per lane (past the tile's end: 0)
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
     i32x4 c4[NC4];
-    if ((reinterpret_cast<uintptr_t>(col_idx) & 15) == 0) {   // uniform
-        const i32x4* col4 = reinterpret_cast<const i32x4*>(col_idx + tile_base);
-#pragma unroll
-        for (int q = 0; q < NC4; q++) {
-            const int e4 = q * OMEGA + lane;              // index of the int4 inside the tile
-            c4[q] = (SIGMA % 4 == 0 || e4 < T / 4) ? __builtin_nontemporal_load(&col4[e4]) : i32x4{0, 0, 0, 0};
-        }
-    } else {      // col_idx is a view at an odd offset into a caller's array: the same four entries, one by one
-        const int32_t* col1 = col_idx + tile_base;
-#pragma unroll
-        for (int q = 0; q < NC4; q++) {
-            const int e4 = q * OMEGA + lane;
-            c4[q] = i32x4{0, 0, 0, 0};
-            if (SIGMA % 4 == 0 || e4 < T / 4) {
-                c4[q].x = __builtin_nontemporal_load(&col1[4 * e4 + 0]);
-                c4[q].y = __builtin_nontemporal_load(&col1[4 * e4 + 1]);
-                c4[q].z = __builtin_nontemporal_load(&col1[4 * e4 + 2]);
-                c4[q].w = __builtin_nontemporal_load(&col1[4 * e4 + 3]);
-            }
-        }
-    }
     VT v[SIGMA];
+    const uint32_t* dp = tile_desc + size_t(tile) * W * OMEGA;
+    uint32_t dw[W];
+    {
+        const auto cols = tile_buffer(col_idx + tile_base, T * 4);
+        const auto vals = tile_buffer(val + tile_base, T * int(sizeof(VT)));
+        const auto descs = tile_buffer(dp, W * OMEGA * 4);
 #pragma unroll
-    for (int j = 0; j < SIGMA; j++) v[j] = __builtin_nontemporal_load(&val[tile_base + j * OMEGA + lane]);
+        for (int q = 0; q < NC4; q++) c4[q] = stream_from<i32x4>(cols, (q * OMEGA + lane) * 16);
+#pragma unroll
+        for (int j = 0; j < SIGMA; j++) v[j] = stream_from<VT>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
+#pragma unroll
+        for (int w = 0; w < W; w++) dw[w] = stream_from<uint32_t>(descs, (w * OMEGA + lane) * 4);
+    }
 
     // ---- descriptor
     const tp_t tp = tile_ptr[tile];
     const bool dirty = (tp & Index<IT>::DIRTY) != 0;
     const tp_t row0_wide = tp & Index<IT>::ROWMASK;
     const uint32_t row0 = uint32_t(row0_wide);
-    const uint32_t* dp = tile_desc + size_t(tile) * W * OMEGA + lane;
-    uint64_t lo = __builtin_nontemporal_load(dp);
-    if (W > 1) lo |= uint64_t(__builtin_nontemporal_load(dp + OMEGA)) << 32;
-    uint64_t hi = 0;
-    if (W > 2) hi = __builtin_nontemporal_load(dp + 2 * OMEGA);
+    uint64_t lo = dw[0], hi = 0;
+    if constexpr (W > 1) lo |= uint64_t(dw[1]) << 32;
+    if constexpr (W > 2) hi = dw[2];
     constexpr int FLAG_BITS = 8 * int(sizeof(flag_t));
     constexpr flag_t FLAG_MASK = (SIGMA == FLAG_BITS) ? ~flag_t(0) : flag_t((flag_t(1) << (SIGMA % FLAG_BITS)) - 1);
     const flag_t flags = flag_t(lo) & FLAG_MASK;
@@ -2071,8 +2085,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (m < 0 || n < 0 || nnz < 0) return CSR5_EINVAL;
     if (!row_ptr) return CSR5_EINVAL;                      // row_ptr has m+1 >= 1 entries
     if (nnz > 0 && (!col_idx || !val || m == 0 || n == 0)) return CSR5_EINVAL;
-    // natural alignment of every element is all the kernels need (the SpMV reads
-    // col_idx sixteen bytes at a time when its base allows that, else four)
+    // natural alignment of every element is all the kernels need
     if ((reinterpret_cast<uintptr_t>(col_idx) & 3) || (reinterpret_cast<uintptr_t>(val) & (sizeof(VT) - 1)) ||
         (reinterpret_cast<uintptr_t>(row_ptr) & (sizeof(IT) - 1))) return CSR5_EINVAL;
     if (sigma == 0) sigma = csr5_sigma_auto(nnz, m);
