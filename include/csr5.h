@@ -160,7 +160,13 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * common rows through LDS, workgroups meet at a word of the array per row (one
  * atomic exchange each when the row touches two workgroups' tiles, a counter
  * otherwise), nobody waits, and whoever comes last stores the row -- again ONE
- * kernel.  Which of these, and whether rows without nonzeros need
+ * kernel.  A matrix of at least 2048 complete tiles (8 <= sigma <= 32), half of which
+ * and more lie inside a single row, whose x has 4 MiB and more is taken by column
+ * instead, its tiles ordered by their first columns: in two kernels, whatever its
+ * size.  The order is laid out by a conversion that blocks; after one with
+ * CSR5_FLAG_NO_HOST_CHECK (or with a flag that fixes the form) the SpMV of such a
+ * matrix is the one described before, and csr5_status does not change that.
+ * Which of these, and whether rows without nonzeros need
  * their zeros written, is in the conversion's status word: the library launches
  * only what the matrix needs once the host has seen that word (csr5_convert and
  * csr5_convert_ex without CSR5_FLAG_NO_HOST_CHECK read it; after an asynchronous
@@ -170,8 +176,9 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * and y must not overlap.  Asynchronous.  Summation order differs from CSR
  * order; rows that the second kernel sums with more than one wavefront and
  * rows cut inside the incomplete tile are added up atomically, so their last
- * bits may differ between runs (the one-kernel forms add in a fixed order).  The handle holds four auxiliary arrays, taken
- * in turn by successive calls: up to four SpMVs on ONE handle may be in flight at
+ * bits may differ between runs.  The one-kernel forms add in a fixed order, and so
+ * does the second kernel of a matrix that is taken by column where it would be one
+ * kernel otherwise.  The handle holds four auxiliary arrays, taken in turn by successive calls: up to four SpMVs on ONE handle may be in flight at
  * the same time (on different streams); a fifth must be ordered after the first.
  */
 int csr5_spmv(csr5_handle_t h, const double *x, double *y);

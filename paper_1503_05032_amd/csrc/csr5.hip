@@ -1782,10 +1782,18 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
 // is the same row R form a run (a row longer than a tile); a shuffle scan sums
 // the carries of a run and its last lane adds the total to y[R], which already
 // holds the part computed by the tile R starts in.  A run wholly inside one
-// wavefront is a plain read-modify-write (nobody else touches y[R] now); a run
-// cut by a wavefront boundary uses atomic adds, which commute.
+// wavefront is a plain read-modify-write (nobody else touches y[R] now).  A run
+// cut by a wavefront boundary uses atomic adds, which commute but arrive in any
+// order, or, with FIXED, the wavefront that holds the run's first tile adds up the
+// rest of the run by itself: the same bits on every call, for matrices that would
+// have them from the one-launch form if their tiles were not taken by column
+// (tile_order).  The rest is usually shorter than a wavefront of tiles, which is
+// asked for with the wavefront's own; beyond that it is a serial chain, RUN_AHEAD
+// wavefronts of tiles per round trip.
 // ----------------------------------------------------------------------------
-template <typename VT, typename IT>
+constexpr int RUN_AHEAD = 16;
+
+template <typename VT, typename IT, bool FIXED>
 __global__ void __launch_bounds__(256)
 k_spmv_fixup(int m, int ntiles,
              const typename Index<IT>::tp_t* __restrict__ tile_ptr, const VT* __restrict__ carry,
@@ -1806,6 +1814,12 @@ k_spmv_fixup(int m, int ntiles,
     VT cs = live ? carry[gid] : VT(0);
     const uint32_t r_after = (gid + 1 < ntiles) ? first_row(gid + 1) : 0xffffffffu;
     const uint32_t r_before = (t0 > 0 && t0 < ntiles) ? first_row(t0 - 1) : 0xffffffffu;
+    uint32_t R2 = 0xffffffffu;                            // the next wavefront's tiles
+    VT c2 = VT(0);
+    if (FIXED && gid + OMEGA < ntiles) {
+        R2 = first_row(gid + OMEGA);
+        c2 = carry[gid + OMEGA];
+    }
     if ((st & BAD_BITS) || t0 >= ntiles) return;
 #pragma unroll
     for (int d = 1; d < OMEGA; d <<= 1) {
@@ -1815,11 +1829,37 @@ k_spmv_fixup(int m, int ntiles,
     }
     const uint32_t rnext = __shfl_down(R, 1, OMEGA);
     const uint32_t rfirst = __shfl(R, 0, OMEGA);
+    if constexpr (FIXED) {
+        const uint32_t rlast = __shfl(R, OMEGA - 1, OMEGA);
+        const bool began_before = rfirst == rlast && r_before == rlast;
+        if (__shfl(r_after, OMEGA - 1, OMEGA) == rlast && !began_before) {      // uniform
+            VT rest = R2 == rlast ? c2 : VT(0);
+            bool goes_on = __shfl(R2, OMEGA - 1, OMEGA) == rlast;
+            for (int t = t0 + 2 * OMEGA; goes_on; t += RUN_AHEAD * OMEGA) {     // behind the last tile every row is 0xfff...
+                uint32_t r[RUN_AHEAD];
+                VT c[RUN_AHEAD];
+#pragma unroll
+                for (int q = 0; q < RUN_AHEAD; q++) {
+                    const int tile = t + q * OMEGA + lane;
+                    r[q] = tile < ntiles ? first_row(tile) : 0xffffffffu;
+                    c[q] = tile < ntiles ? carry[tile] : VT(0);
+                }
+#pragma unroll
+                for (int q = 0; q < RUN_AHEAD; q++)
+                    if (r[q] == rlast) rest += c[q];
+                goes_on = __shfl(r[RUN_AHEAD - 1], OMEGA - 1, OMEGA) == rlast;
+            }
+            rest = wave_sum(rest);
+            if (lane == OMEGA - 1) cs += rest;
+        }
+    }
     const bool run_end = live && ((lane == OMEGA - 1) || (rnext != R));
     if (run_end && cs != VT(0) && R < uint32_t(m)) {
         const bool ext_left = (rfirst == R) && (r_before == R);
         const bool ext_right = (lane == OMEGA - 1) && (r_after == R);
-        if (ext_left || ext_right) atomic_add_fp(&y[R], cs);
+        if (FIXED) {
+            if (!ext_left) y[R] += cs;                    // (else part of the wavefront's sum where the run begins)
+        } else if (ext_left || ext_right) atomic_add_fp(&y[R], cs);
         else y[R] += cs;
     }
 }
@@ -2370,6 +2410,10 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     const bool one_pays = h->g.p <= ONE_LAUNCH_ANY_TILES || h->nnz / (h->m > 0 ? h->m : 1) < ONE_LAUNCH_SHORT_ROWS;
     const bool one = !carry_mem && known >= 0 && !can_look && h->span && !h->order &&
                      (h->aux_form == 2 || (h->aux_form == 0 && one_pays));
+    // A matrix whose tiles are taken by column and that would take that form otherwise has its sums added in a fixed
+    // order as well (second kernel 2.8 us either way).  Not where two kernels are the rule anyway: a row of 29 000 tiles
+    // took the chain 70 us with RUN_AHEAD = 8, the atomics 7.5.
+    const bool fixed = h->order && h->span && one_pays;
     uint64_t* const meet = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(carry) + slot_off_meet(h->g));
     uint32_t* const arrived = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(carry) + slot_off_arrived(h->g, tile_group_waves(h->g.sigma)));
 #define ARGS h->g, h->m, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
@@ -2392,8 +2436,8 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     if ((which & LAUNCH_FIXUP) && carries && !one && h->g.p > 0) {
         int ntiles = h->g.p;                                  // one thread per tile
         size_t nb = (size_t(ntiles) + 255) / 256;
-        hipLaunchKernelGGL((k_spmv_fixup<VT, IT>), dim3(uint32_t(nb)), dim3(256), 0, s, h->m, ntiles,
-                           tile_ptr, carry, y, h->status);
+        hipLaunchKernelGGL((fixed ? k_spmv_fixup<VT, IT, true> : k_spmv_fixup<VT, IT, false>), dim3(uint32_t(nb)), dim3(256), 0, s,
+                           h->m, ntiles, tile_ptr, carry, y, h->status);
         if (hipGetLastError() != hipSuccess) return CSR5_EHIP;
     }
     return CSR5_OK;

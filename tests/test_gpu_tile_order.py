@@ -65,3 +65,30 @@ def test_long_rows_single_precision():
     # a term passes through the walk, the tile's scan and the sum over a row's 20 tiles at most: fewer than 64 additions of 2^-24 each
     assert np.all(np.abs(y.cpu().numpy() - ref) <= 1e-5 * s + 1e-30)
     B.csr5_free(h)
+
+
+@pytest.mark.parametrize("sigma,tiles,long", [(8, 2050, 0), (16, 6200, 0), (8, 8_000, 690_000), (16, 5_500, 690_000)])
+def test_long_rows_same_bits_on_every_call(sigma, tiles, long):
+    """A matrix taken by column that would otherwise be one kernel (short rows on average, or at most 6144 tiles)
+    returns the same bits on every call: rows of 5 to 20 tiles, cut by the 64-tile stretches of the second kernel,
+    and one of `long` entries (1347 and 673 tiles: its sum takes 16 * 64 tiles at a time).  No incomplete tile: its
+    rows are summed atomically."""
+    a = _matrix(sigma, tiles, 0, 700_001, seed=tiles)
+    if long:                                             # some hundred rows in the middle become one
+        lens = np.diff(a.row_ptr).astype(np.int64)
+        at = len(lens) // 2
+        end = at + int(np.searchsorted(np.cumsum(lens[at:]), long))
+        lens = np.concatenate([lens[:at], [lens[at:end].sum()], lens[end:]])
+        assert lens.max() > 2 * 64 * 64 * sigma
+        a = wl.from_row_lengths(lens, 700_001, seed=1, name="one_long")
+    assert a.nnz == tiles * 64 * sigma
+    d = DeviceCsr(a)
+    h = convert(d, sigma=sigma)
+    check_spmv(d, h, (a.name, tiles))
+    first = d.y.clone()
+    for call in range(30):
+        for spmv in (B.csr5_spmv_ex, B.csr5_spmv_static):
+            d.y.fill_(float("nan"))
+            spmv(h, d.x, d.y)
+            assert torch.equal(d.y, first), (call, int((d.y != first).sum()))
+    B.csr5_free(h)
