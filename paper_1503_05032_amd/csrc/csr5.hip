@@ -36,10 +36,6 @@ constexpr uint32_t STATUS_FAR_HEADS = 1u << 18;
 // a single row (the tile order by columns may pay, see tile_order).
 constexpr uint32_t STATUS_LONG_ROWS = 1u << 19;
 constexpr int ORDER_MIN_SHARE = 2;
-// Internal status bit: fewer than one in FEW_LONG_SHARE complete tiles lies inside a
-// single row (see xcd_chunk_for).
-constexpr uint32_t STATUS_FEW_LONG_ROWS = 1u << 20;
-constexpr int FEW_LONG_SHARE = 16;
 // A tile whose first segment continues a row of the previous tile completes
 // that row itself when it can get at the row's head.  The tiles of one
 // workgroup of the tile kernel are neighbours and hand the finished head over
@@ -417,7 +413,6 @@ __device__ __forceinline__ void collect_words(const uint32_t* __restrict__ words
     if (threadIdx.x == 0) {
         const bool long_rows = pc > 0 && inside_rows >= uint32_t(pc / ORDER_MIN_SHARE + 1);
         const uint32_t raise = (far ? STATUS_NEEDS_CARRY : 0u) | (far_heads ? STATUS_FAR_HEADS : 0u) | (long_rows ? STATUS_LONG_ROWS : 0u) |
-                               (inside_rows < uint32_t(pc / FEW_LONG_SHARE) ? STATUS_FEW_LONG_ROWS : 0u) |
                                (bad ? CSR5_STATUS_BAD_ROW_PTR : 0u) | (first ? CSR5_STATUS_HAS_EMPTY_ROWS : 0u);
         if (raise) atomicOr(status, raise);
         if (tail) tile_ptr[pc] |= Index<IT>::DIRTY;
@@ -1920,12 +1915,12 @@ k_stream_floor(int m, int pc, int sigma, int W, uint32_t nb_tiles, uint32_t xcd_
 }
 
 template <int SIGMA, typename VT, typename IT, int MODE>
-hipError_t launch_spmv(const Geom& g, int m, IT nnz, const IT* row_ptr,
+hipError_t launch_spmv(const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
                        const typename Index<IT>::tp_t* tile_ptr,
                        const uint32_t* tile_desc, const IT* eop, const int32_t* eo,
                        const int32_t* col_idx, const VT* val, const VT* x, VT* y,
                        VT* carry, uint64_t* meet, uint32_t* arrived, const uint2* span, const uint32_t* status, const uint32_t* tile_head, const int32_t* last_col,
-                       const VT* last_val, bool zero_rows, uint32_t xcd_chunk, uint32_t far_mode,
+                       const VT* last_val, bool zero_rows, uint32_t far_mode,
                        const uint32_t* order, uint32_t order_second, uint32_t order_len, hipStream_t s) {
     constexpr int WAVES = TransposeShape<SIGMA>::WAVES;
     uint32_t nb_tiles = uint32_t((g.pc + WAVES - 1) / WAVES);
@@ -1936,6 +1931,12 @@ hipError_t launch_spmv(const Geom& g, int m, IT nnz, const IT* row_ptr,
     if (nb_zero > 512) nb_zero = 512;
     uint32_t nb = nb_tiles + has_tail + uint32_t(nb_zero);
     if (nb == 0) return hipSuccess;
+    const size_t x_bytes = size_t(n) * sizeof(VT);
+    uint32_t xcd_chunk = 0;                                        // contiguous eighths
+    if (x_bytes > XCD_CONTIGUOUS_MAX_X_BYTES)                      // x too large for that to pay
+        xcd_chunk = (int64_t(nnz) / (m > 0 ? m : 1) <= g.T / Y_LINE_ROWS) ? 1u : XCD_CHUNK;
+    else if (x_bytes < XCD_CONTIGUOUS_MIN_X_BYTES)                 // x at home in every L2
+        xcd_chunk = XCD_CHUNK;
     hipLaunchKernelGGL((k_spmv<SIGMA, VT, IT, MODE>), dim3(nb), dim3(WAVES * OMEGA), 0, s, m, nnz, g.pc, g.p, nb_tiles, has_tail,
                        xcd_chunk, far_mode, record_bytes(int64_t(nnz)), row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry,
                        meet, arrived, span, status, tile_head, last_col, last_val, order, order_second, order_len);
@@ -2364,24 +2365,6 @@ int csr5_convert(int32_t m, int32_t n, int32_t nnz, const int32_t* row_ptr, int3
 
 }  // extern "C"
 
-// Which of the three tile orders (see XCD_CONTIGUOUS_MAX_X_BYTES) a matrix gets.
-// Beyond the size of x up to which the contiguous one pays in general it still does
-// for a matrix known to have a few long rows, but next to no tile inside one: bands
-// with random rows among them, 1.4 to 8 M rows, contiguous against plain 166.7 against
-// 173.3 us, 334 against 350, 560 against 589, 1167 against 1233 (single precision 463
-// against 478).  With a third of the tiles inside long rows (power-law) it loses 3-4 %
-// as before, and so do stencils, which have no row too long for the look-behind, by
-// 1 % at 140^3.
-static uint32_t xcd_chunk_for(csr5_handle_t h, size_t value_bytes) {
-    const size_t x_bytes = size_t(h->n) * value_bytes;
-    if (x_bytes < XCD_CONTIGUOUS_MIN_X_BYTES) return XCD_CHUNK;                        // x at home in every L2
-    if (x_bytes <= XCD_CONTIGUOUS_MAX_X_BYTES) return 0;                               // contiguous eighths
-    if (h->nnz / (h->m > 0 ? h->m : 1) > h->g.T / Y_LINE_ROWS) return XCD_CHUNK;
-    const int32_t known = h->status_host.load(std::memory_order_relaxed);
-    constexpr uint32_t banded = STATUS_NEEDS_CARRY | STATUS_FEW_LONG_ROWS;
-    return known >= 0 && (uint32_t(known) & banded) == banded ? 0u : 1u;
-}
-
 // One SpMV: the tile kernel, then the carry fix-up if this matrix needs it.
 // `which` selects the launches (measurement only): bit 0 the tile kernel, bit 1
 // the fix-up.
@@ -2419,9 +2402,9 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     const bool fixed = h->order && h->span && one_pays;
     uint64_t* const meet = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(carry) + slot_off_meet(h->g));
     uint32_t* const arrived = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(carry) + slot_off_arrived(h->g, tile_group_waves(h->g.sigma)));
-#define ARGS h->g, h->m, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
+#define ARGS h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
              static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->span, h->status, h->tile_head, h->last_col, \
-             static_cast<const VT*>(h->last_val), zero_rows, xcd_chunk_for(h, sizeof(VT)), far_mode, h->order, h->order_second, h->order_len, s
+             static_cast<const VT*>(h->last_val), zero_rows, far_mode, h->order, h->order_second, h->order_len, s
     if (which & LAUNCH_TILES) {
 #define X(S) case S:                                                                                  \
         if (look_sigma(S) && can_look) e = launch_spmv<S, VT, IT, look_sigma(S) ? MODE_LOOK : MODE_CARRY>(ARGS); \
@@ -2516,7 +2499,13 @@ static int stream_floor(csr5_handle_t h, VT* y, hipStream_t s, int reps, float* 
     using tp_t = typename Index<IT>::tp_t;
     const Geom& g = h->g;
     const uint32_t nb_tiles = uint32_t((g.pc + FLOOR_WAVES - 1) / FLOOR_WAVES);
-    const uint32_t xcd_chunk = xcd_chunk_for(h, sizeof(VT));      // the tile order the SpMV uses for this matrix
+    // the tile order the SpMV uses for this matrix
+    const size_t x_bytes = size_t(h->n) * sizeof(VT);
+    uint32_t xcd_chunk = 0;
+    if (x_bytes > XCD_CONTIGUOUS_MAX_X_BYTES)
+        xcd_chunk = (h->nnz / (h->m > 0 ? h->m : 1) <= g.T / Y_LINE_ROWS) ? 1u : XCD_CHUNK;
+    else if (x_bytes < XCD_CONTIGUOUS_MIN_X_BYTES)
+        xcd_chunk = XCD_CHUNK;
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     int rc = CSR5_OK;
     for (int k = 0; k < 3 && rc == CSR5_OK; k++)
