@@ -163,7 +163,8 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * kernel.  A matrix of at least 2048 complete tiles (8 <= sigma <= 32), half of which
  * and more lie inside a single row, whose x has 4 MiB and more is taken by column
  * instead, its tiles ordered by their first columns: in two kernels, whatever its
- * size.  The order is laid out by a conversion that blocks; after one with
+ * size (not if more than three quarters of those tiles begin in an eighth of the
+ * columns).  The order is laid out by a conversion that blocks; after one with
  * CSR5_FLAG_NO_HOST_CHECK (or with a flag that fixes the form) the SpMV of such a
  * matrix is the one described before, and csr5_status does not change that.
  * Which of these, and whether rows without nonzeros need

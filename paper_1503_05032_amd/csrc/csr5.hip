@@ -506,6 +506,15 @@ __device__ __forceinline__ void scan_epilogue(int pc, int p, IT total, IT* __res
 // ORDER_MIN_SHARE: with half of the tiles inside one row and more the order wins,
 // with a third (power-law, whose long rows all gather from the same low columns)
 // it loses 15-20 %; below ORDER_MIN_TILES the chip takes all tiles at once.
+// ORDER_MAX_CROWD of ORDER_CROWD_PARTS: not where more of the tiles inside one row
+// begin in an eighth of the columns (in the 128 fullest of the 1024 buckets). There
+// the rows' dense stretches are short, in every L2 anyhow, and what gathers from far
+// apart ends up on one or two XCDs.  Rows whose columns thin out like a power law,
+// by number -> by column: a share of 0.83 252 -> 272 us, 0.87 170 -> 191 (single
+// precision 111 -> 158), 0.99 70 -> 91; but 0.74 240 -> 147, 0.70 31.3 -> 31.9 and
+// 315 -> 199, 0.57 375 -> 189, 0.23 (uniform) 490 -> 189 (given up: 0.82 193 -> 150,
+// 0.76 281 -> 270).  The same rows with their columns in random order, a share of
+// 0.2: 347 -> 196, 460 -> 302, 123 -> 108, single precision 227 -> 163.
 // The list: the tiles that hold row ends, in (nearly) their own order, then, from
 // a multiple of `align` on, the tiles inside one row by first column.  A counting
 // sort over 2 * ORDER_BUCKETS keys by one workgroup of SCAN_THREADS, next to the
@@ -515,12 +524,31 @@ __device__ __forceinline__ void scan_epilogue(int pc, int p, IT total, IT* __res
 // ----------------------------------------------------------------------------
 constexpr size_t ORDER_MIN_X_BYTES = 4u << 20;
 constexpr int ORDER_BUCKETS = SCAN_THREADS, ORDER_MIN_TILES = 2048;
+constexpr int ORDER_CROWD_PARTS = 4, ORDER_MAX_CROWD = 3, ORDER_CROWDED = ORDER_BUCKETS / 8;
 
 struct OrderJob {
     int32_t n, align;                // align = 0: nothing to do
     const int32_t* first_col;
     uint32_t *order, *plan;
 };
+
+// Whether the fullest eighth of ORDER_BUCKETS buckets, one per thread, holds more
+// than ORDER_MAX_CROWD of ORDER_CROWD_PARTS of all; no bucket holds more than `most`.
+__device__ bool crowded(uint32_t mine, uint32_t most) {
+    __shared__ uint32_t all, fullest;
+    if (threadIdx.x == 0) all = fullest = 0;
+    __syncthreads();
+    uint32_t lo = 0, hi = most;      // the smallest count that at most ORDER_CROWDED buckets exceed
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (__syncthreads_count(mine > mid) > ORDER_CROWDED) lo = mid + 1; else hi = mid;
+    }
+    const int above = __syncthreads_count(mine > lo);
+    atomicAdd(&all, mine);
+    if (mine > lo) atomicAdd(&fullest, mine);
+    __syncthreads();
+    return uint64_t(fullest + uint32_t(ORDER_CROWDED - above) * lo) * ORDER_CROWD_PARTS > uint64_t(all) * ORDER_MAX_CROWD;
+}
 
 template <typename IT>
 __device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
@@ -544,6 +572,7 @@ __device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>:
 #pragma unroll 8
     for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) atomicAdd(&at[bucket(t)], 1u);
     __syncthreads();
+    if (crowded(at[ORDER_BUCKETS + threadIdx.x], uint32_t(pc))) return;
     // exclusive scan, two buckets per thread
     const int lane = lane_id(), wave = threadIdx.x / OMEGA;
     const uint32_t a = at[2 * threadIdx.x], b = at[2 * threadIdx.x + 1];

@@ -9,7 +9,7 @@ import oracle
 from paper_1503_05032_amd import binding as B
 from paper_1503_05032_amd import workloads as wl
 
-from gpu_util import DeviceCsr, check_format, check_spmv, convert
+from gpu_util import DeviceCsr, check_format, check_spmv, convert, second_kernel_ms
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +40,8 @@ def test_long_rows_with_a_large_x(sigma, tiles, ragged, wide):
             check_format(d, h, (a.name, n))
         for call in range(2):
             check_spmv(d, h, (a.name, n, call), x=np.random.default_rng(call).standard_normal(n))
+        # by column means two kernels; by number matrices of this size and form are one
+        assert (second_kernel_ms(h, d.x, d.y) > 1e-3) == (tiles >= 2048 and n >= 524_288), (a.name, n)
         if not wide:                                     # the entry point with its own cross-tile array takes the same order
             y = d.y.clone()
             d.y.fill_(float("nan"))
@@ -91,4 +93,29 @@ def test_long_rows_same_bits_on_every_call(sigma, tiles, long):
             d.y.fill_(float("nan"))
             spmv(h, d.x, d.y)
             assert torch.equal(d.y, first), (call, int((d.y != first).sum()))
+    B.csr5_free(h)
+
+
+def _low_columns(sigma, tiles, share, n):
+    """As _matrix, but in a first `share` of the matrix all columns lie in the lowest sixteenth of n."""
+    a = _matrix(sigma, tiles, 0, n // 16, seed=int(100 * share))
+    rows = np.repeat(np.arange(a.m), np.diff(a.row_ptr))
+    spread = np.arange(a.nnz) >= share * a.nnz
+    spread = spread[a.row_ptr[rows]]                     # whole rows
+    col = np.where(spread, a.col_idx.astype(np.int64) * 16, a.col_idx).astype(np.int32)
+    x = np.random.default_rng(1).standard_normal(n)
+    return wl.Csr(a.m, n, a.row_ptr, col, a.val, x, f"low{share}")
+
+
+@pytest.mark.parametrize("sigma,tiles", [(8, 2060), (8, 6000), (16, 2500)])
+@pytest.mark.parametrize("share", [0.0, 0.3, 0.55, 0.85, 1.0])
+def test_crowded_columns_are_taken_by_number(sigma, tiles, share):
+    """More than three quarters of the tiles inside one row beginning in an eighth of the columns (the fullest 128 of
+    1024 buckets): by number, as one kernel.  The low sixteenth is 64 buckets; the 64 fullest of the other 960 hold
+    at most 4 of the (1 - share) * 2060 tiles spread over them each, 0.12 of all: 0.55 stays below 0.75."""
+    a = _low_columns(sigma, tiles, share, 700_000)
+    d = DeviceCsr(a)
+    h = convert(d, sigma=sigma)
+    check_spmv(d, h, (a.name, sigma, tiles))
+    assert (second_kernel_ms(h, d.x, d.y) > 1e-3) == (share < 0.75)
     B.csr5_free(h)
