@@ -33,9 +33,10 @@ constexpr uint32_t STATUS_NEEDS_CARRY = 1u << 17;
 // the far part of the records too (see below).
 constexpr uint32_t STATUS_FAR_HEADS = 1u << 18;
 // Internal status bit: at least one in ORDER_MIN_SHARE complete tiles lies inside
-// a single row (the tile order by columns may pay, see tile_order).
+// a single row (the tile order by columns may pay, see order_place).
 constexpr uint32_t STATUS_LONG_ROWS = 1u << 19;
 constexpr int ORDER_MIN_SHARE = 2;
+constexpr int ORDER_BUCKETS = 1024;      // of its sort, twice
 // A tile whose first segment continues a row of the previous tile completes
 // that row itself when it can get at the row's head.  The tiles of one
 // workgroup of the tile kernel are neighbours and hand the finished head over
@@ -245,7 +246,7 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t w, uint32_t nb, uint32_t 
     return (k / chunk) * (NUM_XCD * chunk) + xcd * chunk + (k % chunk);
 }
 
-// Place in the list of tile_order that workgroup w of nb takes (nb and the first
+// Place in the list of order_place that workgroup w of nb takes (nb and the first
 // `ends` places, in workgroups, are multiples of NUM_XCD).  The list's first part
 // is dealt out evenly among its second: the one waits for lines from memory, the
 // other for the L2.  First part: plain; second part: XCD k takes the k-th eighth.
@@ -309,7 +310,7 @@ __global__ void __launch_bounds__(PREP_THREADS)
 k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, int group, int record_reach, uint32_t nb_tiles,
           typename Index<IT>::tp_t* __restrict__ tile_ptr, uint32_t* __restrict__ tile_head, uint32_t* __restrict__ words,
           uint32_t* __restrict__ arrived, uint64_t* __restrict__ meet, size_t slot_bytes, int slots,
-          uint2* __restrict__ span, uint32_t* __restrict__ status) {
+          uint2* __restrict__ span, uint32_t* __restrict__ status, uint32_t* __restrict__ order_total) {
     using tp_t = typename Index<IT>::tp_t;
     const size_t gid = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
     // the one-launch SpMV finds its counters at zero and its meeting places empty, and leaves them so
@@ -320,6 +321,8 @@ k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, i
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
     if (gid < 3) status[gid] = 0u;        // and the plan of the tile order
+    if (order_total)
+        for (size_t b = gid; b < 2 * ORDER_BUCKETS; b += size_t(gridDim.x) * blockDim.x) order_total[b] = 0u;
     uint32_t found = 0;
     if (blockIdx.x >= nb_tiles) {         // ---- rows
         const int64_t stride = int64_t(gridDim.x - nb_tiles) * PREP_THREADS;
@@ -516,67 +519,111 @@ __device__ __forceinline__ void scan_epilogue(int pc, int p, IT total, IT* __res
 // 0.76 281 -> 270).  The same rows with their columns in random order, a share of
 // 0.2: 347 -> 196, 460 -> 302, 123 -> 108, single precision 227 -> 163.
 // The list: the tiles that hold row ends, in (nearly) their own order, then, from
-// a multiple of `align` on, the tiles inside one row by first column.  A counting
-// sort over 2 * ORDER_BUCKETS keys by one workgroup of SCAN_THREADS, next to the
-// scan of empty_offset_ptr; within a bucket any order will do.  plan[0]: where the
-// second part begins, plan[1]: entries in all (those between the parts hold no
-// tile: 0xffffffff); both 0: no order.  first_col: from the transposition.
+// a multiple of `align` on, the tiles inside one row by first column: a counting
+// sort over 2 * ORDER_BUCKETS keys, a slice of the tiles per workgroup.  The slices
+// are counted next to the scan of empty_offset_ptr (order_count; the bucket's total
+// so far is the slice's place in it) and dealt out in the launch that follows
+// (order_place, which first adds the totals up); within a bucket any order will do.
+// Blocking conversions of 33 000 and 488 000 tiles take 185 and 2242 us (216 and 3066
+// with one workgroup for all tiles, 178 and 2220 before there was an order): 0.2 us
+// of the scan's launch, 3 to 4.5 of the next.
+// plan[0]: where the second part begins, plan[1]: entries in all (those between the
+// parts hold no tile: 0xffffffff); both 0: no order.  first_col: from the
+// transposition.
 // ----------------------------------------------------------------------------
 constexpr size_t ORDER_MIN_X_BYTES = 4u << 20;
-constexpr int ORDER_BUCKETS = SCAN_THREADS, ORDER_MIN_TILES = 2048;
+constexpr int ORDER_MIN_TILES = 2048;
 constexpr int ORDER_CROWD_PARTS = 4, ORDER_MAX_CROWD = 3, ORDER_CROWDED = ORDER_BUCKETS / 8;
+constexpr int ORDER_SLICE = 1024, ORDER_MAX_SLICES = 256;
+constexpr int PLACE_THREADS = 256, PLACE_BUCKETS = 2 * ORDER_BUCKETS / PLACE_THREADS;
 
 struct OrderJob {
-    int32_t n, align;                // align = 0: nothing to do
+    int32_t n, align;
+    int32_t slices;                  // 0: nothing to do
     const int32_t* first_col;
+    uint32_t *total, *base;          // per bucket; per slice and bucket
     uint32_t *order, *plan;
 };
 
-// Whether the fullest eighth of ORDER_BUCKETS buckets, one per thread, holds more
-// than ORDER_MAX_CROWD of ORDER_CROWD_PARTS of all; no bucket holds more than `most`.
-__device__ bool crowded(uint32_t mine, uint32_t most) {
-    __shared__ uint32_t all, fullest;
-    if (threadIdx.x == 0) all = fullest = 0;
-    __syncthreads();
-    uint32_t lo = 0, hi = most;      // the smallest count that at most ORDER_CROWDED buckets exceed
-    while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (__syncthreads_count(mine > mid) > ORDER_CROWDED) lo = mid + 1; else hi = mid;
+// Whether this matrix gets the order, as far as its row lengths say (plan was cleared with the status word).
+__device__ __forceinline__ bool order_wanted(const uint32_t* __restrict__ status) {
+    constexpr uint32_t both = STATUS_LONG_ROWS | STATUS_NEEDS_CARRY;
+    return (*status & both) == both;
+}
+
+// f(tile, bucket) for the tiles of slice k, by all threads of the workgroup.
+template <typename IT, typename F>
+__device__ __forceinline__ void order_slice(int pc, const OrderJob& job, int k, const typename Index<IT>::tp_t* __restrict__ tile_ptr, F f) {
+    constexpr auto ROWMASK = Index<IT>::ROWMASK;
+    const float per_col = float(ORDER_BUCKETS) / float(job.n), per_tile = float(ORDER_BUCKETS) / float(pc);
+    const int first = int(int64_t(pc) * k / job.slices), end = int(int64_t(pc) * (k + 1) / job.slices);
+#pragma unroll 4
+    for (int t = first + int(threadIdx.x); t < end; t += int(blockDim.x)) {
+        const int32_t c = job.first_col[t];
+        const bool inside = (tile_ptr[t] & ROWMASK) == (tile_ptr[t + 1] & ROWMASK);
+        const int b = int(inside ? float(c < 0 ? 0 : c) * per_col : float(t) * per_tile);      // (a column out of range: rejected input)
+        f(t, (inside ? ORDER_BUCKETS : 0) + (b < ORDER_BUCKETS ? b : ORDER_BUCKETS - 1));
     }
-    const int above = __syncthreads_count(mine > lo);
-    atomicAdd(&all, mine);
-    if (mine > lo) atomicAdd(&fullest, mine);
-    __syncthreads();
-    return uint64_t(fullest + uint32_t(ORDER_CROWDED - above) * lo) * ORDER_CROWD_PARTS > uint64_t(all) * ORDER_MAX_CROWD;
 }
 
 template <typename IT>
-__device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-                           const uint32_t* __restrict__ status) {
-    if (!(*status & STATUS_LONG_ROWS) || !(*status & STATUS_NEEDS_CARRY)) return;     // (plan was cleared with the status word)
-    __shared__ uint32_t at[2 * ORDER_BUCKETS];
-    __shared__ uint32_t wave_total[SCAN_THREADS / OMEGA];
-    __shared__ uint32_t row_end_tiles;
-    constexpr auto ROWMASK = Index<IT>::ROWMASK;
-    const int32_t* __restrict__ const first_col = job.first_col;
-    uint32_t* __restrict__ const order = job.order;
-    const float per_col = float(ORDER_BUCKETS) / float(job.n), per_tile = float(ORDER_BUCKETS) / float(pc);
-    auto bucket = [&](int t) -> int {
-        const int32_t c = first_col[t];
-        const bool inside = (tile_ptr[t] & ROWMASK) == (tile_ptr[t + 1] & ROWMASK);
-        const int k = int(inside ? float(c < 0 ? 0 : c) * per_col : float(t) * per_tile);      // (a column out of range: rejected input)
-        return (inside ? ORDER_BUCKETS : 0) + (k < ORDER_BUCKETS ? k : ORDER_BUCKETS - 1);
+__device__ void order_count(int pc, const OrderJob& job, int k, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
+                            const uint32_t* __restrict__ status) {
+    if (!order_wanted(status)) return;
+    __shared__ uint32_t count[2 * ORDER_BUCKETS];
+    for (int b = threadIdx.x; b < 2 * ORDER_BUCKETS; b += blockDim.x) count[b] = 0;
+    __syncthreads();
+    order_slice<IT>(pc, job, k, tile_ptr, [&](int, int b) { atomicAdd(&count[b], 1u); });
+    __syncthreads();
+    uint32_t* const base = job.base + size_t(k) * (2 * ORDER_BUCKETS);
+    for (int b = threadIdx.x; b < 2 * ORDER_BUCKETS; b += blockDim.x)
+        base[b] = count[b] ? atomicAdd(&job.total[b], count[b]) : 0u;
+}
+
+// Whether the fullest eighth of the buckets of tiles inside one row holds more than
+// ORDER_MAX_CROWD of ORDER_CROWD_PARTS of them all (`inside`).  One wavefront, without
+// barriers: its bisection is the longest chain of the workgroup that does it.
+__device__ bool crowded(const uint32_t* __restrict__ total, uint32_t inside) {
+    constexpr int PER_LANE = ORDER_BUCKETS / OMEGA;
+    const int lane = lane_id();
+    uint32_t mine[PER_LANE];
+#pragma unroll
+    for (int q = 0; q < PER_LANE; q++) mine[q] = total[ORDER_BUCKETS + q * OMEGA + lane];
+    const auto fuller = [&](uint32_t c) {
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < PER_LANE; q++) n += __popcll(__ballot(mine[q] > c));
+        return n;
     };
-    for (int k = threadIdx.x; k < 2 * ORDER_BUCKETS; k += SCAN_THREADS) at[k] = 0;
-    __syncthreads();
-#pragma unroll 8
-    for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) atomicAdd(&at[bucket(t)], 1u);
-    __syncthreads();
-    if (crowded(at[ORDER_BUCKETS + threadIdx.x], uint32_t(pc))) return;
-    // exclusive scan, two buckets per thread
+    uint32_t lo = 0, hi = inside / ORDER_CROWDED;      // the smallest count that at most ORDER_CROWDED buckets exceed
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (fuller(mid) > ORDER_CROWDED) lo = mid + 1; else hi = mid;
+    }
+    uint32_t fullest = 0;
+#pragma unroll
+    for (int q = 0; q < PER_LANE; q++) fullest += mine[q] > lo ? mine[q] : 0u;
+#pragma unroll
+    for (int d = OMEGA / 2; d >= 1; d >>= 1) fullest += __shfl_xor(fullest, d, OMEGA);
+    fullest += uint32_t(ORDER_CROWDED - fuller(lo)) * lo;
+    return uint64_t(fullest) * ORDER_CROWD_PARTS > uint64_t(inside) * ORDER_MAX_CROWD;
+}
+
+template <typename IT>
+__device__ void order_place(int pc, const OrderJob& job, int k, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
+                            const uint32_t* __restrict__ status) {
+    if (!order_wanted(status)) return;
+    __shared__ uint32_t at[2 * ORDER_BUCKETS];
+    __shared__ uint32_t wave_total[PLACE_THREADS / OMEGA];
+    // exclusive scan of the buckets' totals, PLACE_BUCKETS neighbours per thread
     const int lane = lane_id(), wave = threadIdx.x / OMEGA;
-    const uint32_t a = at[2 * threadIdx.x], b = at[2 * threadIdx.x + 1];
-    uint32_t incl = a + b;
+    uint32_t mine[PLACE_BUCKETS], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PLACE_BUCKETS; q++) {
+        mine[q] = job.total[threadIdx.x * PLACE_BUCKETS + q];
+        sum += mine[q];
+    }
+    uint32_t incl = sum;
 #pragma unroll
     for (int d = 1; d < OMEGA; d <<= 1) {
         const uint32_t up = __shfl_up(incl, d, OMEGA);
@@ -584,21 +631,28 @@ __device__ void tile_order(int pc, const OrderJob job, const typename Index<IT>:
     }
     if (lane == OMEGA - 1) wave_total[wave] = incl;
     __syncthreads();
-    uint32_t before = incl - a - b;
-    for (int w = 0; w < wave; w++) before += wave_total[w];
-    if (2 * threadIdx.x == ORDER_BUCKETS) row_end_tiles = before;
+    uint32_t before = incl - sum, ends = 0;              // ends: tiles that hold row ends, the first half of the buckets
+    for (int w = 0; w < PLACE_THREADS / OMEGA; w++) {
+        if (w < wave) before += wave_total[w];
+        if (w < PLACE_THREADS / OMEGA / 2) ends += wave_total[w];
+    }
+    const uint32_t align = uint32_t(job.align), second = (ends + align - 1) / align * align;
+    if (threadIdx.x >= PLACE_THREADS / 2) before += second - ends;
+    const uint32_t* const base = job.base + size_t(k) * (2 * ORDER_BUCKETS);
+#pragma unroll
+    for (int q = 0; q < PLACE_BUCKETS; q++) {
+        const int b = threadIdx.x * PLACE_BUCKETS + q;
+        at[b] = before + base[b];
+        before += mine[q];
+    }
     __syncthreads();
-    const uint32_t align = uint32_t(job.align), ends = row_end_tiles, second = (ends + align - 1) / align * align;
-    if (2 * threadIdx.x >= ORDER_BUCKETS) before += second - ends;
-    at[2 * threadIdx.x] = before;
-    at[2 * threadIdx.x + 1] = before + a;
-    for (uint32_t q = ends + threadIdx.x; q < second; q += SCAN_THREADS) order[q] = 0xffffffffu;
-    __syncthreads();
-#pragma unroll 8
-    for (int t = threadIdx.x; t < pc; t += SCAN_THREADS) order[atomicAdd(&at[bucket(t)], 1u)] = uint32_t(t);
-    if (threadIdx.x == 0) {
-        job.plan[0] = second;
-        job.plan[1] = uint32_t(pc) + second - ends;
+    order_slice<IT>(pc, job, k, tile_ptr, [&](int t, int b) { job.order[atomicAdd(&at[b], 1u)] = uint32_t(t); });
+    if (k == 0) {
+        for (uint32_t q = ends + threadIdx.x; q < second; q += PLACE_THREADS) job.order[q] = 0xffffffffu;
+        if (wave == 0 && !crowded(job.total, uint32_t(pc) - ends) && lane == 0) {
+            job.plan[0] = second;
+            job.plan[1] = uint32_t(pc) + second - ends;
+        }
     }
 }
 
@@ -606,7 +660,7 @@ template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
            uint32_t* __restrict__ status, const OrderJob job) {
-    if (blockIdx.x == 1) return tile_order<IT>(pc, job, tile_ptr, status);
+    if (blockIdx.x > 0) return order_count<IT>(pc, job, int(blockIdx.x) - 1, tile_ptr, status);
     IT total = 0;
     if (*status & STATUS_SCAN_NEEDED)
         for (int64_t base = 0; base < pc; base += SCAN_CHUNK) total += scan_chunk(eop, base, int64_t(pc), total);
@@ -618,8 +672,8 @@ template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_chunks(int pc, IT* __restrict__ eop, IT* __restrict__ chunk_sum, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
               const uint32_t* __restrict__ status, const OrderJob job) {
-    int chunk = blockIdx.x;
-    if (job.align && chunk-- == 0) return tile_order<IT>(pc, job, tile_ptr, status);       // the longest first
+    const int chunk = int(blockIdx.x) - job.slices;
+    if (chunk < 0) return order_count<IT>(pc, job, int(blockIdx.x), tile_ptr, status);
     if (!(*status & STATUS_SCAN_NEEDED)) return;
     const IT total = scan_chunk(eop, int64_t(chunk) * SCAN_CHUNK, int64_t(pc), IT(0));
     if (threadIdx.x == 0) chunk_sum[chunk] = total;
@@ -668,19 +722,21 @@ k_scan_finish(int pc, int p, IT* __restrict__ eop, const IT* __restrict__ chunk_
 // the column)  of that tile, and its entry is  row - tile_ptr.  Segment 0 of a
 // marked tile may start with the forced flag (a row continued from the previous
 // tile, which is then the tile's first row): its entry is 0 and is written by
-// the extra p_c threads at the end of the grid.
+// the extra p_c threads at the end of the grid.  The first workgroups lay out the
+// tile order where there is one.
 // ----------------------------------------------------------------------------
 template <typename IT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(PLACE_THREADS)
 k_empty_offset(int m, const IT* __restrict__ row_ptr, int sigma, int T, int W, int pc,
                const typename Index<IT>::tp_t* __restrict__ tile_ptr, const uint32_t* __restrict__ desc,
                const IT* __restrict__ eop, int32_t* __restrict__ eo,
-               const uint32_t* __restrict__ status) {
+               const uint32_t* __restrict__ status, const OrderJob job) {
     using tp_t = typename Index<IT>::tp_t;
     constexpr tp_t DIRTY = Index<IT>::DIRTY, ROWMASK = Index<IT>::ROWMASK;
+    if (int(blockIdx.x) < job.slices) return order_place<IT>(pc, job, int(blockIdx.x), tile_ptr, status);
     uint32_t st = *status;
     if (!(st & CSR5_STATUS_HAS_DIRTY) || (st & BAD_BITS)) return;
-    int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    int64_t g = int64_t(int(blockIdx.x) - job.slices) * blockDim.x + threadIdx.x;
     if (g >= int64_t(m)) {
         int64_t t = g - m;
         if (t < pc && (tile_ptr[t] & DIRTY)) eo[eop[t]] = 0;
@@ -778,7 +834,7 @@ struct DescJob {
     void* eop;
     const uint32_t* words;              // of k_prepare
     int32_t nb_tiles, nb_rows;
-    int32_t* first_col;                 // every tile's first column, for tile_order, or NULL
+    int32_t* first_col;                 // every tile's first column, for the tile order, or NULL
 };
 
 template <int SIGMA, bool BACK, typename VT>
@@ -1426,7 +1482,7 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
     int tile;
-    if (MODE == MODE_CARRY && order) {      // the list of tile_order
+    if (MODE == MODE_CARRY && order) {      // the list of order_place
         const uint32_t k = order_place(blockIdx.x - has_tail, nb_tiles, order_second / WAVES) * WAVES + wave;
         const uint32_t t = k < order_len ? order[k] : 0xffffffffu;
         tile = t < uint32_t(pc) ? int(t) : pc;
@@ -1814,7 +1870,7 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
 // order, or, with FIXED, the wavefront that holds the run's first tile adds up the
 // rest of the run by itself: the same bits on every call, for matrices that would
 // have them from the one-launch form if their tiles were not taken by column
-// (tile_order).  The rest is usually shorter than a wavefront of tiles, which is
+// (order_place).  The rest is usually shorter than a wavefront of tiles, which is
 // asked for with the wavefront's own; beyond that it is a serial chain, RUN_AHEAD
 // wavefronts of tiles per round trip.
 // ----------------------------------------------------------------------------
@@ -2089,7 +2145,7 @@ struct csr5_handle_s {
     // small and for large sigma): two views of one array of LAST_REC_BYTES-byte records
     int32_t* last_col;
     void* last_val;
-    // The tile kernel's order of the tiles (tile_order), in the place of the records; NULL: by number
+    // The tile kernel's order of the tiles (order_place), in the place of the records; NULL: by number
     uint32_t* order;
     uint32_t order_second, order_len;
     void* owned;           // hipMalloc'ed block, or NULL when a workspace was given
@@ -2103,8 +2159,8 @@ struct csr5_handle_s {
 
 namespace {
 
-constexpr int WORDS_RESERVED = 8192;
-static_assert(PREP_TILE_WG + PREP_ROW_WG <= WORDS_RESERVED, "words of k_prepare");
+constexpr int WORDS_RESERVED = 8192, ORDER_TOTAL_AT = WORDS_RESERVED - 2 * ORDER_BUCKETS;     // the sort's totals: the last of them
+static_assert(PREP_TILE_WG + PREP_ROW_WG <= ORDER_TOTAL_AT, "words of k_prepare");
 
 struct Layout {
     size_t off_tile_ptr, off_tile_head, off_span, off_desc, off_eop, off_eo, off_carry, off_last, off_scan, off_words, off_status, total;
@@ -2281,14 +2337,20 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     uint32_t* const words = reinterpret_cast<uint32_t*>(basep + L.off_words);
     // The tile order goes along with the scan where it may pay and the host will know of it (see below).  It sorts by
     // the tiles' first columns, which the transposition leaves in the first carry array, and takes the records' place.
-    OrderJob order = {n, 0, nullptr, nullptr, h->status + 1};
+    OrderJob order = {n, NUM_XCD * tile_group_waves(g.sigma), 0, nullptr, nullptr, nullptr, nullptr, h->status + 1};
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK) && h->last_val && h->aux_form == 0 && g.pc >= ORDER_MIN_TILES &&
         size_t(n) * sizeof(VT) >= ORDER_MIN_X_BYTES) {
-        order.align = NUM_XCD * tile_group_waves(g.sigma);
+        order.slices = (g.pc + ORDER_SLICE - 1) / ORDER_SLICE < ORDER_MAX_SLICES ? (g.pc + ORDER_SLICE - 1) / ORDER_SLICE : ORDER_MAX_SLICES;
         order.first_col = static_cast<const int32_t*>(h->carry);
-        order.order = static_cast<uint32_t*>(h->last_val);             // pc + align words: the records have 96 bytes and more per tile
+        order.total = words + ORDER_TOTAL_AT;
+        order.order = static_cast<uint32_t*>(h->last_val);             // pc + align words
+        order.base = order.order + g.pc + order.align;                 // 2 * ORDER_BUCKETS words per slice
+        // the records are 24 words and more per tile: enough for the fewest tiles, and for every further slice
+        constexpr int words_per_tile = NEAR_REC_BYTES / 4 / tile_group_waves(LOOK_MIN_SIGMA);
+        static_assert(ORDER_MIN_TILES * words_per_tile >= ORDER_MIN_TILES + 64 + (ORDER_MIN_TILES / ORDER_SLICE + 1) * 2 * ORDER_BUCKETS &&
+                      ORDER_SLICE * words_per_tile >= ORDER_SLICE + 2 * ORDER_BUCKETS, "list and bases in the records' place");
     }
-    DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.align ? static_cast<int32_t*>(h->carry) : nullptr};
+    DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.slices ? static_cast<int32_t*>(h->carry) : nullptr};
     {   // step 2a
         const size_t nb_tiles = (size_t(g.p) + 1 + PREP_THREADS - 1) / PREP_THREADS;
         const size_t nb_rows = (size_t(m) + PREP_THREADS * PREP_UNROLL - 1) / (PREP_THREADS * PREP_UNROLL);
@@ -2299,7 +2361,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
                            h->tile_head, words,
                            reinterpret_cast<uint32_t*>(basep + L.off_carry + slot_off_arrived(g, tile_group_waves(g.sigma))),
                            reinterpret_cast<uint64_t*>(basep + L.off_carry + slot_off_meet(g)), L.carry_slot_bytes,
-                           one_launch_fits(g.sigma, g.p) ? int(CARRY_SLOTS) : 0, reinterpret_cast<uint2*>(basep + L.off_span), h->status);
+                           one_launch_fits(g.sigma, g.p) ? int(CARRY_SLOTS) : 0, reinterpret_cast<uint2*>(basep + L.off_span), h->status, order.total);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {            // steps 2b, 3a, 3b (descriptors, inside the same kernel) + 4
@@ -2312,12 +2374,12 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         }
     }
     if (e == hipSuccess && g.pc <= SCAN_SINGLE) {
-        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(order.align ? 2 : 1), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr, h->status, order);
+        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr, h->status, order);
         e = hipGetLastError();
     } else if (e == hipSuccess) {
         IT* chunk_sum = reinterpret_cast<IT*>(basep + L.off_scan);
         const int nchunks = (g.pc + SCAN_CHUNK - 1) / SCAN_CHUNK;      // <= 2^26 / 2^13 = SCAN_CHUNK
-        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + (order.align ? 1 : 0)), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
+        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + order.slices), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
                            tile_ptr, h->status, order);
         e = hipGetLastError();
         if (e == hipSuccess) {
@@ -2328,9 +2390,9 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     }
     if (e == hipSuccess && g.pc > 0 && m > 0) {
         size_t threads = size_t(m) + size_t(g.pc);
-        hipLaunchKernelGGL(k_empty_offset<IT>, dim3(uint32_t((threads + 255) / 256)), dim3(256), 0, s, m,
-                           row_ptr, g.sigma, g.T, g.W, g.pc, tile_ptr, h->tile_desc, eop, h->eo,
-                           h->status);
+        hipLaunchKernelGGL(k_empty_offset<IT>, dim3(uint32_t((threads + PLACE_THREADS - 1) / PLACE_THREADS) + uint32_t(order.slices)),
+                           dim3(PLACE_THREADS), 0, s, m, row_ptr, g.sigma, g.T, g.W, g.pc, tile_ptr, h->tile_desc, eop, h->eo,
+                           h->status, order);
         e = hipGetLastError();
     }
     if (e != hipSuccess) {
@@ -2343,7 +2405,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
         uint32_t got[3] = {0, 0, 0};      // the status word and the plan of the tile order behind it
-        int rc = read_status(h, got, order.align ? 3 : 1);
+        int rc = read_status(h, got, order.slices ? 3 : 1);
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];

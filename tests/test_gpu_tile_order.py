@@ -119,3 +119,39 @@ def test_crowded_columns_are_taken_by_number(sigma, tiles, share):
     check_spmv(d, h, (a.name, sigma, tiles))
     assert (second_kernel_ms(h, d.x, d.y) > 1e-3) == (share < 0.75)
     B.csr5_free(h)
+
+
+def test_sort_of_many_tiles():
+    """127 k tiles (the scan over several workgroups, 124 slices of the sort): results, and the sort beside the
+    conversion, of which one workgroup for all tiles made 200 us."""
+    L, m, n, sigma = 20_000, 3250, 600_000, 8
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(7)
+    u = torch.rand((m, L), generator=g, device="cuda:0", dtype=torch.float64)
+    col = ((torch.arange(L, device="cuda:0") + u) * (n / L)).long().clamp_(max=n - 1).to(torch.int32).flatten()
+    val = torch.rand(m * L, generator=g, device="cuda:0", dtype=torch.float64) - 0.5
+    x = torch.rand(n, generator=g, device="cuda:0", dtype=torch.float64) - 0.5
+    row_ptr = torch.arange(m + 1, device="cuda:0", dtype=torch.int32) * L
+    products = (val * x[col.long()]).view(m, L)
+    ref, s = products.sum(1), products.abs().sum(1)
+    before = col.clone()
+    ws = torch.empty(B.csr5_workspace_bytes(m, m * L, sigma), dtype=torch.uint8, device="cuda:0")
+    y = torch.empty(m, dtype=torch.float64, device="cuda:0")
+    ms = {0: [], B.CSR5_FLAG_NO_HOST_CHECK: []}
+    for call in range(6):
+        for flags in ms:
+            t0, t1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            t0.record()
+            h = B.csr5_convert_ex(m, n, m * L, row_ptr, col, val, sigma=sigma, workspace=ws, flags=flags)
+            t1.record()
+            y.fill_(float("nan"))
+            B.csr5_spmv_ex(h, x, y)
+            torch.cuda.synchronize()
+            ms[flags].append(t0.elapsed_time(t1))
+            assert bool(((y - ref).abs() <= 1e-12 * s).all())
+            B.csr5_to_csr(h)
+            torch.cuda.synchronize()
+            B.csr5_free(h)
+            assert torch.equal(col, before)
+    print("blocking, enqueued (ms):", *(min(v) for v in ms.values()))
+    assert min(ms[0]) < min(ms[B.CSR5_FLAG_NO_HOST_CHECK]) + 0.1
