@@ -46,3 +46,30 @@ def test_non_finite_values_stay_in_their_row(sigma, cut, dtype):
             same[r] = bool(torch.isnan(y[r])) if poison != poison else bool(y[r] == poison)
             assert bool(same.all()), (r, poison, torch.nonzero(~same).flatten().tolist())
     B.csr5_free(h)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 4])
+@pytest.mark.parametrize("nnz", [1024, 4096, 5 * 4096 + 77, 3 * 1024 + 1])
+def test_single_precision_tile_loads(nnz, offset):
+    """Single precision with the look-behind at 16 entries per column: col_idx 16-byte aligned and not, one and
+    several workgroups, the last one partly filled, an incomplete tile."""
+    rng = np.random.default_rng(nnz + offset)
+    lens = rng.integers(0, 33, nnz)
+    lens = lens[:int(np.searchsorted(np.cumsum(lens), nnz))]
+    lens = np.append(lens, nnz - lens.sum())
+    m, n = len(lens), 5000
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = rng.integers(0, n, nnz).astype(np.int32)
+    dev = "cuda:0"
+    whole = torch.zeros(nnz + offset, dtype=torch.int32, device=dev)
+    whole[offset:] = torch.from_numpy(col).to(dev)
+    val = torch.from_numpy(rng.uniform(-1, 1, nnz)).to(dev, torch.float32)
+    x = torch.from_numpy(rng.uniform(-1, 1, n)).to(dev, torch.float32)
+    y = torch.full((m,), float("nan"), dtype=torch.float32, device=dev)
+    products = val.double().cpu().numpy() * x.double().cpu().numpy()[col]
+    ref, s = (np.add.reduceat(np.append(p, 0.0), row_ptr[:-1]) * (lens > 0) for p in (products, np.abs(products)))
+    h = B.csr5s_convert_ex(m, n, nnz, torch.from_numpy(row_ptr).to(dev), whole[offset:], val, sigma=16)
+    B.csr5s_spmv_ex(h, x, y)
+    # a term passes through 16 + 6 + 4 additions and its product at most, 2^-24 each
+    assert np.all(np.abs(y.double().cpu().numpy() - ref) <= 32 * 2.0 ** -24 * s)
+    B.csr5_free(h)
