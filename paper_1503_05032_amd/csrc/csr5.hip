@@ -798,6 +798,13 @@ __device__ __forceinline__ void wave_sync_lds() {
 }
 
 constexpr int FLAG_ROWS_MAX = 4096;
+// Rows beyond a tile's first 64 are asked for this many wavefronts of them at a time:
+// one at a time made the conversion of very short rows in tall tiles slower than one
+// thread per row was (6 M rows of one entry, height 48: 82.6 us by a thread per row,
+// 105.5, now 84.6; height 32 83.7, 92.0, 83.7; height 16 82.0, 74.5, 66.2; 8 M rows of 0
+// to 2 entries, height 16: 616, 113.3, 102.5); 2 at a time leave 3-7 % of that, 8 add
+// nothing.
+constexpr int FLAG_ROWS_AHEAD = 4;
 
 // A tile's arrays through buffer descriptors: the address of a load is the
 // descriptor, a lane offset that all loads of the tile share and a constant, so the
@@ -1018,13 +1025,27 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
                 };
                 if (row1 - row0 <= FLAG_ROWS_MAX) {        // uniform
                     bool empty = false;
-                    for (int k = lane; k < row1 - row0; k += OMEGA) {      // row row0 + 1 + k
-                        if (k != lane) {
-                            begins = row_at(row0 + 1 + k);
-                            ends = row_at(row0 + 2 + k);
-                        }
-                        if (begins == ends) empty = true;
-                        else if (begins >= lo_e && begins < lo_e + T) flag_at(begins);
+                    const int rows = row1 - row0;
+                    const auto take = [&](int64_t from, int64_t to) {        // a row, row0 + 1 + k for the lane's k
+                        if (from == to) empty = true;
+                        else if (from >= lo_e && from < lo_e + T) flag_at(from);
+                    };
+                    if (lane < rows) take(begins, ends);
+                    for (int k = OMEGA + lane; k - lane < rows; k += FLAG_ROWS_AHEAD * OMEGA) {
+                        int64_t from[FLAG_ROWS_AHEAD], to[FLAG_ROWS_AHEAD];
+                        const auto ask = [&](const auto* __restrict__ row_ptr) {
+#pragma unroll
+                            for (int q = 0; q < FLAG_ROWS_AHEAD; q++) {
+                                const int r = row0 + 1 + (k + q * OMEGA < rows ? k + q * OMEGA : rows - 1);
+                                from[q] = row_ptr[r];
+                                to[q] = row_ptr[r + 1];
+                            }
+                        };
+                        if (job.wide) ask(static_cast<const int64_t*>(job.row_ptr));
+                        else ask(static_cast<const int32_t*>(job.row_ptr));
+#pragma unroll
+                        for (int q = 0; q < FLAG_ROWS_AHEAD; q++)
+                            if (k + q * OMEGA < rows) take(from[q], to[q]);
                     }
                     marked = __any(empty);
                 } else {

@@ -60,3 +60,21 @@ def test_exact_range_limits(sigma):
         torch.cuda.synchronize()
         assert np.array_equal(d.col_idx.cpu().numpy(), a.col_idx)
         B.csr5_free(h)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("sigma", [1, 8, 16, 24, 48])
+def test_rows_per_tile(sigma, wide):
+    """Tiles in which exactly so many rows begin: a row per lane, one more, and the steps of four more per lane."""
+    T = 64 * sigma
+    for rows in (1, 63, 64, 65, 128, 129, 319, 320, 321, 577, T - 1, T):
+        if rows > T:
+            continue
+        tile = np.concatenate([np.ones(rows - 1, dtype=np.int64), [T - rows + 1]])
+        lens = np.concatenate([tile, tile, [0, 0], tile, tile[:rows // 2]])
+        a = wl.from_row_lengths(lens, T + 50, seed=rows, name=f"rows{rows}")
+        d = DeviceCsr(a, wide=wide)
+        h = convert(d, sigma=sigma)
+        check_format(d, h, (a.name, sigma))
+        check_spmv(d, h, (a.name, sigma))
+        B.csr5_free(h)
