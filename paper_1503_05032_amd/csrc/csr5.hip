@@ -1993,7 +1993,8 @@ k_spmv_fixup(int m, int ntiles,
 // ----------------------------------------------------------------------------
 // Measurement aid: what the memory system charges for the tile kernel's streams
 // alone.  One wavefront per complete tile, the same workgroup shape and tile
-// order as the tile kernel's most common instantiation; it reads the tile's
+// order as the tile kernel's most common instantiation (by number also for a matrix
+// that the tile kernel takes by column); it reads the tile's
 // col_idx, val and descriptors with 16-byte non-temporal loads (all of a tile in
 // flight at once up to sigma = 16) and, if asked, stores one value to every row
 // the tile starts (the rows of y that tile's wavefront writes in an SpMV).  No
@@ -2633,7 +2634,7 @@ static int stream_floor(csr5_handle_t h, VT* y, hipStream_t s, int reps, float* 
     using tp_t = typename Index<IT>::tp_t;
     const Geom& g = h->g;
     const uint32_t nb_tiles = uint32_t((g.pc + FLOOR_WAVES - 1) / FLOOR_WAVES);
-    // the tile order the SpMV uses for this matrix
+    // the SpMV's order by number for this matrix
     const size_t x_bytes = size_t(h->n) * sizeof(VT);
     uint32_t xcd_chunk = 0;
     if (x_bytes > XCD_CONTIGUOUS_MAX_X_BYTES)

@@ -63,6 +63,8 @@ def test_long_rows_single_precision():
     h = B.csr5s_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val, sigma=16)
     B.csr5s_spmv_ex(h, x, y)
     torch.cuda.synchronize()
+    assert min(B.csr5s_spmv_profile(h, x, y, reps=100)[1] for _ in range(2)) > 1e-3      # by column: two kernels
+    torch.cuda.synchronize()
     ref, s = oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val.astype(np.float32).astype(np.float64), x.cpu().numpy().astype(np.float64))
     # a term passes through the walk, the tile's scan and the sum over a row's 20 tiles at most: fewer than 64 additions of 2^-24 each
     assert np.all(np.abs(y.cpu().numpy() - ref) <= 1e-5 * s + 1e-30)
@@ -155,3 +157,17 @@ def test_sort_of_many_tiles():
             assert torch.equal(col, before)
     print("blocking, enqueued (ms):", *(min(v) for v in ms.values()))
     assert min(ms[0]) < min(ms[B.CSR5_FLAG_NO_HOST_CHECK]) + 0.1
+
+
+def test_only_a_blocking_conversion_lays_out_the_order():
+    """After CSR5_FLAG_NO_HOST_CHECK the matrix keeps its other form, also once csr5_status has been called."""
+    a = _matrix(8, 2100, 5, 700_001, seed=11)
+    for flags, two in ((B.CSR5_FLAG_NONE, True), (B.CSR5_FLAG_NO_HOST_CHECK, False), (B.CSR5_FLAG_AUX_ONE_KERNEL, False),
+                       (B.CSR5_FLAG_AUX_TWO_KERNELS, True)):
+        d = DeviceCsr(a)
+        h = convert(d, sigma=8, flags=flags)
+        check_spmv(d, h, (a.name, flags))
+        assert B.csr5_status(h) & 3 == 0
+        check_spmv(d, h, (a.name, flags))
+        assert (second_kernel_ms(h, d.x, d.y) > 1e-3) == two, flags
+        B.csr5_free(h)
