@@ -44,7 +44,9 @@ def line_matrix(m, per_row, n, partners=(), far=False, seed=5):
 
 
 def tile_kernel_ms(a, reps=30):
-    """Mean duration of the tile kernel at sigma = 16 (best of three series)."""
+    """Mean duration of the tile kernel at sigma = 16 (best of three series), tiles in
+    the order of their numbers (a flag that fixes the form: the order by column of
+    matrices with long rows would bring table 1's gathers closer together)."""
     import torch
     from . import binding as B
     dev = torch.device("cuda:0")
@@ -53,7 +55,7 @@ def tile_kernel_ms(a, reps=30):
     val = torch.from_numpy(a.val).to(dev)
     x = torch.from_numpy(a.x).to(dev)
     y = torch.empty(a.m, dtype=torch.float64, device=dev)
-    h = B.csr5_convert_ex(a.m, a.n, a.nnz, row_ptr, col, val, sigma=16)
+    h = B.csr5_convert_ex(a.m, a.n, a.nnz, row_ptr, col, val, sigma=16, flags=B.CSR5_FLAG_AUX_TWO_KERNELS)
     B.csr5_status(h)
     for _ in range(5):
         B.csr5_spmv_ex(h, x, y)
