@@ -69,12 +69,13 @@ constexpr int MODE_CARRY = 0, MODE_LOOK = 1, MODE_ONE = 2;
 // The one-launch form saves the second kernel (3 us and a launch) and pays for
 // one or two atomics with a return value per group of tiles (0.2-1 ns of kernel
 // time each, whenever they are sent).  Measured against the
-// two-kernel form: matrices of a few thousand tiles gain 10-20 % whatever their
-// rows look like (a dense 2000 x 2000 matrix 14.9 -> 12.0 us); with rows of 701
-// or 2000 entries throughout the gain is gone at 6 M nonzeros and turns into a
-// loss of 4-13 % at 8-21 M; matrices whose rows are short on average and that
-// take this path for a few long rows still gain at 17 M (power-law: 2.7 %) and are
-// level at 34 M.  Hence: up to ONE_LAUNCH_ANY_TILES tiles always, up to
+// two-kernel form: matrices of a few thousand tiles gain 7-20 % whatever their
+// rows look like (a dense 2000 x 2000 matrix 13.1 -> 10.7 us); with rows of 701
+// or 2000 entries throughout the gain is 2-7 % at 6 M nonzeros and level, within
+// 2 %, at 10-21 M (it was gone at 6 M and a loss of 4-13 % at 8-21 M when the line
+// was drawn, before the tile's loads went through buffer descriptors); matrices
+// whose rows are short on average and that take this path for a few long rows still
+// gain at 17 M (power-law: 2.3 %) and are level at 30 M.  Hence: up to ONE_LAUNCH_ANY_TILES tiles always, up to
 // ONE_LAUNCH_MAX_TILES when the average row is shorter than ONE_LAUNCH_SHORT_ROWS.
 constexpr int ONE_LAUNCH_ANY_TILES = 6144;
 constexpr int ONE_LAUNCH_MAX_TILES = 32768;
@@ -813,8 +814,8 @@ constexpr int FLAG_ROWS_AHEAD = 4;
 // offset took four loads each); nothing outside the tile is read.  Measured on the
 // tile kernel (plain 64-bit addresses before): 100 000 rows of 100 random columns
 // 65.4 -> 58.4 us, 30 000 rows of 201 38.2 -> 36.3, dense rows with the tile order
-// 226 -> 200, 60 000 short rows 11.8 -> 10.9, 100^3 stencil 61.6 -> 61.0, single
-// precision 44.7 -> 44.1.
+// 226 -> 200, 60 000 short rows 11.8 -> 10.9, 100^3 stencil 61.6 -> 61.0, rows of 700
+// in single precision 95.4 -> 91.3 (one instantiation reads plainly, see k_spmv).
 // Non-temporal: without it the streams stay in the 256 MB memory-side cache as far
 // as they fit, and one matrix multiplied again and again gains (90^3 stencil 43.2 ->
 // 37.7 us, 100^3 with half of its tiles 61.0 -> 51.5), but matrices used in turn,
