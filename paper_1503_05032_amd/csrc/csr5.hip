@@ -118,6 +118,7 @@ constexpr int RULE_R = 16, RULE_S = 16, RULE_T = 256, RULE_U = 16;
 // ones are within 2 % either way between 12 M and 20 M.
 constexpr int64_t RULE_MIN_TILES = 3 * 256 * 16;
 constexpr int RULE_SIGMA_SMALL = 8;
+constexpr bool rule_sigma(int sigma) { return sigma == RULE_SIGMA_SMALL || sigma == RULE_R; }
 
 // Index width of row_ptr, tile_ptr and empty_offset_ptr.  int32 is the layout the
 // paper describes first (tile_ptr: 31-bit row index, top bit = "tile holds an
@@ -816,21 +817,32 @@ constexpr int FLAG_ROWS_AHEAD = 4;
 // 65.4 -> 58.4 us, 30 000 rows of 201 38.2 -> 36.3, dense rows with the tile order
 // 226 -> 200, 60 000 short rows 11.8 -> 10.9, 100^3 stencil 61.6 -> 61.0, rows of 700
 // in single precision 95.4 -> 91.3 (one instantiation reads plainly, see k_spmv).
-// Non-temporal: without it the streams stay in the 256 MB memory-side cache as far
-// as they fit, and one matrix multiplied again and again gains (90^3 stencil 43.2 ->
-// 37.7 us, 100^3 with half of its tiles 61.0 -> 51.5), but matrices used in turn,
-// and the first product of any, lose (44.8 -> 52.1, 61.2 -> 67.5): not known here
-// which it is.
-constexpr int POLICY_STREAM = 2;                          // nt
+// Non-temporal, as a rule: without it the streams stay in the 256 MB memory-side cache
+// as far as they fit, and one matrix multiplied again and again gains (90^3 stencil
+// 43.2 -> 37.7 us, 100^3 with half of its tiles 61.0 -> 51.5), but matrices used in
+// turn lose (44.8 -> 52.1, 61.2 -> 67.5): not known here which it is.
+// KEEP: plain, where the next use of the entries is known to be near.  See keep_near.
+constexpr int POLICY_STREAM = 2, POLICY_KEEP = 0;         // nt; none
 template <typename P>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_buffer(P* first, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<typename std::remove_const<P>::type*>(first), 0, bytes, 0x00020000);
 }
-template <typename P>
+template <typename P, bool KEEP>
 __device__ __forceinline__ P stream_from(__amdgpu_buffer_rsrc_t r, int offset) {
-    if constexpr (sizeof(P) == 16) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, POLICY_STREAM));
-    else if constexpr (sizeof(P) == 8) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b64(r, offset, 0, POLICY_STREAM));
-    else return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, POLICY_STREAM));
+    constexpr int POLICY = KEEP ? POLICY_KEEP : POLICY_STREAM;
+    if constexpr (sizeof(P) == 16) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, POLICY));
+    else if constexpr (sizeof(P) == 8) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b64(r, offset, 0, POLICY));
+    else return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, POLICY));
+}
+template <bool KEEP, typename P>
+__device__ __forceinline__ P stream_from(const P* a) {
+    if constexpr (KEEP) return *a;
+    else return __builtin_nontemporal_load(a);
+}
+template <bool KEEP, typename P>
+__device__ __forceinline__ void stream_to(P* a, P v) {
+    if constexpr (KEEP) *a = v;
+    else __builtin_nontemporal_store(v, a);
 }
 
 // What the forward pass needs of the conversion beside the entries themselves.
@@ -845,7 +857,7 @@ struct DescJob {
     int32_t* first_col;                 // every tile's first column, for the tile order, or NULL
 };
 
-template <int SIGMA, bool BACK, typename VT>
+template <int SIGMA, bool BACK, bool KEEP, typename VT>
 __global__ void __launch_bounds__(TransposeShape<SIGMA>::WAVES * OMEGA)
 k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __restrict__ val,
             uint32_t* __restrict__ status, int32_t* __restrict__ last_col, VT* __restrict__ last_val, int rec_bytes, const DescJob job) {
@@ -901,7 +913,7 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
     int64_t begins = 0, ends = 0;        // of row row0 + 1 + lane
     if (active) {
 #pragma unroll
-        for (int k = 0; k < SIGMA; k++) v[k] = __builtin_nontemporal_load(&val[base + k * OMEGA + lane]);
+        for (int k = 0; k < SIGMA; k++) v[k] = stream_from<KEEP>(&val[base + k * OMEGA + lane]);
         if constexpr (!BACK) {
             if (row1 >= job.m) row1 = job.m - 1;
             if (lane < row1 - row0) {
@@ -947,7 +959,7 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
             }
         }
 #pragma unroll
-        for (int k = 0; k < SIGMA; k++) __builtin_nontemporal_store(v[k], &val[base + k * OMEGA + lane]);
+        for (int k = 0; k < SIGMA; k++) stream_to<KEEP>(&val[base + k * OMEGA + lane], v[k]);
     }
     wave_sync_lds();    // every wavefront works in its own LDS slice
     // ---- col_idx, same path through the same LDS buffer
@@ -955,7 +967,7 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
     if (active) {
 #pragma unroll
         for (int k = 0; k < SIGMA; k++) {
-            c[k] = __builtin_nontemporal_load(&col_idx[base + k * OMEGA + lane]);
+            c[k] = stream_from<KEEP>(&col_idx[base + k * OMEGA + lane]);
             bad |= (c[k] < 0) | (c[k] >= n);
         }
         if constexpr (!BACK && look_sigma(SIGMA)) {
@@ -995,7 +1007,7 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
             }
         }
 #pragma unroll
-        for (int k = 0; k < SIGMA; k++) __builtin_nontemporal_store(c[k], &col_idx[base + k * OMEGA + lane]);
+        for (int k = 0; k < SIGMA; k++) stream_to<KEEP>(&col_idx[base + k * OMEGA + lane], c[k]);
     }
     if (!BACK && blockIdx.x == gridDim.x - 1) {
         for (size_t e = size_t(pc) * T + threadIdx.x; e < size_t(nnz); e += blockDim.x) {
@@ -1449,7 +1461,7 @@ __device__ void spmv_tail(int m, IT nnz, IT first, uint32_t row_first,
     }
 }
 
-template <int SIGMA, typename VT, typename IT, int MODE>
+template <int SIGMA, typename VT, typename IT, int MODE, bool KEEP>
 __global__ void __launch_bounds__(TransposeShape<SIGMA>::WAVES * OMEGA)
 k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint32_t xcd_chunk, uint32_t far_mode,
        int rec_bytes, const IT* __restrict__ row_ptr, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
@@ -1581,26 +1593,26 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
         if ((reinterpret_cast<uintptr_t>(col_idx) & 15) == 0) {
             const i32x4* const col4 = reinterpret_cast<const i32x4*>(col_idx + tile_base);
 #pragma unroll
-            for (int q = 0; q < NC4; q++) c4[q] = __builtin_nontemporal_load(&col4[q * OMEGA + lane]);
+            for (int q = 0; q < NC4; q++) c4[q] = stream_from<KEEP>(&col4[q * OMEGA + lane]);
         } else {      // a view at an odd offset
             const auto cols = tile_buffer(col_idx + tile_base, T * 4);
 #pragma unroll
-            for (int q = 0; q < NC4; q++) c4[q] = stream_from<i32x4>(cols, (q * OMEGA + lane) * 16);
+            for (int q = 0; q < NC4; q++) c4[q] = stream_from<i32x4, KEEP>(cols, (q * OMEGA + lane) * 16);
         }
 #pragma unroll
-        for (int j = 0; j < SIGMA; j++) v[j] = __builtin_nontemporal_load(&val[tile_base + j * OMEGA + lane]);
+        for (int j = 0; j < SIGMA; j++) v[j] = stream_from<KEEP>(&val[tile_base + j * OMEGA + lane]);
 #pragma unroll
-        for (int w = 0; w < W; w++) dw[w] = __builtin_nontemporal_load(&dp[w * OMEGA + lane]);
+        for (int w = 0; w < W; w++) dw[w] = stream_from<KEEP>(&dp[w * OMEGA + lane]);
     } else {
         const auto cols = tile_buffer(col_idx + tile_base, T * 4);
         const auto vals = tile_buffer(val + tile_base, T * int(sizeof(VT)));
         const auto descs = tile_buffer(dp, W * OMEGA * 4);
 #pragma unroll
-        for (int q = 0; q < NC4; q++) c4[q] = stream_from<i32x4>(cols, (q * OMEGA + lane) * 16);
+        for (int q = 0; q < NC4; q++) c4[q] = stream_from<i32x4, KEEP>(cols, (q * OMEGA + lane) * 16);
 #pragma unroll
-        for (int j = 0; j < SIGMA; j++) v[j] = stream_from<VT>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
+        for (int j = 0; j < SIGMA; j++) v[j] = stream_from<VT, KEEP>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
 #pragma unroll
-        for (int w = 0; w < W; w++) dw[w] = stream_from<uint32_t>(descs, (w * OMEGA + lane) * 4);
+        for (int w = 0; w < W; w++) dw[w] = stream_from<uint32_t, KEEP>(descs, (w * OMEGA + lane) * 4);
     }
 
     // ---- descriptor
@@ -2045,7 +2057,7 @@ k_stream_floor(int m, int pc, int sigma, int W, uint32_t nb_tiles, uint32_t xcd_
 }
 
 template <int SIGMA, typename VT, typename IT, int MODE>
-hipError_t launch_spmv(const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
+hipError_t launch_spmv(bool keep, const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
                        const typename Index<IT>::tp_t* tile_ptr,
                        const uint32_t* tile_desc, const IT* eop, const int32_t* eo,
                        const int32_t* col_idx, const VT* val, const VT* x, VT* y,
@@ -2067,20 +2079,22 @@ hipError_t launch_spmv(const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
         xcd_chunk = (int64_t(nnz) / (m > 0 ? m : 1) <= g.T / Y_LINE_ROWS) ? 1u : XCD_CHUNK;
     else if (x_bytes < XCD_CONTIGUOUS_MIN_X_BYTES)                 // x at home in every L2
         xcd_chunk = XCD_CHUNK;
-    hipLaunchKernelGGL((k_spmv<SIGMA, VT, IT, MODE>), dim3(nb), dim3(WAVES * OMEGA), 0, s, m, nnz, g.pc, g.p, nb_tiles, has_tail,
+    const auto kernel = keep && rule_sigma(SIGMA) ? k_spmv<SIGMA, VT, IT, MODE, rule_sigma(SIGMA)> : k_spmv<SIGMA, VT, IT, MODE, false>;
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(WAVES * OMEGA), 0, s, m, nnz, g.pc, g.p, nb_tiles, has_tail,
                        xcd_chunk, far_mode, record_bytes(int64_t(nnz)), row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry,
                        meet, arrived, span, status, tile_head, last_col, last_val, order, order_second, order_len);
     return hipGetLastError();
 }
 
 template <int SIGMA, bool BACK, typename VT>
-hipError_t launch_transpose(const Geom& g, int n, int64_t nnz, int32_t* col_idx, VT* val,
+hipError_t launch_transpose(bool keep, const Geom& g, int n, int64_t nnz, int32_t* col_idx, VT* val,
                             uint32_t* status, int32_t* last_col, VT* last_val, const DescJob& job, hipStream_t s) {
     constexpr int WAVES = TransposeShape<SIGMA>::WAVES;
     uint32_t nb = uint32_t((g.pc + WAVES - 1) / WAVES);
     if (nb == 0) nb = BACK ? 0 : 1;   // forward pass still validates the tail's columns and collects the words of k_prepare
     if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_transpose<SIGMA, BACK, VT>), dim3(nb), dim3(WAVES * OMEGA), 0, s, g.pc, n, nnz,
+    const auto kernel = keep && rule_sigma(SIGMA) ? k_transpose<SIGMA, BACK, rule_sigma(SIGMA), VT> : k_transpose<SIGMA, BACK, false, VT>;
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(WAVES * OMEGA), 0, s, g.pc, n, nnz,
                        col_idx, val, status, last_col, last_val, record_bytes(nnz), job);
     return hipGetLastError();
 }
@@ -2182,7 +2196,7 @@ struct csr5_handle_s {
     // many SpMVs on one handle may be in flight at once (on different streams).
     void* carry;
     size_t carry_slot_bytes;
-    std::atomic<uint32_t> carry_turn;
+    std::atomic<uint32_t> carry_turn;      // SpMVs so far
     uint32_t* tile_head;   // per tile: entries of its first row that lie before it, saturated at 32 bits
     int aux_form;          // 0: the size rule decides how the auxiliary-array path adds its sums; 1: always the second kernel; 2: inside the tile kernel wherever span exists
     uint2* span;           // per tile: the groups of tiles that row touches (first, how many); NULL where the one-launch SpMV cannot run
@@ -2301,6 +2315,43 @@ static int read_status(csr5_handle_t h, uint32_t* got, int words) {
     return CSR5_OK;
 }
 
+// Where the entries' next use is near, so that plain loads and stores leave them in the
+// 256 MB memory-side cache for it instead of passing it by (the rule, see tile_buffer):
+//  * The transposition: its matrix is multiplied next.  One conversion, one product and
+//    the way back, matrices used in turn (3 and 6 of them, so none is still there from
+//    its own last turn): 100^3 stencil (318 MB) 293 -> 270 us, 90^3 220 -> 201, 75^3 137 ->
+//    121, power-law of 2 M rows 242 -> 231, dense 4000^2 219 -> 198, 15 M random entries
+//    370 -> 356.  With the product left non-temporal half of that or less (100^3: 295),
+//    with only the stores or only the loads plain less (291) or nothing.
+//  * The first products of a handle, hence.  After that nobody knows whether the handle
+//    is used alone (plain gains, 5 products of a 90^3 stencil 397 -> 360) or is one of many
+//    (it loses), so only as many as follow a conversion anyhow: one; KEEP_CALLS where x
+//    is at home in every L2 (with x of 3 to 10 MB and random columns the streams push it
+//    out: five products of 19 M entries, x of 3.2 MB, 702 -> 714 with eight, 694 with one);
+//    KEEP_CALLS_L2 where the entries fit the L2s together (50 products of a 40^3 stencil
+//    and the conversion 509 -> 455).  Guessed wrong it costs 5-20 % of these calls, in all
+//    less than the conversion before them did.
+//  * The way back is their last use: non-temporal, or it pushes out what comes next (75^3:
+//    121 -> 134), except for the small, where the stores return sooner (dense 2000^2,
+//    48 MB, 82 -> 76; 50^3, 40 MB, 55 -> 50; 60^3, 70 MB, 73.3 -> 72.1 but 78.9 with six
+//    in turn).
+// The line, entries with x and y: 387 MB (105^3) 336 -> 312 us, 409 MB (107^3) 380 -> 357,
+// 390 MB (1.85 M rows, mixed) 539 -> 532, but 417 MB (power-law, 3.5 M rows) 399 -> 407, 445 MB
+// (110^3) 381 -> 394, 570 MB (120^3) 487 -> 510.  For the heights the automatic rule picks;
+// the others keep one form.
+constexpr int64_t L2_BYTES = 32 << 20, KEEP_MAX_BYTES = 384 << 20, KEEP_BACK_MAX_BYTES = 48 << 20;
+constexpr uint32_t KEEP_CALLS = 8, KEEP_CALLS_L2 = 64;
+static int64_t entry_bytes(int64_t nnz, size_t value_bytes) { return nnz * int64_t(value_bytes + 4); }
+static bool keep_near(int32_t m, int32_t n, int64_t nnz, size_t value_bytes) {
+    return entry_bytes(nnz, value_bytes) + (int64_t(m) + n) * int64_t(value_bytes) <= KEEP_MAX_BYTES;
+}
+static bool keep_product(int32_t m, int32_t n, int64_t nnz, size_t value_bytes, uint32_t call) {
+    if (!keep_near(m, n, nnz, value_bytes)) return false;
+    if (entry_bytes(nnz, value_bytes) <= L2_BYTES) return call < KEEP_CALLS_L2;
+    return call < (size_t(n) * value_bytes < XCD_CONTIGUOUS_MIN_X_BYTES ? KEEP_CALLS : 1u);
+}
+static bool keep_back(int64_t nnz, size_t value_bytes) { return entry_bytes(nnz, value_bytes) <= KEEP_BACK_MAX_BYTES; }
+
 template <typename VT, typename IT>
 static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t* col_idx,
                         VT* val, int32_t sigma, void* workspace, size_t workspace_bytes,
@@ -2411,7 +2462,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     }
     if (e == hipSuccess) {            // steps 2b, 3a, 3b (descriptors, inside the same kernel) + 4
         switch (sigma) {
-#define X(S) case S: e = launch_transpose<S, false, VT>(g, n, nnz, col_idx, val, h->status, h->last_col,      \
+#define X(S) case S: e = launch_transpose<S, false, VT>(keep_near(m, n, nnz, sizeof(VT)), g, n, nnz, col_idx, val, h->status, h->last_col,      \
                                                         static_cast<VT*>(h->last_val), job, s); break;
             CSR5_FOR_SIGMA(X)
 #undef X
@@ -2514,7 +2565,8 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     const IT* eop = static_cast<const IT*>(h->eop);
     hipError_t e = hipSuccess;
     // a whole SpMV takes the next of the handle's carry arrays; partial launches (measurement) the first
-    const uint32_t turn = (which == LAUNCH_BOTH) ? h->carry_turn.fetch_add(1, std::memory_order_relaxed) % CARRY_SLOTS : 0u;
+    const uint32_t call = (which == LAUNCH_BOTH) ? h->carry_turn.fetch_add(1, std::memory_order_relaxed) : 0u, turn = call % CARRY_SLOTS;
+    const bool keep = which == LAUNCH_BOTH && keep_product(h->m, h->n, h->nnz, sizeof(VT), call);
     VT* carry = static_cast<VT*>(carry_mem ? carry_mem : static_cast<void*>(static_cast<char*>(h->carry) + turn * h->carry_slot_bytes));
     // What the matrix needs beyond its tiles is known once the host has seen the
     // status word of the conversion; until then everything is launched (the
@@ -2538,7 +2590,7 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     const bool fixed = h->order && h->span && one_pays;
     uint64_t* const meet = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(carry) + slot_off_meet(h->g));
     uint32_t* const arrived = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(carry) + slot_off_arrived(h->g, tile_group_waves(h->g.sigma)));
-#define ARGS h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
+#define ARGS keep, h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
              static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->span, h->status, h->tile_head, h->last_col, \
              static_cast<const VT*>(h->last_val), zero_rows, far_mode, h->order, h->order_second, h->order_len, s
     if (which & LAUNCH_TILES) {
@@ -2708,12 +2760,13 @@ int csr5_to_csr(csr5_handle_t h, void* hip_stream) {
     if (!h->in_csr5_order) return CSR5_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = hipSuccess;
+    const bool keep = keep_back(h->nnz, h->dtype == CSR5_DTYPE_F32 ? 4 : 8);
     if (h->nnz > 0) {
         switch (h->g.sigma) {
 #define X(S) case S: e = (h->dtype == CSR5_DTYPE_F32)                                                            \
-        ? launch_transpose<S, true, float>(h->g, h->n, h->nnz, h->col_idx, static_cast<float*>(h->val), h->status,     \
+        ? launch_transpose<S, true, float>(keep, h->g, h->n, h->nnz, h->col_idx, static_cast<float*>(h->val), h->status,     \
                                            nullptr, nullptr, DescJob{}, s)                                             \
-        : launch_transpose<S, true, double>(h->g, h->n, h->nnz, h->col_idx, static_cast<double*>(h->val), h->status,   \
+        : launch_transpose<S, true, double>(keep, h->g, h->n, h->nnz, h->col_idx, static_cast<double*>(h->val), h->status,   \
                                             nullptr, nullptr, DescJob{}, s);                                            \
         break;
             CSR5_FOR_SIGMA(X)

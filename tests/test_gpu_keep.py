@@ -1,0 +1,71 @@
+"""GPU parity where the kernels choose between plain and non-temporal loads and stores:
+by size (the entries against 32 MB for the products, 48 MB for the way back, 384 MB with
+the vectors for all) and by how many products a handle has had (1, 8, 64)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1503_05032_amd import binding as B
+from paper_1503_05032_amd import workloads as wl
+
+from gpu_util import DeviceCsr, check_format, check_spmv, convert
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(nnz, n, seed):
+    """Exactly nnz entries: rows of 0 to 60, one of 3000, the last one what is missing."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 61, size=nnz // 25 + 100)
+    lens[5] = 3000
+    lens = lens[:np.searchsorted(np.cumsum(lens), nnz - 60)]
+    return wl.from_row_lengths(np.append(lens, nnz - lens.sum()), n, seed=seed, name=f"keep{nnz}_{n}")
+
+
+@pytest.mark.parametrize("nnz,n,sigma,wide", [
+    ((32 << 20) // 12, 50_000, 0, False), ((32 << 20) // 12 + 1, 50_000, 0, False), ((32 << 20) // 12 + 1, 400_000, 0, True),
+    ((48 << 20) // 12, 50_000, 16, False), ((48 << 20) // 12 + 1, 350_000, 8, True), (300_000, 3000, 0, False)])
+def test_every_product_of_a_handle_is_the_same(nnz, n, sigma, wide):
+    a = _matrix(nnz, n, seed=nnz % 1000 + n)
+    assert a.nnz == nnz
+    print("keep", nnz, n, sigma, wide, flush=True)
+    d = DeviceCsr(a, wide=wide)
+    for flags in (B.CSR5_FLAG_NONE, B.CSR5_FLAG_NO_HOST_CHECK):
+        h = convert(d, sigma=sigma, flags=flags)
+        check_format(d, h, (a.name, flags))
+        check_spmv(d, h, (a.name, flags, "first"))
+        first = d.y.clone()
+        for call in range(66):
+            d.y.fill_(float("nan"))
+            B.csr5_spmv_ex(h, d.x, d.y)
+            if flags == B.CSR5_FLAG_NONE:                # one kernel, which adds in a fixed order
+                assert torch.equal(d.y, first), (a.name, call)
+        check_spmv(d, h, (a.name, flags, "last"))
+        B.csr5_to_csr(h)
+        torch.cuda.synchronize()
+        assert np.array_equal(d.col_idx.cpu().numpy(), a.col_idx)
+        assert np.array_equal(d.val.cpu().numpy(), a.val)
+        B.csr5_free(h)
+
+
+@pytest.mark.parametrize("nnz", [(32 << 20) // 8 + 1, (48 << 20) // 8 + 1])
+def test_single_precision(nnz):
+    a = _matrix(nnz, 60_000, seed=9)
+    d = DeviceCsr(a)
+    val, x = d.val.float(), d.x.float()
+    kept = val.clone()
+    y = torch.empty(a.m, dtype=torch.float32, device="cuda:0")
+    h = B.csr5s_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val)
+    products = kept.double() * x.double()[torch.from_numpy(a.col_idx).long().cuda()]
+    want = torch.segment_reduce(products, "sum", offsets=d.row_ptr.long(), initial=0)
+    scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)
+    first = None
+    for call in range(10):
+        B.csr5s_spmv_ex(h, x, y)
+        assert bool(((y.double() - want).abs() <= 1e-5 * scale + 1e-30).all()), call      # at most 64 additions per term: 64 * 2^-24 = 3.8e-6
+        first = y.clone() if first is None else first
+        assert torch.equal(y, first), call
+    B.csr5_to_csr(h)
+    torch.cuda.synchronize()
+    assert torch.equal(val, kept) and np.array_equal(d.col_idx.cpu().numpy(), a.col_idx)
+    B.csr5_free(h)
