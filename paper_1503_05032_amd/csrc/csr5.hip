@@ -322,7 +322,7 @@ k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, i
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
-    if (gid < 3) status[gid] = 0u;        // and the plan of the tile order
+    if (gid < 4) status[gid] = 0u;        // and the plan of the tile order, the answer of sample_columns
     if (order_total)
         for (size_t b = gid; b < 2 * ORDER_BUCKETS; b += size_t(gridDim.x) * blockDim.x) order_total[b] = 0u;
     uint32_t found = 0;
@@ -658,10 +658,84 @@ __device__ void order_place(int pc, const OrderJob& job, int k, const typename I
     }
 }
 
+// How many of SAMPLES pairs of neighbouring entries lie in different lines of x, 0 if the
+// columns are none for k_spmv_staged: what the host needs beside sizes to decide for it
+// (staged_min_entries).  A sample of SAMPLE_TILES tiles (in CSR5 order already), two neighbours of
+// each of a tile's 64 columns, by one workgroup of SCAN_THREADS threads beside the scan.
+// Different lines: each entry is a line from the L2 (random columns 0.95-1.0; stencils 0.36,
+// power-law rows 0.35, rows with a sixth of all columns 0.37, dense 0).  Not for it are
+//  * fewer than half in different lines (rows of 2000 out of 12 000 columns, 20 M entries 58.5 -> 65.7).
+//  * tiles whose entries do not spread over half of x or SAMPLE_WIDE_BYTES: the entries that
+//    a CU has at a time share what its L1 holds, and every part of x would be read for
+//    nothing (random columns, and bands of 160 KB: all tiles spread; stencils none,
+//    power-law rows one in six).
+//  * columns that all together fall on far fewer lines than random ones would (1.0; normally
+//    distributed 0.7): a few columns have most entries, and the L1 holds those (power-law
+//    columns in random order, x of 480 KB: 0.35 and 14.1 us, here 16.8).
+constexpr int SAMPLE_TILES = 64, SAMPLES = SAMPLE_TILES * OMEGA, SAMPLE_MAX_LINES = 32768;
+constexpr int SAMPLE_WIDE_BYTES = 128 << 10, SAMPLE_WIDE_PERCENT = 90, SAMPLE_LINES_PERCENT = 60, SAMPLE_MIN_PERCENT = 50;
+
+struct SampleJob {
+    const int32_t* col_idx;          // NULL: nothing to do
+    int32_t n, sigma, value_bytes;   // at most SAMPLE_MAX_LINES lines of x
+    uint32_t* changes;               // the answer; cleared with the status word
+};
+
+__device__ void sample_columns(int pc, const SampleJob& job) {
+    __shared__ uint32_t seen[SAMPLE_MAX_LINES / 4];       // a byte per line of x, which many may set at a time
+    __shared__ uint32_t changes, wide, lines;
+    const int lane = lane_id(), wave = threadIdx.x / OMEGA;
+    const uint32_t per_line = 128u / uint32_t(job.value_bytes), last = uint32_t(job.n - 1), words = last / per_line / 4 + 1;
+    const uint32_t spread = last / 2 < SAMPLE_WIDE_BYTES / uint32_t(job.value_bytes) ? last / 2 : SAMPLE_WIDE_BYTES / uint32_t(job.value_bytes);
+    // everything is asked for at once: one round trip
+    constexpr int PER_WAVE = SAMPLE_TILES / (SCAN_THREADS / OMEGA);
+    uint32_t at[PER_WAVE], next[PER_WAVE];
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++) {
+        const int q = wave * PER_WAVE + u;
+        // rows of one length repeat in step with the columns: another place in them for every 16 lanes, and from tile to tile
+        // (every lane its own would be 16 lines a load, 9 us in all)
+        const int j = (q + lane / 16 * job.sigma / 4) % (job.sigma - 1);
+        const int32_t* const pair = job.col_idx + int64_t(pc) * q / SAMPLE_TILES * (job.sigma * OMEGA) + j * OMEGA + lane;
+        at[u] = uint32_t(pair[0]);
+        next[u] = uint32_t(pair[OMEGA]);
+    }
+    for (uint32_t w = threadIdx.x; w < words; w += SCAN_THREADS) seen[w] = 0;
+    if (threadIdx.x == 0) changes = wide = lines = 0;
+    __syncthreads();
+    uint32_t my_changes = 0, my_wide = 0;                 // of the wavefront's tiles
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++) {
+        const uint32_t a = at[u] < last ? at[u] : last, b = next[u] < last ? next[u] : last;      // (out of range: rejected input)
+        const uint32_t line = a / per_line, next_line = b / per_line;
+        reinterpret_cast<uint8_t*>(seen)[line] = 1;
+        reinterpret_cast<uint8_t*>(seen)[next_line] = 1;
+        my_changes += uint32_t(__popcll(__ballot(line != next_line)));
+        // `spread` columns between the outermost two: bounded from below by what lies furthest on either side of lane 0's
+        const uint32_t from = __builtin_amdgcn_readfirstlane(a), up = a > from ? a - from : 0u, down = a < from ? from - a : 0u;
+        my_wide += __ballot(up > spread || down > spread) != 0 || (__ballot(up > spread / 2) != 0 && __ballot(down > spread / 2) != 0) ? 1u : 0u;
+    }
+    if (lane == 0) {
+        atomicAdd(&changes, my_changes);
+        atomicAdd(&wide, my_wide);
+    }
+    __syncthreads();
+    uint32_t mine = 0;
+    for (uint32_t w = threadIdx.x; w < words; w += SCAN_THREADS) mine += uint32_t(__popc(seen[w]));
+    if (mine) atomicAdd(&lines, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const float all = float(last / per_line + 1), random = all * (1.0f - expf(-float(2 * SAMPLES) / all));
+        if (changes * 100 >= uint32_t(SAMPLES * SAMPLE_MIN_PERCENT) && wide * 100 >= uint32_t(SAMPLE_TILES * SAMPLE_WIDE_PERCENT) &&
+            float(lines) * 100.0f >= random * float(SAMPLE_LINES_PERCENT)) *job.changes = changes;
+    }
+}
+
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-           uint32_t* __restrict__ status, const OrderJob job) {
+           uint32_t* __restrict__ status, const OrderJob job, const SampleJob sample) {
+    if (sample.col_idx && blockIdx.x == gridDim.x - 1) return sample_columns(pc, sample);
     if (blockIdx.x > 0) return order_count<IT>(pc, job, int(blockIdx.x) - 1, tile_ptr, status);
     IT total = 0;
     if (*status & STATUS_SCAN_NEEDED)
@@ -1461,6 +1535,49 @@ __device__ void spmv_tail(int m, IT nnz, IT first, uint32_t row_first,
     }
 }
 
+// The per-column walk and the in-tile segmented sum of a tile (flags, yo: the lane's
+// column; v, xv: its entries and their x).  Every segment's sum goes to yb[its number];
+// returns the number of segments.
+template <int SIGMA, typename VT>
+__device__ __forceinline__ uint32_t walk_columns(typename FlagWord<SIGMA>::type flags, uint32_t yo, const VT* v, const VT* xv, VT* yb, int lane) {
+    constexpr int T = OMEGA * SIGMA;
+    VT sum = VT(0), red = VT(0);
+    bool seen = false;
+    uint32_t seg = yo;
+#pragma unroll
+    for (int j = 0; j < SIGMA; j++) {
+        if ((flags >> j) & 1) {
+            if (seen) {                                   // a green segment ends
+                if (seg < uint32_t(T)) yb[seg] = sum;
+                seg++;
+            } else {                                      // the red head ends (empty when j == 0)
+                red = sum;
+                seen = true;
+            }
+            sum = VT(0);
+        }
+        sum = fma(v[j], xv[j], sum);
+    }
+    VT blue = sum;
+    if (!seen) { red = sum; blue = VT(0); }                 // whole column is red
+
+    // ---- in-tile segmented sum of the red partials
+    uint64_t heads = __ballot(seen);                      // bit 0 is always set
+    VT tmp = from_row<DPP_SHIFT_DOWN + 1>(red);          // the next lane's; 0 for the last
+    {
+        const VT from16 = from_lane(red, 16), from32 = from_lane(red, 32), from48 = from_lane(red, 48);
+        if (lane == 15) tmp = from16;
+        if (lane == 31) tmp = from32;
+        if (lane == 47) tmp = from48;
+    }
+    uint64_t right = (lane == OMEGA - 1) ? 0ull : (heads >> (lane + 1));
+    int end = right ? (lane + __builtin_ctzll(right)) : (OMEGA - 1);   // last lane of my segment
+    tmp = sum_to_next_head(tmp, heads, lane, end);
+    if (seen && seg < uint32_t(T)) yb[seg] = blue + tmp;
+    // number of segments of the tile = flags before the last column + its own
+    return __builtin_amdgcn_readlane(seen ? seg + 1 : seg, OMEGA - 1);
+}
+
 template <int SIGMA, typename VT, typename IT, int MODE, bool KEEP>
 __global__ void __launch_bounds__(TransposeShape<SIGMA>::WAVES * OMEGA)
 k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint32_t xcd_chunk, uint32_t far_mode,
@@ -1736,45 +1853,11 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
         }
     }
 
-    // ---- per-column walk.  Finished segment sums are parked in LDS (the buffer
-    // is free again), slot = segment number inside the tile, and written to y
-    // afterwards, 64 consecutive segments per store instruction.
+    // ---- finished segment sums go to LDS (the buffer is free again), slot = segment
+    // number inside the tile, and are written to y afterwards, 64 consecutive segments
+    // per store instruction.
     VT* const yb = xb;                                // T <= 64*PITCH slots
-    VT sum = VT(0), red = VT(0);
-    bool seen = false;
-    uint32_t seg = yo;
-#pragma unroll
-    for (int j = 0; j < SIGMA; j++) {
-        if ((flags >> j) & 1) {
-            if (seen) {                                   // a green segment ends
-                if (seg < uint32_t(T)) yb[seg] = sum;
-                seg++;
-            } else {                                      // the red head ends (empty when j == 0)
-                red = sum;
-                seen = true;
-            }
-            sum = VT(0);
-        }
-        sum = fma(v[j], xv[j], sum);
-    }
-    VT blue = sum;
-    if (!seen) { red = sum; blue = VT(0); }                 // whole column is red
-
-    // ---- in-tile segmented sum of the red partials
-    uint64_t heads = __ballot(seen);                      // bit 0 is always set
-    VT tmp = from_row<DPP_SHIFT_DOWN + 1>(red);          // the next lane's; 0 for the last
-    {
-        const VT from16 = from_lane(red, 16), from32 = from_lane(red, 32), from48 = from_lane(red, 48);
-        if (lane == 15) tmp = from16;
-        if (lane == 31) tmp = from32;
-        if (lane == 47) tmp = from48;
-    }
-    uint64_t right = (lane == OMEGA - 1) ? 0ull : (heads >> (lane + 1));
-    int end = right ? (lane + __builtin_ctzll(right)) : (OMEGA - 1);   // last lane of my segment
-    tmp = sum_to_next_head(tmp, heads, lane, end);
-    if (seen && seg < uint32_t(T)) yb[seg] = blue + tmp;
-    // number of segments of the tile = flags before the last column + its own
-    uint32_t nseg = __builtin_amdgcn_readlane(seen ? seg + 1 : seg, OMEGA - 1);
+    uint32_t nseg = walk_columns<SIGMA, VT>(flags, yo, v, xv, yb, lane);
     if (nseg > uint32_t(T)) nseg = T;
     if (dirty && nseg > nseg_t) nseg = nseg_t;            // cannot happen for a consistent format
     wave_sync_lds();
@@ -1912,6 +1995,273 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
             assemble_row<VT>(carry, meet, arrived, group, group + int(span_out.y) - 1, y, row_out, m, lane);
         }
     }
+}
+
+// ----------------------------------------------------------------------------
+// SpMV with x through LDS, for matrices whose columns are spread over an x that an L2
+// holds and an L1 does not.  k_spmv gathers from the L1, and every entry there is a
+// 128-byte line from the L2: 225 G/s on the whole chip whatever the kernel does (6 M
+// entries in rows of 201, x of 480 KB: 27 of 36.7 us).  Here one workgroup per CU
+// takes WAVES * K tiles at a time, keeps their columns in registers, and has x come by in parts
+// through two buffers in LDS, straight from memory to LDS, one on its way while the
+// other is read; in each part every entry whose column lies in it picks its x (which
+// lanes read is the execution mask, so a step is a subtraction, a comparison and the
+// read).  x is read once per workgroup, in whole lines, instead of a line per entry.
+// Bound by the LDS reads, one per entry and part, and by the stream in front of them:
+// 1.0-1.25 us per part of 79 KB, and 18.5 us for everything else on that matrix.
+// Whole SpMV, before -> after: that matrix 36.7 -> 23.8 us, single precision 34.5 ->
+// 16.5; 6 M entries in rows of 100, x of 160 KB 34.6 -> 18.9, of 800 KB 37.7 -> 28.5;
+// 12.4 M, x of 320 KB 68.8 -> 40.5; in rows of 500 (height 16), 6 M, x of 480 KB 34.9 ->
+// 23.3, 20 M in single precision 92 -> 49.
+// Where it is taken: staged_tiles, sample_columns.
+// Tried: x through registers instead of straight to LDS, one buffer of 156 KB: 31.4; 12
+// or 8 wavefronts with more tiles each, height 8: 27.4, 31.0 (at height 16 in double precision 12
+// with two tiles, 23.3, against 16 with two 30.1: spills; 16 with one 31.8: two rounds);
+// the first two parts asked for up front: 26.2; another tile's values in the second part:
+// the same.
+//
+// Columns of a tile stay with their owner lane (no reordering: LDS does not care), so
+// the sums are those of k_spmv: walk_columns for each tile, then the rows that cross
+// tiles inside the workgroup in one step over the tiles (lane = tile).  A row that
+// crosses workgroups is settled like in the one-launch form (see there), its groups
+// being the workgroups here.  One launch; rows without nonzeros are zeroed on the way,
+// a share per workgroup.
+// ----------------------------------------------------------------------------
+constexpr int STAGE_BYTES = 79 * 1024;     // twice, and the tail's few hundred bytes: of 160 KB
+constexpr int WAIT_LDS = 0xc07f, WAIT_LOADS = 0x0f70;       // s_waitcnt: lgkmcnt(0); vmcnt(0)
+
+// 16 or 4 bytes per lane from a buffer to consecutive bytes of LDS (counted as a load of the wavefront)
+__device__ __forceinline__ void to_lds_16(__amdgpu_buffer_rsrc_t r, char* lds, int offset) {
+#ifdef __HIP_DEVICE_COMPILE__
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, offset, 0, 0, 0);
+#endif
+}
+__device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, int offset) {
+#ifdef __HIP_DEVICE_COMPILE__
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 4, offset, 0, 0, 0);
+#endif
+}
+
+struct RowSpan { int first, groups; };     // the workgroups a row touches
+
+// part_bytes: of x, a multiple of 1024, at most STAGE_BYTES; parts * part_bytes covers x
+template <int SIGMA, int WAVES, int K, bool KEEP, typename VT>
+__global__ void __launch_bounds__(WAVES * OMEGA)
+k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail, uint32_t zero_rows, int part_bytes, int parts,
+              const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ tile_ptr,
+              const uint32_t* __restrict__ tile_desc, const int32_t* __restrict__ eop, const int32_t* __restrict__ eo,
+              const int32_t* __restrict__ col_idx, const VT* __restrict__ val, const VT* __restrict__ x, VT* __restrict__ y,
+              VT* __restrict__ carry, uint64_t* __restrict__ meet, uint32_t* __restrict__ arrived,
+              const uint32_t* __restrict__ tile_head) {
+    constexpr uint32_t ROWMASK = Index<int32_t>::ROWMASK, DIRTY = Index<int32_t>::DIRTY;
+    constexpr int T = OMEGA * SIGMA, THREADS = WAVES * OMEGA, TILES = WAVES * K;
+    constexpr int YSH = SIGMA + SBITS;
+    static_assert(YSH + 32 - __builtin_clz(uint32_t(T - 1)) <= 32, "one descriptor word");
+    static_assert(TILES <= OMEGA && (WAVES + 1) / 2 * T * int(sizeof(VT)) <= STAGE_BYTES, "one lane per tile; the segment sums in the stage's place");
+    // two arrays, not the halves of one: the compiler has the reads of one wait for what is on its way to it only
+    __shared__ __align__(16) char xs0[STAGE_BYTES], xs1[STAGE_BYTES];
+    __shared__ VT first_sum[TILES], last_sum[TILES];
+    __shared__ uint32_t tile_bits[TILES];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
+    const int last_group = int(groups);            // the incomplete tile's
+    const auto group_of = [&](int e) -> int { const int tile = e / T; return tile < pc ? tile / TILES : last_group; };
+    const auto span_of = [&](uint32_t row) -> RowSpan {
+        const int g0 = group_of(row_ptr[row]);
+        return RowSpan{g0, group_of(row_ptr[row + 1] - 1) - g0 + 1};
+    };
+    if (blockIdx.x < has_tail) {
+        const uint32_t row = tile_ptr[pc] & ROWMASK;
+        const RowSpan s = row < uint32_t(m) ? span_of(row) : RowSpan{0, 1};
+        spmv_tail<VT, int32_t>(m, nnz, pc * T, row, row_ptr, col_idx, val, x, y, carry + pc, carry, meet, arrived,
+                               uint2{uint32_t(s.first), uint32_t(s.groups)}, nullptr, nullptr);
+        return;
+    }
+    const int group = int(blockIdx.x - has_tail);
+    const int tile0 = group * TILES, mine = tile0 + wave * K;
+
+    // ---- x, first part; behind it the tiles' columns, the values of the first tile
+    const auto xbuf = tile_buffer(x, n * int(sizeof(VT)));
+    const bool wide16 = (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+    const auto stage = [&](int part, char* to) {     // (what lies behind x reads as 0)
+        for (int at = wave * 1024; at < part_bytes; at += WAVES * 1024) {
+            const int off = part * part_bytes + at;
+            if (wide16 && off + 1024 <= n * int(sizeof(VT))) {
+                to_lds_16(xbuf, to + at, off + lane * 16);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; q++) to_lds_4(xbuf, to + at + q * 256, off + q * 256 + lane * 4);
+            }
+        }
+    };
+    stage(0, xs0);
+    asm volatile("" ::: "memory");
+    int32_t c[K][SIGMA];
+    uint32_t dw[K], tp[K], head[K + 1];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int tile = mine + k;
+        const auto cols = tile_buffer(col_idx + size_t(tile < pc ? tile : 0) * T, tile < pc ? T * 4 : 0);    // (an empty buffer reads as 0)
+        const auto descs = tile_buffer(tile_desc + size_t(tile < pc ? tile : 0) * OMEGA, tile < pc ? OMEGA * 4 : 0);
+#pragma unroll
+        for (int j = 0; j < SIGMA; j++) c[k][j] = stream_from<int32_t, KEEP>(cols, (j * OMEGA + lane) * 4) * int(sizeof(VT));
+        dw[k] = stream_from<uint32_t, KEEP>(descs, lane * 4);
+    }
+#pragma unroll
+    for (int k = 0; k <= K; k++) {
+        const int tile = mine + k < pc ? mine + k : pc;
+        head[k] = tile_head[tile];
+        if (k < K) tp[k] = tile_ptr[tile];
+    }
+    uint32_t row_in = 0, row_out = 0;
+    RowSpan si = {0, 1}, so = {0, 1};
+    if (wave == 0) {
+        row_in = tile_ptr[tile0] & ROWMASK;
+        row_out = tile_ptr[tile0 + TILES < pc ? tile0 + TILES : pc] & ROWMASK;
+        if (row_in < uint32_t(m)) si = span_of(row_in);
+        if (row_out < uint32_t(m)) so = span_of(row_out);
+    }
+    asm volatile("" ::: "memory");
+    VT v[K][SIGMA];
+    const auto load_v = [&](int k) {
+        const int tile = mine + k;
+        const auto vals = tile_buffer(val + size_t(tile < pc ? tile : 0) * T, tile < pc ? T * int(sizeof(VT)) : 0);
+#pragma unroll
+        for (int j = 0; j < SIGMA; j++) v[k][j] = stream_from<VT, KEEP>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
+    };
+    load_v(0);
+    if (zero_rows) {
+        const int r1 = int(int64_t(m) * (group + 1) / int(groups));
+        for (int r = int(int64_t(m) * group / int(groups)) + int(threadIdx.x); r < r1; r += THREADS)
+            if (row_ptr[r] == row_ptr[r + 1]) y[r] = VT(0);
+    }
+    // ---- gather: every entry takes its x from the part that holds its column
+    VT xv[K][SIGMA];
+#pragma unroll
+    for (int k = 0; k < K; k++)
+#pragma unroll
+        for (int j = 0; j < SIGMA; j++) xv[k][j] = VT(0);
+    const auto take = [&](int part, const char* from, char* next) {
+        // This part has arrived: what this wavefront asked for before the columns came before
+        // them (loads return in order); later parts, and its reads of the part before.
+        __builtin_amdgcn_s_waitcnt(WAIT_LDS);
+        if (part > 0) __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
+        else asm volatile("" :: "v"(c[K - 1][SIGMA - 1]), "v"(dw[K - 1]) : "memory");
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();      // everybody's share of it, and nobody reads the part before any more
+        asm volatile("" ::: "memory");
+        if (part + 1 < parts) stage(part + 1, next);
+        const uint32_t base = uint32_t(part * part_bytes);
+#pragma unroll
+        for (int k = 0; k < K; k++)
+#pragma unroll
+            for (int j = 0; j < SIGMA; j++) {
+                const uint32_t at = uint32_t(c[k][j]) - base;
+                if (at < uint32_t(part_bytes)) xv[k][j] = *reinterpret_cast<const VT*>(from + at);
+            }
+    };
+    for (int part = 0; part < parts; part += 2) {
+        take(part, xs0, xs1);
+        if (part + 1 < parts) take(part + 1, xs1, xs0);
+    }
+    __syncthreads();                   // the segment sums go where x was
+#pragma unroll
+    for (int k = 1; k < K; k++) load_v(k);
+
+    // ---- the tiles, one after the other, as in k_spmv
+    VT* const yb = reinterpret_cast<VT*>(wave % 2 ? xs1 : xs0) + wave / 2 * T;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int tile = mine + k;
+        if (tile >= pc) {              // uniform
+            if (lane == 0) tile_bits[wave * K + k] = 0;
+            continue;
+        }
+        constexpr uint32_t FLAG_MASK = (1u << SIGMA) - 1;
+        uint32_t nseg = walk_columns<SIGMA, VT>(dw[k] & FLAG_MASK, uint32_t(uint64_t(dw[k]) >> YSH), v[k], xv[k], yb, lane);
+        if (nseg > uint32_t(T)) nseg = T;
+        const bool dirty = (tp[k] & DIRTY) != 0;
+        const uint32_t row0 = tp[k] & ROWMASK;
+        const int32_t* eo_t = nullptr;
+        if (dirty) {
+            const int32_t e0 = eop[tile], e1 = eop[tile + 1];
+            eo_t = eo + e0;
+            if (nseg > uint32_t(e1 - e0)) nseg = uint32_t(e1 - e0);
+        }
+        wave_sync_lds();
+        const bool cont0 = head[k] != 0, goes_on = head[k + 1] != 0;
+        for (uint32_t s0 = 0; s0 < nseg; s0 += OMEGA) {
+            const uint32_t sg = s0 + lane;
+            if (sg < nseg) {
+                const uint32_t row = row0 + (dirty ? uint32_t(eo_t[sg]) : sg);
+                if (!(sg == 0 && cont0) && !(sg == nseg - 1 && goes_on) && row < uint32_t(m)) y[row] = yb[sg];
+            }
+        }
+        if (lane == 0) {
+            first_sum[wave * K + k] = nseg ? yb[0] : VT(0);
+            last_sum[wave * K + k] = nseg ? yb[nseg - 1] : VT(0);
+            tile_bits[wave * K + k] = 1u | (cont0 ? 2u : 0u) | (goes_on ? 4u : 0u) | (nseg == 1 ? 8u : 0u);
+        }
+        wave_sync_lds();
+    }
+    __syncthreads();
+    if (wave != 0) return;
+
+    // ---- rows that cross the workgroup's tiles, lane = tile: a tile inside a row passes
+    // on what it got and its own sum
+    const uint32_t bits = lane < TILES ? tile_bits[lane] : 0u;
+    const bool live = bits & 1u, cont0 = bits & 2u, goes_on = bits & 4u, single = bits & 8u;
+    const VT first = live ? first_sum[lane] : VT(0);
+    const bool inside = live && single && cont0;                   // what it got goes through it
+    VT sum = live ? (inside ? first : last_sum[lane]) : VT(0);
+    const uint64_t begins = __ballot(live && !inside);
+    const uint64_t upto = begins & (~0ull >> (OMEGA - 1 - lane));  // of the lanes up to this one
+    const int from = upto ? OMEGA - 1 - __builtin_clzll(upto) : 0; // where the run of this lane begins
+#pragma unroll
+    for (int d = 1; d < OMEGA; d <<= 1) {
+        const VT up = __shfl_up(sum, d, OMEGA);
+        if (lane - d >= from) sum += up;
+    }
+    const VT before = __shfl_up(sum, 1, OMEGA);
+    const VT total = lane > 0 ? before + first : first;
+    const bool outside = cont0 && (begins & ((1ull << lane) - 1)) == 0;     // the row began before the workgroup
+    const bool ends = cont0 && !(single && goes_on);
+    const uint32_t my_row = live ? tile_ptr[tile0 + lane] & ROWMASK : 0u;
+    if (ends && !outside && my_row < uint32_t(m)) y[my_row] = total;
+    // what crosses the workgroup's own boundaries: at most one row at each
+    const int lanes = __popcll(__ballot(live));
+    const bool pub_in = (__ballot(cont0) & 1u) != 0;
+    const bool pub_out = begins != 0 && ((__ballot(goes_on) >> (lanes - 1)) & 1u) != 0;
+    if (!pub_in && !pub_out) return;
+    const uint64_t ended = __ballot(ends && outside);
+    const VT out_part = __shfl(sum, lanes - 1, OMEGA);
+    const VT in_part = ended ? __shfl(total, __builtin_ctzll(ended), OMEGA) : out_part;
+    uint64_t other_in = MEET_EMPTY, other_out = MEET_EMPTY;
+    uint32_t before_in = 0, before_out = 0;
+    const bool count_row_in = pub_in && si.groups != 2, count_row_out = pub_out && so.groups != 2;
+    if (lane == 0) {
+        if (pub_in && !count_row_in) other_in = swap_in(meet_at(meet, si.first), meet_word(in_part));
+        if (pub_out && !count_row_out) other_out = swap_in(meet_at(meet, group), meet_word(out_part));
+        if (count_row_in) publish(carry + group, in_part);
+        if (count_row_out) publish(meet_at(meet, group), meet_word(out_part));
+        if (count_row_in || count_row_out) {
+            wait_for_memory();
+            if (count_row_in) before_in = count_in(arrived + si.first);
+            if (count_row_out) before_out = count_in(arrived + group);
+        }
+        if (pub_in && !count_row_in && other_in != MEET_EMPTY) {
+            if (row_in < uint32_t(m)) y[row_in] = meet_value<VT>(other_in) + in_part;
+            publish(meet_at(meet, si.first), MEET_EMPTY);
+        }
+        if (pub_out && !count_row_out && other_out != MEET_EMPTY) {
+            if (row_out < uint32_t(m)) y[row_out] = out_part + meet_value<VT>(other_out);
+            publish(meet_at(meet, group), MEET_EMPTY);
+        }
+    }
+    if (count_row_in && __shfl(before_in, 0, OMEGA) == uint32_t(si.groups - 1))
+        assemble_row<VT>(carry, meet, arrived, si.first, si.first + si.groups - 1, y, row_in, m, lane);
+    if (count_row_out && __shfl(before_out, 0, OMEGA) == uint32_t(so.groups - 1))
+        assemble_row<VT>(carry, meet, arrived, group, group + so.groups - 1, y, row_out, m, lane);
 }
 
 // ----------------------------------------------------------------------------
@@ -2086,6 +2436,56 @@ hipError_t launch_spmv(bool keep, const Geom& g, int m, int n, IT nnz, const IT*
     return hipGetLastError();
 }
 
+// The shapes of k_spmv_staged: as many tiles per wavefront as its registers hold.
+constexpr int staged_most(int sigma, size_t value_bytes) { return sigma == RULE_SIGMA_SMALL ? (value_bytes == 8 ? 3 : 4) : 2; }
+constexpr int staged_waves(int sigma, size_t value_bytes, int k) { return sigma == RULE_R && value_bytes == 8 && k == 2 ? 12 : 16; }
+constexpr int STAGE_CUS = 256;
+inline int staged_parts(int n, size_t value_bytes) { return int((int64_t(n) * int64_t(value_bytes) + STAGE_BYTES - 1) / STAGE_BYTES); }
+inline int staged_rounds(const Geom& g, size_t value_bytes, int k) {       // of one workgroup per CU
+    const int tiles = staged_waves(g.sigma, value_bytes, k) * k;
+    return ((g.pc + tiles - 1) / tiles + (g.p > g.pc ? 1 : 0) + STAGE_CUS - 1) / STAGE_CUS;
+}
+// Tiles per wavefront for a matrix that may be one for k_spmv_staged, 0 for the others:
+// the fewest that give the fewest rounds (8 M entries in single precision: 4 in one round 20.5 us, 2 in
+// two 25.3, 3 in two 28.8).  Below STAGE_MIN_TILES too few CUs have work (1 M entries in
+// rows of 100, x of 64 KB: 7.5 -> 8.3).
+constexpr int STAGE_MIN_TILES = 3072;
+constexpr int64_t STAGE_MIN_X = 16 << 10;
+inline int staged_tiles(const Geom& g, int n, size_t value_bytes) {
+    if (!rule_sigma(g.sigma) || g.p < STAGE_MIN_TILES || int64_t(n) * int64_t(value_bytes) < STAGE_MIN_X) return 0;
+    int k = staged_most(g.sigma, value_bytes);
+    const int fewest = staged_rounds(g, value_bytes, k);
+    while (k > 1 && staged_rounds(g, value_bytes, k - 1) == fewest) k--;
+    return k;
+}
+// The fewest entries that gather a line of their own for the kernel to pay.  What it costs is
+// parts of x, one per round and STAGE_BYTES of x, 1.0-1.25 us each; such an entry costs k_spmv 3.4 us
+// per million beyond its stream.  Measured at 1 to 28 M entries, x of 24 KB to 1.2 MB:
+// with STAGE_MIN_ENTRIES per part it gains 8 % or more nearly everywhere (6 M entries, 15
+// parts: 38.4 -> 35.3; 4 M in rows of 500, 10 parts: 25.1 -> 22.0), and what it passes by would gain no
+// more (2 M, 6 parts: 14.6 -> 13.4) or lose (10 M, 15 parts in two rounds: 59.5 ->
+// 66.5).  At height 16 in double precision several rounds cost more, there is no other workgroup to fill the
+// gaps between them: 20 M entries, 6 parts in four rounds 98.1 -> 83.5, 12 parts 100.7 ->
+// 115.6.
+constexpr int64_t STAGE_MIN_ENTRIES = 400 * 1000, STAGE_MIN_ENTRIES_16 = 720 * 1000;
+inline int64_t staged_min_entries(const Geom& g, int n, size_t value_bytes, int k) {
+    const int rounds = staged_rounds(g, value_bytes, k);
+    return int64_t(rounds) * staged_parts(n, value_bytes) * (g.sigma == RULE_R && value_bytes == 8 && rounds > 1 ? STAGE_MIN_ENTRIES_16 : STAGE_MIN_ENTRIES);
+}
+
+template <int SIGMA, int K, typename VT>
+hipError_t launch_staged(bool keep, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
+                         const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
+                         uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
+    constexpr int WAVES = staged_waves(SIGMA, sizeof(VT), K);
+    const uint32_t groups = uint32_t((g.pc + WAVES * K - 1) / (WAVES * K)), has_tail = g.p > g.pc ? 1u : 0u;
+    const int bytes = n * int(sizeof(VT)), parts = staged_parts(n, sizeof(VT)), part_bytes = ((bytes + parts - 1) / parts + 1023) / 1024 * 1024;
+    const auto kernel = keep ? k_spmv_staged<SIGMA, WAVES, K, true, VT> : k_spmv_staged<SIGMA, WAVES, K, false, VT>;
+    hipLaunchKernelGGL(kernel, dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
+                       part_bytes, parts, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head);
+    return hipGetLastError();
+}
+
 template <int SIGMA, bool BACK, typename VT>
 hipError_t launch_transpose(bool keep, const Geom& g, int n, int64_t nnz, int32_t* col_idx, VT* val,
                             uint32_t* status, int32_t* last_col, VT* last_val, const DescJob& job, hipStream_t s) {
@@ -2207,6 +2607,7 @@ struct csr5_handle_s {
     // The tile kernel's order of the tiles (order_place), in the place of the records; NULL: by number
     uint32_t* order;
     uint32_t order_second, order_len;
+    int staged;            // tiles per wavefront of k_spmv_staged; 0: not for this matrix
     void* owned;           // hipMalloc'ed block, or NULL when a workspace was given
     hipStream_t conv_stream;
     int device;            // HIP device that was current at conversion
@@ -2411,6 +2812,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     h->last_val = L.has_last ? basep + L.off_last : nullptr;                               // record + 0
     h->last_col = L.has_last ? reinterpret_cast<int32_t*>(basep + L.off_last + LOOK * 8) : nullptr;
     h->status = reinterpret_cast<uint32_t*>(basep + L.off_status);
+    h->staged = 0;
     h->order = nullptr;
     h->order_second = h->order_len = 0;
     h->conv_stream = s;
@@ -2446,6 +2848,12 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         static_assert(ORDER_MIN_TILES * words_per_tile >= ORDER_MIN_TILES + 64 + (ORDER_MIN_TILES / ORDER_SLICE + 1) * 2 * ORDER_BUCKETS &&
                       ORDER_SLICE * words_per_tile >= ORDER_SLICE + 2 * ORDER_BUCKETS, "list and bases in the records' place");
     }
+    // Whether k_spmv_staged is for this matrix is looked up along with the scan where its size is right
+    SampleJob sample = {nullptr, n, sigma, int(sizeof(VT)), h->status + 3};
+    static_assert(STAGE_MIN_TILES >= SAMPLE_TILES && one_launch_fits(RULE_R, SCAN_SINGLE) && !one_launch_fits(RULE_R, SCAN_SINGLE + 1), "taken by k_scan_eop");
+    const int staged = !wide && !(flags & CSR5_FLAG_NO_HOST_CHECK) && h->span && h->aux_form == 0 ? staged_tiles(g, n, sizeof(VT)) : 0;
+    const int64_t staged_entries = staged ? staged_min_entries(g, n, sizeof(VT), staged) : 0;
+    if (staged && int64_t(nnz) >= staged_entries && int64_t(n) * int64_t(sizeof(VT)) <= SAMPLE_MAX_LINES * 128) sample.col_idx = col_idx;
     DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.slices ? static_cast<int32_t*>(h->carry) : nullptr};
     {   // step 2a
         const size_t nb_tiles = (size_t(g.p) + 1 + PREP_THREADS - 1) / PREP_THREADS;
@@ -2470,7 +2878,8 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         }
     }
     if (e == hipSuccess && g.pc <= SCAN_SINGLE) {
-        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr, h->status, order);
+        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices + (sample.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr,
+                           h->status, order, sample);
         e = hipGetLastError();
     } else if (e == hipSuccess) {
         IT* chunk_sum = reinterpret_cast<IT*>(basep + L.off_scan);
@@ -2500,8 +2909,9 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK)) {
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
-        uint32_t got[3] = {0, 0, 0};      // the status word and the plan of the tile order behind it
-        int rc = read_status(h, got, order.slices ? 3 : 1);
+        uint32_t got[4] = {0, 0, 0, 0};   // the status word, behind it the plan of the tile order and the answer on the columns
+        int rc = read_status(h, got, sample.col_idx ? 4 : (order.slices ? 3 : 1));
+        if (rc == CSR5_OK && got[3] && int64_t(nnz) * got[3] >= staged_entries * SAMPLES) h->staged = staged;
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];
@@ -2593,6 +3003,23 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
 #define ARGS keep, h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
              static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->span, h->status, h->tile_head, h->last_col, \
              static_cast<const VT*>(h->last_val), zero_rows, far_mode, h->order, h->order_second, h->order_len, s
+    // x through LDS: one launch, which wants the handle's own slot like the one-launch form
+    if constexpr (std::is_same<IT, int32_t>::value) {
+        if (h->staged && !carry_mem) {
+            if (!(which & LAUNCH_TILES)) return CSR5_OK;
+#define STAGED(S, K) e = launch_staged<S, K, VT>(keep, h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx, \
+                                               static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->tile_head, zero_rows, s)
+            if (h->g.sigma == RULE_R) {
+                if (h->staged == 1) STAGED(RULE_R, 1);
+                else STAGED(RULE_R, 2);
+            } else if (h->staged == 1) STAGED(RULE_SIGMA_SMALL, 1);
+            else if (h->staged == 2) STAGED(RULE_SIGMA_SMALL, 2);
+            else if (h->staged == 3) STAGED(RULE_SIGMA_SMALL, 3);
+            else if constexpr (staged_most(RULE_SIGMA_SMALL, sizeof(VT)) >= 4) STAGED(RULE_SIGMA_SMALL, 4);
+#undef STAGED
+            return e == hipSuccess ? CSR5_OK : CSR5_EHIP;
+        }
+    }
     if (which & LAUNCH_TILES) {
 #define X(S) case S:                                                                                  \
         if (look_sigma(S) && can_look) e = launch_spmv<S, VT, IT, look_sigma(S) ? MODE_LOOK : MODE_CARRY>(ARGS); \
