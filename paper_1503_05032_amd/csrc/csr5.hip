@@ -322,7 +322,7 @@ k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, i
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
-    if (gid < 4) status[gid] = 0u;        // and the plan of the tile order, the answer of sample_columns
+    if (gid < 5) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
     if (order_total)
         for (size_t b = gid; b < 2 * ORDER_BUCKETS; b += size_t(gridDim.x) * blockDim.x) order_total[b] = 0u;
     uint32_t found = 0;
@@ -731,11 +731,83 @@ __device__ void sample_columns(int pc, const SampleJob& job) {
     }
 }
 
+// Orders LDS traffic between the lanes of ONE wavefront: LDS instructions of a
+// wavefront execute in order, so what is needed is that the compiler keeps the
+// stores before and the loads after this point.
+__device__ __forceinline__ void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The part of x that a workgroup of k_spmv_staged's window form keeps in LDS: around the place
+// where the diagonal passes through its rows (r0 to r1), in bytes.  slope: columns per row.
+// As much as lets two workgroups share a CU (in single precision 52 KB and three workgroups
+// gain 3 % on rows with a window of 40 KB and lose 22 % on one of 80 KB).
+constexpr int WINDOW_BYTES = 78 * 1024;
+__device__ __forceinline__ int window_first(uint32_t r0, uint32_t r1, float slope, int x_bytes, int value_bytes) {
+    const int first = int(float(r0 + (r1 - r0) / 2) * slope) * value_bytes - WINDOW_BYTES / 2;
+    const int most = x_bytes > WINDOW_BYTES ? x_bytes - WINDOW_BYTES : 0;
+    return (first < 0 ? 0 : (first < most ? first : most)) & ~127;
+}
+
+// Of the same sample: how many entries lie in their workgroup's window, and in how many
+// lines of it, tile by tile; what the host needs beside sizes to decide for the window form
+// (window_pays).
+struct WindowJob {
+    const int32_t* col_idx;          // NULL: nothing to do
+    const uint32_t* tile_ptr;
+    int32_t m, n, sigma, value_bytes, tiles;     // tiles of a workgroup
+    float slope;
+    uint32_t* answer;                // entries << 16 | lines; cleared with the status word
+};
+
+__device__ void sample_window(int pc, const WindowJob& job) {
+    constexpr int WAVES = SCAN_THREADS / OMEGA, PER_WAVE = SAMPLE_TILES / WAVES, LINES = WINDOW_BYTES / 128;
+    __shared__ uint32_t seen[WAVES][(LINES + 3) / 4];     // a byte per line
+    __shared__ uint32_t near, lines;
+    const int lane = lane_id(), wave = threadIdx.x / OMEGA;
+    if (threadIdx.x == 0) near = lines = 0;
+    uint32_t at[PER_WAVE], next[PER_WAVE];
+    int first[PER_WAVE];
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++) {
+        const int q = wave * PER_WAVE + u, tile = int(int64_t(pc) * q / SAMPLE_TILES), tile0 = tile / job.tiles * job.tiles;
+        const int j = (q + lane / 16 * job.sigma / 4) % (job.sigma - 1);           // see sample_columns
+        const int32_t* const pair = job.col_idx + int64_t(tile) * (job.sigma * OMEGA) + j * OMEGA + lane;
+        at[u] = uint32_t(pair[0]);
+        next[u] = uint32_t(pair[OMEGA]);
+        const uint32_t r0 = job.tile_ptr[tile0] & Index<int32_t>::ROWMASK, r1 = job.tile_ptr[tile0 + job.tiles < pc ? tile0 + job.tiles : pc] & Index<int32_t>::ROWMASK;
+        first[u] = window_first(r0, r1, job.slope, job.n * job.value_bytes, job.value_bytes);
+    }
+    __syncthreads();
+    constexpr uint32_t window = WINDOW_BYTES;
+    uint32_t my_near = 0, my_lines = 0;                    // of the wavefront's tiles; of the lane
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++) {
+        for (int w = lane; w < (LINES + 3) / 4; w += OMEGA) seen[wave][w] = 0;
+        wave_sync_lds();
+        const uint32_t last = uint32_t(job.n - 1);         // (out of range: rejected input)
+        const uint32_t a = (at[u] < last ? at[u] : last) * uint32_t(job.value_bytes) - uint32_t(first[u]);
+        const uint32_t b = (next[u] < last ? next[u] : last) * uint32_t(job.value_bytes) - uint32_t(first[u]);
+        if (a < window) reinterpret_cast<uint8_t*>(seen[wave])[a / 128] = 1;
+        if (b < window) reinterpret_cast<uint8_t*>(seen[wave])[b / 128] = 1;
+        my_near += uint32_t(__popcll(__ballot(a < window)) + __popcll(__ballot(b < window)));
+        wave_sync_lds();
+        for (int w = lane; w < (LINES + 3) / 4; w += OMEGA) my_lines += uint32_t(__popc(seen[wave][w]));
+        wave_sync_lds();
+    }
+    if (lane == 0) atomicAdd(&near, my_near);
+    if (my_lines) atomicAdd(&lines, my_lines);
+    __syncthreads();
+    if (threadIdx.x == 0) *job.answer = near << 16 | lines;
+}
+
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-           uint32_t* __restrict__ status, const OrderJob job, const SampleJob sample) {
-    if (sample.col_idx && blockIdx.x == gridDim.x - 1) return sample_columns(pc, sample);
+           uint32_t* __restrict__ status, const OrderJob job, const SampleJob sample, const WindowJob window) {
+    if (window.col_idx && blockIdx.x == gridDim.x - 1) return sample_window(pc, window);
+    if (sample.col_idx && blockIdx.x == gridDim.x - (window.col_idx ? 2u : 1u)) return sample_columns(pc, sample);
     if (blockIdx.x > 0) return order_count<IT>(pc, job, int(blockIdx.x) - 1, tile_ptr, status);
     IT total = 0;
     if (*status & STATUS_SCAN_NEEDED)
@@ -747,7 +819,8 @@ k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* 
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_chunks(int pc, IT* __restrict__ eop, IT* __restrict__ chunk_sum, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-              const uint32_t* __restrict__ status, const OrderJob job) {
+              const uint32_t* __restrict__ status, const OrderJob job, const WindowJob window) {
+    if (window.col_idx && blockIdx.x == gridDim.x - 1) return sample_window(pc, window);
     const int chunk = int(blockIdx.x) - job.slices;
     if (chunk < 0) return order_count<IT>(pc, job, int(blockIdx.x), tile_ptr, status);
     if (!(*status & STATUS_SCAN_NEEDED)) return;
@@ -864,14 +937,6 @@ struct TransposeShape {
     static constexpr int WAVES = tile_group_waves(SIGMA);
     static constexpr int PITCH = SIGMA | 1;
 };
-
-// Orders LDS traffic between the lanes of ONE wavefront: LDS instructions of a
-// wavefront execute in order, so what is needed is that the compiler keeps the
-// stores before and the loads after this point.
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 constexpr int FLAG_ROWS_MAX = 4096;
 // Rows beyond a tile's first 64 are asked for this many wavefronts of them at a time:
@@ -2027,6 +2092,7 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
 // being the workgroups here.  One launch; rows without nonzeros are zeroed on the way,
 // a share per workgroup.
 // ----------------------------------------------------------------------------
+constexpr int LDS_BYTES = 160 * 1024;       // of a CU
 constexpr int STAGE_BYTES = 79 * 1024;     // twice, and the tail's few hundred bytes: of 160 KB
 constexpr int WAIT_LDS = 0xc07f, WAIT_LOADS = 0x0f70;       // s_waitcnt: lgkmcnt(0); vmcnt(0)
 
@@ -2044,22 +2110,41 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 
 struct RowSpan { int first, groups; };     // the workgroups a row touches
 
-// part_bytes: of x, a multiple of 1024, at most STAGE_BYTES; parts * part_bytes covers x
-template <int SIGMA, int WAVES, int K, bool KEEP, typename VT>
-__global__ void __launch_bounds__(WAVES * OMEGA)
+// part_bytes: of x, a multiple of 1024, at most STAGE_BYTES; parts * part_bytes covers x.
+//
+// WINDOW, for matrices most of whose entries lie near the diagonal but not in order: a band
+// with random columns, wider than an L1 and narrower than LDS.  k_spmv takes a line from the
+// L2 for each of those entries, too.  Here the workgroup keeps the one part of x around its
+// rows' place on the diagonal (window_first), and the entries outside it come from memory as in
+// k_spmv, asked for while the window is on its way.  Neighbouring workgroups run on one XCD
+// (contiguous order), so that a window is read from memory once per L2.  Two workgroups of
+// WINDOW_WAVES per CU, smaller than in the form above: nothing is read twice for it, and one has its
+// loads in flight while the other walks.
+// Bound by the stream and, where there are some, by the lines from outside the window.  Whole
+// SpMV, before -> after: rows of 8-16 entries within +-5000 columns, 30 M 124.0 -> 92.7 us,
+// 6 M 31.3 -> 23.6, single precision 4 M 18.3 -> 11.9; rows of 40-80, 45 M 154.5 -> 111.3; a
+// fifth of the rows random (mixed), 12.6 M 83.9 -> 69.5, 34 M 270 -> 254, 136 M 1233 ->
+// 1185 (59 M lines from memory are 1000 of it).
+// Tried: 16 wavefronts of one tile at height 8: 500 000 rows of mixed 49.2 -> 50.5; 4 of four
+// 54.2; 8 of three 48.9, but 23.2 -> 28.2 at 200 000 rows.
+// Rows that cross workgroups: as above where the handle's slot has what that wants (meet),
+// through the auxiliary array and k_spmv_fixup otherwise, one sum per workgroup.
+template <int SIGMA, int WAVES, int K, bool KEEP, bool WINDOW, typename VT>
+__global__ void __launch_bounds__(WAVES * OMEGA, WINDOW ? WAVES * (LDS_BYTES / WINDOW_BYTES) / 4 : 1)
 k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail, uint32_t zero_rows, int part_bytes, int parts,
               const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ tile_ptr,
               const uint32_t* __restrict__ tile_desc, const int32_t* __restrict__ eop, const int32_t* __restrict__ eo,
               const int32_t* __restrict__ col_idx, const VT* __restrict__ val, const VT* __restrict__ x, VT* __restrict__ y,
               VT* __restrict__ carry, uint64_t* __restrict__ meet, uint32_t* __restrict__ arrived,
-              const uint32_t* __restrict__ tile_head) {
+              const uint32_t* __restrict__ tile_head, float slope) {
     constexpr uint32_t ROWMASK = Index<int32_t>::ROWMASK, DIRTY = Index<int32_t>::DIRTY;
     constexpr int T = OMEGA * SIGMA, THREADS = WAVES * OMEGA, TILES = WAVES * K;
     constexpr int YSH = SIGMA + SBITS;
     static_assert(YSH + 32 - __builtin_clz(uint32_t(T - 1)) <= 32, "one descriptor word");
-    static_assert(TILES <= OMEGA && (WAVES + 1) / 2 * T * int(sizeof(VT)) <= STAGE_BYTES, "one lane per tile; the segment sums in the stage's place");
+    static_assert(TILES <= OMEGA && (WINDOW ? WAVES * T * int(sizeof(VT)) <= WINDOW_BYTES : (WAVES + 1) / 2 * T * int(sizeof(VT)) <= STAGE_BYTES),
+                  "one lane per tile; the segment sums in the stage's place");
     // two arrays, not the halves of one: the compiler has the reads of one wait for what is on its way to it only
-    __shared__ __align__(16) char xs0[STAGE_BYTES], xs1[STAGE_BYTES];
+    __shared__ __align__(16) char xs0[WINDOW ? WINDOW_BYTES : STAGE_BYTES], xs1[WINDOW ? 16 : STAGE_BYTES];
     __shared__ VT first_sum[TILES], last_sum[TILES];
     __shared__ uint32_t tile_bits[TILES];
     const int lane = lane_id();
@@ -2073,19 +2158,22 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
     if (blockIdx.x < has_tail) {
         const uint32_t row = tile_ptr[pc] & ROWMASK;
         const RowSpan s = row < uint32_t(m) ? span_of(row) : RowSpan{0, 1};
-        spmv_tail<VT, int32_t>(m, nnz, pc * T, row, row_ptr, col_idx, val, x, y, carry + pc, carry, meet, arrived,
+        spmv_tail<VT, int32_t>(m, nnz, pc * T, row, row_ptr, col_idx, val, x, y, carry + pc, WINDOW && !meet ? nullptr : carry, meet, arrived,
                                uint2{uint32_t(s.first), uint32_t(s.groups)}, nullptr, nullptr);
         return;
     }
-    const int group = int(blockIdx.x - has_tail);
+    const int group = int(WINDOW ? xcd_order(blockIdx.x - has_tail, groups, 0) : blockIdx.x - has_tail);
     const int tile0 = group * TILES, mine = tile0 + wave * K;
+    int window = 0;
+    if constexpr (WINDOW)
+        window = window_first(tile_ptr[tile0] & ROWMASK, tile_ptr[tile0 + TILES < pc ? tile0 + TILES : pc] & ROWMASK, slope, n * int(sizeof(VT)), int(sizeof(VT)));
 
     // ---- x, first part; behind it the tiles' columns, the values of the first tile
     const auto xbuf = tile_buffer(x, n * int(sizeof(VT)));
     const bool wide16 = (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const auto stage = [&](int part, char* to) {     // (what lies behind x reads as 0)
         for (int at = wave * 1024; at < part_bytes; at += WAVES * 1024) {
-            const int off = part * part_bytes + at;
+            const int off = (WINDOW ? window : part * part_bytes) + at;
             if (wide16 && off + 1024 <= n * int(sizeof(VT))) {
                 to_lds_16(xbuf, to + at, off + lane * 16);
             } else {
@@ -2094,7 +2182,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
             }
         }
     };
-    stage(0, xs0);
+    if constexpr (!WINDOW) stage(0, xs0);
     asm volatile("" ::: "memory");
     int32_t c[K][SIGMA];
     uint32_t dw[K], tp[K], head[K + 1];
@@ -2130,6 +2218,13 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         for (int j = 0; j < SIGMA; j++) v[k][j] = stream_from<VT, KEEP>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
     };
     load_v(0);
+    if constexpr (WINDOW) {
+#pragma unroll
+        for (int k = 1; k < K; k++) load_v(k);
+        asm volatile("" ::: "memory");
+        stage(0, xs0);
+        asm volatile("" ::: "memory");
+    }
     if (zero_rows) {
         const int r1 = int(int64_t(m) * (group + 1) / int(groups));
         for (int r = int(int64_t(m) * group / int(groups)) + int(threadIdx.x); r < r1; r += THREADS)
@@ -2160,16 +2255,40 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
                 if (at < uint32_t(part_bytes)) xv[k][j] = *reinterpret_cast<const VT*>(from + at);
             }
     };
-    for (int part = 0; part < parts; part += 2) {
-        take(part, xs0, xs1);
-        if (part + 1 < parts) take(part + 1, xs1, xs0);
+    if constexpr (WINDOW) {
+        // what lies outside the window comes from memory, on its way while the window is waited for
+#pragma unroll
+        for (int k = 0; k < K; k++)
+#pragma unroll
+            for (int j = 0; j < SIGMA; j++)
+                if (uint32_t(c[k][j]) - uint32_t(window) >= uint32_t(part_bytes))
+                    xv[k][j] = *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(x) + uint32_t(c[k][j]));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < K; k++)
+#pragma unroll
+            for (int j = 0; j < SIGMA; j++) {
+                const uint32_t at = uint32_t(c[k][j]) - uint32_t(window);
+                if (at < uint32_t(part_bytes)) xv[k][j] = *reinterpret_cast<const VT*>(xs0 + at);
+            }
+    } else {
+        for (int part = 0; part < parts; part += 2) {
+            take(part, xs0, xs1);
+            if (part + 1 < parts) take(part + 1, xs1, xs0);
+        }
     }
     __syncthreads();                   // the segment sums go where x was
+    if constexpr (!WINDOW) {
 #pragma unroll
-    for (int k = 1; k < K; k++) load_v(k);
+        for (int k = 1; k < K; k++) load_v(k);
+    }
 
     // ---- the tiles, one after the other, as in k_spmv
-    VT* const yb = reinterpret_cast<VT*>(wave % 2 ? xs1 : xs0) + wave / 2 * T;
+    VT* const yb = WINDOW ? reinterpret_cast<VT*>(xs0) + wave * T : reinterpret_cast<VT*>(wave % 2 ? xs1 : xs0) + wave / 2 * T;
 #pragma unroll
     for (int k = 0; k < K; k++) {
         const int tile = mine + k;
@@ -2232,10 +2351,15 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
     const int lanes = __popcll(__ballot(live));
     const bool pub_in = (__ballot(cont0) & 1u) != 0;
     const bool pub_out = begins != 0 && ((__ballot(goes_on) >> (lanes - 1)) & 1u) != 0;
-    if (!pub_in && !pub_out) return;
+    if ((!WINDOW || meet) && !pub_in && !pub_out) return;
     const uint64_t ended = __ballot(ends && outside);
     const VT out_part = __shfl(sum, lanes - 1, OMEGA);
     const VT in_part = ended ? __shfl(total, __builtin_ctzll(ended), OMEGA) : out_part;
+    if (WINDOW && !meet) {             // two kernels: to the auxiliary array, as the sum of the first tile
+        if (live) carry[tile0 + lane] = lane == 0 && pub_in ? in_part : VT(0);
+        if (lane == 0 && pub_out && row_out < uint32_t(m)) y[row_out] = out_part;
+        return;
+    }
     uint64_t other_in = MEET_EMPTY, other_out = MEET_EMPTY;
     uint32_t before_in = 0, before_out = 0;
     const bool count_row_in = pub_in && si.groups != 2, count_row_out = pub_out && so.groups != 2;
@@ -2480,9 +2604,44 @@ hipError_t launch_staged(bool keep, const Geom& g, int m, int n, int nnz, const 
     constexpr int WAVES = staged_waves(SIGMA, sizeof(VT), K);
     const uint32_t groups = uint32_t((g.pc + WAVES * K - 1) / (WAVES * K)), has_tail = g.p > g.pc ? 1u : 0u;
     const int bytes = n * int(sizeof(VT)), parts = staged_parts(n, sizeof(VT)), part_bytes = ((bytes + parts - 1) / parts + 1023) / 1024 * 1024;
-    const auto kernel = keep ? k_spmv_staged<SIGMA, WAVES, K, true, VT> : k_spmv_staged<SIGMA, WAVES, K, false, VT>;
+    const auto kernel = keep ? k_spmv_staged<SIGMA, WAVES, K, true, false, VT> : k_spmv_staged<SIGMA, WAVES, K, false, false, VT>;
     hipLaunchKernelGGL(kernel, dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
-                       part_bytes, parts, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head);
+                       part_bytes, parts, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, 0.0f);
+    return hipGetLastError();
+}
+
+// The window form of k_spmv_staged: its shape, and the matrices it is for.  In entries per
+// sample, rows of 8-16 entries unless said otherwise:
+//  * At least half near the diagonal: with 0.7 4.8 M entries take 31.6 -> 28.7 us, with 0.4
+//    32.2 -> 33.7, with 0.15 32.8 -> 38.9.
+//  * Lines, of 128 entries near it in a tile: a band of +-1300 columns (0.67) 24 M 71.1 -> 71.2
+//    and 3.6 M 15.4 -> 14.5, +-1600 (0.74) 76.0 -> 71.2, +-1000 (0.63) 67.0 -> 71.1; single
+//    precision +-2000 58.9 -> 57.0, +-1600 54.3 -> 56.9; rows of 2000-4000 within +-5000 columns
+//    (0.5) 103 -> 113.  Stencils have 0.25-0.4, and the L1 holds what they use.
+//  * Tiles: below WINDOW_MIN_TILES of them some CUs have two workgroups and most have one
+//    (mixed, 2.5 M entries 17.6 -> 18.0, 3.1 M 20.8 -> 21.3, 3.9 M 26.0 -> 22.9); where nearly
+//    all entries gain, half of that will do (1.6 M 10.4 -> 9.9, 2.2 M 15.3 -> 13.4, but 0.7 M
+//    7.2 -> 8.5).
+constexpr int WINDOW_WAVES = 8, WINDOW_MIN_TILES = 6400, WINDOW_MIN_TILES_NEAR = 3072;
+constexpr uint32_t WINDOW_NEAR_PERCENT = 50, WINDOW_ALL_NEAR_PERCENT = 85, WINDOW_LINES_PERCENT = 70;
+constexpr int window_tiles(int sigma) { return sigma == RULE_SIGMA_SMALL ? 2 : 1; }       // per wavefront
+inline bool window_fits(const Geom& g, int n, size_t value_bytes) {
+    const int64_t x_bytes = int64_t(n) * int64_t(value_bytes);
+    return rule_sigma(g.sigma) && g.pc >= WINDOW_MIN_TILES_NEAR && x_bytes >= WINDOW_BYTES && x_bytes <= (1 << 30);
+}
+inline bool window_pays(const Geom& g, uint32_t near, uint32_t lines) {
+    const uint32_t percent = g.pc >= WINDOW_MIN_TILES ? WINDOW_NEAR_PERCENT : WINDOW_ALL_NEAR_PERCENT;
+    return near * 100 >= 2u * SAMPLES * percent && lines * 100 >= near * WINDOW_LINES_PERCENT;
+}
+template <int SIGMA, typename VT>
+hipError_t launch_window(bool keep, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
+                         const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
+                         uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
+    constexpr int WAVES = WINDOW_WAVES, K = window_tiles(SIGMA), TILES = WAVES * K;
+    const uint32_t groups = uint32_t((g.pc + TILES - 1) / TILES), has_tail = g.p > g.pc ? 1u : 0u;
+    const auto kernel = keep ? k_spmv_staged<SIGMA, WAVES, K, true, true, VT> : k_spmv_staged<SIGMA, WAVES, K, false, true, VT>;
+    hipLaunchKernelGGL(kernel, dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
+                       WINDOW_BYTES, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, float(n) / float(m));
     return hipGetLastError();
 }
 
@@ -2608,6 +2767,7 @@ struct csr5_handle_s {
     uint32_t* order;
     uint32_t order_second, order_len;
     int staged;            // tiles per wavefront of k_spmv_staged; 0: not for this matrix
+    bool window;           // the window form of k_spmv_staged is for this matrix
     void* owned;           // hipMalloc'ed block, or NULL when a workspace was given
     hipStream_t conv_stream;
     int device;            // HIP device that was current at conversion
@@ -2813,6 +2973,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     h->last_col = L.has_last ? reinterpret_cast<int32_t*>(basep + L.off_last + LOOK * 8) : nullptr;
     h->status = reinterpret_cast<uint32_t*>(basep + L.off_status);
     h->staged = 0;
+    h->window = false;
     h->order = nullptr;
     h->order_second = h->order_len = 0;
     h->conv_stream = s;
@@ -2854,6 +3015,13 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     const int staged = !wide && !(flags & CSR5_FLAG_NO_HOST_CHECK) && h->span && h->aux_form == 0 ? staged_tiles(g, n, sizeof(VT)) : 0;
     const int64_t staged_entries = staged ? staged_min_entries(g, n, sizeof(VT), staged) : 0;
     if (staged && int64_t(nnz) >= staged_entries && int64_t(n) * int64_t(sizeof(VT)) <= SAMPLE_MAX_LINES * 128) sample.col_idx = col_idx;
+    WindowJob window = {nullptr, nullptr, m, n, sigma, int(sizeof(VT)), WINDOW_WAVES * window_tiles(sigma), float(n) / float(m > 0 ? m : 1), h->status + 4};
+    if constexpr (!wide) {
+        if (!(flags & CSR5_FLAG_NO_HOST_CHECK) && h->aux_form == 0 && window_fits(g, n, sizeof(VT))) {
+            window.col_idx = col_idx;
+            window.tile_ptr = tile_ptr;
+        }
+    }
     DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.slices ? static_cast<int32_t*>(h->carry) : nullptr};
     {   // step 2a
         const size_t nb_tiles = (size_t(g.p) + 1 + PREP_THREADS - 1) / PREP_THREADS;
@@ -2878,14 +3046,14 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         }
     }
     if (e == hipSuccess && g.pc <= SCAN_SINGLE) {
-        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices + (sample.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, tile_ptr,
-                           h->status, order, sample);
+        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices + (sample.col_idx ? 1 : 0) + (window.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s,
+                           g.pc, g.p, eop, tile_ptr, h->status, order, sample, window);
         e = hipGetLastError();
     } else if (e == hipSuccess) {
         IT* chunk_sum = reinterpret_cast<IT*>(basep + L.off_scan);
         const int nchunks = (g.pc + SCAN_CHUNK - 1) / SCAN_CHUNK;      // <= 2^26 / 2^13 = SCAN_CHUNK
-        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + order.slices), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
-                           tile_ptr, h->status, order);
+        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + order.slices + (window.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
+                           tile_ptr, h->status, order, window);
         e = hipGetLastError();
         if (e == hipSuccess) {
             hipLaunchKernelGGL(k_scan_finish<IT>, dim3(nchunks), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, chunk_sum,
@@ -2909,14 +3077,15 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK)) {
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
-        uint32_t got[4] = {0, 0, 0, 0};   // the status word, behind it the plan of the tile order and the answer on the columns
-        int rc = read_status(h, got, sample.col_idx ? 4 : (order.slices ? 3 : 1));
+        uint32_t got[5] = {0, 0, 0, 0, 0};      // the status word, behind it the plan of the tile order and the answers on the columns
+        int rc = read_status(h, got, window.col_idx ? 5 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
         if (rc == CSR5_OK && got[3] && int64_t(nnz) * got[3] >= staged_entries * SAMPLES) h->staged = staged;
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];
             h->order_len = got[2];
         }
+        h->window = rc == CSR5_OK && !h->staged && !h->order && window_pays(g, got[4] >> 16, got[4] & 0xffffu);
         if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);
             (void)hipStreamSynchronize(s);
@@ -3020,7 +3189,20 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
             return e == hipSuccess ? CSR5_OK : CSR5_EHIP;
         }
     }
-    if (which & LAUNCH_TILES) {
+    // a window of x in LDS: one launch where the handle's slot has what that wants, otherwise two
+    bool window = false, window_one = false;
+    if constexpr (std::is_same<IT, int32_t>::value) {
+        window = h->window;
+        window_one = window && h->span && !carry_mem;
+        if (window && (which & LAUNCH_TILES)) {
+#define WINDOWED(S) e = launch_window<S, VT>(keep, h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
+                                             static_cast<const VT*>(h->val), x, y, carry, window_one ? meet : nullptr, arrived, h->tile_head, zero_rows, s)
+            if (h->g.sigma == RULE_R) WINDOWED(RULE_R);
+            else WINDOWED(RULE_SIGMA_SMALL);
+#undef WINDOWED
+        }
+    }
+    if ((which & LAUNCH_TILES) && !window) {
 #define X(S) case S:                                                                                  \
         if (look_sigma(S) && can_look) e = launch_spmv<S, VT, IT, look_sigma(S) ? MODE_LOOK : MODE_CARRY>(ARGS); \
         else if (look_sigma(S) && one) e = launch_spmv<S, VT, IT, look_sigma(S) ? MODE_ONE : MODE_CARRY>(ARGS);  \
@@ -3034,7 +3216,7 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
 #undef ARGS
     }
     if (e != hipSuccess) return CSR5_EHIP;
-    if ((which & LAUNCH_FIXUP) && carries && !one && h->g.p > 0) {
+    if ((which & LAUNCH_FIXUP) && (window ? !window_one : carries && !one) && h->g.p > 0) {
         int ntiles = h->g.p;                                  // one thread per tile
         size_t nb = (size_t(ntiles) + 255) / 256;
         hipLaunchKernelGGL((fixed ? k_spmv_fixup<VT, IT, true> : k_spmv_fixup<VT, IT, false>), dim3(uint32_t(nb)), dim3(256), 0, s,
