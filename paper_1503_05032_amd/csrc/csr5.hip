@@ -756,30 +756,36 @@ __device__ __forceinline__ int window_first(uint32_t r0, uint32_t r1, float slop
 struct WindowJob {
     const int32_t* col_idx;          // NULL: nothing to do
     const uint32_t* tile_ptr;
-    int32_t m, n, sigma, value_bytes, tiles;     // tiles of a workgroup
+    int32_t m, n, sigma, value_bytes, tiles;     // tiles of a workgroup, a power of two
     float slope;
     uint32_t* answer;                // entries << 16 | lines; cleared with the status word
 };
 
 __device__ void sample_window(int pc, const WindowJob& job) {
     constexpr int WAVES = SCAN_THREADS / OMEGA, PER_WAVE = SAMPLE_TILES / WAVES, LINES = WINDOW_BYTES / 128;
+    static_assert(PER_WAVE < RULE_SIGMA_SMALL, "one turn around a tile's rows");
     __shared__ uint32_t seen[WAVES][(LINES + 3) / 4];     // a byte per line
     __shared__ uint32_t near, lines;
-    const int lane = lane_id(), wave = threadIdx.x / OMEGA;
-    if (threadIdx.x == 0) near = lines = 0;
-    uint32_t at[PER_WAVE], next[PER_WAVE];
-    int first[PER_WAVE];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
+    // everything is asked for at once, see sample_columns; what the rows say is looked at behind the barrier
+    // (with every tile's wait of its own 0.5-1 us more)
+    uint32_t at[PER_WAVE], next[PER_WAVE], r0[PER_WAVE], r1[PER_WAVE];
+    const int j = (wave * PER_WAVE + lane / 16 * (job.sigma / 4)) % (job.sigma - 1);
 #pragma unroll
     for (int u = 0; u < PER_WAVE; u++) {
-        const int q = wave * PER_WAVE + u, tile = int(int64_t(pc) * q / SAMPLE_TILES), tile0 = tile / job.tiles * job.tiles;
-        const int j = (q + lane / 16 * job.sigma / 4) % (job.sigma - 1);           // see sample_columns
-        const int32_t* const pair = job.col_idx + int64_t(tile) * (job.sigma * OMEGA) + j * OMEGA + lane;
+        const int tile = int(int64_t(pc) * (wave * PER_WAVE + u) / SAMPLE_TILES), tile0 = tile & -job.tiles;
+        const int32_t* const pair = job.col_idx + int64_t(tile) * (job.sigma * OMEGA) + (j + u < job.sigma - 1 ? j + u : j + u - (job.sigma - 1)) * OMEGA + lane;
         at[u] = uint32_t(pair[0]);
         next[u] = uint32_t(pair[OMEGA]);
-        const uint32_t r0 = job.tile_ptr[tile0] & Index<int32_t>::ROWMASK, r1 = job.tile_ptr[tile0 + job.tiles < pc ? tile0 + job.tiles : pc] & Index<int32_t>::ROWMASK;
-        first[u] = window_first(r0, r1, job.slope, job.n * job.value_bytes, job.value_bytes);
+        r0[u] = job.tile_ptr[tile0];
+        r1[u] = job.tile_ptr[tile0 + job.tiles < pc ? tile0 + job.tiles : pc];
     }
+    if (threadIdx.x == 0) near = lines = 0;
     __syncthreads();
+    int first[PER_WAVE];
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++)
+        first[u] = window_first(r0[u] & Index<int32_t>::ROWMASK, r1[u] & Index<int32_t>::ROWMASK, job.slope, job.n * job.value_bytes, job.value_bytes);
     constexpr uint32_t window = WINDOW_BYTES;
     uint32_t my_near = 0, my_lines = 0;                    // of the wavefront's tiles; of the lane
 #pragma unroll
@@ -2619,19 +2625,20 @@ hipError_t launch_staged(bool keep, const Geom& g, int m, int n, int nnz, const 
 //    precision +-2000 58.9 -> 57.0, +-1600 54.3 -> 56.9; rows of 2000-4000 within +-5000 columns
 //    (0.5) 103 -> 113.  Stencils have 0.25-0.4, and the L1 holds what they use.
 //  * Tiles: below WINDOW_MIN_TILES of them some CUs have two workgroups and most have one
-//    (mixed, 2.5 M entries 17.6 -> 18.0, 3.1 M 20.8 -> 21.3, 3.9 M 26.0 -> 22.9); where nearly
-//    all entries gain, half of that will do (1.6 M 10.4 -> 9.9, 2.2 M 15.3 -> 13.4, but 0.7 M
-//    7.2 -> 8.5).
-constexpr int WINDOW_WAVES = 8, WINDOW_MIN_TILES = 6400, WINDOW_MIN_TILES_NEAR = 3072;
-constexpr uint32_t WINDOW_NEAR_PERCENT = 50, WINDOW_ALL_NEAR_PERCENT = 85, WINDOW_LINES_PERCENT = 70;
+//    (mixed, 2.5 M entries 17.6 -> 18.0, 3.1 M 20.8 -> 21.3, 3.9 M 26.0 -> 22.9), and the sample
+//    costs more than most would gain: 2-4 us of a conversion, asked of every matrix of the size
+//    (conversion, one SpMV and back, 60^3 stencil 93.7 -> 97.3, 40^3 would be 61.0 -> 64.6,
+//    power-law of 2 M rows 229.3 -> 231.6).
+constexpr int WINDOW_WAVES = 8, WINDOW_MIN_TILES = 6400;
+constexpr uint32_t WINDOW_NEAR_PERCENT = 50, WINDOW_LINES_PERCENT = 70;
+static_assert((WINDOW_WAVES & (WINDOW_WAVES - 1)) == 0, "sample_window");
 constexpr int window_tiles(int sigma) { return sigma == RULE_SIGMA_SMALL ? 2 : 1; }       // per wavefront
 inline bool window_fits(const Geom& g, int n, size_t value_bytes) {
     const int64_t x_bytes = int64_t(n) * int64_t(value_bytes);
-    return rule_sigma(g.sigma) && g.pc >= WINDOW_MIN_TILES_NEAR && x_bytes >= WINDOW_BYTES && x_bytes <= (1 << 30);
+    return rule_sigma(g.sigma) && g.pc >= WINDOW_MIN_TILES && x_bytes >= WINDOW_BYTES && x_bytes <= (1 << 30);
 }
-inline bool window_pays(const Geom& g, uint32_t near, uint32_t lines) {
-    const uint32_t percent = g.pc >= WINDOW_MIN_TILES ? WINDOW_NEAR_PERCENT : WINDOW_ALL_NEAR_PERCENT;
-    return near * 100 >= 2u * SAMPLES * percent && lines * 100 >= near * WINDOW_LINES_PERCENT;
+inline bool window_pays(uint32_t near, uint32_t lines) {
+    return near * 100 >= 2u * SAMPLES * WINDOW_NEAR_PERCENT && lines * 100 >= near * WINDOW_LINES_PERCENT;
 }
 template <int SIGMA, typename VT>
 hipError_t launch_window(bool keep, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
@@ -3085,7 +3092,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
             h->order_second = got[1];
             h->order_len = got[2];
         }
-        h->window = rc == CSR5_OK && !h->staged && !h->order && window_pays(g, got[4] >> 16, got[4] & 0xffffu);
+        h->window = rc == CSR5_OK && !h->staged && !h->order && window_pays(got[4] >> 16, got[4] & 0xffffu);
         if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);
             (void)hipStreamSynchronize(s);

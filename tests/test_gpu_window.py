@@ -39,7 +39,7 @@ def _band(m, n, lo, hi, w, far=0.0, uneven=False, seed=0):
     (20_000, WINDOW + 1, 165, 215, 4000, 0.0, 0, False),           # x of one window and an entry
     (20_000, WINDOW + 17, 165, 215, 4000, 0.0, 0, True),
     (20_001, 90_003, 165, 215, 5000, 0.0, 0, False),               # wide
-    (400_003, 50_001, 5, 13, 5000, 0.1, 0, True),                 # tall
+    (430_003, 50_001, 5, 13, 5000, 0.1, 0, True),                 # tall
     (20_000, 300_000, 165, 215, 7000, 0.1, 0, True),              # a band wider than the window
     (20_000, 200_000, 200, 200, 5000, 0.4, 0, False),             # rows of one length, many entries elsewhere
     (45_000, 90_000, 165, 215, 5000, 0.2, 16, True),               # height 16
@@ -120,7 +120,7 @@ def test_other_columns_take_the_general_kernel(w, far, n):
 
 
 def test_graph_replays():
-    a = _band(40_001, 90_003, 60, 110, 5000, 0.1, True, seed=9)
+    a = _band(50_001, 90_003, 60, 110, 5000, 0.1, True, seed=9)
     d = DeviceCsr(a)
     h = convert(d)
     check_spmv(d, h, "eager")
