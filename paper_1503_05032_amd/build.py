@@ -9,6 +9,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = [os.path.join(PKG, "csrc", "csr5.hip")]
+HEADERS = [os.path.join(PKG, "csrc", "row_share.h")]
 INC = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "libcsr5.so")
 
@@ -42,7 +43,7 @@ def is_stale() -> bool:
     if not os.path.exists(OUT):
         return True
     t = os.path.getmtime(OUT)
-    deps = SRC + [os.path.join(INC, "csr5.h")]
+    deps = SRC + HEADERS + [os.path.join(INC, "csr5.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

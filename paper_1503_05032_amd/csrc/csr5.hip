@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "csr5.h"
+#include "row_share.h"
 
 namespace {
 
@@ -2232,9 +2233,8 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         asm volatile("" ::: "memory");
     }
     if (zero_rows) {
-        const int r1 = int(int64_t(m) * (group + 1) / int(groups));
-        for (int r = int(int64_t(m) * group / int(groups)) + int(threadIdx.x); r < r1; r += THREADS)
-            if (row_ptr[r] == row_ptr[r + 1]) y[r] = VT(0);
+        for (RowShare r(m, uint32_t(group), groups, threadIdx.x); r.more(); r.next(THREADS))
+            if (row_ptr[r.row] == row_ptr[r.row + 1]) y[r.row] = VT(0);
     }
     // ---- gather: every entry takes its x from the part that holds its column
     VT xv[K][SIGMA];
