@@ -280,6 +280,21 @@ int csr5_get_info(csr5_handle_t h, int32_t *omega, int32_t *sigma, int32_t *p, i
 int csr5_get_shape(csr5_handle_t h, int32_t *m, int32_t *n);
 
 /*
+ * What the next csr5_spmv_ex (csr5s_spmv_ex) of this handle on this stream would launch
+ * (used by the tests; launches and changes nothing).  Host scalars, may be NULL.
+ *   kernel        CSR5_KERNEL_TILES  the tile kernel, in one of the forms described at csr5_spmv
+ *                 CSR5_KERNEL_PARTS  x comes by in parts through LDS: random columns over an x
+ *                                    that an L2 holds; one kernel
+ *                 CSR5_KERNEL_WINDOW the part of x around the diagonal in LDS; one kernel up to
+ *                                    32768 tiles, two beyond
+ *   wave_tiles    tiles of a wavefront (1 for CSR5_KERNEL_TILES)
+ *   plain         1: col_idx, val and the descriptors would be read with plain loads, 0: with
+ *                 non-temporal ones (a hint to the caches, the result is the same)
+ */
+enum { CSR5_KERNEL_TILES = 0, CSR5_KERNEL_PARTS = 1, CSR5_KERNEL_WINDOW = 2 };
+int csr5_get_form(csr5_handle_t h, void *hip_stream, int32_t *kernel, int32_t *wave_tiles, int32_t *plain);
+
+/*
  * Device pointers to the handle's arrays (valid until csr5_free):
  *   tile_ptr          uint32[p+1]   bit 31 = tile holds an empty row (Section 3.3)
  *   tile_desc         uint32[p_c*W*64]; word k of column i of tile t at (t*W+k)*64+i;

@@ -27,12 +27,13 @@ CSR5_FLAG_AUX_TWO_KERNELS, CSR5_FLAG_AUX_ONE_KERNEL = 2, 4
 CSR5_STATUS_BAD_ROW_PTR, CSR5_STATUS_BAD_COL_IDX, CSR5_STATUS_HAS_DIRTY = 1, 2, 4
 CSR5_STATUS_HAS_EMPTY_ROWS = 8
 CSR5_ARRAY_TILE_PTR, CSR5_ARRAY_TILE_DESC, CSR5_ARRAY_EMPTY_OFFSET_PTR, CSR5_ARRAY_EMPTY_OFFSET = 0, 1, 2, 3
+CSR5_KERNEL_TILES, CSR5_KERNEL_PARTS, CSR5_KERNEL_WINDOW = 0, 1, 2
 
 # every symbol include/csr5.h declares
 SYMBOLS = [
     "csr5_sigma_auto", "csr5_workspace_bytes", "csr5_convert", "csr5_convert_ex", "csr5_spmv",
     "csr5_spmv_ex", "csr5_spmv_static", "csr5_spmv_profile", "csr5_stream_floor", "csr5_to_csr", "csr5_free", "csr5_status", "csr5_get_info",
-    "csr5_get_shape", "csr5_get_arrays",
+    "csr5_get_shape", "csr5_get_form", "csr5_get_arrays",
     "csr5_read_array", "csr5_strerror", "csr5_baseline_csr_scalar", "csr5_baseline_csr_vector",
     "csr5s_convert_ex", "csr5s_spmv_ex", "csr5s_spmv_profile",
     "csr5l_workspace_bytes", "csr5l_convert_ex", "csr5l_get_arrays",
@@ -100,6 +101,8 @@ def load():
     lib.csr5_get_info.argtypes = [vp] + [C.POINTER(i32)] * 6
     lib.csr5_get_shape.restype = C.c_int
     lib.csr5_get_shape.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
+    lib.csr5_get_form.restype = C.c_int
+    lib.csr5_get_form.argtypes = [vp, vp] + [C.POINTER(i32)] * 3
     lib.csr5_get_arrays.restype = C.c_int
     lib.csr5_get_arrays.argtypes = [vp] + [C.POINTER(vp)] * 4
     lib.csr5_read_array.restype = C.c_int
@@ -352,6 +355,13 @@ def csr5_get_info(h):
     _chk(load().csr5_get_info(h, *[C.byref(a) for a in v]), "csr5_get_info", True)
     keys = ["omega", "sigma", "p", "p_complete", "desc_words_per_lane", "empty_offset_len"]
     return {k: a.value for k, a in zip(keys, v)}
+
+
+def csr5_get_form(h, stream=None):
+    """dict(kernel, wave_tiles, plain): what the next SpMV of the handle on the stream would launch."""
+    v = [C.c_int32() for _ in range(3)]
+    _chk(load().csr5_get_form(h, _stream(stream), *[C.byref(a) for a in v]), "csr5_get_form", True)
+    return {k: a.value for k, a in zip(["kernel", "wave_tiles", "plain"], v)}
 
 
 def csr5_get_arrays(h, check=True):

@@ -3437,6 +3437,15 @@ int csr5_get_shape(csr5_handle_t h, int32_t* m, int32_t* n) {
     return CSR5_OK;
 }
 
+int csr5_get_form(csr5_handle_t h, void* hip_stream, int32_t* kernel, int32_t* wave_tiles, int32_t* plain) {
+    (void)hip_stream;
+    if (!h || !h->in_csr5_order) return CSR5_EINVAL;
+    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->window ? CSR5_KERNEL_WINDOW : CSR5_KERNEL_TILES);
+    if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window ? window_tiles(h->g.sigma) : 1);
+    if (plain) *plain = rule_sigma(h->g.sigma) && keep_product(h->m, h->n, h->nnz, h->dtype == CSR5_DTYPE_F32 ? 4 : 8, h->carry_turn.load(std::memory_order_relaxed));
+    return CSR5_OK;
+}
+
 int csr5_get_arrays(csr5_handle_t h, const uint32_t** tile_ptr, const uint32_t** tile_desc,
                     const int32_t** empty_offset_ptr, const int32_t** empty_offset) {
     if (!h || h->wide) return CSR5_EINVAL;
