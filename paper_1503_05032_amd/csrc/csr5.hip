@@ -2136,7 +2136,7 @@ struct RowSpan { int first, groups; };     // the workgroups a row touches
 // 54.2; 8 of three 48.9, but 23.2 -> 28.2 at 200 000 rows.
 // Rows that cross workgroups: as above where the handle's slot has what that wants (meet),
 // through the auxiliary array and k_spmv_fixup otherwise, one sum per workgroup.
-template <int SIGMA, int WAVES, int K, bool KEEP, bool WINDOW, typename VT>
+template <int SIGMA, int WAVES, int K, bool WINDOW, typename VT>
 __global__ void __launch_bounds__(WAVES * OMEGA, WINDOW ? WAVES * (LDS_BYTES / WINDOW_BYTES) / 4 : 1)
 k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail, uint32_t zero_rows, int part_bytes, int parts,
               const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ tile_ptr,
@@ -2199,8 +2199,8 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         const auto cols = tile_buffer(col_idx + size_t(tile < pc ? tile : 0) * T, tile < pc ? T * 4 : 0);    // (an empty buffer reads as 0)
         const auto descs = tile_buffer(tile_desc + size_t(tile < pc ? tile : 0) * OMEGA, tile < pc ? OMEGA * 4 : 0);
 #pragma unroll
-        for (int j = 0; j < SIGMA; j++) c[k][j] = stream_from<int32_t, KEEP>(cols, (j * OMEGA + lane) * 4) * int(sizeof(VT));
-        dw[k] = stream_from<uint32_t, KEEP>(descs, lane * 4);
+        for (int j = 0; j < SIGMA; j++) c[k][j] = stream_from<int32_t, false>(cols, (j * OMEGA + lane) * 4) * int(sizeof(VT));
+        dw[k] = stream_from<uint32_t, false>(descs, lane * 4);
     }
 #pragma unroll
     for (int k = 0; k <= K; k++) {
@@ -2222,7 +2222,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         const int tile = mine + k;
         const auto vals = tile_buffer(val + size_t(tile < pc ? tile : 0) * T, tile < pc ? T * int(sizeof(VT)) : 0);
 #pragma unroll
-        for (int j = 0; j < SIGMA; j++) v[k][j] = stream_from<VT, KEEP>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
+        for (int j = 0; j < SIGMA; j++) v[k][j] = stream_from<VT, false>(vals, (j * OMEGA + lane) * int(sizeof(VT)));
     };
     load_v(0);
     if constexpr (WINDOW) {
@@ -2604,14 +2604,13 @@ inline int64_t staged_min_entries(const Geom& g, int n, size_t value_bytes, int 
 }
 
 template <int SIGMA, int K, typename VT>
-hipError_t launch_staged(bool keep, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
+hipError_t launch_staged(const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
                          const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
                          uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
     constexpr int WAVES = staged_waves(SIGMA, sizeof(VT), K);
     const uint32_t groups = uint32_t((g.pc + WAVES * K - 1) / (WAVES * K)), has_tail = g.p > g.pc ? 1u : 0u;
     const int bytes = n * int(sizeof(VT)), parts = staged_parts(n, sizeof(VT)), part_bytes = ((bytes + parts - 1) / parts + 1023) / 1024 * 1024;
-    const auto kernel = keep ? k_spmv_staged<SIGMA, WAVES, K, true, false, VT> : k_spmv_staged<SIGMA, WAVES, K, false, false, VT>;
-    hipLaunchKernelGGL(kernel, dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
+    hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, false, VT>), dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
                        part_bytes, parts, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, 0.0f);
     return hipGetLastError();
 }
@@ -2641,13 +2640,12 @@ inline bool window_pays(uint32_t near, uint32_t lines) {
     return near * 100 >= 2u * SAMPLES * WINDOW_NEAR_PERCENT && lines * 100 >= near * WINDOW_LINES_PERCENT;
 }
 template <int SIGMA, typename VT>
-hipError_t launch_window(bool keep, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
+hipError_t launch_window(const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
                          const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
                          uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
     constexpr int WAVES = WINDOW_WAVES, K = window_tiles(SIGMA), TILES = WAVES * K;
     const uint32_t groups = uint32_t((g.pc + TILES - 1) / TILES), has_tail = g.p > g.pc ? 1u : 0u;
-    const auto kernel = keep ? k_spmv_staged<SIGMA, WAVES, K, true, true, VT> : k_spmv_staged<SIGMA, WAVES, K, false, true, VT>;
-    hipLaunchKernelGGL(kernel, dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
+    hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, true, VT>), dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
                        WINDOW_BYTES, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, float(n) / float(m));
     return hipGetLastError();
 }
@@ -2763,6 +2761,8 @@ struct csr5_handle_s {
     void* carry;
     size_t carry_slot_bytes;
     std::atomic<uint32_t> carry_turn;      // SpMVs so far
+    uint64_t number;       // of the handle, see use_latest
+    std::atomic<bool> near;                // what reads the entries next has so far followed what wrote or read them last (keep_product)
     uint32_t* tile_head;   // per tile: entries of its first row that lie before it, saturated at 32 bits
     int aux_form;          // 0: the size rule decides how the auxiliary-array path adds its sums; 1: always the second kernel; 2: inside the tile kernel wherever span exists
     uint2* span;           // per tile: the groups of tiles that row touches (first, how many); NULL where the one-launch SpMV cannot run
@@ -2884,41 +2884,69 @@ static int read_status(csr5_handle_t h, uint32_t* got, int words) {
 }
 
 // Where the entries' next use is near, so that plain loads and stores leave them in the
-// 256 MB memory-side cache for it instead of passing it by (the rule, see tile_buffer):
-//  * The transposition: its matrix is multiplied next.  One conversion, one product and
-//    the way back, matrices used in turn (3 and 6 of them, so none is still there from
-//    its own last turn): 100^3 stencil (318 MB) 293 -> 270 us, 90^3 220 -> 201, 75^3 137 ->
-//    121, power-law of 2 M rows 242 -> 231, dense 4000^2 219 -> 198, 15 M random entries
-//    370 -> 356.  With the product left non-temporal half of that or less (100^3: 295),
-//    with only the stores or only the loads plain less (291) or nothing.
-//  * The first products of a handle, hence.  After that nobody knows whether the handle
-//    is used alone (plain gains, 5 products of a 90^3 stencil 397 -> 360) or is one of many
-//    (it loses), so only as many as follow a conversion anyhow: one; KEEP_CALLS where x
-//    is at home in every L2 (with x of 3 to 10 MB and random columns the streams push it
-//    out: five products of 19 M entries, x of 3.2 MB, 702 -> 714 with eight, 694 with one);
-//    KEEP_CALLS_L2 where the entries fit the L2s together (50 products of a 40^3 stencil
-//    and the conversion 509 -> 455).  Guessed wrong it costs 5-20 % of these calls, in all
-//    less than the conversion before them did.
+// 256 MB memory-side cache for it instead of passing it by (the rule, see tile_buffer).  Near
+// is what the order of the calls says: nothing else of the library was enqueued on the device in
+// between (use_latest), and the stream is not being captured.
+//  * The transposition, whose matrix is multiplied next, unless the call before was another
+//    handle's conversion: several are converted first then.  One conversion, one product and the
+//    way back, three matrices in turn, non-temporal throughout -> now: 100^3 stencil (318 MB) 319 -> 298 us,
+//    90^3 246 -> 228, 75^3 162 -> 148, power-law of 2 M rows 245 -> 236, dense 4000^2 220 -> 203,
+//    15 M random entries 370 -> 356.  With the product left non-temporal half of that or less
+//    (100^3: 324), with only the stores or only the loads plain less or nothing.
+//  * The product that follows it, if this handle's conversion was the call before.  Any first
+//    product and any transposition plain: three matrices converted and then multiplied push each other
+//    out, and the first product of each waits for the other ones' entries to be written (100^3 70 -> 86 us,
+//    90^3 52 -> 67, power-law 66 -> 80; now 71, 55, 66).
+//  * The second product in a row of a handle whose entries fit the L2s together brings them
+//    there, where the later ones find them, plain or not: products 9 to 64 of dense 1500^2
+//    9.4 -> 7.9, 40^3 6.6 -> 5.8, 1.2 M entries 10.4 -> 9.1.  With plain loads up to the eighth the same,
+//    up to the 64th 40^3 5.6 and mixed of 1.7 M entries 11.2 -> 10.9, but power-law of 1.8 M 9.9 -> 11.0 and
+//    45^3 7.7 -> 8.3.
 //  * The way back is their last use: non-temporal, or it pushes out what comes next (75^3:
 //    121 -> 134), except for the small, where the stores return sooner (dense 2000^2,
 //    48 MB, 82 -> 76; 50^3, 40 MB, 55 -> 50; 60^3, 70 MB, 73.3 -> 72.1 but 78.9 with six
 //    in turn).
-// The line, entries with x and y: 387 MB (105^3) 336 -> 312 us, 409 MB (107^3) 380 -> 357,
+// The upper line, entries with x and y: 387 MB (105^3) 336 -> 312 us, 409 MB (107^3) 380 -> 357,
 // 390 MB (1.85 M rows, mixed) 539 -> 532, but 417 MB (power-law, 3.5 M rows) 399 -> 407, 445 MB
-// (110^3) 381 -> 394, 570 MB (120^3) 487 -> 510.  For the heights the automatic rule picks;
-// the others keep one form.
-constexpr int64_t L2_BYTES = 32 << 20, KEEP_MAX_BYTES = 384 << 20, KEEP_BACK_MAX_BYTES = 48 << 20;
-constexpr uint32_t KEEP_CALLS = 8, KEEP_CALLS_L2 = 64;
+// (110^3) 381 -> 394, 570 MB (120^3) 487 -> 510.  The lower one, entries, the same cycle with one
+// product: 20 MB (40^3) 63.5 -> 62.9, 27 MB (dense 1500^2) 70.9 -> 67.9, but 12 MB (dense 1000^2) 55.9 -> 58.4,
+// 13 MB (35^3) 58.7 -> 60.1, 17 MB (dense 1200^2) 61.6 -> 64.1: what the transposition leaves in the
+// L2s has to be written from there at its end.
+// For the heights the automatic rule picks; the others keep one form, and so does k_spmv_staged (the
+// product that follows a conversion, 12.6 M entries mixed 70.4 -> 78.3, in rows of 201 27.8 -> 28.0).
+constexpr int64_t L2_BYTES = 32 << 20, KEEP_MIN_BYTES = 18 << 20, KEEP_MAX_BYTES = 384 << 20, KEEP_BACK_MAX_BYTES = 48 << 20;
 static int64_t entry_bytes(int64_t nnz, size_t value_bytes) { return nnz * int64_t(value_bytes + 4); }
 static bool keep_near(int32_t m, int32_t n, int64_t nnz, size_t value_bytes) {
     return entry_bytes(nnz, value_bytes) + (int64_t(m) + n) * int64_t(value_bytes) <= KEEP_MAX_BYTES;
 }
-static bool keep_product(int32_t m, int32_t n, int64_t nnz, size_t value_bytes, uint32_t call) {
-    if (!keep_near(m, n, nnz, value_bytes)) return false;
-    if (entry_bytes(nnz, value_bytes) <= L2_BYTES) return call < KEEP_CALLS_L2;
-    return call < (size_t(n) * value_bytes < XCD_CONTIGUOUS_MIN_X_BYTES ? KEEP_CALLS : 1u);
+
+// What the library enqueued last on a device: 2 * the handle's number, and 1 more if it was the
+// handle's conversion.  Handles are numbered in the order of their conversions and no number is
+// used twice.  Threads may race here: what they decide is a hint to the caches.
+static std::atomic<uint64_t> handles_made, latest_use[MAX_DEVICES];
+static uint64_t latest(int dev) { return dev >= 0 && dev < MAX_DEVICES ? latest_use[dev].load(std::memory_order_relaxed) : 0; }
+static uint64_t use_latest(int dev, uint64_t use) {       // returns the one before
+    const uint64_t before = latest(dev);
+    if (before != use && dev >= 0 && dev < MAX_DEVICES) latest_use[dev].store(use, std::memory_order_relaxed);
+    return before;
 }
-static bool keep_back(int64_t nnz, size_t value_bytes) { return entry_bytes(nnz, value_bytes) <= KEEP_BACK_MAX_BYTES; }
+
+// A graph is replayed at any time, in turn with anything.  (An error is a capture elsewhere that forbids the question.)
+static bool may_be_captured(hipStream_t s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// before: what use_latest returned
+static bool keep_product(csr5_handle_t h, uint32_t call, uint64_t before, hipStream_t s) {
+    if (!h->near.load(std::memory_order_relaxed)) return false;
+    const int64_t bytes = entry_bytes(h->nnz, h->dtype == CSR5_DTYPE_F32 ? 4 : 8);
+    const bool soon = call == 0 ? bytes > KEEP_MIN_BYTES : call == 1 && bytes <= L2_BYTES;
+    return soon && before / 2 == h->number && !may_be_captured(s);
+}
+static bool keep_back(int64_t nnz, size_t value_bytes) { return entry_bytes(nnz, value_bytes) > KEEP_MIN_BYTES && entry_bytes(nnz, value_bytes) <= KEEP_BACK_MAX_BYTES; }
 
 template <typename VT, typename IT>
 static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t* col_idx,
@@ -2991,6 +3019,11 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     }
     h->in_csr5_order = true;
     h->status_host.store(-1, std::memory_order_relaxed);
+    h->number = handles_made.fetch_add(1, std::memory_order_relaxed) + 1;
+    const bool among_conversions = use_latest(h->device, 2 * h->number + 1) & 1;
+    const bool near = keep_near(m, n, nnz, sizeof(VT)) && !among_conversions && !may_be_captured(s);
+    const bool keep = near && entry_bytes(nnz, sizeof(VT)) > KEEP_MIN_BYTES;
+    h->near.store(near, std::memory_order_relaxed);
     {   // set-up time on this device: resolve the static scratch's address now, so
         // that csr5_spmv_static has nothing left to look up (failure is reported there)
         void* unused = nullptr;
@@ -3045,7 +3078,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     }
     if (e == hipSuccess) {            // steps 2b, 3a, 3b (descriptors, inside the same kernel) + 4
         switch (sigma) {
-#define X(S) case S: e = launch_transpose<S, false, VT>(keep_near(m, n, nnz, sizeof(VT)), g, n, nnz, col_idx, val, h->status, h->last_col,      \
+#define X(S) case S: e = launch_transpose<S, false, VT>(keep, g, n, nnz, col_idx, val, h->status, h->last_col,      \
                                                         static_cast<VT*>(h->last_val), job, s); break;
             CSR5_FOR_SIGMA(X)
 #undef X
@@ -3152,7 +3185,9 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     hipError_t e = hipSuccess;
     // a whole SpMV takes the next of the handle's carry arrays; partial launches (measurement) the first
     const uint32_t call = (which == LAUNCH_BOTH) ? h->carry_turn.fetch_add(1, std::memory_order_relaxed) : 0u, turn = call % CARRY_SLOTS;
-    const bool keep = which == LAUNCH_BOTH && keep_product(h->m, h->n, h->nnz, sizeof(VT), call);
+    const uint64_t before = use_latest(h->device, 2 * h->number);
+    const bool keep = which == LAUNCH_BOTH && keep_product(h, call, before, s);
+    if (before / 2 != h->number) h->near.store(false, std::memory_order_relaxed);
     VT* carry = static_cast<VT*>(carry_mem ? carry_mem : static_cast<void*>(static_cast<char*>(h->carry) + turn * h->carry_slot_bytes));
     // What the matrix needs beyond its tiles is known once the host has seen the
     // status word of the conversion; until then everything is launched (the
@@ -3183,7 +3218,7 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     if constexpr (std::is_same<IT, int32_t>::value) {
         if (h->staged && !carry_mem) {
             if (!(which & LAUNCH_TILES)) return CSR5_OK;
-#define STAGED(S, K) e = launch_staged<S, K, VT>(keep, h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx, \
+#define STAGED(S, K) e = launch_staged<S, K, VT>(h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx, \
                                                static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->tile_head, zero_rows, s)
             if (h->g.sigma == RULE_R) {
                 if (h->staged == 1) STAGED(RULE_R, 1);
@@ -3202,7 +3237,7 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
         window = h->window;
         window_one = window && h->span && !carry_mem;
         if (window && (which & LAUNCH_TILES)) {
-#define WINDOWED(S) e = launch_window<S, VT>(keep, h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
+#define WINDOWED(S) e = launch_window<S, VT>(h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
                                              static_cast<const VT*>(h->val), x, y, carry, window_one ? meet : nullptr, arrived, h->tile_head, zero_rows, s)
             if (h->g.sigma == RULE_R) WINDOWED(RULE_R);
             else WINDOWED(RULE_SIGMA_SMALL);
@@ -3377,6 +3412,7 @@ int csr5_to_csr(csr5_handle_t h, void* hip_stream) {
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = hipSuccess;
     const bool keep = keep_back(h->nnz, h->dtype == CSR5_DTYPE_F32 ? 4 : 8);
+    (void)use_latest(h->device, 2 * h->number);
     if (h->nnz > 0) {
         switch (h->g.sigma) {
 #define X(S) case S: e = (h->dtype == CSR5_DTYPE_F32)                                                            \
@@ -3438,11 +3474,12 @@ int csr5_get_shape(csr5_handle_t h, int32_t* m, int32_t* n) {
 }
 
 int csr5_get_form(csr5_handle_t h, void* hip_stream, int32_t* kernel, int32_t* wave_tiles, int32_t* plain) {
-    (void)hip_stream;
     if (!h || !h->in_csr5_order) return CSR5_EINVAL;
     if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->window ? CSR5_KERNEL_WINDOW : CSR5_KERNEL_TILES);
     if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window ? window_tiles(h->g.sigma) : 1);
-    if (plain) *plain = rule_sigma(h->g.sigma) && keep_product(h->m, h->n, h->nnz, h->dtype == CSR5_DTYPE_F32 ? 4 : 8, h->carry_turn.load(std::memory_order_relaxed));
+    if (plain)
+        *plain = !h->staged && !h->window && rule_sigma(h->g.sigma) &&
+                 keep_product(h, h->carry_turn.load(std::memory_order_relaxed), latest(h->device), static_cast<hipStream_t>(hip_stream));
     return CSR5_OK;
 }
 

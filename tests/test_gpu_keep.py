@@ -1,6 +1,7 @@
 """GPU parity where the kernels choose between plain and non-temporal loads and stores:
-by size (the entries against 32 MB for the products, 48 MB for the way back, 384 MB with
-the vectors for all) and by how many products a handle has had (1, 8, 64)."""
+by size (the entries against 18 and 32 MB for the products, 18 and 48 MB for the way back, 384 MB
+with the vectors for all), by how many products a handle has had, and by what was called
+before."""
 import numpy as np
 import pytest
 import torch
@@ -68,4 +69,83 @@ def test_single_precision(nnz):
     B.csr5_to_csr(h)
     torch.cuda.synchronize()
     assert torch.equal(val, kept) and np.array_equal(d.col_idx.cpu().numpy(), a.col_idx)
+    B.csr5_free(h)
+
+
+def _plain(h):
+    return B.csr5_get_form(h)["plain"]
+
+
+def _anything():
+    """A product of another handle, so that the call before a conversion is none."""
+    a = _matrix(20_000, 500, seed=1)
+    d = DeviceCsr(a)
+    h = convert(d)
+    check_spmv(d, h, "anything")
+    B.csr5_free(h)
+
+
+@pytest.mark.parametrize("nnz,want", [((18 << 20) // 12, [0, 1, 0]), ((18 << 20) // 12 + 1, [1, 1, 0]),
+                                      ((32 << 20) // 12, [1, 1, 0]), ((32 << 20) // 12 + 1, [1, 0, 0])])
+def test_first_products_in_a_row(nnz, want):
+    a = _matrix(nnz, 300_000, seed=3)
+    _anything()
+    d = DeviceCsr(a)
+    h = convert(d)
+    for call, plain in enumerate(want):
+        assert _plain(h) == plain, call
+        check_spmv(d, h, call)
+    B.csr5_free(h)
+
+
+def test_plain_only_where_nothing_came_between():
+    a = [_matrix((32 << 20) // 12 - 20_000 + k, 300_000, seed=k) for k in range(3)]
+    _anything()
+    d = [DeviceCsr(k) for k in a]
+    h = [convert(d[0])]
+    assert _plain(h[0]) == 1
+    h.append(convert(d[1]))                        # several are converted first: they push each other out
+    assert _plain(h[0]) == 0 and _plain(h[1]) == 0
+    for k in (0, 1, 0):
+        check_spmv(d[k], h[k], "used in turn")
+        assert _plain(h[0]) == 0 and _plain(h[1]) == 0
+    h.append(convert(d[2]))
+    assert _plain(h[2]) == 1
+    check_spmv(d[2], h[2], "alone")
+    assert _plain(h[2]) == 1
+    check_spmv(d[0], h[0], "used in turn")
+    assert _plain(h[2]) == 0
+    check_spmv(d[2], h[2], "used in turn")
+    B.csr5_to_csr(h[0])
+    B.csr5_free(h[0])
+    d[0] = DeviceCsr(a[0])
+    h[0] = convert(d[0])
+    assert _plain(h[0]) == 1
+    B.csr5_to_csr(h[1])                            # another one's way back comes between, too
+    assert _plain(h[0]) == 0
+    for k in h:
+        B.csr5_free(k)
+
+
+def test_no_plain_streams_in_a_graph():
+    """A graph is replayed at any time, in turn with anything."""
+    a = _matrix((32 << 20) // 12 + 1, 300_000, seed=4)
+    _anything()
+    d = DeviceCsr(a)
+    h = convert(d)
+    assert _plain(h) == 1
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        inside = _plain(h)
+        B.csr5_spmv_ex(h, d.x, d.y)
+    assert inside == 0
+    want = None
+    for replay in range(4):
+        d.y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = d.y.clone()
+        check_spmv(d, h, ("eager", replay))
+        want = d.y.clone() if want is None else want
+        assert torch.equal(got[:-1], want[:-1]) and torch.equal(d.y[:-1], want[:-1]), replay
     B.csr5_free(h)
