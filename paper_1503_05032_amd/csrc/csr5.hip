@@ -669,7 +669,7 @@ __device__ void order_place(int pc, const OrderJob& job, int k, const typename I
 //  * tiles whose entries do not spread over half of x or SAMPLE_WIDE_BYTES: the entries that
 //    a CU has at a time share what its L1 holds, and every part of x would be read for
 //    nothing (random columns, and bands of 160 KB: all tiles spread; stencils none,
-//    power-law rows one in six).
+//    power-law rows one in six; a band with a few entries elsewhere does, see window_rather).
 //  * columns that all together fall on far fewer lines than random ones would (1.0; normally
 //    distributed 0.7): a few columns have most entries, and the L1 holds those (power-law
 //    columns in random order, x of 480 KB: 0.35 and 14.1 us, here 16.8).
@@ -2639,6 +2639,18 @@ inline bool window_fits(const Geom& g, int n, size_t value_bytes) {
 inline bool window_pays(uint32_t near, uint32_t lines) {
     return near * 100 >= 2u * SAMPLES * WINDOW_NEAR_PERCENT && lines * 100 >= near * WINDOW_LINES_PERCENT;
 }
+// A band with entries elsewhere may suit both forms: a few of them make a tile wide for
+// sample_columns.  A part costs a round about a microsecond whatever its entries are, the window's far
+// entries 2 us per million, and one round of parts has 5.5 us less to wait for in front of it.  Parts, window, in
+// us (k_spmv 24 to 57): 8.5 M entries in single precision, 2 rounds of 5 parts, a tenth far 33.7, 26.7,
+// two fifths 33.5, 31.5; 12.7 M, 2 rounds of 8, a tenth 46.1, 33.4; 9.5 M in double precision, 2 rounds of 6, a fifth
+// 40.7, 35.9, two fifths 40.5, 38.5 (left to the parts); 6.7 M, 2 rounds of 4, a tenth 28.9, 27.4, two
+// fifths 28.8, 30.9; 4.3 M, one round of 6, a tenth 20.4, 21.2, two fifths 20.4, 23.8; 6 M in single
+// precision, one round of 4, a tenth 17.5, 19.6.
+inline bool window_rather(const Geom& g, int n, int64_t nnz, size_t value_bytes, int k, uint32_t near) {
+    const int64_t far = nnz * int64_t(2u * SAMPLES - near) / int64_t(2 * SAMPLES);
+    return 2 * far + 5500 * 1000 < int64_t(staged_rounds(g, value_bytes, k)) * staged_parts(n, value_bytes) * 1000 * 1000;
+}
 template <int SIGMA, typename VT>
 hipError_t launch_window(const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
                          const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
@@ -3119,13 +3131,18 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         // transposition and refuse
         uint32_t got[5] = {0, 0, 0, 0, 0};      // the status word, behind it the plan of the tile order and the answers on the columns
         int rc = read_status(h, got, window.col_idx ? 5 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
-        if (rc == CSR5_OK && got[3] && int64_t(nnz) * got[3] >= staged_entries * SAMPLES) h->staged = staged;
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];
             h->order_len = got[2];
         }
-        h->window = rc == CSR5_OK && !h->staged && !h->order && window_pays(got[4] >> 16, got[4] & 0xffffu);
+        const uint32_t near = got[4] >> 16, lines = got[4] & 0xffffu;
+        h->window = rc == CSR5_OK && !h->order && window_pays(near, lines);
+        if (rc == CSR5_OK && got[3] && int64_t(nnz) * got[3] >= staged_entries * SAMPLES &&
+            !(h->window && window_rather(g, n, int64_t(nnz), sizeof(VT), staged, near))) {
+            h->staged = staged;
+            h->window = false;
+        }
         if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);
             (void)hipStreamSynchronize(s);

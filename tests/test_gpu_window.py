@@ -92,6 +92,40 @@ def test_single_precision(m, n, sigma, w):
     B.csr5_free(h)
 
 
+def _single(a, sigma, kernel, calls=3):
+    """Products in single precision against sums in double precision; the form is the one named."""
+    d = DeviceCsr(a)
+    val, x = d.val.float(), d.x.float()
+    products = val.double() * x.double()[d.col_idx.long()]
+    want = torch.segment_reduce(products, "sum", offsets=d.row_ptr.long(), initial=0)
+    scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)
+    y = torch.empty(a.m, dtype=torch.float32, device="cuda:0")
+    h = B.csr5s_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val, sigma=sigma)
+    assert B.csr5_get_form(h)["kernel"] == kernel, B.csr5_get_form(h)
+    for call in range(calls):
+        y.fill_(float("nan"))
+        B.csr5s_spmv_ex(h, x, y)
+        assert bool(((y.double() - want).abs() <= 1e-5 * scale + 1e-30).all()), call      # at most 64 additions per term: 64 * 2^-24 = 3.8e-6
+    B.csr5_free(h)
+
+
+@pytest.mark.parametrize("m,lo,hi,w,far,single,kernel", [
+    (50_000, 165, 215, 5000, 0.2, False, B.CSR5_KERNEL_WINDOW),       # two rounds of 6 parts, 2 M entries elsewhere
+    (50_000, 60, 110, 5000, 0.2, False, B.CSR5_KERNEL_PARTS),         # one round
+    (100_000, 60, 110, 7000, 0.1, True, B.CSR5_KERNEL_WINDOW),
+    (70_000, 60, 110, 7000, 0.3, True, B.CSR5_KERNEL_PARTS)])
+def test_bands_that_either_form_may_have(m, lo, hi, w, far, single, kernel):
+    a = _band(m, m, lo, hi, w, far, seed=4)
+    if single:
+        return _single(a, 0, kernel)
+    d = DeviceCsr(a)
+    h = convert(d)
+    assert B.csr5_get_form(h)["kernel"] == kernel, B.csr5_get_form(h)
+    for call in range(3):
+        check_spmv(d, h, call)
+    B.csr5_free(h)
+
+
 def test_nan_and_infinities_of_x_reach_their_rows_only():
     a = _band(40_001, 90_003, 60, 110, 5000, 0.1, seed=3)
     d = DeviceCsr(a)
