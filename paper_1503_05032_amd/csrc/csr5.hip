@@ -104,6 +104,9 @@ constexpr int record_bytes(int64_t nnz) { return nnz <= LOOK_FAR_MAX_NNZ ? LAST_
 template <typename VT> constexpr int far_val_at() { return (LOOK * 8 + LOOK * 4) / int(sizeof(VT)); }
 constexpr int FAR_COL_AT = (LOOK * 8 + LOOK * 4 + LOOK_FAR * 8 - LOOK * 8) / 4;
 constexpr uint32_t STATUS_PUBLIC = 0xffu;
+// Where sample_window adds up, in words from the status word: in another line than that, at which
+// every workgroup of the transposition may queue up.
+constexpr int WINDOW_ANSWER_AT = 32;
 constexpr int NUM_XCD = 8;  // MI355X: 8 accelerator dies, each with its own L2
 
 // sigma rule constants <r, s, t, u> for MI355X (Section 3.2 leaves them to the
@@ -323,7 +326,7 @@ k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, i
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
-    if (gid < 5) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
+    if (gid <= WINDOW_ANSWER_AT) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
     if (order_total)
         for (size_t b = gid; b < 2 * ORDER_BUCKETS; b += size_t(gridDim.x) * blockDim.x) order_total[b] = 0u;
     uint32_t found = 0;
@@ -751,70 +754,69 @@ __device__ __forceinline__ int window_first(uint32_t r0, uint32_t r1, float slop
     return (first < 0 ? 0 : (first < most ? first : most)) & ~127;
 }
 
-// Of the same sample: how many entries lie in their workgroup's window, and in how many
-// lines of it, tile by tile; what the host needs beside sizes to decide for the window form
-// (window_pays).
+// A sample for the window form, taken by the transposition: two neighbours in each of the 64 columns of
+// one tile in 1 << shift, 64 to 127 tiles in all (another place among its workgroup's tiles for each).
+// What the host needs beside sizes (window_pays) is how many of the entries lie in their
+// workgroup's window, and in how many lines of it, tile by tile.
 struct WindowJob {
-    const int32_t* col_idx;          // NULL: nothing to do
-    const uint32_t* tile_ptr;
-    int32_t m, n, sigma, value_bytes, tiles;     // tiles of a workgroup, a power of two
+    uint32_t* answer;                // entries << 16 | lines; cleared with the status word.  NULL: nothing to do
+    int32_t shift, tiles;            // tiles of a workgroup, a power of two
     float slope;
-    uint32_t* answer;                // entries << 16 | lines; cleared with the status word
 };
+inline int window_shift(int pc) {                         // of at least SAMPLE_TILES tiles
+    int shift = 0;
+    while (pc >> (shift + 1) >= SAMPLE_TILES) shift++;
+    return shift;
+}
+constexpr bool window_sampled(const WindowJob& job, int tile) {
+    return (tile & ((1 << job.shift) - 1)) == ((tile >> job.shift) & (job.tiles - 1));
+}
+inline uint32_t window_samples(const WindowJob& job, int pc) {      // entries in it
+    const int strides = pc >> job.shift, last = strides << job.shift | (strides & (job.tiles - 1));
+    return uint32_t(strides + (last < pc ? 1 : 0)) * (2 * OMEGA);
+}
 
-__device__ void sample_window(int pc, const WindowJob& job) {
-    constexpr int WAVES = SCAN_THREADS / OMEGA, PER_WAVE = SAMPLE_TILES / WAVES, LINES = WINDOW_BYTES / 128;
-    static_assert(PER_WAVE < RULE_SIGMA_SMALL, "one turn around a tile's rows");
-    __shared__ uint32_t seen[WAVES][(LINES + 3) / 4];     // a byte per line
-    __shared__ uint32_t near, lines;
-    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
-    // everything is asked for at once, see sample_columns; what the rows say is looked at behind the barrier
-    // (with every tile's wait of its own 0.5-1 us more)
-    uint32_t at[PER_WAVE], next[PER_WAVE], r0[PER_WAVE], r1[PER_WAVE];
-    const int j = (wave * PER_WAVE + lane / 16 * (job.sigma / 4)) % (job.sigma - 1);
+// One tile of it, by its wavefront.  c: columns of a tile column in the order of CSR; who: LDS of the
+// wavefront, a word per line of the window; r0, r1: the rows that the workgroup's tiles begin and end in.
+// The few wavefronts that come here are among the last where the matrix has one round of them: nothing is
+// waited for but two LDS accesses.  (Beside the scan, by one workgroup of its own, 2-6 us of every conversion of
+// the size: 60^3 stencil there and back with one product 101.9 -> 98.8, power-law of 2 M rows 237.0 -> 234.0,
+// mixed of 12.6 M entries 212.4 -> 206.7.)
+constexpr int WINDOW_LINES = WINDOW_BYTES / 128;
+template <int SIGMA>
+__device__ void sample_window(const WindowJob& job, int tile, const int32_t* c, uint32_t* who, uint32_t r0, uint32_t r1, int n, int value_bytes) {
+    const int lane = lane_id();
+    // rows of one length repeat in step with the columns: another place in them for every 16 lanes, and from tile to tile
+    const int at = ((tile >> job.shift) + lane / 16 * (SIGMA / 4)) % (SIGMA - 1);
+    int32_t first = 0, second = 0;
 #pragma unroll
-    for (int u = 0; u < PER_WAVE; u++) {
-        const int tile = int(int64_t(pc) * (wave * PER_WAVE + u) / SAMPLE_TILES), tile0 = tile & -job.tiles;
-        const int32_t* const pair = job.col_idx + int64_t(tile) * (job.sigma * OMEGA) + (j + u < job.sigma - 1 ? j + u : j + u - (job.sigma - 1)) * OMEGA + lane;
-        at[u] = uint32_t(pair[0]);
-        next[u] = uint32_t(pair[OMEGA]);
-        r0[u] = job.tile_ptr[tile0];
-        r1[u] = job.tile_ptr[tile0 + job.tiles < pc ? tile0 + job.tiles : pc];
+    for (int j = 0; j < SIGMA - 1; j++) {
+        if (j == at) {
+            first = c[j];
+            second = c[j + 1];
+        }
     }
-    if (threadIdx.x == 0) near = lines = 0;
-    __syncthreads();
-    int first[PER_WAVE];
-#pragma unroll
-    for (int u = 0; u < PER_WAVE; u++)
-        first[u] = window_first(r0[u] & Index<int32_t>::ROWMASK, r1[u] & Index<int32_t>::ROWMASK, job.slope, job.n * job.value_bytes, job.value_bytes);
-    constexpr uint32_t window = WINDOW_BYTES;
-    uint32_t my_near = 0, my_lines = 0;                    // of the wavefront's tiles; of the lane
-#pragma unroll
-    for (int u = 0; u < PER_WAVE; u++) {
-        for (int w = lane; w < (LINES + 3) / 4; w += OMEGA) seen[wave][w] = 0;
-        wave_sync_lds();
-        const uint32_t last = uint32_t(job.n - 1);         // (out of range: rejected input)
-        const uint32_t a = (at[u] < last ? at[u] : last) * uint32_t(job.value_bytes) - uint32_t(first[u]);
-        const uint32_t b = (next[u] < last ? next[u] : last) * uint32_t(job.value_bytes) - uint32_t(first[u]);
-        if (a < window) reinterpret_cast<uint8_t*>(seen[wave])[a / 128] = 1;
-        if (b < window) reinterpret_cast<uint8_t*>(seen[wave])[b / 128] = 1;
-        my_near += uint32_t(__popcll(__ballot(a < window)) + __popcll(__ballot(b < window)));
-        wave_sync_lds();
-        for (int w = lane; w < (LINES + 3) / 4; w += OMEGA) my_lines += uint32_t(__popc(seen[wave][w]));
-        wave_sync_lds();
-    }
-    if (lane == 0) atomicAdd(&near, my_near);
-    if (my_lines) atomicAdd(&lines, my_lines);
-    __syncthreads();
-    if (threadIdx.x == 0) *job.answer = near << 16 | lines;
+    const uint32_t window = uint32_t(window_first(r0, r1, job.slope, n * value_bytes, value_bytes));
+    const uint32_t last = uint32_t(n - 1);                 // (out of range: rejected input)
+    const uint32_t a = (uint32_t(first) < last ? uint32_t(first) : last) * uint32_t(value_bytes) - window;
+    const uint32_t b = (uint32_t(second) < last ? uint32_t(second) : last) * uint32_t(value_bytes) - window;
+    const bool a_near = a < uint32_t(WINDOW_BYTES), b_near = b < uint32_t(WINDOW_BYTES);
+    wave_sync_lds();
+    if (a_near) who[a / 128] = uint32_t(lane);            // of the entries in a line one stays
+    if (b_near) who[b / 128] = uint32_t(OMEGA + lane);
+    wave_sync_lds();
+    const uint32_t near = uint32_t(__popcll(__ballot(a_near)) + __popcll(__ballot(b_near)));
+    const uint32_t lines = uint32_t(__popcll(__ballot(a_near && who[a / 128] == uint32_t(lane))) +
+                                    __popcll(__ballot(b_near && who[b / 128] == uint32_t(OMEGA + lane))));
+    wave_sync_lds();
+    if (lane == 0) atomicAdd(job.answer, near << 16 | lines);
 }
 
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-           uint32_t* __restrict__ status, const OrderJob job, const SampleJob sample, const WindowJob window) {
-    if (window.col_idx && blockIdx.x == gridDim.x - 1) return sample_window(pc, window);
-    if (sample.col_idx && blockIdx.x == gridDim.x - (window.col_idx ? 2u : 1u)) return sample_columns(pc, sample);
+           uint32_t* __restrict__ status, const OrderJob job, const SampleJob sample) {
+    if (sample.col_idx && blockIdx.x == gridDim.x - 1) return sample_columns(pc, sample);
     if (blockIdx.x > 0) return order_count<IT>(pc, job, int(blockIdx.x) - 1, tile_ptr, status);
     IT total = 0;
     if (*status & STATUS_SCAN_NEEDED)
@@ -826,8 +828,7 @@ k_scan_eop(int pc, int p, IT* __restrict__ eop, const typename Index<IT>::tp_t* 
 template <typename IT>
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_chunks(int pc, IT* __restrict__ eop, IT* __restrict__ chunk_sum, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
-              const uint32_t* __restrict__ status, const OrderJob job, const WindowJob window) {
-    if (window.col_idx && blockIdx.x == gridDim.x - 1) return sample_window(pc, window);
+              const uint32_t* __restrict__ status, const OrderJob job) {
     const int chunk = int(blockIdx.x) - job.slices;
     if (chunk < 0) return order_count<IT>(pc, job, int(blockIdx.x), tile_ptr, status);
     if (!(*status & STATUS_SCAN_NEEDED)) return;
@@ -1001,6 +1002,7 @@ struct DescJob {
     const uint32_t* words;              // of k_prepare
     int32_t nb_tiles, nb_rows;
     int32_t* first_col;                 // every tile's first column, for the tile order, or NULL
+    WindowJob window;
 };
 
 template <int SIGMA, bool BACK, bool KEEP, typename VT>
@@ -1051,6 +1053,16 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
         if (active) {
             row0 = tile_row(tile);
             row1 = tile_row(tile + 1);
+        }
+    }
+    bool sampled = false;                // uniform per wavefront
+    int group0 = 0, group1 = 0;          // rows, see sample_window
+    if constexpr (!BACK && rule_sigma(SIGMA)) {
+        sampled = active && job.window.answer && window_sampled(job.window, tile);
+        if (sampled) {
+            const int t0 = tile & -job.window.tiles;
+            group0 = tile_row(t0);
+            group1 = tile_row(t0 + job.window.tiles < pc ? t0 + job.window.tiles : pc);
         }
     }
 
@@ -1154,6 +1166,10 @@ k_transpose(int pc, int n, int64_t nnz, int32_t* __restrict__ col_idx, VT* __res
         }
 #pragma unroll
         for (int k = 0; k < SIGMA; k++) stream_to<KEEP>(&col_idx[base + k * OMEGA + lane], c[k]);
+        if constexpr (!BACK && rule_sigma(SIGMA)) {
+            static_assert(WINDOW_LINES * 4 <= int(sizeof(lds[0])), "in the wavefront's slice");
+            if (sampled) sample_window<SIGMA>(job.window, tile, c, reinterpret_cast<uint32_t*>(lds[wave]), uint32_t(group0), uint32_t(group1), n, int(sizeof(VT)));
+        }
     }
     if (!BACK && blockIdx.x == gridDim.x - 1) {
         for (size_t e = size_t(pc) * T + threadIdx.x; e < size_t(nnz); e += blockDim.x) {
@@ -2624,20 +2640,17 @@ hipError_t launch_staged(const Geom& g, int m, int n, int nnz, const int32_t* ro
 //    precision +-2000 58.9 -> 57.0, +-1600 54.3 -> 56.9; rows of 2000-4000 within +-5000 columns
 //    (0.5) 103 -> 113.  Stencils have 0.25-0.4, and the L1 holds what they use.
 //  * Tiles: below WINDOW_MIN_TILES of them some CUs have two workgroups and most have one
-//    (mixed, 2.5 M entries 17.6 -> 18.0, 3.1 M 20.8 -> 21.3, 3.9 M 26.0 -> 22.9), and the sample
-//    costs more than most would gain: 2-4 us of a conversion, asked of every matrix of the size
-//    (conversion, one SpMV and back, 60^3 stencil 93.7 -> 97.3, 40^3 would be 61.0 -> 64.6,
-//    power-law of 2 M rows 229.3 -> 231.6).
+//    (mixed, 2.5 M entries 17.6 -> 18.0, 3.1 M 20.8 -> 21.3, 3.9 M 26.0 -> 22.9).
 constexpr int WINDOW_WAVES = 8, WINDOW_MIN_TILES = 6400;
 constexpr uint32_t WINDOW_NEAR_PERCENT = 50, WINDOW_LINES_PERCENT = 70;
-static_assert((WINDOW_WAVES & (WINDOW_WAVES - 1)) == 0, "sample_window");
+static_assert((WINDOW_WAVES & (WINDOW_WAVES - 1)) == 0, "window_sampled");
 constexpr int window_tiles(int sigma) { return sigma == RULE_SIGMA_SMALL ? 2 : 1; }       // per wavefront
 inline bool window_fits(const Geom& g, int n, size_t value_bytes) {
     const int64_t x_bytes = int64_t(n) * int64_t(value_bytes);
     return rule_sigma(g.sigma) && g.pc >= WINDOW_MIN_TILES && x_bytes >= WINDOW_BYTES && x_bytes <= (1 << 30);
 }
-inline bool window_pays(uint32_t near, uint32_t lines) {
-    return near * 100 >= 2u * SAMPLES * WINDOW_NEAR_PERCENT && lines * 100 >= near * WINDOW_LINES_PERCENT;
+inline bool window_pays(uint32_t samples, uint32_t near, uint32_t lines) {
+    return near * 100 >= samples * WINDOW_NEAR_PERCENT && lines * 100 >= near * WINDOW_LINES_PERCENT;
 }
 // A band with entries elsewhere may suit both forms: a few of them make a tile wide for
 // sample_columns.  A part costs a round about a microsecond whatever its entries are, the window's far
@@ -2647,9 +2660,8 @@ inline bool window_pays(uint32_t near, uint32_t lines) {
 // 40.7, 35.9, two fifths 40.5, 38.5 (left to the parts); 6.7 M, 2 rounds of 4, a tenth 28.9, 27.4, two
 // fifths 28.8, 30.9; 4.3 M, one round of 6, a tenth 20.4, 21.2, two fifths 20.4, 23.8; 6 M in single
 // precision, one round of 4, a tenth 17.5, 19.6.
-inline bool window_rather(const Geom& g, int n, int64_t nnz, size_t value_bytes, int k, uint32_t near) {
-    const int64_t far = nnz * int64_t(2u * SAMPLES - near) / int64_t(2 * SAMPLES);
-    return 2 * far + 5500 * 1000 < int64_t(staged_rounds(g, value_bytes, k)) * staged_parts(n, value_bytes) * 1000 * 1000;
+inline bool window_rather(const Geom& g, int n, int64_t nnz, size_t value_bytes, int k, uint32_t far, uint32_t samples) {
+    return 2 * (nnz * far / samples) + 5500 * 1000 < int64_t(staged_rounds(g, value_bytes, k)) * staged_parts(n, value_bytes) * 1000 * 1000;
 }
 template <int SIGMA, typename VT>
 hipError_t launch_window(const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
@@ -3067,14 +3079,12 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     const int staged = !wide && !(flags & CSR5_FLAG_NO_HOST_CHECK) && h->span && h->aux_form == 0 ? staged_tiles(g, n, sizeof(VT)) : 0;
     const int64_t staged_entries = staged ? staged_min_entries(g, n, sizeof(VT), staged) : 0;
     if (staged && int64_t(nnz) >= staged_entries && int64_t(n) * int64_t(sizeof(VT)) <= SAMPLE_MAX_LINES * 128) sample.col_idx = col_idx;
-    WindowJob window = {nullptr, nullptr, m, n, sigma, int(sizeof(VT)), WINDOW_WAVES * window_tiles(sigma), float(n) / float(m > 0 ? m : 1), h->status + 4};
-    if constexpr (!wide) {
-        if (!(flags & CSR5_FLAG_NO_HOST_CHECK) && h->aux_form == 0 && window_fits(g, n, sizeof(VT))) {
-            window.col_idx = col_idx;
-            window.tile_ptr = tile_ptr;
-        }
+    WindowJob window = {nullptr, 0, WINDOW_WAVES * window_tiles(sigma), float(n) / float(m > 0 ? m : 1)};
+    if (!wide && !(flags & CSR5_FLAG_NO_HOST_CHECK) && h->aux_form == 0 && window_fits(g, n, sizeof(VT))) {
+        window.answer = h->status + WINDOW_ANSWER_AT;
+        window.shift = window_shift(g.pc);
     }
-    DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.slices ? static_cast<int32_t*>(h->carry) : nullptr};
+    DescJob job = {m, wide ? 1 : 0, row_ptr, tile_ptr, h->tile_desc, eop, words, 0, 0, order.slices ? static_cast<int32_t*>(h->carry) : nullptr, window};
     {   // step 2a
         const size_t nb_tiles = (size_t(g.p) + 1 + PREP_THREADS - 1) / PREP_THREADS;
         const size_t nb_rows = (size_t(m) + PREP_THREADS * PREP_UNROLL - 1) / (PREP_THREADS * PREP_UNROLL);
@@ -3098,14 +3108,14 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         }
     }
     if (e == hipSuccess && g.pc <= SCAN_SINGLE) {
-        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices + (sample.col_idx ? 1 : 0) + (window.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s,
-                           g.pc, g.p, eop, tile_ptr, h->status, order, sample, window);
+        hipLaunchKernelGGL(k_scan_eop<IT>, dim3(1 + order.slices + (sample.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s,
+                           g.pc, g.p, eop, tile_ptr, h->status, order, sample);
         e = hipGetLastError();
     } else if (e == hipSuccess) {
         IT* chunk_sum = reinterpret_cast<IT*>(basep + L.off_scan);
         const int nchunks = (g.pc + SCAN_CHUNK - 1) / SCAN_CHUNK;      // <= 2^26 / 2^13 = SCAN_CHUNK
-        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + order.slices + (window.col_idx ? 1 : 0)), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
-                           tile_ptr, h->status, order, window);
+        hipLaunchKernelGGL(k_scan_chunks<IT>, dim3(nchunks + order.slices), dim3(SCAN_THREADS), 0, s, g.pc, eop, chunk_sum,
+                           tile_ptr, h->status, order);
         e = hipGetLastError();
         if (e == hipSuccess) {
             hipLaunchKernelGGL(k_scan_finish<IT>, dim3(nchunks), dim3(SCAN_THREADS), 0, s, g.pc, g.p, eop, chunk_sum,
@@ -3129,17 +3139,17 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK)) {
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
-        uint32_t got[5] = {0, 0, 0, 0, 0};      // the status word, behind it the plan of the tile order and the answers on the columns
-        int rc = read_status(h, got, window.col_idx ? 5 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
+        uint32_t got[WINDOW_ANSWER_AT + 1] = {};      // the status word, behind it the plan of the tile order and the answers on the columns
+        int rc = read_status(h, got, window.answer ? WINDOW_ANSWER_AT + 1 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];
             h->order_len = got[2];
         }
-        const uint32_t near = got[4] >> 16, lines = got[4] & 0xffffu;
-        h->window = rc == CSR5_OK && !h->order && window_pays(near, lines);
+        const uint32_t samples = window.answer ? window_samples(window, g.pc) : 0u, near = got[WINDOW_ANSWER_AT] >> 16, lines = got[WINDOW_ANSWER_AT] & 0xffffu;
+        h->window = rc == CSR5_OK && window.answer && !h->order && window_pays(samples, near, lines);
         if (rc == CSR5_OK && got[3] && int64_t(nnz) * got[3] >= staged_entries * SAMPLES &&
-            !(h->window && window_rather(g, n, int64_t(nnz), sizeof(VT), staged, near))) {
+            !(h->window && window_rather(g, n, int64_t(nnz), sizeof(VT), staged, samples - near, samples))) {
             h->staged = staged;
             h->window = false;
         }
