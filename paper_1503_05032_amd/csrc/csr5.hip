@@ -2260,7 +2260,9 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         for (int j = 0; j < SIGMA; j++) xv[k][j] = VT(0);
     const auto take = [&](int part, const char* from, char* next) {
         // This part has arrived: what this wavefront asked for before the columns came before
-        // them (loads return in order); later parts, and its reads of the part before.
+        // them (loads return in order); later parts, and its reads of the part before (which the
+        // compiler could move behind a wait that does not say that it is about memory).
+        asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(WAIT_LDS);
         if (part > 0) __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
         else asm volatile("" :: "v"(c[K - 1][SIGMA - 1]), "v"(dw[K - 1]) : "memory");
