@@ -24,8 +24,9 @@ def _matrix(nnz, n, seed):
 
 
 @pytest.mark.parametrize("nnz,n,sigma,wide", [
-    ((32 << 20) // 12, 50_000, 0, False), ((32 << 20) // 12 + 1, 50_000, 0, False), ((32 << 20) // 12 + 1, 400_000, 0, True),
-    ((48 << 20) // 12, 50_000, 16, False), ((48 << 20) // 12 + 1, 350_000, 8, True), (300_000, 3000, 0, False)])
+    ((18 << 20) // 12, 300_000, 0, False), ((18 << 20) // 12 + 1, 300_000, 0, False),
+    ((32 << 20) // 12, 300_000, 0, False), ((32 << 20) // 12 + 1, 300_000, 0, False), ((32 << 20) // 12 + 1, 400_000, 0, True),
+    ((48 << 20) // 12, 500_000, 16, False), ((48 << 20) // 12 + 1, 350_000, 8, True), (300_000, 3000, 0, False)])
 def test_every_product_of_a_handle_is_the_same(nnz, n, sigma, wide):
     a = _matrix(nnz, n, seed=nnz % 1000 + n)
     assert a.nnz == nnz
@@ -33,6 +34,7 @@ def test_every_product_of_a_handle_is_the_same(nnz, n, sigma, wide):
     d = DeviceCsr(a, wide=wide)
     for flags in (B.CSR5_FLAG_NONE, B.CSR5_FLAG_NO_HOST_CHECK):
         h = convert(d, sigma=sigma, flags=flags)
+        assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_TILES
         check_format(d, h, (a.name, flags))
         check_spmv(d, h, (a.name, flags, "first"))
         first = d.y.clone()
@@ -51,12 +53,13 @@ def test_every_product_of_a_handle_is_the_same(nnz, n, sigma, wide):
 
 @pytest.mark.parametrize("nnz", [(32 << 20) // 8 + 1, (48 << 20) // 8 + 1])
 def test_single_precision(nnz):
-    a = _matrix(nnz, 60_000, seed=9)
+    a = _matrix(nnz, 900_000, seed=9)
     d = DeviceCsr(a)
     val, x = d.val.float(), d.x.float()
     kept = val.clone()
     y = torch.empty(a.m, dtype=torch.float32, device="cuda:0")
     h = B.csr5s_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_TILES
     products = kept.double() * x.double()[torch.from_numpy(a.col_idx).long().cuda()]
     want = torch.segment_reduce(products, "sum", offsets=d.row_ptr.long(), initial=0)
     scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)

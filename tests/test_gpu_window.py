@@ -1,7 +1,8 @@
 """GPU parity of the SpMV that keeps the part of x around the diagonal in LDS: x just above
 the window and a little more, tall and wide matrices, entries in and outside the window,
 rows across several workgroups and empty ones, both tile heights, one and two kernels, x
-at an odd address; and which columns are left to the general kernel."""
+at an odd address; and which columns are left to the general kernel.  Every test asks the
+library which kernel it is about."""
 import numpy as np
 import pytest
 import torch
@@ -39,11 +40,11 @@ def _band(m, n, lo, hi, w, far=0.0, uneven=False, seed=0):
     (20_000, WINDOW + 1, 165, 215, 4000, 0.0, 0, False),           # x of one window and an entry
     (20_000, WINDOW + 17, 165, 215, 4000, 0.0, 0, True),
     (20_001, 90_003, 165, 215, 5000, 0.0, 0, False),               # wide
-    (430_003, 50_001, 5, 13, 5000, 0.1, 0, True),                 # tall
+    (430_003, 100_001, 5, 13, 5000, 0.1, 0, True),                # tall
     (20_000, 300_000, 165, 215, 7000, 0.1, 0, True),              # a band wider than the window
     (20_000, 200_000, 200, 200, 5000, 0.4, 0, False),             # rows of one length, many entries elsewhere
     (45_000, 90_000, 165, 215, 5000, 0.2, 16, True),               # height 16
-    (95_000, 200_001, 165, 215, 5000, 0.1, 8, True)])             # more than 32768 tiles: two kernels
+    (110_000, 200_001, 165, 215, 5000, 0.1, 8, True)])            # more than 32768 tiles: two kernels
 def test_parity(m, n, lo, hi, w, far, sigma, uneven):
     a = _band(m, n, lo, hi, w, far, uneven, seed=m % 97)
     print("window", m, n, lo, hi, w, far, sigma, uneven, a.nnz, flush=True)
@@ -51,16 +52,17 @@ def test_parity(m, n, lo, hi, w, far, sigma, uneven):
     h = convert(d, sigma=sigma)
     check_format(d, h, a.name)
     info, first = B.csr5_get_info(h), None
+    assert B.csr5_get_form(h) == {"kernel": B.CSR5_KERNEL_WINDOW, "wave_tiles": 2 if info["sigma"] == 8 else 1, "plain": 0}
     one = info["p"] <= 32768
+    assert one == (m < 100_000 or lo < 160), info["p"]
     whole_tiles = info["p_complete"] * 64 * info["sigma"]
     fixed = int(np.searchsorted(a.row_ptr, whole_tiles, side="right")) - 1      # rows in the incomplete tile are added in any order
-    for call in range(10):                         # the meeting words come back to rest; plain and non-temporal streams
+    for call in range(10):                         # the meeting words come back to rest
         check_spmv(d, h, (a.name, call))
         first = d.y.clone() if first is None else first
         if one:
             assert torch.equal(d.y[:fixed], first[:fixed]), (a.name, call)
-    if lo > 160 and info["p"] > 6144:              # too long for the look-behind and the one-launch form: the general kernel would want the second one
-        assert (second_kernel_ms(h, d.x, d.y) < 1e-3) == one, a.name
+    assert (second_kernel_ms(h, d.x, d.y) < 1e-3) == one, a.name
     _, s = oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val, a.x)
     whole = torch.empty(n + 1, dtype=torch.float64, device="cuda:0")            # x at an odd address
     whole[1:] = d.x
@@ -75,24 +77,7 @@ def test_parity(m, n, lo, hi, w, far, sigma, uneven):
     B.csr5_free(h)
 
 
-@pytest.mark.parametrize("m,n,sigma,w", [(60_000, 2 * WINDOW + 3, 0, 9000), (70_000, 150_001, 0, 5000), (120_000, 120_000, 16, 9500)])
-def test_single_precision(m, n, sigma, w):
-    a = _band(m, n, 60, 110, w, 0.1, True, seed=5)
-    d = DeviceCsr(a)
-    val, x = d.val.float(), d.x.float()
-    products = val.double() * x.double()[d.col_idx.long()]
-    want = torch.segment_reduce(products, "sum", offsets=d.row_ptr.long(), initial=0)
-    scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)
-    y = torch.empty(a.m, dtype=torch.float32, device="cuda:0")
-    h = B.csr5s_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val, sigma=sigma)
-    for call in range(3):
-        y.fill_(float("nan"))
-        B.csr5s_spmv_ex(h, x, y)
-        assert bool(((y.double() - want).abs() <= 1e-5 * scale + 1e-30).all()), call      # at most 64 additions per term: 64 * 2^-24 = 3.8e-6
-    B.csr5_free(h)
-
-
-def _single(a, sigma, kernel, calls=3):
+def _single(a, sigma, kernel, calls=10):
     """Products in single precision against sums in double precision; the form is the one named."""
     d = DeviceCsr(a)
     val, x = d.val.float(), d.x.float()
@@ -107,6 +92,15 @@ def _single(a, sigma, kernel, calls=3):
         B.csr5s_spmv_ex(h, x, y)
         assert bool(((y.double() - want).abs() <= 1e-5 * scale + 1e-30).all()), call      # at most 64 additions per term: 64 * 2^-24 = 3.8e-6
     B.csr5_free(h)
+
+
+@pytest.mark.parametrize("m,n,sigma,w,far", [
+    (60_000, 2 * WINDOW + 1, 0, 4000, 0.0),                        # x of one window and an entry
+    (60_000, 150_001, 0, 5000, 0.0), (70_000, 150_001, 0, 5000, 0.1),
+    (110_000, 150_001, 16, 9500, 0.1),                             # height 16; a band as wide as the window
+    (300_000, 400_003, 8, 9500, 0.05)])                            # more than 32768 tiles: two kernels
+def test_single_precision(m, n, sigma, w, far):
+    _single(_band(m, n, 60, 110, w, far, True, seed=5), sigma, B.CSR5_KERNEL_WINDOW)
 
 
 @pytest.mark.parametrize("m,lo,hi,w,far,single,kernel", [
@@ -130,6 +124,7 @@ def test_nan_and_infinities_of_x_reach_their_rows_only():
     a = _band(40_001, 90_003, 60, 110, 5000, 0.1, seed=3)
     d = DeviceCsr(a)
     h = convert(d)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_WINDOW
     x = a.x.copy()
     x[[0, WINDOW - 1, WINDOW, 90_002]] = [np.nan, np.inf, -np.inf, np.nan]
     d.x = torch.from_numpy(x).cuda()
@@ -148,6 +143,7 @@ def test_other_columns_take_the_general_kernel(w, far, n):
     a = _band(20_000, n, 200, 200, w, far, seed=2)
     d = DeviceCsr(a)
     h = convert(d)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_TILES
     check_spmv(d, h, w)
     assert second_kernel_ms(h, d.x, d.y) > 1e-3, w
     B.csr5_free(h)
@@ -157,6 +153,7 @@ def test_graph_replays():
     a = _band(50_001, 90_003, 60, 110, 5000, 0.1, True, seed=9)
     d = DeviceCsr(a)
     h = convert(d)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_WINDOW
     check_spmv(d, h, "eager")
     want = d.y.clone()[:-1]                        # (not the long row that ends in the incomplete tile)
     yg = torch.empty_like(d.y)
