@@ -167,6 +167,11 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * columns).  The order is laid out by a conversion that blocks; after one with
  * CSR5_FLAG_NO_HOST_CHECK (or with a flag that fixes the form) the SpMV of such a
  * matrix is the one described before, and csr5_status does not change that.
+ * After a conversion that blocks, with 32-bit indices and sigma 8 or 16, matrices
+ * with random columns over an x of up to 4 MiB (at most 32768 tiles) or mostly
+ * within a band of some thousand columns (6400 tiles and more) have their x brought through
+ * LDS, whatever their rows: in ONE kernel, the band in two where it has more than
+ * 32768 tiles (csr5_get_form tells).
  * Which of these, and whether rows without nonzeros need
  * their zeros written, is in the conversion's status word: the library launches
  * only what the matrix needs once the host has seen that word (csr5_convert and
@@ -196,7 +201,8 @@ int csr5_spmv_ex(csr5_handle_t h, const double *x, double *y, void *hip_stream);
  * CSR5_STATIC_MAX_TILES tiles (p, the incomplete tile included).  A matrix that
  * takes the auxiliary-array path always gets the two-kernel form here (the
  * one-kernel form keeps words of its own between calls, which a shared array
- * cannot promise).  Every slot the second kernel reads has been written by the
+ * cannot promise), and so does a band whose x is brought through LDS; random columns
+ * over a small x get the tile kernel.  Every slot the second kernel reads has been written by the
  * first, so nothing needs clearing between calls.  All calls on one GPU share the array, whatever their handle:
  * calls that overlap in time on one GPU race; order them (one stream, or events).
  */
