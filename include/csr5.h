@@ -120,6 +120,10 @@ size_t csr5_workspace_bytes(int32_t m, int32_t nnz, int32_t sigma);
  *               (bit_flag, y_offset, seg_offset packed as in Section 3.5) and
  *               empty_offset with its per-tile start array.
  *
+ * For a matrix with many columns anywhere in a large x (see csr5_spmv) a conversion that blocks and
+ * allocates for itself also allocates up to 16 bytes per such entry, and up to four times
+ * 256 MiB (more beyond 8 GiB of them), if that is no more than an eighth of the memory that is free.
+ *
  * csr5_convert picks sigma itself, allocates with hipMalloc, runs on the default
  * stream and waits for the conversion's device-side checks of the input
  * (row_ptr[0] = 0, row_ptr[m] = nnz, non-decreasing; column indices in range):
@@ -172,6 +176,13 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * within a band of some thousand columns (6400 tiles and more) have their x brought through
  * LDS, whatever their rows: in ONE kernel, the band in two where it has more than
  * 32768 tiles (csr5_get_form tells).
+ * After csr5_convert, or a csr5_convert_ex (csr5s_convert_ex) that blocks and allocates for
+ * itself, at the automatic sigma or 8 or 16, a matrix many of whose columns are anywhere in an x
+ * larger than the L2s (some 10 million such entries and more, x of up to 128 MiB) has the x of
+ * these gathered into a buffer by a kernel of its own before the tile kernel: two
+ * kernels, and a third for the sums where the band has it; larger matrices in
+ * several such pairs.  The lists for it are made by the conversion, which takes about twice
+ * as long, and pay for that within 8 products.
  * Which of these, and whether rows without nonzeros need
  * their zeros written, is in the conversion's status word: the library launches
  * only what the matrix needs once the host has seen that word (csr5_convert and
@@ -202,7 +213,7 @@ int csr5_spmv_ex(csr5_handle_t h, const double *x, double *y, void *hip_stream);
  * takes the auxiliary-array path always gets the two-kernel form here (the
  * one-kernel form keeps words of its own between calls, which a shared array
  * cannot promise), and so does a band whose x is brought through LDS; random columns
- * over a small x get the tile kernel.  Every slot the second kernel reads has been written by the
+ * over a small x, and over a large one that has them gathered, get the tile kernel.  Every slot the second kernel reads has been written by the
  * first, so nothing needs clearing between calls.  All calls on one GPU share the array, whatever their handle:
  * calls that overlap in time on one GPU race; order them (one stream, or events).
  */
@@ -293,11 +304,13 @@ int csr5_get_shape(csr5_handle_t h, int32_t *m, int32_t *n);
  *                                    that an L2 holds; one kernel
  *                 CSR5_KERNEL_WINDOW the part of x around the diagonal in LDS; one kernel up to
  *                                    32768 tiles, two beyond
+ *                 CSR5_KERNEL_GATHERED the same, or no part of x, with the other entries' x gathered
+ *                                    into a buffer by a kernel before it
  *   wave_tiles    tiles of a wavefront (1 for CSR5_KERNEL_TILES)
  *   plain         1: col_idx, val and the descriptors would be read with plain loads, 0: with
  *                 non-temporal ones (a hint to the caches, the result is the same)
  */
-enum { CSR5_KERNEL_TILES = 0, CSR5_KERNEL_PARTS = 1, CSR5_KERNEL_WINDOW = 2 };
+enum { CSR5_KERNEL_TILES = 0, CSR5_KERNEL_PARTS = 1, CSR5_KERNEL_WINDOW = 2, CSR5_KERNEL_GATHERED = 3 };
 int csr5_get_form(csr5_handle_t h, void *hip_stream, int32_t *kernel, int32_t *wave_tiles, int32_t *plain);
 
 /*

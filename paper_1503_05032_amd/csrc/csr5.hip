@@ -106,7 +106,7 @@ constexpr int FAR_COL_AT = (LOOK * 8 + LOOK * 4 + LOOK_FAR * 8 - LOOK * 8) / 4;
 constexpr uint32_t STATUS_PUBLIC = 0xffu;
 // Where sample_window adds up, in words from the status word: in another line than that, at which
 // every workgroup of the transposition may queue up.
-constexpr int WINDOW_ANSWER_AT = 32;
+constexpr int WINDOW_ANSWER_AT = 32, FAR_ANSWER_AT = 40;
 constexpr int NUM_XCD = 8;  // MI355X: 8 accelerator dies, each with its own L2
 
 // sigma rule constants <r, s, t, u> for MI355X (Section 3.2 leaves them to the
@@ -326,7 +326,7 @@ k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, i
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
-    if (gid <= WINDOW_ANSWER_AT) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
+    if (gid <= WINDOW_ANSWER_AT + 1) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
     if (order_total)
         for (size_t b = gid; b < 2 * ORDER_BUCKETS; b += size_t(gridDim.x) * blockDim.x) order_total[b] = 0u;
     uint32_t found = 0;
@@ -757,9 +757,11 @@ __device__ __forceinline__ int window_first(uint32_t r0, uint32_t r1, float slop
 // A sample for the window form, taken by the transposition: two neighbours in each of the 64 columns of
 // one tile in 1 << shift, 64 to 127 tiles in all (another place among its workgroup's tiles for each).
 // What the host needs beside sizes (window_pays) is how many of the entries lie in their
-// workgroup's window, and in how many lines of it, tile by tile.
+// workgroup's window, and in how many lines of it, tile by tile; and for k_far_gather how many lie further
+// from it than an L2 reaches, and in how many of the tiles these spread over more than that.
+constexpr int FAR_REACH_BYTES = 2 << 20;
 struct WindowJob {
-    uint32_t* answer;                // entries << 16 | lines; cleared with the status word.  NULL: nothing to do
+    uint32_t* answer;                // entries << 16 | lines, further entries << 16 | tiles; cleared with the status word.  NULL: nothing to do
     int32_t shift, tiles;            // tiles of a workgroup, a power of two
     float slope;
 };
@@ -809,7 +811,15 @@ __device__ void sample_window(const WindowJob& job, int tile, const int32_t* c, 
     const uint32_t lines = uint32_t(__popcll(__ballot(a_near && who[a / 128] == uint32_t(lane))) +
                                     __popcll(__ballot(b_near && who[b / 128] == uint32_t(OMEGA + lane))));
     wave_sync_lds();
-    if (lane == 0) atomicAdd(job.answer, near << 16 | lines);
+    const bool a_far = a + FAR_REACH_BYTES >= uint32_t(2 * FAR_REACH_BYTES), b_far = b + FAR_REACH_BYTES >= uint32_t(2 * FAR_REACH_BYTES);
+    const uint64_t far_lanes = __ballot(a_far);
+    const uint32_t far = uint32_t(__popcll(far_lanes) + __popcll(__ballot(b_far)));
+    const uint32_t one = __builtin_amdgcn_readlane(a, far_lanes ? __builtin_ctzll(far_lanes) : 0);
+    const bool spread = far_lanes && __ballot(a_far && a - one + 2 * FAR_REACH_BYTES >= uint32_t(4 * FAR_REACH_BYTES)) != 0;
+    if (lane == 0) {
+        atomicAdd(job.answer, near << 16 | lines);
+        if (far) atomicAdd(job.answer + 1, far << 16 | (spread ? 1u : 0u));
+    }
 }
 
 template <typename IT>
@@ -979,6 +989,7 @@ __device__ __forceinline__ P stream_from(__amdgpu_buffer_rsrc_t r, int offset) {
     constexpr int POLICY = KEEP ? POLICY_KEEP : POLICY_STREAM;
     if constexpr (sizeof(P) == 16) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, POLICY));
     else if constexpr (sizeof(P) == 8) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b64(r, offset, 0, POLICY));
+    else if constexpr (sizeof(P) == 2) return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b16(r, offset, 0, POLICY));
     else return __builtin_bit_cast(P, __builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, POLICY));
 }
 template <bool KEEP, typename P>
@@ -2131,6 +2142,324 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 #endif
 }
 
+// ----------------------------------------------------------------------------
+// Entries whose x no cache near them holds: columns anywhere in an x larger than the L2s.
+//
+// A gather from such an x is a 128-byte line from memory for one value, 55 G/s on the whole chip
+// (rows of 30 random columns out of 4 M: 80 M entries 1350 us, 8 times their stream).  So these
+// entries' values of x are brought to them in two steps, both in whole lines:
+//  1. k_far_gather: x in blocks of FAR_BLOCK_BYTES through LDS, one per workgroup; from each it
+//     picks the values that the matrix asks of it, in a list of 2-byte columns, and writes them
+//     to a buffer one after the other.  x is read once.
+//  2. k_spmv_staged (FORM_FAR): a workgroup of FAR_ENTRIES entries fetches its own from the
+//     buffer.  The list of a block is in the order of the workgroups, so what one of them takes
+//     from a block lies together (7 entries and more on the matrices this is for), and the rest of the line is
+//     its neighbours', which run on the same XCD.  They go to LDS, to the entry's place among the
+//     workgroup's (which of the two, 4 and 2 bytes, is a list as well), when the entries near
+//     the diagonal have taken theirs from the window there; from LDS every lane picks its own.
+// 26 to 40 bytes an entry instead of 128 and more.  Whole SpMV, before -> after:
+// mixed (four fifths of the rows within +-5000 columns, the others anywhere) 136 M entries 1185 -> 708
+// us, single precision 1020 -> 472, 51 M 422 -> 260, 34 M 253 -> 185; rows of 0-20 columns out of 4 M
+// 690 -> 326, 582 -> 214.  Of the 708, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 565
+// the second: 193 for the lists and the buffer, 70 for the stores of y, 45 for the window.
+// The buffer is a handle's (one for each of its CARRY_SLOTS), of FAR_BUFFER_BYTES at most; a matrix
+// with more such entries goes through it in chunks of workgroups (136 M entries in 1, 2, 4, 8 chunks 717,
+// 709, 717, 789; 34 M in 1, 2, 4 187, 196, 219: a drained chip between any two kernels).
+// Tried: the buffer read past the caches (nt) 709 -> 808; written so 709 -> 712, single precision 472 ->
+// 490; 4 entries per thread asked for ahead of the window instead of 8 709 -> 722.
+//
+// The lists are the conversion's (far_make): where it blocks, allocates for itself and the columns
+// pay for it.  A block's entries are counted per workgroup (k_far_count), the counts scanned in
+// the order chunk, block, workgroup (k_far_segments, k_far_bases, k_far_starts), and every workgroup
+// sorts its entries by block in LDS and writes them to their places (k_far_place).  The order of
+// a workgroup's entries in a block is any; the sums do not depend on it.
+// ----------------------------------------------------------------------------
+constexpr int FAR_THREADS = 512, FAR_ENTRIES = 8192, FAR_PLACE_BITS = 13, FAR_AHEAD = 8;
+constexpr int FAR_BLOCK_BYTES = 128 << 10, FAR_MAX_BLOCKS = 1024, FAR_SEGMENT = 64, FAR_MAX_CHUNKS = 32, FAR_PAD = 16;
+constexpr int64_t FAR_BUFFER_BYTES = 256 << 20;
+template <typename VT> constexpr int far_block_shift() { return sizeof(VT) == 8 ? 14 : 15; }
+
+struct FarShape {
+    int pc, n, groups, blocks, segments, chunks;      // workgroups, blocks of x, FAR_SEGMENTs of workgroups, chunks of segments
+    int window_bytes;                                 // 0: all entries go through the buffer
+    float slope;
+};
+constexpr int far_chunk_segment(const FarShape& f, int chunk) { return int(int64_t(f.segments) * chunk / f.chunks); }
+
+// Calls take(column, place) for the entries of a workgroup's tiles outside its window
+template <int SIGMA, typename VT, typename F>
+__device__ __forceinline__ void far_each(const FarShape& f, int group, const uint32_t* __restrict__ tile_ptr, const int32_t* __restrict__ col_idx, F take) {
+    constexpr uint32_t ROWMASK = Index<int32_t>::ROWMASK;
+    constexpr int T = OMEGA * SIGMA, TILES = FAR_ENTRIES / T, EACH = FAR_ENTRIES / FAR_THREADS;
+    const int tile0 = group * TILES, tiles = f.pc - tile0 < TILES ? f.pc - tile0 : TILES;
+    const uint32_t window = uint32_t(window_first(tile_ptr[tile0] & ROWMASK, tile_ptr[tile0 + TILES < f.pc ? tile0 + TILES : f.pc] & ROWMASK,
+                                                  f.slope, f.n * int(sizeof(VT)), int(sizeof(VT))));
+    const auto cols = tile_buffer(col_idx + size_t(tile0) * T, tiles * T * 4);
+    int32_t c[EACH];
+#pragma unroll
+    for (int u = 0; u < EACH; u++) c[u] = stream_from<int32_t, false>(cols, (u * FAR_THREADS + int(threadIdx.x)) * 4);
+#pragma unroll
+    for (int u = 0; u < EACH; u++) {
+        const int place = u * FAR_THREADS + int(threadIdx.x);
+        if (place < tiles * T && uint32_t(c[u]) * uint32_t(sizeof(VT)) - window >= uint32_t(f.window_bytes)) take(c[u], place);
+    }
+}
+
+template <int SIGMA, typename VT>
+__global__ void __launch_bounds__(FAR_THREADS)
+k_far_count(const FarShape f, const uint32_t* __restrict__ tile_ptr, const int32_t* __restrict__ col_idx, uint16_t* __restrict__ counts, uint32_t* __restrict__ base) {
+    __shared__ uint32_t count[FAR_MAX_BLOCKS], all;
+    for (int b = threadIdx.x; b < f.blocks; b += FAR_THREADS) count[b] = 0;
+    if (threadIdx.x == 0) all = 0;
+    __syncthreads();
+    const int group = int(xcd_order(blockIdx.x, uint32_t(f.groups), 0));
+    far_each<SIGMA, VT>(f, group, tile_ptr, col_idx, [&](int32_t c, int) { atomicAdd(&count[c >> far_block_shift<VT>()], 1u); });
+    __syncthreads();
+    uint32_t mine = 0;
+    for (int b = threadIdx.x; b < f.blocks; b += FAR_THREADS) {
+        counts[size_t(group) * f.blocks + b] = uint16_t(count[b]);
+        mine += count[b];
+    }
+    if (mine) atomicAdd(&all, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) base[group] = all;
+}
+
+// sums over FAR_SEGMENT workgroups
+__global__ void __launch_bounds__(FAR_THREADS)
+k_far_segments(const FarShape f, const uint16_t* __restrict__ counts, uint32_t* __restrict__ sums) {
+    const int g0 = blockIdx.x * FAR_SEGMENT, g1 = g0 + FAR_SEGMENT < f.groups ? g0 + FAR_SEGMENT : f.groups;
+    for (int b = threadIdx.x; b < f.blocks; b += FAR_THREADS) {
+        uint32_t s = 0;
+#pragma unroll 16
+        for (int g = g0; g < g1; g++) s += counts[size_t(g) * f.blocks + b];
+        sums[size_t(blockIdx.x) * f.blocks + b] = s;
+    }
+}
+
+// Workgroup k < chunks: in the chunk's list, by block of x, where each segment's share begins (in place of its sum), and where each
+// block's does.  The last workgroup: where each group's list begins.
+__global__ void __launch_bounds__(SCAN_THREADS)
+k_far_bases(const FarShape f, uint32_t* __restrict__ sums, uint32_t* __restrict__ range, uint32_t* __restrict__ base, uint32_t* __restrict__ totals) {
+    static_assert(FAR_MAX_BLOCKS == SCAN_THREADS, "a thread per block");
+    if (int(blockIdx.x) == f.chunks) {
+        uint32_t carry = 0;
+        for (int64_t at = 0; at < f.groups; at += SCAN_CHUNK) carry += scan_chunk<uint32_t>(base, at, f.groups, carry);
+        if (threadIdx.x == 0) base[f.groups] = totals[f.chunks] = carry;
+        return;
+    }
+    __shared__ uint32_t wave_sum[SCAN_THREADS / OMEGA];
+    const int lane = lane_id(), wave = threadIdx.x / OMEGA, b = threadIdx.x;
+    const int s0 = far_chunk_segment(f, blockIdx.x), s1 = far_chunk_segment(f, blockIdx.x + 1);
+    uint32_t all = 0;
+    if (b < f.blocks) {
+#pragma unroll 16
+        for (int s = s0; s < s1; s++) all += sums[size_t(s) * f.blocks + b];
+    }
+    all = (all + FAR_PAD - 1) / FAR_PAD * FAR_PAD;
+    uint32_t incl = all;
+#pragma unroll
+    for (int d = 1; d < OMEGA; d <<= 1) {
+        const uint32_t up = __shfl_up(incl, d, OMEGA);
+        if (lane >= d) incl += up;
+    }
+    if (lane == OMEGA - 1) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int w = 0; w < wave; w++) before += wave_sum[w];
+    uint32_t at = before + incl - all;
+    uint32_t* const my_range = range + size_t(blockIdx.x) * (f.blocks + 1);
+    if (b < f.blocks) my_range[b] = at;
+    if (b == f.blocks - 1) my_range[f.blocks] = totals[blockIdx.x] = at + all;
+    if (b < f.blocks) {
+#pragma unroll 16
+        for (int s = s0; s < s1; s++) {
+            const uint32_t v = sums[size_t(s) * f.blocks + b];
+            sums[size_t(s) * f.blocks + b] = at;
+            at += v;
+        }
+    }
+}
+
+// Where in its chunk's list each workgroup's share of a block begins
+__global__ void __launch_bounds__(FAR_THREADS)
+k_far_starts(const FarShape f, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ sums, uint32_t* __restrict__ starts) {
+    const int g0 = blockIdx.x * FAR_SEGMENT, g1 = g0 + FAR_SEGMENT < f.groups ? g0 + FAR_SEGMENT : f.groups;
+    for (int b = threadIdx.x; b < f.blocks; b += FAR_THREADS) {
+        uint32_t at = sums[size_t(blockIdx.x) * f.blocks + b];
+#pragma unroll 16
+        for (int g = g0; g < g1; g++) {
+            starts[size_t(g) * f.blocks + b] = at;
+            at += counts[size_t(g) * f.blocks + b];
+        }
+    }
+}
+
+template <int SIGMA, typename VT>
+__global__ void __launch_bounds__(FAR_THREADS)
+k_far_place(const FarShape f, const uint32_t* __restrict__ tile_ptr, const int32_t* __restrict__ col_idx, const uint16_t* __restrict__ counts,
+            const uint32_t* __restrict__ starts, const uint32_t* __restrict__ range, const uint32_t* __restrict__ base, uint32_t* __restrict__ src,
+            uint16_t* __restrict__ place, uint16_t* __restrict__ cols) {
+    __shared__ uint32_t next[FAR_MAX_BLOCKS], from[FAR_MAX_BLOCKS], entry[FAR_ENTRIES], wave_sum[FAR_THREADS / OMEGA];
+    __shared__ uint16_t block_of[FAR_ENTRIES];
+    constexpr int SHIFT = far_block_shift<VT>(), EACH = FAR_MAX_BLOCKS / FAR_THREADS;
+    static_assert(FAR_PLACE_BITS + SHIFT <= 32 && (1 << FAR_PLACE_BITS) == FAR_ENTRIES, "place and column in a word");
+    const int group = int(xcd_order(blockIdx.x, uint32_t(f.groups), 0)), segment = group / FAR_SEGMENT;
+    const int lane = lane_id(), wave = threadIdx.x / OMEGA;
+    int chunk = 0;
+    size_t first = 0;                                     // of the chunk's columns
+    while (far_chunk_segment(f, chunk + 1) <= segment) first += range[size_t(chunk++) * (f.blocks + 1) + f.blocks];
+    uint32_t n[EACH], at[EACH], s = 0;
+#pragma unroll
+    for (int u = 0; u < EACH; u++) {
+        const int b = threadIdx.x * EACH + u;
+        n[u] = at[u] = 0;
+        if (b < f.blocks) {
+            at[u] = starts[size_t(group) * f.blocks + b];
+            n[u] = counts[size_t(group) * f.blocks + b];
+        }
+        s += n[u];
+    }
+    uint32_t incl = s;
+#pragma unroll
+    for (int d = 1; d < OMEGA; d <<= 1) {
+        const uint32_t up = __shfl_up(incl, d, OMEGA);
+        if (lane >= d) incl += up;
+    }
+    if (lane == OMEGA - 1) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - s;
+    for (int w = 0; w < wave; w++) before += wave_sum[w];
+#pragma unroll
+    for (int u = 0; u < EACH; u++) {
+        const int b = threadIdx.x * EACH + u;
+        next[b] = before;
+        from[b] = at[u] - before;                         // of the chunk's list, less the place in the group's
+        before += n[u];
+    }
+    __syncthreads();
+    far_each<SIGMA, VT>(f, group, tile_ptr, col_idx, [&](int32_t c, int p) {
+        const int b = c >> SHIFT;
+        const uint32_t k = atomicAdd(&next[b], 1u);
+        entry[k] = uint32_t(p) | (uint32_t(c) & ((1u << SHIFT) - 1)) << FAR_PLACE_BITS;
+        block_of[k] = uint16_t(b);
+    });
+    __syncthreads();
+    const uint32_t my = base[group], count = base[group + 1] - my;
+    for (uint32_t k = threadIdx.x; k < count; k += FAR_THREADS) {
+        const uint32_t e = entry[k], to = from[block_of[k]] + k;
+        src[my + k] = to;
+        place[my + k] = uint16_t(e & (FAR_ENTRIES - 1));
+        cols[first + to] = uint16_t(e >> FAR_PLACE_BITS);
+    }
+}
+
+constexpr int FAR_GATHER_THREADS = 1024, FAR_GATHER_AHEAD = 8;
+template <typename VT>
+__global__ void __launch_bounds__(FAR_GATHER_THREADS)
+k_far_gather(int n, int pieces, const uint32_t* __restrict__ range, const uint16_t* __restrict__ cols, const VT* __restrict__ x, VT* __restrict__ values) {
+    constexpr int SHIFT = far_block_shift<VT>(), WAVES = FAR_GATHER_THREADS / OMEGA, STEP = FAR_GATHER_THREADS * 2;
+    constexpr uint32_t COLS = 1u << SHIFT;
+    typedef VT pair_t __attribute__((ext_vector_type(2)));
+    __shared__ __align__(16) char xs[FAR_BLOCK_BYTES];
+    const int block = blockIdx.x / pieces, piece = blockIdx.x % pieces;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
+    const uint32_t lo = range[block], hi = range[block + 1];
+    const uint32_t share = ((hi - lo) / uint32_t(pieces) + FAR_PAD) / FAR_PAD * FAR_PAD;
+    const uint32_t begin = lo + share * uint32_t(piece), end = begin + share < hi ? begin + share : hi;
+    if (begin >= end) return;
+    const auto list = tile_buffer(cols + begin, int((end - begin) * 2));
+    uint32_t c[FAR_GATHER_AHEAD];
+    const auto ask = [&](uint32_t k0) {
+#pragma unroll
+        for (int u = 0; u < FAR_GATHER_AHEAD; u++) c[u] = stream_from<uint32_t, false>(list, int((k0 + uint32_t(u * STEP) + threadIdx.x * 2) * 2));
+    };
+    ask(0);
+    const auto xbuf = tile_buffer(x, n * int(sizeof(VT)));
+    const bool wide16 = (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+    for (int at = wave * 1024; at < FAR_BLOCK_BYTES; at += WAVES * 1024) {
+        const int64_t off = int64_t(block) * FAR_BLOCK_BYTES + at;
+        if (wide16 && off + 1024 <= int64_t(n) * int64_t(sizeof(VT))) {
+            to_lds_16(xbuf, xs + at, int(off) + lane * 16);
+        } else if (off < int64_t(n) * int64_t(sizeof(VT))) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) to_lds_4(xbuf, xs + at + q * 256, int(off) + q * 256 + lane * 4);
+        }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    for (uint32_t k0 = 0;;) {
+        pair_t v[FAR_GATHER_AHEAD];
+#pragma unroll
+        for (int u = 0; u < FAR_GATHER_AHEAD; u++) {      // (the padding behind a block's columns holds anything)
+            v[u].x = reinterpret_cast<const VT*>(xs)[c[u] & (COLS - 1)];
+            v[u].y = reinterpret_cast<const VT*>(xs)[c[u] >> 16 & (COLS - 1)];
+        }
+        const uint32_t k1 = k0 + FAR_GATHER_AHEAD * STEP;
+        const bool more = begin + k1 < end;
+        if (more) ask(k1);
+#pragma unroll
+        for (int u = 0; u < FAR_GATHER_AHEAD; u++) {
+            const uint32_t k = begin + k0 + uint32_t(u * STEP) + threadIdx.x * 2;
+            if (k < end) *reinterpret_cast<pair_t*>(values + k) = v[u];
+        }
+        if (!more) break;
+        k0 = k1;
+    }
+}
+
+// Of a sample of entries (two neighbours in each column of FAR_SAMPLE_TILES tiles), how many lie far outside
+// their window (answer[0]), and on how many lines of x (answer[1]).  One workgroup; only for matrices whose
+// first sample (sample_window) speaks for it.
+constexpr int FAR_SAMPLE_TILES = 128;
+template <int SIGMA, typename VT>
+__global__ void __launch_bounds__(SCAN_THREADS)
+k_far_sample(const FarShape f, const uint32_t* __restrict__ tile_ptr, const int32_t* __restrict__ col_idx, uint32_t* __restrict__ answer) {
+    constexpr uint32_t ROWMASK = Index<int32_t>::ROWMASK;
+    constexpr int T = OMEGA * SIGMA, TILES = FAR_ENTRIES / T, PER_WAVE = FAR_SAMPLE_TILES / (SCAN_THREADS / OMEGA);
+    constexpr int WORDS = FAR_BLOCK_BYTES / 128 * FAR_MAX_BLOCKS / 32;                // a bit per line of x
+    __shared__ uint32_t seen[WORDS];
+    __shared__ uint32_t far, lines;
+    const int lane = lane_id(), wave = threadIdx.x / OMEGA;
+    int32_t c[PER_WAVE][2];
+    uint32_t window[PER_WAVE];
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++) {
+        const int q = wave * PER_WAVE + u, tile = int(int64_t(f.pc) * q / FAR_SAMPLE_TILES), tile0 = tile / TILES * TILES;
+        const int j = (q + lane / 16 * SIGMA / 4) % (SIGMA - 1);
+        const int32_t* const pair = col_idx + size_t(tile) * T + j * OMEGA + lane;
+        c[u][0] = pair[0];
+        c[u][1] = pair[OMEGA];
+        window[u] = uint32_t(window_first(tile_ptr[tile0] & ROWMASK, tile_ptr[tile0 + TILES < f.pc ? tile0 + TILES : f.pc] & ROWMASK,
+                                          f.slope, f.n * int(sizeof(VT)), int(sizeof(VT))));
+    }
+    for (int w = threadIdx.x; w < WORDS; w += SCAN_THREADS) seen[w] = 0;
+    if (threadIdx.x == 0) far = lines = 0;
+    __syncthreads();
+    uint32_t my_far = 0, my_lines = 0;
+#pragma unroll
+    for (int u = 0; u < PER_WAVE; u++) {
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            const uint32_t b = uint32_t(c[u][e]) * uint32_t(sizeof(VT));
+            if (b - window[u] + FAR_REACH_BYTES >= uint32_t(2 * FAR_REACH_BYTES)) {
+                const uint32_t bit = 1u << (b / 128 % 32);
+                if (!(atomicOr(&seen[b / 4096], bit) & bit)) my_lines++;
+                my_far++;
+            }
+        }
+    }
+    if (my_far) atomicAdd(&far, my_far);
+    if (my_lines) atomicAdd(&lines, my_lines);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        answer[0] = far;
+        answer[1] = lines;
+    }
+}
+
 struct RowSpan { int first, groups; };     // the workgroups a row touches
 
 // part_bytes: of x, a multiple of 1024, at most STAGE_BYTES; parts * part_bytes covers x.
@@ -2152,14 +2481,26 @@ struct RowSpan { int first, groups; };     // the workgroups a row touches
 // 54.2; 8 of three 48.9, but 23.2 -> 28.2 at 200 000 rows.
 // Rows that cross workgroups: as above where the handle's slot has what that wants (meet),
 // through the auxiliary array and k_spmv_fixup otherwise, one sum per workgroup.
-template <int SIGMA, int WAVES, int K, bool WINDOW, typename VT>
-__global__ void __launch_bounds__(WAVES * OMEGA, WINDOW ? WAVES * (LDS_BYTES / WINDOW_BYTES) / 4 : 1)
+//
+// FORM_FAR: the window form, with the entries outside the window from the buffer of k_far_gather.
+constexpr int FORM_PARTS = 0, FORM_WINDOW = 1, FORM_FAR = 2;
+struct FarEntries {                // of FORM_FAR
+    int first, count;              // the launch's workgroups
+    const uint32_t* base;          // where a workgroup's share of the lists begins
+    const uint32_t* src;           // an entry's place in the buffer
+    const uint16_t* place;         // and among the workgroup's entries
+    const void* values;            // the buffer
+    int value_bytes;
+};
+template <int SIGMA, int WAVES, int K, int FORM, typename VT>
+__global__ void __launch_bounds__(WAVES * OMEGA, FORM != FORM_PARTS ? WAVES * (LDS_BYTES / WINDOW_BYTES) / 4 : 1)
 k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail, uint32_t zero_rows, int part_bytes, int parts,
               const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ tile_ptr,
               const uint32_t* __restrict__ tile_desc, const int32_t* __restrict__ eop, const int32_t* __restrict__ eo,
               const int32_t* __restrict__ col_idx, const VT* __restrict__ val, const VT* __restrict__ x, VT* __restrict__ y,
               VT* __restrict__ carry, uint64_t* __restrict__ meet, uint32_t* __restrict__ arrived,
-              const uint32_t* __restrict__ tile_head, float slope) {
+              const uint32_t* __restrict__ tile_head, float slope, const FarEntries far) {
+    constexpr bool FAR = FORM == FORM_FAR, WINDOW = FORM != FORM_PARTS;
     constexpr uint32_t ROWMASK = Index<int32_t>::ROWMASK, DIRTY = Index<int32_t>::DIRTY;
     constexpr int T = OMEGA * SIGMA, THREADS = WAVES * OMEGA, TILES = WAVES * K;
     constexpr int YSH = SIGMA + SBITS;
@@ -2185,7 +2526,8 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
                                uint2{uint32_t(s.first), uint32_t(s.groups)}, nullptr, nullptr);
         return;
     }
-    const int group = int(WINDOW ? xcd_order(blockIdx.x - has_tail, groups, 0) : blockIdx.x - has_tail);
+    const int group = FAR ? far.first + int(xcd_order(blockIdx.x - has_tail, uint32_t(far.count), 0))
+                          : int(WINDOW ? xcd_order(blockIdx.x - has_tail, groups, 0) : blockIdx.x - has_tail);
     const int tile0 = group * TILES, mine = tile0 + wave * K;
     int window = 0;
     if constexpr (WINDOW)
@@ -2206,6 +2548,40 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         }
     };
     if constexpr (!WINDOW) stage(0, xs0);
+    // Entries whose x comes through the buffer: where from and where to, the first FAR_AHEAD of each thread
+    uint32_t far_count = 0;
+    __amdgpu_buffer_rsrc_t far_src, far_place, far_values;
+    uint32_t fs[FAR_AHEAD], fp[FAR_AHEAD];
+    VT fv[FAR_AHEAD];
+    const auto far_lists = [&](uint32_t k0) {
+#pragma unroll
+        for (int u = 0; u < FAR_AHEAD; u++) {
+            const uint32_t k = k0 + uint32_t(u * THREADS) + threadIdx.x;
+            fs[u] = stream_from<uint32_t, false>(far_src, int(k * 4));         // (reads as 0 behind the end)
+            fp[u] = uint32_t(stream_from<uint16_t, false>(far_place, int(k * 2)));
+        }
+    };
+    const auto far_fetch = [&](uint32_t k0) {
+#pragma unroll
+        for (int u = 0; u < FAR_AHEAD; u++) {
+            const uint32_t k = k0 + uint32_t(u * THREADS) + threadIdx.x;
+            fv[u] = stream_from<VT, true>(far_values, k < far_count ? int(fs[u] * uint32_t(sizeof(VT))) : INT32_MAX - 15);
+        }
+    };
+    const auto far_put = [&](uint32_t k0) {
+#pragma unroll
+        for (int u = 0; u < FAR_AHEAD; u++) {
+            const uint32_t k = k0 + uint32_t(u * THREADS) + threadIdx.x;
+            if (k < far_count) *reinterpret_cast<VT*>(xs0 + fp[u] * uint32_t(sizeof(VT))) = fv[u];
+        }
+    };
+    if constexpr (FAR) {
+        const uint32_t at = far.base[group];
+        far_count = far.base[group + 1] - at;
+        far_src = tile_buffer(far.src + at, int(far_count * 4));
+        far_place = tile_buffer(far.place + at, int(far_count * 2));
+        far_values = tile_buffer(static_cast<const VT*>(far.values), far.value_bytes);
+    }
     asm volatile("" ::: "memory");
     int32_t c[K][SIGMA];
     uint32_t dw[K], tp[K], head[K + 1];
@@ -2218,6 +2594,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         for (int j = 0; j < SIGMA; j++) c[k][j] = stream_from<int32_t, false>(cols, (j * OMEGA + lane) * 4) * int(sizeof(VT));
         dw[k] = stream_from<uint32_t, false>(descs, lane * 4);
     }
+    if constexpr (FAR) far_lists(0);
 #pragma unroll
     for (int k = 0; k <= K; k++) {
         const int tile = mine + k < pc ? mine + k : pc;
@@ -2229,8 +2606,10 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
     if (wave == 0) {
         row_in = tile_ptr[tile0] & ROWMASK;
         row_out = tile_ptr[tile0 + TILES < pc ? tile0 + TILES : pc] & ROWMASK;
-        if (row_in < uint32_t(m)) si = span_of(row_in);
-        if (row_out < uint32_t(m)) so = span_of(row_out);
+        if (!WINDOW || meet) {
+            if (row_in < uint32_t(m)) si = span_of(row_in);
+            if (row_out < uint32_t(m)) so = span_of(row_out);
+        }
     }
     asm volatile("" ::: "memory");
     VT v[K][SIGMA];
@@ -2244,6 +2623,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
     if constexpr (WINDOW) {
 #pragma unroll
         for (int k = 1; k < K; k++) load_v(k);
+        if constexpr (FAR) far_fetch(0);
         asm volatile("" ::: "memory");
         stage(0, xs0);
         asm volatile("" ::: "memory");
@@ -2281,12 +2661,14 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
     };
     if constexpr (WINDOW) {
         // what lies outside the window comes from memory, on its way while the window is waited for
+        if constexpr (!FAR) {
 #pragma unroll
-        for (int k = 0; k < K; k++)
+            for (int k = 0; k < K; k++)
 #pragma unroll
-            for (int j = 0; j < SIGMA; j++)
-                if (uint32_t(c[k][j]) - uint32_t(window) >= uint32_t(part_bytes))
-                    xv[k][j] = *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(x) + uint32_t(c[k][j]));
+                for (int j = 0; j < SIGMA; j++)
+                    if (uint32_t(c[k][j]) - uint32_t(window) >= uint32_t(part_bytes))
+                        xv[k][j] = *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(x) + uint32_t(c[k][j]));
+        }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
         asm volatile("" ::: "memory");
@@ -2299,6 +2681,22 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
                 const uint32_t at = uint32_t(c[k][j]) - uint32_t(window);
                 if (at < uint32_t(part_bytes)) xv[k][j] = *reinterpret_cast<const VT*>(xs0 + at);
             }
+        if constexpr (FAR) {
+            __syncthreads();           // the other entries' values go where the window was, in the tiles' order
+            far_put(0);
+            for (uint32_t k0 = FAR_AHEAD * THREADS; k0 < far_count; k0 += FAR_AHEAD * THREADS) {
+                far_lists(k0);
+                far_fetch(k0);
+                far_put(k0);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; k++)
+#pragma unroll
+                for (int j = 0; j < SIGMA; j++)
+                    if (uint32_t(c[k][j]) - uint32_t(window) >= uint32_t(part_bytes))
+                        xv[k][j] = *reinterpret_cast<const VT*>(xs0 + uint32_t(((wave * K + k) * T + j * OMEGA + lane) * int(sizeof(VT))));
+        }
     } else {
         for (int part = 0; part < parts; part += 2) {
             take(part, xs0, xs1);
@@ -2628,8 +3026,8 @@ hipError_t launch_staged(const Geom& g, int m, int n, int nnz, const int32_t* ro
     constexpr int WAVES = staged_waves(SIGMA, sizeof(VT), K);
     const uint32_t groups = uint32_t((g.pc + WAVES * K - 1) / (WAVES * K)), has_tail = g.p > g.pc ? 1u : 0u;
     const int bytes = n * int(sizeof(VT)), parts = staged_parts(n, sizeof(VT)), part_bytes = ((bytes + parts - 1) / parts + 1023) / 1024 * 1024;
-    hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, false, VT>), dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
-                       part_bytes, parts, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, 0.0f);
+    hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, FORM_PARTS, VT>), dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
+                       part_bytes, parts, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, 0.0f, FarEntries{});
     return hipGetLastError();
 }
 
@@ -2671,9 +3069,63 @@ hipError_t launch_window(const Geom& g, int m, int n, int nnz, const int32_t* ro
                          uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
     constexpr int WAVES = WINDOW_WAVES, K = window_tiles(SIGMA), TILES = WAVES * K;
     const uint32_t groups = uint32_t((g.pc + TILES - 1) / TILES), has_tail = g.p > g.pc ? 1u : 0u;
-    hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, true, VT>), dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
-                       WINDOW_BYTES, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, float(n) / float(m));
+    hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, FORM_WINDOW, VT>), dim3(groups + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc, groups, has_tail, zero_rows ? 1u : 0u,
+                       WINDOW_BYTES, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet, arrived, tile_head, float(n) / float(m), FarEntries{});
     return hipGetLastError();
+}
+
+// What a handle keeps for k_far_gather and FORM_FAR
+struct FarPlan {
+    void* tables;                          // hipMalloc'ed: base, range, and what the conversion counted
+    void* lists;                           // hipMalloc'ed: src, place, cols, CARRY_SLOTS buffers; NULL: no plan
+    FarShape shape;
+    const uint32_t* base;
+    const uint32_t* range;                 // per chunk: where the blocks' lists begin
+    const uint32_t* src;
+    const uint16_t* place;
+    const uint16_t* cols;                  // in its block, of the buffer's entries
+    char* values;
+    size_t values_bytes;                   // of one buffer
+    int pieces;                            // workgroups per block
+    uint32_t first[FAR_MAX_CHUNKS + 1];    // of a chunk, in cols
+};
+// In how many products the plan has to come back, in what it costs a conversion and csr5_free (us per million
+// entries, and in any case: allocation and release, and what waits for them) and gives a product (us per million far entries; nothing
+// where the L2s hold x).  Conversion and free longer by, product before -> after: mixed in double precision
+// 25.6 M entries 634, 177 -> 134 (not taken); 34 M 639, 263 -> 173; 51 M 780, 422 -> 261; 136 M 1458, 1211 -> 710; single precision 34 M 658,
+// 176 -> 126 (not taken); 68 M 881, 469 -> 236; random columns out of 1 M, 15 M entries 422, 160 -> 114 (not taken), out of 4 M, 40 M
+// entries 575, 690 -> 326.
+constexpr double FAR_PAYBACK = 8, FAR_COST = 400, FAR_COST_PER_M = 8, FAR_GAIN_PER_M = 8.5, FAR_L2_BYTES = 4 << 20;
+// Lines, of 100 entries far away (random columns 95-99, power-law ones 23-32; columns that all together are on fewer lines are in
+// the caches), and tiles that spread them, of 100 (random 85-100; power-law columns and rows as long as several tiles 17).
+constexpr uint32_t FAR_LINES_PERCENT = 85, FAR_SPREAD_PERCENT = 75;
+// Near ones, for the window to be loaded: 0.3 us per million entries for it, 5.6 for a million more through the buffer.
+constexpr uint32_t FAR_WINDOW_PERCENT = 6;
+inline bool far_pays(int64_t nnz, int64_t x_bytes, double far_share) {
+    return FAR_COST + FAR_COST_PER_M * 1e-6 * double(nnz) <=
+           FAR_PAYBACK * FAR_GAIN_PER_M * 1e-6 * double(nnz) * far_share * (1 - FAR_L2_BYTES / double(x_bytes));
+}
+
+template <int SIGMA, typename VT>
+hipError_t launch_far(const FarPlan& plan, int turn, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
+                      const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
+                      uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
+    constexpr int WAVES = WINDOW_WAVES, K = window_tiles(SIGMA);
+    static_assert(WAVES * K * SIGMA * OMEGA == FAR_ENTRIES && WAVES * OMEGA == FAR_THREADS, "a workgroup's entries");
+    const FarShape& f = plan.shape;
+    VT* const values = reinterpret_cast<VT*>(plan.values + size_t(turn) * plan.values_bytes);
+    for (int c = 0; c < f.chunks; c++) {
+        hipLaunchKernelGGL(k_far_gather<VT>, dim3(uint32_t(f.blocks * plan.pieces)), dim3(FAR_GATHER_THREADS), 0, s, n, plan.pieces,
+                           plan.range + size_t(c) * (f.blocks + 1), plan.cols + plan.first[c], x, values);
+        const int first = far_chunk_segment(f, c) * FAR_SEGMENT, last = c + 1 < f.chunks ? far_chunk_segment(f, c + 1) * FAR_SEGMENT : f.groups;
+        const uint32_t has_tail = c == 0 && g.p > g.pc ? 1u : 0u;
+        hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, FORM_FAR, VT>), dim3(uint32_t(last - first) + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc,
+                           uint32_t(f.groups), has_tail, zero_rows ? 1u : 0u, f.window_bytes, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet,
+                           arrived, tile_head, f.slope, FarEntries{first, last - first, plan.base, plan.src, plan.place, values, int(plan.values_bytes)});
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int SIGMA, bool BACK, typename VT>
@@ -2801,6 +3253,7 @@ struct csr5_handle_s {
     uint32_t order_second, order_len;
     int staged;            // tiles per wavefront of k_spmv_staged; 0: not for this matrix
     bool window;           // the window form of k_spmv_staged is for this matrix
+    FarPlan far;           // lists != NULL: FORM_FAR is for this matrix
     void* owned;           // hipMalloc'ed block, or NULL when a workspace was given
     hipStream_t conv_stream;
     int device;            // HIP device that was current at conversion
@@ -2974,6 +3427,102 @@ static bool keep_product(csr5_handle_t h, uint32_t call, uint64_t before, hipStr
 }
 static bool keep_back(int64_t nnz, size_t value_bytes) { return entry_bytes(nnz, value_bytes) > KEEP_MIN_BYTES && entry_bytes(nnz, value_bytes) <= KEEP_BACK_MAX_BYTES; }
 
+// The plan of FORM_FAR.  Nothing is left where it does not pay or there is no memory for it.
+static void far_release(csr5_handle_t h) {
+    if (h->far.tables) (void)hipFree(h->far.tables);
+    if (h->far.lists) (void)hipFree(h->far.lists);
+    h->far.tables = h->far.lists = nullptr;
+}
+static void* far_alloc(size_t bytes) {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+template <typename T>
+static bool far_read(T* to, const T* from, int count, hipStream_t s) {
+    return hipGetLastError() == hipSuccess && hipMemcpyAsync(to, from, count * sizeof(T), hipMemcpyDeviceToHost, s) == hipSuccess &&
+           hipStreamSynchronize(s) == hipSuccess;
+}
+// Whether the plan is made; what was launched for it may still run if it is not.
+template <int SIGMA, typename VT>
+static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double far_share) {
+    FarPlan& plan = h->far;
+    FarShape& f = plan.shape;
+    const int64_t x_bytes = int64_t(h->n) * int64_t(sizeof(VT)), want_chunks = int64_t(double(h->nnz) * far_share * sizeof(VT)) / FAR_BUFFER_BYTES + 1;
+    constexpr int tiles = FAR_ENTRIES / (SIGMA * OMEGA);
+    f.pc = h->g.pc;
+    f.n = h->n;
+    f.groups = (h->g.pc + tiles - 1) / tiles;
+    f.blocks = int((x_bytes + FAR_BLOCK_BYTES - 1) / FAR_BLOCK_BYTES);
+    f.segments = (f.groups + FAR_SEGMENT - 1) / FAR_SEGMENT;
+    f.chunks = int(want_chunks < f.segments ? want_chunks : f.segments);
+    if (f.chunks > FAR_MAX_CHUNKS) f.chunks = FAR_MAX_CHUNKS;
+    f.window_bytes = window_bytes;
+    f.slope = float(h->n) / float(h->m);
+    const uint32_t* const tile_ptr = static_cast<const uint32_t*>(h->tile_ptr);
+    uint32_t got[2];
+    hipLaunchKernelGGL((k_far_sample<SIGMA, VT>), dim3(1), dim3(SCAN_THREADS), 0, s, f, tile_ptr, h->col_idx, h->status + FAR_ANSWER_AT);
+    if (!far_read(got, h->status + FAR_ANSWER_AT, 2, s) || got[1] * 100 < got[0] * FAR_LINES_PERCENT) return false;
+    const size_t counts_bytes = align256(size_t(f.groups) * f.blocks * 2), starts_bytes = align256(size_t(f.groups) * f.blocks * 4), sums_bytes = align256(size_t(f.segments) * f.blocks * 4);
+    const size_t range_bytes = align256(size_t(f.chunks) * (f.blocks + 1) * 4), base_bytes = align256((size_t(f.groups) + 1) * 4);
+    plan.tables = far_alloc(counts_bytes + starts_bytes + sums_bytes + range_bytes + base_bytes + 256);
+    if (!plan.tables) return false;
+    char* at = static_cast<char*>(plan.tables);
+    uint32_t* const totals = reinterpret_cast<uint32_t*>(at);
+    uint32_t* const base = reinterpret_cast<uint32_t*>(at += 256);
+    uint32_t* const range = reinterpret_cast<uint32_t*>(at += base_bytes);
+    uint32_t* const sums = reinterpret_cast<uint32_t*>(at += range_bytes);
+    uint32_t* const starts = reinterpret_cast<uint32_t*>(at += sums_bytes);
+    uint16_t* const counts = reinterpret_cast<uint16_t*>(at += starts_bytes);
+    hipLaunchKernelGGL((k_far_count<SIGMA, VT>), dim3(uint32_t(f.groups)), dim3(FAR_THREADS), 0, s, f, tile_ptr, h->col_idx, counts, base);
+    hipLaunchKernelGGL(k_far_segments, dim3(uint32_t(f.segments)), dim3(FAR_THREADS), 0, s, f, counts, sums);
+    hipLaunchKernelGGL(k_far_bases, dim3(uint32_t(f.chunks + 1)), dim3(SCAN_THREADS), 0, s, f, sums, range, base, totals);
+    hipLaunchKernelGGL(k_far_starts, dim3(uint32_t(f.segments)), dim3(FAR_THREADS), 0, s, f, counts, sums, starts);
+    uint32_t total[FAR_MAX_CHUNKS + 1], most = 0;
+    static_assert(sizeof(total) <= 256, "totals");
+    if (!far_read(total, totals, f.chunks + 1, s)) return false;
+    plan.first[0] = 0;
+    for (int c = 0; c < f.chunks; c++) {
+        plan.first[c + 1] = plan.first[c] + total[c];
+        if (total[c] > most) most = total[c];
+    }
+    const uint32_t all = total[f.chunks];
+    const size_t src_bytes = align256(size_t(all) * 4), place_bytes = align256(size_t(all) * 2), cols_bytes = align256(size_t(plan.first[f.chunks]) * 2);
+    plan.values_bytes = align256(size_t(most) * sizeof(VT));
+    const size_t bytes = src_bytes + place_bytes + cols_bytes + CARRY_SLOTS * plan.values_bytes;
+    size_t free_bytes = 0, device_bytes = 0;          // not where it would take what the program may want itself
+    if (plan.values_bytes > size_t(1) << 30 || hipMemGetInfo(&free_bytes, &device_bytes) != hipSuccess || bytes > free_bytes / 8) return false;
+    plan.lists = far_alloc(bytes);
+    if (!plan.lists) return false;
+    at = static_cast<char*>(plan.lists);
+    uint32_t* const src = reinterpret_cast<uint32_t*>(at);
+    uint16_t* const place = reinterpret_cast<uint16_t*>(at += src_bytes);
+    uint16_t* const cols = reinterpret_cast<uint16_t*>(at += place_bytes);
+    plan.values = at + cols_bytes;
+    plan.base = base;
+    plan.range = range;
+    plan.src = src;
+    plan.place = place;
+    plan.cols = cols;
+    plan.pieces = STAGE_CUS / f.blocks > 1 ? STAGE_CUS / f.blocks : 1;
+    hipLaunchKernelGGL((k_far_place<SIGMA, VT>), dim3(uint32_t(f.groups)), dim3(FAR_THREADS), 0, s, f, tile_ptr, h->col_idx, counts, starts, range, base, src, place, cols);
+    return hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
+}
+// near, far, spread: of `samples` entries, see WindowJob
+template <typename VT>
+static void far_plan(csr5_handle_t h, hipStream_t s, uint32_t samples, uint32_t near, uint32_t far, uint32_t spread) {
+    const int64_t x_bytes = int64_t(h->n) * int64_t(sizeof(VT));
+    if (x_bytes > int64_t(FAR_BLOCK_BYTES) * FAR_MAX_BLOCKS || spread * 100 < samples / (2 * OMEGA) * FAR_SPREAD_PERCENT ||
+        !far_pays(h->nnz, x_bytes, double(far) / samples)) return;
+    const int window = near * 100 >= samples * FAR_WINDOW_PERCENT ? WINDOW_BYTES : 0;
+    const double share = window ? double(samples - near) / samples : 1.0;
+    if (h->g.sigma == RULE_R ? far_make<RULE_R, VT>(h, s, window, share) : far_make<RULE_SIGMA_SMALL, VT>(h, s, window, share)) return;
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(s);         // before the memory goes
+    far_release(h);
+}
+
 template <typename VT, typename IT>
 static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t* col_idx,
                         VT* val, int32_t sigma, void* workspace, size_t workspace_bytes,
@@ -3035,6 +3584,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     h->status = reinterpret_cast<uint32_t*>(basep + L.off_status);
     h->staged = 0;
     h->window = false;
+    h->far.tables = h->far.lists = nullptr;
     h->order = nullptr;
     h->order_second = h->order_len = 0;
     h->conv_stream = s;
@@ -3141,8 +3691,8 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK)) {
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
-        uint32_t got[WINDOW_ANSWER_AT + 1] = {};      // the status word, behind it the plan of the tile order and the answers on the columns
-        int rc = read_status(h, got, window.answer ? WINDOW_ANSWER_AT + 1 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
+        uint32_t got[WINDOW_ANSWER_AT + 2] = {};      // the status word, behind it the plan of the tile order and the answers on the columns
+        int rc = read_status(h, got, window.answer ? WINDOW_ANSWER_AT + 2 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];
@@ -3154,6 +3704,10 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
             !(h->window && window_rather(g, n, int64_t(nnz), sizeof(VT), staged, samples - near, samples))) {
             h->staged = staged;
             h->window = false;
+        }
+        if constexpr (!wide) {
+            if (rc == CSR5_OK && !(got[0] & BAD_BITS) && window.answer && h->owned && !h->order && !h->staged)
+                far_plan<VT>(h, s, samples, near, got[WINDOW_ANSWER_AT + 1] >> 16, got[WINDOW_ANSWER_AT + 1] & 0xffffu);
         }
         if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);
@@ -3263,9 +3817,16 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     // a window of x in LDS: one launch where the handle's slot has what that wants, otherwise two
     bool window = false, window_one = false;
     if constexpr (std::is_same<IT, int32_t>::value) {
-        window = h->window;
+        const bool far = h->far.lists && !carry_mem;
+        window = h->window || far;
         window_one = window && h->span && !carry_mem;
-        if (window && (which & LAUNCH_TILES)) {
+        if (far && (which & LAUNCH_TILES)) {
+#define FARRED(S) e = launch_far<S, VT>(h->far, int(turn), h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
+                                      static_cast<const VT*>(h->val), x, y, carry, window_one ? meet : nullptr, arrived, h->tile_head, zero_rows, s)
+            if (h->g.sigma == RULE_R) FARRED(RULE_R);
+            else FARRED(RULE_SIGMA_SMALL);
+#undef FARRED
+        } else if (window && (which & LAUNCH_TILES)) {
 #define WINDOWED(S) e = launch_window<S, VT>(h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
                                              static_cast<const VT*>(h->val), x, y, carry, window_one ? meet : nullptr, arrived, h->tile_head, zero_rows, s)
             if (h->g.sigma == RULE_R) WINDOWED(RULE_R);
@@ -3464,6 +4025,7 @@ int csr5_free(csr5_handle_t h) {
     if (!h) return CSR5_OK;
     int rc = CSR5_OK;
     if (h->owned && hipFree(h->owned) != hipSuccess) rc = CSR5_EHIP;
+    far_release(h);
     delete h;
     return rc;
 }
@@ -3504,10 +4066,10 @@ int csr5_get_shape(csr5_handle_t h, int32_t* m, int32_t* n) {
 
 int csr5_get_form(csr5_handle_t h, void* hip_stream, int32_t* kernel, int32_t* wave_tiles, int32_t* plain) {
     if (!h || !h->in_csr5_order) return CSR5_EINVAL;
-    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->window ? CSR5_KERNEL_WINDOW : CSR5_KERNEL_TILES);
-    if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window ? window_tiles(h->g.sigma) : 1);
+    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->far.lists ? CSR5_KERNEL_GATHERED : (h->window ? CSR5_KERNEL_WINDOW : CSR5_KERNEL_TILES));
+    if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window || h->far.lists ? window_tiles(h->g.sigma) : 1);
     if (plain)
-        *plain = !h->staged && !h->window && rule_sigma(h->g.sigma) &&
+        *plain = !h->staged && !h->window && !h->far.lists && rule_sigma(h->g.sigma) &&
                  keep_product(h, h->carry_turn.load(std::memory_order_relaxed), latest(h->device), static_cast<hipStream_t>(hip_stream));
     return CSR5_OK;
 }

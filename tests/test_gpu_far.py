@@ -1,0 +1,204 @@
+"""GPU parity of the SpMV that has the x of far entries gathered into a buffer by a kernel of its own: x at and
+around the edges of the gathered blocks, with and without a window, tall and wide matrices, empty and long rows,
+both tile heights, one and two kernels for the sums, several chunks; and which matrices are left alone.  Every
+test asks the library which kernel it is about."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1503_05032_amd import binding as B
+from paper_1503_05032_amd import workloads as wl
+
+from gpu_util import DeviceCsr, check_format, check_spmv, convert, second_kernel_ms
+
+pytestmark = pytest.mark.gpu
+
+BLOCK = 128 * 1024 // 8        # entries of x in a block
+
+
+def _far(m, n, lo, hi, near, uneven=False, seed=0):
+    """Rows of lo to hi entries, a share `near` of them within +-4000 columns of the diagonal, the others anywhere;
+    uneven: a tenth of the rows empty, one in the middle and the last one long."""
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    lens = torch.randint(lo, hi + 1, (m,), generator=g, device="cuda:0")
+    if uneven:
+        lens[torch.rand(m, generator=g, device="cuda:0") < 0.1] = 0
+        lens[m // 2], lens[-1] = 30_000, 20_000
+    rows = torch.repeat_interleave(torch.arange(m, device="cuda:0"), lens)
+    col = torch.randint(0, n, rows.shape, generator=g, device="cuda:0")
+    band = (rows * n // m + torch.randint(-4000, 4001, rows.shape, generator=g, device="cuda:0")).clamp_(0, n - 1)
+    col = torch.where(torch.rand(rows.shape, generator=g, device="cuda:0") < near, band, col)
+    col[0], col[-1] = 0, n - 1
+    col = (torch.sort(rows * n + col).values - rows * n).int()                  # (columns may repeat)
+    row_ptr = torch.zeros(m + 1, dtype=torch.int64, device="cuda:0")
+    torch.cumsum(lens, 0, out=row_ptr[1:])
+    rng = np.random.default_rng(seed)
+    return wl.Csr(m=m, n=n, row_ptr=row_ptr.int().cpu().numpy(), col_idx=col.cpu().numpy(), val=rng.uniform(-1, 1, rows.numel()),
+                  x=rng.uniform(-1, 1, n), name=f"far{m}x{n}")
+
+
+@pytest.mark.parametrize("m,n,lo,hi,near,sigma,uneven", [
+    (600_000, 200 * BLOCK, 15, 25, 0.0, 0, False),             # whole blocks, no window, height 8
+    (600_001, 200 * BLOCK + 1, 15, 25, 0.0, 0, True),
+    (400_000, 300 * BLOCK - 1, 30, 60, 0.3, 16, True),        # height 16, one kernel for the sums
+    (5_000_000, 200 * BLOCK + 17, 1, 6, 0.1, 0, True),        # tall
+    (30_001, 8_000_001, 500, 700, 0.2, 16, True),              # wide, rows longer than half a tile
+    (900_000, 250 * BLOCK + 5, 18, 26, 0.15, 8, True),        # more than 32768 tiles: a kernel more
+    (700_000, 1024 * BLOCK, 15, 25, 0.0, 0, False)])           # the largest x
+def test_parity(m, n, lo, hi, near, sigma, uneven):
+    a = _far(m, n, lo, hi, near, uneven, seed=m % 97)
+    print("far", m, n, lo, hi, near, sigma, uneven, a.nnz, flush=True)
+    d = DeviceCsr(a)
+    h = convert(d, sigma=sigma, use_workspace=False)
+    check_format(d, h, a.name)
+    info, first = B.csr5_get_info(h), None
+    assert B.csr5_get_form(h) == {"kernel": B.CSR5_KERNEL_GATHERED, "wave_tiles": 2 if info["sigma"] == 8 else 1, "plain": 0}
+    one = info["p"] <= 32768
+    assert one == (sigma != 8), info["p"]
+    whole_tiles = info["p_complete"] * 64 * info["sigma"]
+    fixed = int(np.searchsorted(a.row_ptr, whole_tiles, side="right")) - 1      # rows in the incomplete tile are added in any order
+    for call in range(6):                          # every one of the handle's buffers
+        check_spmv(d, h, (a.name, call))
+        first = d.y.clone() if first is None else first
+        if one:
+            assert torch.equal(d.y[:fixed], first[:fixed]), (a.name, call)
+    assert (second_kernel_ms(h, d.x, d.y) < 1e-3) == one, a.name
+    _, s = oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val, a.x)
+    whole = torch.empty(n + 1, dtype=torch.float64, device="cuda:0")            # x at an odd address
+    whole[1:] = d.x
+    d.y.fill_(float("nan"))
+    B.csr5_spmv_ex(h, whole[1:], d.y)
+    torch.cuda.synchronize()
+    assert np.all(np.abs((d.y - first).cpu().numpy()) <= 2e-12 * s + 1e-300)
+    d.y.fill_(float("nan"))                        # the entry point that uses no buffer
+    B.csr5_spmv_static(h, d.x, d.y)
+    torch.cuda.synchronize()
+    assert np.all(np.abs((d.y - first).cpu().numpy()) <= 2e-12 * s + 1e-300)
+    B.csr5_to_csr(h)
+    torch.cuda.synchronize()
+    assert np.array_equal(d.col_idx.cpu().numpy(), a.col_idx) and np.array_equal(d.val.cpu().numpy(), a.val)
+    B.csr5_free(h)
+
+
+@pytest.mark.parametrize("m,n,lo,hi,near,sigma,single", [
+    (700_000, 2 * 260 * BLOCK + 1, 15, 25, 0.0, 0, True), (700_000, 2 * 260 * BLOCK - 1, 15, 25, 0.2, 16, True),
+    (3_000_000, 4_000_001, 10, 20, 0.1, 0, False),             # 37 M entries through the buffer, in two chunks
+    (3_000_000, 6_000_001, 20, 30, 0.05, 0, True)])             # 68 M, two chunks
+def test_against_sums_in_double_precision(m, n, lo, hi, near, sigma, single):
+    a = _far(m, n, lo, hi, near, True, seed=5)
+    d = DeviceCsr(a)
+    val, x = (d.val.float(), d.x.float()) if single else (d.val, d.x)
+    products = val.double() * x.double()[d.col_idx.long()]
+    want = torch.segment_reduce(products, "sum", offsets=d.row_ptr.long(), initial=0)
+    scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)
+    del products
+    y = torch.empty(a.m, dtype=val.dtype, device="cuda:0")
+    h = (B.csr5s_convert_ex if single else B.csr5_convert_ex)(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, val, sigma=sigma)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED, B.csr5_get_form(h)
+    # single precision: at most 64 additions per term, 64 * 2^-24 = 3.8e-6; double: the bar of gpu_util
+    rel, tiny = (1e-5, 1e-30) if single else (1e-12, 1e-300)
+    for call in range(5):
+        y.fill_(float("nan"))
+        (B.csr5s_spmv_ex if single else B.csr5_spmv_ex)(h, x, y)
+        assert bool(((y.double() - want).abs() <= rel * scale + tiny).all()), call
+    B.csr5_free(h)
+
+
+def test_products_in_flight_on_four_streams_and_other_vectors():
+    a = _far(600_001, 200 * BLOCK + 1, 25, 35, 0.2, True, seed=3)
+    d = DeviceCsr(a)
+    h = convert(d, use_workspace=False)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    xs = [d.x, -d.x, d.x.flip(0).contiguous(), d.x * 3]
+    want = []
+    for x in xs:
+        B.csr5_spmv_ex(h, x, d.y)
+        want.append(d.y.clone())
+    torch.cuda.synchronize()
+    for call in range(3):
+        ys = [torch.full_like(d.y, float("nan")) for _ in xs]
+        torch.cuda.synchronize()
+        for s, x, y in zip(streams, xs, ys):
+            B.csr5_spmv_ex(h, x, y, stream=s)
+        torch.cuda.synchronize()
+        for y, w in zip(ys, want):
+            assert torch.equal(y[:-1], w[:-1]), call        # (not the long row that ends in the incomplete tile)
+    B.csr5_free(h)
+
+
+def test_graph_replays():
+    a = _far(600_001, 200 * BLOCK + 1, 25, 35, 0.2, True, seed=9)
+    d = DeviceCsr(a)
+    h = convert(d, use_workspace=False)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
+    check_spmv(d, h, "eager")
+    want = d.y.clone()[:-1]                        # (not the long row that ends in the incomplete tile)
+    yg = torch.empty_like(d.y)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.csr5_spmv_ex(h, d.x, yg)
+    for replay in range(4):
+        yg.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(yg[:-1], want), replay
+        B.csr5_spmv_ex(h, d.x, d.y)
+        torch.cuda.synchronize()
+        assert torch.equal(d.y[:-1], want), replay
+    B.csr5_free(h)
+
+
+def test_nan_and_infinities_of_x_reach_their_rows_only():
+    a = _far(600_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=4)
+    d = DeviceCsr(a)
+    h = convert(d, use_workspace=False)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
+    x = a.x.copy()
+    x[[0, BLOCK - 1, BLOCK, 200 * BLOCK]] = [np.nan, np.inf, -np.inf, np.nan]
+    d.x = torch.from_numpy(x).cuda()
+    B.csr5_spmv_ex(h, d.x, d.y)
+    torch.cuda.synchronize()
+    y, (want, s) = d.y.cpu().numpy(), oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val, x)
+    odd = ~np.isfinite(want)
+    assert 0 < odd.sum() < a.m and np.array_equal(np.isnan(y), np.isnan(want)) and np.array_equal(y[odd & ~np.isnan(want)], want[odd & ~np.isnan(want)])
+    assert np.all(np.abs(y[~odd] - want[~odd]) <= 1e-12 * s[~odd] + 1e-300)
+    B.csr5_free(h)
+
+
+@pytest.mark.parametrize("n,how", [(200 * BLOCK, "workspace"), (200 * BLOCK, "not waited for"), (200 * BLOCK, "two kernels"),
+                                   (200_000, "small x"), (1024 * BLOCK + 1, "largest x")])
+def test_left_alone(n, how):
+    """What a conversion that enqueues only, brings its memory or fixes the form gets, and x that caches hold or that has too many blocks."""
+    a = _far(600_000, n, 15, 25, 0.0, seed=2)
+    d = DeviceCsr(a)
+    flags = {"not waited for": B.CSR5_FLAG_NO_HOST_CHECK, "two kernels": B.CSR5_FLAG_AUX_TWO_KERNELS}.get(how, B.CSR5_FLAG_NONE)
+    h = convert(d, use_workspace=how == "workspace", flags=flags)
+    assert B.csr5_get_form(h)["kernel"] != B.CSR5_KERNEL_GATHERED
+    check_spmv(d, h, how)
+    B.csr5_free(h)
+
+
+def test_columns_that_few_lines_hold_are_left_alone():
+    """Power-law columns in random order, a band too wide for a window, rows as long as several tiles."""
+    g = np.random.default_rng(7)
+    for kind in ("power law", "band", "long rows"):
+        n = 200 * BLOCK
+        m, length = (5000, 2400) if kind == "long rows" else (600_000, 20)
+        rows = np.repeat(np.arange(m, dtype=np.int64), length)
+        if kind == "power law":
+            col = g.permutation(n)[np.minimum(g.zipf(1.5, rows.size) - 1, n - 1)]
+        elif kind == "band":
+            col = (rows * n // m + g.integers(-100_000, 100_001, rows.size)).clip(0, n - 1)
+        else:
+            col = g.integers(0, n, rows.size)
+        col = (np.sort(rows * n + col) - rows * n).astype(np.int32)
+        a = wl.Csr(m=m, n=n, row_ptr=np.arange(0, m * length + 1, length, dtype=np.int32), col_idx=col, val=g.uniform(-1, 1, rows.size),
+                   x=g.uniform(-1, 1, n), name=kind)
+        d = DeviceCsr(a)
+        h = convert(d, use_workspace=False)
+        assert B.csr5_get_form(h)["kernel"] != B.CSR5_KERNEL_GATHERED, kind
+        check_spmv(d, h, kind)
+        B.csr5_free(h)
