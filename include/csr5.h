@@ -306,11 +306,13 @@ int csr5_get_shape(csr5_handle_t h, int32_t *m, int32_t *n);
  *                                    32768 tiles, two beyond
  *                 CSR5_KERNEL_GATHERED the same, or no part of x, with the other entries' x gathered
  *                                    into a buffer by a kernel before it
+ *                 CSR5_KERNEL_PAIRS  the tile kernel in its one-kernel form for single precision, with
+ *                                    neighbouring columns gathered two at a time
  *   wave_tiles    tiles of a wavefront (1 for CSR5_KERNEL_TILES)
  *   plain         1: col_idx, val and the descriptors would be read with plain loads, 0: with
  *                 non-temporal ones (a hint to the caches, the result is the same)
  */
-enum { CSR5_KERNEL_TILES = 0, CSR5_KERNEL_PARTS = 1, CSR5_KERNEL_WINDOW = 2, CSR5_KERNEL_GATHERED = 3 };
+enum { CSR5_KERNEL_TILES = 0, CSR5_KERNEL_PARTS = 1, CSR5_KERNEL_WINDOW = 2, CSR5_KERNEL_GATHERED = 3, CSR5_KERNEL_PAIRS = 4 };
 int csr5_get_form(csr5_handle_t h, void *hip_stream, int32_t *kernel, int32_t *wave_tiles, int32_t *plain);
 
 /*

@@ -27,7 +27,7 @@ CSR5_FLAG_AUX_TWO_KERNELS, CSR5_FLAG_AUX_ONE_KERNEL = 2, 4
 CSR5_STATUS_BAD_ROW_PTR, CSR5_STATUS_BAD_COL_IDX, CSR5_STATUS_HAS_DIRTY = 1, 2, 4
 CSR5_STATUS_HAS_EMPTY_ROWS = 8
 CSR5_ARRAY_TILE_PTR, CSR5_ARRAY_TILE_DESC, CSR5_ARRAY_EMPTY_OFFSET_PTR, CSR5_ARRAY_EMPTY_OFFSET = 0, 1, 2, 3
-CSR5_KERNEL_TILES, CSR5_KERNEL_PARTS, CSR5_KERNEL_WINDOW, CSR5_KERNEL_GATHERED = 0, 1, 2, 3
+CSR5_KERNEL_TILES, CSR5_KERNEL_PARTS, CSR5_KERNEL_WINDOW, CSR5_KERNEL_GATHERED, CSR5_KERNEL_PAIRS = range(5)
 
 # every symbol include/csr5.h declares
 SYMBOLS = [

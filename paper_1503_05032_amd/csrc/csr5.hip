@@ -326,7 +326,7 @@ k_prepare(int m, IT nnz, const IT* __restrict__ row_ptr, int T, int p, int pc, i
         for (size_t t = gid; t < groups; t += stride) arrived[slot * (slot_bytes / 4) + t] = 0u;
         for (size_t w = gid; w < groups * MEET_STRIDE; w += stride) meet[slot * (slot_bytes / 8) + w] = MEET_EMPTY;
     }
-    if (gid <= WINDOW_ANSWER_AT + 1) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
+    if (gid <= WINDOW_ANSWER_AT + 2) status[gid] = 0u;        // and the plan of the tile order, the answers of sample_columns and sample_window
     if (order_total)
         for (size_t b = gid; b < 2 * ORDER_BUCKETS; b += size_t(gridDim.x) * blockDim.x) order_total[b] = 0u;
     uint32_t found = 0;
@@ -758,10 +758,11 @@ __device__ __forceinline__ int window_first(uint32_t r0, uint32_t r1, float slop
 // one tile in 1 << shift, 64 to 127 tiles in all (another place among its workgroup's tiles for each).
 // What the host needs beside sizes (window_pays) is how many of the entries lie in their
 // workgroup's window, and in how many lines of it, tile by tile; and for k_far_gather how many lie further
-// from it than an L2 reaches, and in how many of the tiles these spread over more than that.
+// from it than an L2 reaches, and in how many of the tiles these spread over more than that; and for
+// gather_pairs how many of the second ones lie next to the first, and how many a line and more away.
 constexpr int FAR_REACH_BYTES = 2 << 20;
 struct WindowJob {
-    uint32_t* answer;                // entries << 16 | lines, further entries << 16 | tiles; cleared with the status word.  NULL: nothing to do
+    uint32_t* answer;                // entries << 16 | lines, further entries << 16 | tiles, next << 16 | away; cleared with the status word.  NULL: nothing to do
     int32_t shift, tiles;            // tiles of a workgroup, a power of two
     float slope;
 };
@@ -816,8 +817,11 @@ __device__ void sample_window(const WindowJob& job, int tile, const int32_t* c, 
     const uint32_t far = uint32_t(__popcll(far_lanes) + __popcll(__ballot(b_far)));
     const uint32_t one = __builtin_amdgcn_readlane(a, far_lanes ? __builtin_ctzll(far_lanes) : 0);
     const bool spread = far_lanes && __ballot(a_far && a - one + 2 * FAR_REACH_BYTES >= uint32_t(4 * FAR_REACH_BYTES)) != 0;
+    const uint32_t next = uint32_t(__popcll(__ballot(first + 1 == second)));
+    const uint32_t away = uint32_t(__popcll(__ballot(uint32_t(second - first + 32) >= 64u)));
     if (lane == 0) {
         atomicAdd(job.answer, near << 16 | lines);
+        atomicAdd(job.answer + 2, next << 16 | away);
         if (far) atomicAdd(job.answer + 1, far << 16 | (spread ? 1u : 0u));
     }
 }
@@ -1372,7 +1376,7 @@ struct FlagWord {
 // 40^3 stencil 6.82 -> 6.38, 100^3 stencil 60.9 -> 59.6, single precision 45.3 ->
 // 44.2, 20 000 rows with dense ones 7.2 -> 6.85; matrices bound by their gathers
 // 0-1 %.
-constexpr int DPP_SHIFT_DOWN = 0x100, DPP_ROTATE = 0x120;
+constexpr int DPP_SHIFT_DOWN = 0x100, DPP_SHIFT_UP = 0x110, DPP_ROTATE = 0x120;
 template <int CTRL>
 __device__ __forceinline__ float from_row(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
@@ -1677,9 +1681,42 @@ __device__ __forceinline__ uint32_t walk_columns(typename FlagWord<SIGMA>::type 
     return __builtin_amdgcn_readlane(seen ? seg + 1 : seg, OMEGA - 1);
 }
 
-template <int SIGMA, typename VT, typename IT, int MODE, bool KEEP>
+// Gathers in single precision, two entries at a time.  What a gather costs in the L1 goes by the lanes that
+// ask, unless they ask for one stretch of a line: next to a stream of 8 bytes an entry that is the bound (100^3
+// stencil: L1 busy 29 us with 43 accesses per 64 entries, of 45).  So where the entry of an odd lane has
+// the column next to that of the lane before it, that one loads 8 bytes and the odd lane asks for nothing.
+// Single precision, whole SpMV, before -> after: 27-point stencil 100^3 45.0 -> 40.4 us, 140^3 124 -> 114;
+// blocks of 3 columns (9 a row) 49.1 -> 40.6, of 4 (7) 45.5 -> 38.6, of 6 (5) 42.4 -> 39.4; 9-point stencil
+// 40.0 -> 38.4, 5-point 42.1 -> 40.2.  Not for entries one by one (24 diagonals 46.7 -> 51.4, 20 random
+// columns a row 98 -> 104) and not where a gather is one stretch already (tridiagonal 37.1 -> 38.9, five
+// diagonals 37.4 -> 40.0): the host decides, see pairs_pay.
+// Tried: three and four entries at a time (44.3, 45.4 on the 100^3 stencil: more registers, and 12 and 16
+// bytes a lane to bring back); pairs at any place, not only from even lanes: the same; in double precision
+// (16 bytes) 60.3 -> 71.7; either way in one kernel, decided per tile: 44.0 (98 registers instead of 79).
+constexpr size_t PAIR_MAX_X_BYTES = 0x7fffff00, PAIR_NOWHERE = 0x7ffffff0;       // outside of any x
+constexpr int DPP_QUAD_EVEN = 0xa0;                               // lanes 0, 0, 2, 2 of every four
+template <int COUNT>
+__device__ __forceinline__ void gather_pairs(const float* x, int x_bytes, const int32_t* c, float* xv) {
+    typedef float pair_t __attribute__((ext_vector_type(2)));
+    const auto xbuf = tile_buffer(x, x_bytes);
+    pair_t got[COUNT];
+    bool second[COUNT];
+#pragma unroll
+    for (int k = 0; k < COUNT; k++) {
+        // (in this form: the difference of the two came out with its sign changed)
+        second[k] = __builtin_amdgcn_update_dpp(0, c[k], DPP_QUAD_EVEN, 0xf, 0xf, true) + 1 == c[k];
+        got[k] = __builtin_bit_cast(pair_t, __builtin_amdgcn_raw_buffer_load_b64(xbuf, second[k] ? int(PAIR_NOWHERE) : c[k] * 4, 0, 0));
+    }
+#pragma unroll
+    for (int k = 0; k < COUNT; k++) {
+        const float from_even = from_row<DPP_QUAD_EVEN>(float(got[k].y));
+        xv[k] = second[k] ? from_even : float(got[k].x);
+    }
+}
+
+template <int SIGMA, typename VT, typename IT, int MODE, bool KEEP, bool PAIRS = false>
 __global__ void __launch_bounds__(TransposeShape<SIGMA>::WAVES * OMEGA)
-k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint32_t xcd_chunk, uint32_t far_mode,
+k_spmv(int m, int x_bytes, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint32_t xcd_chunk, uint32_t far_mode,
        int rec_bytes, const IT* __restrict__ row_ptr, const typename Index<IT>::tp_t* __restrict__ tile_ptr,
        const uint32_t* __restrict__ tile_desc, const IT* __restrict__ eop,
        const int32_t* __restrict__ eo, const int32_t* __restrict__ col_idx,
@@ -1929,10 +1966,16 @@ k_spmv(int m, IT nnz, int pc, int p, uint32_t nb_tiles, uint32_t has_tail, uint3
                 }
             }
         }
+        if constexpr (PAIRS) {
+            static_assert(sizeof(VT) == 4 && GROUP == SIGMA, "all at once");
+            gather_pairs<SIGMA>(x, x_bytes, c, xv);
+        }
 #pragma unroll
         for (int k0 = 0; k0 < SIGMA; k0 += GROUP) {
+            if constexpr (!PAIRS) {
 #pragma unroll
-            for (int k = k0; k < k0 + GROUP && k < SIGMA; k++) xv[k] = x[c[k]];
+                for (int k = k0; k < k0 + GROUP && k < SIGMA; k++) xv[k] = x[c[k]];
+            }
 #pragma unroll
             for (int k = k0; k < k0 + GROUP && k < SIGMA; k++) {
                 const int e = k * OMEGA + lane;
@@ -2952,8 +2995,17 @@ k_stream_floor(int m, int pc, int sigma, int W, uint32_t nb_tiles, uint32_t xcd_
     }
 }
 
+// Whether the entries' x is gathered in pairs (gather_pairs), by a sample of neighbouring entries: of 100 of them, how many are
+// one column on (blocks of 2 to 8 columns 50-87, 27-point stencil 67, 9-point 67, 5-point 40, all of which gain; 7-point 29, which
+// gains 2 %; a star of 25 32, which loses 3 %), and how many a line of x and more (those 60-13; tridiagonal and five
+// diagonals 0, which lose 5-7 %).
+constexpr uint32_t PAIR_NEXT_PERCENT = 36, PAIR_AWAY_PERCENT = 12;
+inline bool pairs_pay(int n, uint32_t sampled, uint32_t next, uint32_t away) {
+    return sampled && size_t(n) * sizeof(float) <= PAIR_MAX_X_BYTES && next * 100 >= sampled * PAIR_NEXT_PERCENT && away * 100 >= sampled * PAIR_AWAY_PERCENT;
+}
+
 template <int SIGMA, typename VT, typename IT, int MODE>
-hipError_t launch_spmv(bool keep, const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
+hipError_t launch_spmv(bool keep, bool pairs, const Geom& g, int m, int n, IT nnz, const IT* row_ptr,
                        const typename Index<IT>::tp_t* tile_ptr,
                        const uint32_t* tile_desc, const IT* eop, const int32_t* eo,
                        const int32_t* col_idx, const VT* val, const VT* x, VT* y,
@@ -2975,8 +3027,10 @@ hipError_t launch_spmv(bool keep, const Geom& g, int m, int n, IT nnz, const IT*
         xcd_chunk = (int64_t(nnz) / (m > 0 ? m : 1) <= g.T / Y_LINE_ROWS) ? 1u : XCD_CHUNK;
     else if (x_bytes < XCD_CONTIGUOUS_MIN_X_BYTES)                 // x at home in every L2
         xcd_chunk = XCD_CHUNK;
-    const auto kernel = keep && rule_sigma(SIGMA) ? k_spmv<SIGMA, VT, IT, MODE, rule_sigma(SIGMA)> : k_spmv<SIGMA, VT, IT, MODE, false>;
-    hipLaunchKernelGGL(kernel, dim3(nb), dim3(WAVES * OMEGA), 0, s, m, nnz, g.pc, g.p, nb_tiles, has_tail,
+    auto kernel = keep && rule_sigma(SIGMA) ? k_spmv<SIGMA, VT, IT, MODE, rule_sigma(SIGMA)> : k_spmv<SIGMA, VT, IT, MODE, false>;
+    if constexpr (sizeof(VT) == 4 && rule_sigma(SIGMA) && MODE == MODE_LOOK)
+        if (pairs) kernel = keep ? k_spmv<SIGMA, VT, IT, MODE, true, true> : k_spmv<SIGMA, VT, IT, MODE, false, true>;
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(WAVES * OMEGA), 0, s, m, int(x_bytes), nnz, g.pc, g.p, nb_tiles, has_tail,
                        xcd_chunk, far_mode, record_bytes(int64_t(nnz)), row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry,
                        meet, arrived, span, status, tile_head, last_col, last_val, order, order_second, order_len);
     return hipGetLastError();
@@ -3253,6 +3307,7 @@ struct csr5_handle_s {
     uint32_t order_second, order_len;
     int staged;            // tiles per wavefront of k_spmv_staged; 0: not for this matrix
     bool window;           // the window form of k_spmv_staged is for this matrix
+    bool pairs;            // its entries' x may be gathered in pairs (gather_pairs)
     FarPlan far;           // lists != NULL: FORM_FAR is for this matrix
     void* owned;           // hipMalloc'ed block, or NULL when a workspace was given
     hipStream_t conv_stream;
@@ -3583,7 +3638,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     h->last_col = L.has_last ? reinterpret_cast<int32_t*>(basep + L.off_last + LOOK * 8) : nullptr;
     h->status = reinterpret_cast<uint32_t*>(basep + L.off_status);
     h->staged = 0;
-    h->window = false;
+    h->window = h->pairs = false;
     h->far.tables = h->far.lists = nullptr;
     h->order = nullptr;
     h->order_second = h->order_len = 0;
@@ -3691,8 +3746,8 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     if (!(flags & CSR5_FLAG_NO_HOST_CHECK)) {
         // blocking variant: wait for the device-side verdict; on bad input undo the
         // transposition and refuse
-        uint32_t got[WINDOW_ANSWER_AT + 2] = {};      // the status word, behind it the plan of the tile order and the answers on the columns
-        int rc = read_status(h, got, window.answer ? WINDOW_ANSWER_AT + 2 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
+        uint32_t got[WINDOW_ANSWER_AT + 3] = {};      // the status word, behind it the plan of the tile order and the answers on the columns
+        int rc = read_status(h, got, window.answer ? WINDOW_ANSWER_AT + 3 : (sample.col_idx ? 4 : (order.slices ? 3 : 1)));
         if (rc == CSR5_OK && got[2]) {
             h->order = order.order;
             h->order_second = got[1];
@@ -3708,6 +3763,9 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
         if constexpr (!wide) {
             if (rc == CSR5_OK && !(got[0] & BAD_BITS) && window.answer && h->owned && !h->order && !h->staged)
                 far_plan<VT>(h, s, samples, near, got[WINDOW_ANSWER_AT + 1] >> 16, got[WINDOW_ANSWER_AT + 1] & 0xffffu);
+            // (the instantiation with the look-behind only)
+            h->pairs = rc == CSR5_OK && sizeof(VT) == 4 && h->last_col && !(got[0] & STATUS_NEEDS_CARRY) && !h->staged && !h->window && !h->far.lists &&
+                       pairs_pay(n, samples / 2, got[WINDOW_ANSWER_AT + 2] >> 16, got[WINDOW_ANSWER_AT + 2] & 0xffffu);
         }
         if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);
@@ -3794,7 +3852,7 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
     const bool fixed = h->order && h->span && one_pays;
     uint64_t* const meet = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(carry) + slot_off_meet(h->g));
     uint32_t* const arrived = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(carry) + slot_off_arrived(h->g, tile_group_waves(h->g.sigma)));
-#define ARGS keep, h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
+#define ARGS keep, h->pairs, h->g, h->m, h->n, IT(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,              \
              static_cast<const VT*>(h->val), x, y, carry, meet, arrived, h->span, h->status, h->tile_head, h->last_col, \
              static_cast<const VT*>(h->last_val), zero_rows, far_mode, h->order, h->order_second, h->order_len, s
     // x through LDS: one launch, which wants the handle's own slot like the one-launch form
@@ -4066,7 +4124,7 @@ int csr5_get_shape(csr5_handle_t h, int32_t* m, int32_t* n) {
 
 int csr5_get_form(csr5_handle_t h, void* hip_stream, int32_t* kernel, int32_t* wave_tiles, int32_t* plain) {
     if (!h || !h->in_csr5_order) return CSR5_EINVAL;
-    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->far.lists ? CSR5_KERNEL_GATHERED : (h->window ? CSR5_KERNEL_WINDOW : CSR5_KERNEL_TILES));
+    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->far.lists ? CSR5_KERNEL_GATHERED : (h->window ? CSR5_KERNEL_WINDOW : (h->pairs ? CSR5_KERNEL_PAIRS : CSR5_KERNEL_TILES)));
     if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window || h->far.lists ? window_tiles(h->g.sigma) : 1);
     if (plain)
         *plain = !h->staged && !h->window && !h->far.lists && rule_sigma(h->g.sigma) &&
