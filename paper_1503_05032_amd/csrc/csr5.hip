@@ -2202,16 +2202,18 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 //     its neighbours', which run on the same XCD.  They go to LDS, to the entry's place among the
 //     workgroup's (which of the two, 4 and 2 bytes, is a list as well), when the entries near
 //     the diagonal have taken theirs from the window there; from LDS every lane picks its own.
-// 26 to 40 bytes an entry instead of 128 and more.  Whole SpMV, before -> after:
-// mixed (four fifths of the rows within +-5000 columns, the others anywhere) 136 M entries 1185 -> 708
-// us, single precision 1020 -> 472, 51 M 422 -> 260, 34 M 253 -> 185; rows of 0-20 columns out of 4 M
-// 690 -> 326, 582 -> 214.  Of the 708, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 565
-// the second: 193 for the lists and the buffer, 70 for the stores of y, 45 for the window.
+// Where few entries are near the diagonal all of them go that way, and the tile kernel reads no columns
+// (FORM_ALL).  22 to 40 bytes an entry instead of 128 and more.  Whole SpMV, before -> after:
+// mixed (four fifths of the rows within +-5000 columns, the others anywhere) 136 M entries 1185 -> 691
+// us, single precision 1020 -> 470, 51 M 422 -> 257, 34 M 253 -> 180; rows of 0-20 columns out of 4 M
+// 690 -> 268, 582 -> 181.  Of the 691, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 545
+// the second: 175 for the lists and the buffer, 70 for the stores of y, 45 for the window.
 // The buffer is a handle's (one for each of its CARRY_SLOTS), of FAR_BUFFER_BYTES at most; a matrix
 // with more such entries goes through it in chunks of workgroups (136 M entries in 1, 2, 4, 8 chunks 717,
 // 709, 717, 789; 34 M in 1, 2, 4 187, 196, 219: a drained chip between any two kernels).
 // Tried: the buffer read past the caches (nt) 709 -> 808; written so 709 -> 712, single precision 472 ->
-// 490; 4 entries per thread asked for ahead of the window instead of 8 709 -> 722.
+// 490; 4, 8, 9, 11, 12 and 14 entries per thread asked for ahead of the window instead of 10: 722, 708, 700, 691,
+// 696, 739; without a window 10 and 13 instead of 16: rows of 0-20 268 -> 279, 291; blocks of 64 KB 708 -> 720.
 //
 // The lists are the conversion's (far_make): where it blocks, allocates for itself and the columns
 // pay for it.  A block's entries are counted per workgroup (k_far_count), the counts scanned in
@@ -2219,7 +2221,7 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 // sorts its entries by block in LDS and writes them to their places (k_far_place).  The order of
 // a workgroup's entries in a block is any; the sums do not depend on it.
 // ----------------------------------------------------------------------------
-constexpr int FAR_THREADS = 512, FAR_ENTRIES = 8192, FAR_PLACE_BITS = 13, FAR_AHEAD = 8;
+constexpr int FAR_THREADS = 512, FAR_ENTRIES = 8192, FAR_PLACE_BITS = 13, FAR_AHEAD = 10, FAR_AHEAD_ALL = 16;
 constexpr int FAR_BLOCK_BYTES = 128 << 10, FAR_MAX_BLOCKS = 1024, FAR_SEGMENT = 64, FAR_MAX_CHUNKS = 32, FAR_PAD = 16;
 constexpr int64_t FAR_BUFFER_BYTES = 256 << 20;
 template <typename VT> constexpr int far_block_shift() { return sizeof(VT) == 8 ? 14 : 15; }
@@ -2528,7 +2530,8 @@ struct RowSpan { int first, groups; };     // the workgroups a row touches
 // through the auxiliary array and k_spmv_fixup otherwise, one sum per workgroup.
 //
 // FORM_FAR: the window form, with the entries outside the window from the buffer of k_far_gather.
-constexpr int FORM_PARTS = 0, FORM_WINDOW = 1, FORM_FAR = 2;
+// FORM_ALL: all entries from there; no window, and the columns are not read.
+constexpr int FORM_PARTS = 0, FORM_WINDOW = 1, FORM_FAR = 2, FORM_ALL = 3;
 struct FarEntries {                // of FORM_FAR
     int first, count;              // the launch's workgroups
     const uint32_t* base;          // where a workgroup's share of the lists begins
@@ -2545,7 +2548,8 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
               const int32_t* __restrict__ col_idx, const VT* __restrict__ val, const VT* __restrict__ x, VT* __restrict__ y,
               VT* __restrict__ carry, uint64_t* __restrict__ meet, uint32_t* __restrict__ arrived,
               const uint32_t* __restrict__ tile_head, float slope, const FarEntries far) {
-    constexpr bool FAR = FORM == FORM_FAR, WINDOW = FORM != FORM_PARTS;
+    constexpr bool ALL = FORM == FORM_ALL, FAR = FORM == FORM_FAR || ALL, WINDOW = FORM != FORM_PARTS;
+    constexpr int AHEAD = ALL ? FAR_AHEAD_ALL : FAR_AHEAD;
     constexpr uint32_t ROWMASK = Index<int32_t>::ROWMASK, DIRTY = Index<int32_t>::DIRTY;
     constexpr int T = OMEGA * SIGMA, THREADS = WAVES * OMEGA, TILES = WAVES * K;
     constexpr int YSH = SIGMA + SBITS;
@@ -2593,14 +2597,14 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         }
     };
     if constexpr (!WINDOW) stage(0, xs0);
-    // Entries whose x comes through the buffer: where from and where to, the first FAR_AHEAD of each thread
+    // Entries whose x comes through the buffer: where from and where to, the first AHEAD of each thread
     uint32_t far_count = 0;
     __amdgpu_buffer_rsrc_t far_src, far_place, far_values;
-    uint32_t fs[FAR_AHEAD], fp[FAR_AHEAD];
-    VT fv[FAR_AHEAD];
+    uint32_t fs[AHEAD], fp[AHEAD];
+    VT fv[AHEAD];
     const auto far_lists = [&](uint32_t k0) {
 #pragma unroll
-        for (int u = 0; u < FAR_AHEAD; u++) {
+        for (int u = 0; u < AHEAD; u++) {
             const uint32_t k = k0 + uint32_t(u * THREADS) + threadIdx.x;
             fs[u] = stream_from<uint32_t, false>(far_src, int(k * 4));         // (reads as 0 behind the end)
             fp[u] = uint32_t(stream_from<uint16_t, false>(far_place, int(k * 2)));
@@ -2608,14 +2612,14 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
     };
     const auto far_fetch = [&](uint32_t k0) {
 #pragma unroll
-        for (int u = 0; u < FAR_AHEAD; u++) {
+        for (int u = 0; u < AHEAD; u++) {
             const uint32_t k = k0 + uint32_t(u * THREADS) + threadIdx.x;
             fv[u] = stream_from<VT, true>(far_values, k < far_count ? int(fs[u] * uint32_t(sizeof(VT))) : INT32_MAX - 15);
         }
     };
     const auto far_put = [&](uint32_t k0) {
 #pragma unroll
-        for (int u = 0; u < FAR_AHEAD; u++) {
+        for (int u = 0; u < AHEAD; u++) {
             const uint32_t k = k0 + uint32_t(u * THREADS) + threadIdx.x;
             if (k < far_count) *reinterpret_cast<VT*>(xs0 + fp[u] * uint32_t(sizeof(VT))) = fv[u];
         }
@@ -2628,7 +2632,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         far_values = tile_buffer(static_cast<const VT*>(far.values), far.value_bytes);
     }
     asm volatile("" ::: "memory");
-    int32_t c[K][SIGMA];
+    int32_t c[K][SIGMA];               // (ALL: not used)
     uint32_t dw[K], tp[K], head[K + 1];
 #pragma unroll
     for (int k = 0; k < K; k++) {
@@ -2636,7 +2640,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         const auto cols = tile_buffer(col_idx + size_t(tile < pc ? tile : 0) * T, tile < pc ? T * 4 : 0);    // (an empty buffer reads as 0)
         const auto descs = tile_buffer(tile_desc + size_t(tile < pc ? tile : 0) * OMEGA, tile < pc ? OMEGA * 4 : 0);
 #pragma unroll
-        for (int j = 0; j < SIGMA; j++) c[k][j] = stream_from<int32_t, false>(cols, (j * OMEGA + lane) * 4) * int(sizeof(VT));
+        for (int j = 0; j < SIGMA; j++) c[k][j] = ALL ? 0 : stream_from<int32_t, false>(cols, (j * OMEGA + lane) * 4) * int(sizeof(VT));
         dw[k] = stream_from<uint32_t, false>(descs, lane * 4);
     }
     if constexpr (FAR) far_lists(0);
@@ -2719,17 +2723,19 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+        if constexpr (!ALL) {
 #pragma unroll
-        for (int k = 0; k < K; k++)
+            for (int k = 0; k < K; k++)
 #pragma unroll
-            for (int j = 0; j < SIGMA; j++) {
-                const uint32_t at = uint32_t(c[k][j]) - uint32_t(window);
-                if (at < uint32_t(part_bytes)) xv[k][j] = *reinterpret_cast<const VT*>(xs0 + at);
-            }
+                for (int j = 0; j < SIGMA; j++) {
+                    const uint32_t at = uint32_t(c[k][j]) - uint32_t(window);
+                    if (at < uint32_t(part_bytes)) xv[k][j] = *reinterpret_cast<const VT*>(xs0 + at);
+                }
+        }
         if constexpr (FAR) {
-            __syncthreads();           // the other entries' values go where the window was, in the tiles' order
+            if constexpr (!ALL) __syncthreads();       // the other entries' values go where the window was, in the tiles' order
             far_put(0);
-            for (uint32_t k0 = FAR_AHEAD * THREADS; k0 < far_count; k0 += FAR_AHEAD * THREADS) {
+            for (uint32_t k0 = AHEAD * THREADS; k0 < far_count; k0 += AHEAD * THREADS) {
                 far_lists(k0);
                 far_fetch(k0);
                 far_put(k0);
@@ -2739,7 +2745,7 @@ k_spmv_staged(int m, int n, int nnz, int pc, uint32_t groups, uint32_t has_tail,
             for (int k = 0; k < K; k++)
 #pragma unroll
                 for (int j = 0; j < SIGMA; j++)
-                    if (uint32_t(c[k][j]) - uint32_t(window) >= uint32_t(part_bytes))
+                    if (ALL || uint32_t(c[k][j]) - uint32_t(window) >= uint32_t(part_bytes))
                         xv[k][j] = *reinterpret_cast<const VT*>(xs0 + uint32_t(((wave * K + k) * T + j * OMEGA + lane) * int(sizeof(VT))));
         }
     } else {
@@ -3155,8 +3161,9 @@ constexpr double FAR_PAYBACK = 8, FAR_COST = 400, FAR_COST_PER_M = 8, FAR_GAIN_P
 // Lines, of 100 entries far away (random columns 95-99, power-law ones 23-32; columns that all together are on fewer lines are in
 // the caches), and tiles that spread them, of 100 (random 85-100; power-law columns and rows as long as several tiles 17).
 constexpr uint32_t FAR_LINES_PERCENT = 85, FAR_SPREAD_PERCENT = 75;
-// Near ones, for the window to be loaded: 0.3 us per million entries for it, 5.6 for a million more through the buffer.
-constexpr uint32_t FAR_WINDOW_PERCENT = 6;
+// Near ones, of 100, for the window and the columns to be loaded.  48 M entries, a share near the diagonal, with the window
+// and without: 0.1 356, 306 us; 0.3 326, 320; 0.4 269, 326; single precision 253, 205; 223, 204; 194, 203.
+constexpr uint32_t FAR_WINDOW_PERCENT = 33;
 inline bool far_pays(int64_t nnz, int64_t x_bytes, double far_share) {
     return FAR_COST + FAR_COST_PER_M * 1e-6 * double(nnz) <=
            FAR_PAYBACK * FAR_GAIN_PER_M * 1e-6 * double(nnz) * far_share * (1 - FAR_L2_BYTES / double(x_bytes));
@@ -3175,7 +3182,7 @@ hipError_t launch_far(const FarPlan& plan, int turn, const Geom& g, int m, int n
                            plan.range + size_t(c) * (f.blocks + 1), plan.cols + plan.first[c], x, values);
         const int first = far_chunk_segment(f, c) * FAR_SEGMENT, last = c + 1 < f.chunks ? far_chunk_segment(f, c + 1) * FAR_SEGMENT : f.groups;
         const uint32_t has_tail = c == 0 && g.p > g.pc ? 1u : 0u;
-        hipLaunchKernelGGL((k_spmv_staged<SIGMA, WAVES, K, FORM_FAR, VT>), dim3(uint32_t(last - first) + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc,
+        hipLaunchKernelGGL((f.window_bytes ? k_spmv_staged<SIGMA, WAVES, K, FORM_FAR, VT> : k_spmv_staged<SIGMA, WAVES, K, FORM_ALL, VT>), dim3(uint32_t(last - first) + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc,
                            uint32_t(f.groups), has_tail, zero_rows ? 1u : 0u, f.window_bytes, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet,
                            arrived, tile_head, f.slope, FarEntries{first, last - first, plan.base, plan.src, plan.place, values, int(plan.values_bytes)});
         const hipError_t e = hipGetLastError();

@@ -42,10 +42,11 @@ def _far(m, n, lo, hi, near, uneven=False, seed=0):
 @pytest.mark.parametrize("m,n,lo,hi,near,sigma,uneven", [
     (600_000, 200 * BLOCK, 15, 25, 0.0, 0, False),             # whole blocks, no window, height 8
     (600_001, 200 * BLOCK + 1, 15, 25, 0.0, 0, True),
-    (400_000, 300 * BLOCK - 1, 30, 60, 0.3, 16, True),        # height 16, one kernel for the sums
+    (400_000, 300 * BLOCK - 1, 60, 100, 0.5, 16, True),       # a window; height 16, one kernel for the sums
     (5_000_000, 200 * BLOCK + 17, 1, 6, 0.1, 0, True),        # tall
-    (30_001, 8_000_001, 500, 700, 0.2, 16, True),              # wide, rows longer than half a tile
-    (900_000, 250 * BLOCK + 5, 18, 26, 0.15, 8, True),        # more than 32768 tiles: a kernel more
+    (30_001, 8_000_001, 600, 800, 0.45, 16, True),             # wide, rows longer than half a tile, a window
+    (900_000, 250 * BLOCK + 5, 30, 40, 0.45, 8, True),        # a window; more than 32768 tiles: a kernel more
+    (900_000, 250 * BLOCK + 5, 18, 26, 0.15, 8, True),        # the same without
     (700_000, 1024 * BLOCK, 15, 25, 0.0, 0, False)])           # the largest x
 def test_parity(m, n, lo, hi, near, sigma, uneven):
     a = _far(m, n, lo, hi, near, uneven, seed=m % 97)
@@ -83,7 +84,8 @@ def test_parity(m, n, lo, hi, near, sigma, uneven):
 
 
 @pytest.mark.parametrize("m,n,lo,hi,near,sigma,single", [
-    (700_000, 2 * 260 * BLOCK + 1, 15, 25, 0.0, 0, True), (700_000, 2 * 260 * BLOCK - 1, 15, 25, 0.2, 16, True),
+    (700_000, 2 * 260 * BLOCK + 1, 15, 25, 0.0, 0, True), (700_000, 2 * 260 * BLOCK - 1, 30, 50, 0.45, 16, True),
+    (3_000_000, 4_000_001, 25, 35, 0.45, 0, False),            # 45 M entries through the buffer, in two chunks
     (3_000_000, 4_000_001, 10, 20, 0.1, 0, False),             # 37 M entries through the buffer, in two chunks
     (3_000_000, 6_000_001, 20, 30, 0.05, 0, True)])             # 68 M, two chunks
 def test_against_sums_in_double_precision(m, n, lo, hi, near, sigma, single):
@@ -107,7 +109,7 @@ def test_against_sums_in_double_precision(m, n, lo, hi, near, sigma, single):
 
 
 def test_products_in_flight_on_four_streams_and_other_vectors():
-    a = _far(600_001, 200 * BLOCK + 1, 25, 35, 0.2, True, seed=3)
+    a = _far(600_001, 200 * BLOCK + 1, 45, 55, 0.45, True, seed=3)
     d = DeviceCsr(a)
     h = convert(d, use_workspace=False)
     assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
