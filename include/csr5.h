@@ -121,8 +121,11 @@ size_t csr5_workspace_bytes(int32_t m, int32_t nnz, int32_t sigma);
  *               empty_offset with its per-tile start array.
  *
  * For a matrix with many columns anywhere in a large x (see csr5_spmv) a conversion that blocks and
- * allocates for itself also allocates up to 16 bytes per such entry, and up to four times
- * 256 MiB (more beyond 8 GiB of them), if that is no more than an eighth of the memory that is free.
+ * allocates for itself also allocates 8 bytes per such entry, 6 bytes per 8192 entries of the matrix and
+ * 128 KiB of x, and four buffers for the values of x, of up to 256 MiB each (more where they are more
+ * than 8 GiB), if that is no more than an eighth of the memory that is free.
+ * The verdict of a conversion that blocks comes through a page of pinned memory, 8 KiB per device, that
+ * the first one allocates and the process keeps.
  *
  * csr5_convert picks sigma itself, allocates with hipMalloc, runs on the default
  * stream and waits for the conversion's device-side checks of the input
@@ -351,7 +354,8 @@ const char *csr5_strerror(int code);
  * Measurement helper: launches each of the SpMV's two kernels `reps` times in a
  * row on the stream, HIP events before and after each series, waits, and returns
  * the mean duration per launch in milliseconds: ms[0] the tile kernel (all
- * complete tiles plus the workgroup for the incomplete one), ms[1] the carry
+ * complete tiles plus the workgroup for the incomplete one, and the kernel that
+ * gathers for it where there is one), ms[1] the carry
  * fix-up (0 when this matrix does not need it or settles its carries inside the
  * tile kernel).  ms is a host array of 2 floats.
  * A full SpMV follows the two series, so y ends up holding A*x as after
