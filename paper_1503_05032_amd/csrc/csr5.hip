@@ -2205,7 +2205,7 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 // Where few entries are near the diagonal all of them go that way, and the tile kernel reads no columns
 // (FORM_ALL).  22 to 40 bytes an entry instead of 128 and more.  Whole SpMV, before -> after:
 // mixed (four fifths of the rows within +-5000 columns, the others anywhere) 136 M entries 1185 -> 691
-// us, single precision 1020 -> 470, 51 M 422 -> 257, 34 M 253 -> 180; rows of 0-20 columns out of 4 M
+// us, single precision 1020 -> 470, 51 M 422 -> 256, 34 M 253 -> 171; rows of 0-20 columns out of 4 M
 // 690 -> 268, 582 -> 181.  Of the 691, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 545
 // the second: 175 for the lists and the buffer, 70 for the stores of y, 45 for the window.
 // The buffer is a handle's (one for each of its CARRY_SLOTS), of FAR_BUFFER_BYTES at most; a matrix
@@ -3152,21 +3152,20 @@ struct FarPlan {
     uint32_t first[FAR_MAX_CHUNKS + 1];    // of a chunk, in cols
 };
 // In how many products the plan has to come back, in what it costs a conversion and csr5_free (us per million
-// entries, and in any case: allocation and release, and what waits for them) and gives a product (us per million far entries; nothing
-// where the L2s hold x).  Conversion and free longer by, product before -> after: mixed in double precision
+// entries, and in any case: allocation and release, and what waits for them) and gives a product (us per million entries further
+// from their window than an L2 reaches).  Conversion and free longer by, product before -> after: mixed in double precision
 // 25.6 M entries 634, 177 -> 134 (not taken); 34 M 639, 263 -> 173; 51 M 780, 422 -> 261; 136 M 1458, 1211 -> 710; single precision 34 M 658,
 // 176 -> 126 (not taken); 68 M 881, 469 -> 236; random columns out of 1 M, 15 M entries 422, 160 -> 114 (not taken), out of 4 M, 40 M
 // entries 575, 690 -> 326.
-constexpr double FAR_PAYBACK = 8, FAR_COST = 400, FAR_COST_PER_M = 8, FAR_GAIN_PER_M = 8.5, FAR_L2_BYTES = 4 << 20;
+constexpr double FAR_PAYBACK = 8, FAR_COST = 400, FAR_COST_PER_M = 8, FAR_GAIN_PER_M = 8.5;
 // Lines, of 100 entries far away (random columns 95-99, power-law ones 23-32; columns that all together are on fewer lines are in
 // the caches), and tiles that spread them, of 100 (random 85-100; power-law columns and rows as long as several tiles 17).
 constexpr uint32_t FAR_LINES_PERCENT = 85, FAR_SPREAD_PERCENT = 75;
 // Near ones, of 100, for the window and the columns to be loaded.  48 M entries, a share near the diagonal, with the window
 // and without: 0.1 356, 306 us; 0.3 326, 320; 0.4 269, 326; single precision 253, 205; 223, 204; 194, 203.
 constexpr uint32_t FAR_WINDOW_PERCENT = 33;
-inline bool far_pays(int64_t nnz, int64_t x_bytes, double far_share) {
-    return FAR_COST + FAR_COST_PER_M * 1e-6 * double(nnz) <=
-           FAR_PAYBACK * FAR_GAIN_PER_M * 1e-6 * double(nnz) * far_share * (1 - FAR_L2_BYTES / double(x_bytes));
+inline bool far_pays(int64_t nnz, double far_share) {
+    return FAR_COST + FAR_COST_PER_M * 1e-6 * double(nnz) <= FAR_PAYBACK * FAR_GAIN_PER_M * 1e-6 * double(nnz) * far_share;
 }
 
 template <int SIGMA, typename VT>
@@ -3636,7 +3635,7 @@ template <typename VT>
 static void far_plan(csr5_handle_t h, hipStream_t s, uint32_t samples, uint32_t near, uint32_t far, uint32_t spread) {
     const int64_t x_bytes = int64_t(h->n) * int64_t(sizeof(VT));
     if (x_bytes > int64_t(FAR_BLOCK_BYTES) * FAR_MAX_BLOCKS || spread * 100 < samples / (2 * OMEGA) * FAR_SPREAD_PERCENT ||
-        !far_pays(h->nnz, x_bytes, double(far) / samples)) return;
+        !far_pays(h->nnz, double(far) / samples)) return;
     const int window = near * 100 >= samples * FAR_WINDOW_PERCENT ? WINDOW_BYTES : 0;
     const double share = window ? double(samples - near) / samples : 1.0;
     if (h->g.sigma == RULE_R ? far_make<RULE_R, VT>(h, s, window, share) : far_make<RULE_SIGMA_SMALL, VT>(h, s, window, share)) return;
