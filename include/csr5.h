@@ -124,8 +124,6 @@ size_t csr5_workspace_bytes(int32_t m, int32_t nnz, int32_t sigma);
  * allocates for itself also allocates 8 bytes per such entry, 6 bytes per 8192 entries of the matrix and
  * 128 KiB of x, and four buffers for the values of x, of up to 256 MiB each (more where they are more
  * than 8 GiB), if that is no more than an eighth of the memory that is free.
- * The verdict of a conversion that blocks comes through a page of pinned memory, 8 KiB per device, that
- * the first one allocates and the process keeps.
  *
  * csr5_convert picks sigma itself, allocates with hipMalloc, runs on the default
  * stream and waits for the conversion's device-side checks of the input

@@ -9,9 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
-#include <chrono>
 #include <cstdint>
-#include <cstring>
 #include <new>
 #include <type_traits>
 
@@ -3417,81 +3415,10 @@ size_t csr5l_workspace_bytes(int32_t m, int64_t nnz, int32_t sigma) {
 
 }  // extern "C"
 
-// A graph is replayed at any time, in turn with anything.  (An error is a capture elsewhere that forbids the question.)
-static bool may_be_captured(hipStream_t s) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
-}
-
-// Where a conversion that is waited for tells its result: a page of pinned memory of REPORT_SLOTS per device, allocated by
-// the first such conversion on it and held until the process ends.  A kernel at the end of the
-// stream writes the status words there and a number that no other report has, and the
-// host looks for that number: 12 us less than a copy into the caller's memory and a wait for the stream (four
-// kernels and that 35.1 us, with this 23.2; power-law of 2 M rows there and back with one product 230 -> 218).
-constexpr int REPORT_SLOTS = 32, REPORT_WORDS = 64, REPORT_SPIN_US = 2000;
-static std::atomic<uint32_t*> report_page[MAX_DEVICES];
-static std::atomic<uint32_t> report_taken[MAX_DEVICES];      // a bit per slot
-static std::atomic<uint32_t> report_number;
-__global__ void __launch_bounds__(REPORT_WORDS)
-k_report(const uint32_t* __restrict__ from, int words, uint32_t* __restrict__ to, uint32_t number) {
-    if (int(threadIdx.x) < words) to[threadIdx.x] = from[threadIdx.x];
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(to + REPORT_WORDS - 1, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// A slot of the current device's page, -1 if there is none (then the words are copied)
-static int report_slot(int dev) {
-    if (dev < 0 || dev >= MAX_DEVICES) return -1;
-    if (!report_page[dev].load(std::memory_order_acquire)) {
-        void* page = nullptr;
-        if (hipHostMalloc(&page, REPORT_SLOTS * REPORT_WORDS * 4, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            (void)hipGetLastError();
-            return -1;
-        }
-        std::memset(page, 0, REPORT_SLOTS * REPORT_WORDS * 4);
-        uint32_t* none = nullptr;
-        if (!report_page[dev].compare_exchange_strong(none, static_cast<uint32_t*>(page), std::memory_order_acq_rel)) (void)hipHostFree(page);
-    }
-    uint32_t taken = report_taken[dev].load(std::memory_order_relaxed);
-    while (taken != 0xffffffffu) {
-        const int slot = __builtin_ctz(~taken);
-        if (report_taken[dev].compare_exchange_weak(taken, taken | 1u << slot, std::memory_order_acquire)) return slot;
-    }
-    return -1;
-}
-static bool report_wait(const uint32_t* flag, uint32_t number) {
-    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(REPORT_SPIN_US);
-    for (int spin = 0; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != number; spin++) {
-        __builtin_ia32_pause();
-        if (spin % 64 == 63 && std::chrono::steady_clock::now() > until) return false;
-    }
-    return true;
-}
-
-// `words` words of device memory, when everything before on the stream is done
-static bool read_words(int device, hipStream_t s, const uint32_t* from, uint32_t* got, int words) {
-    int dev = -1;
-    const int slot = hipGetDevice(&dev) == hipSuccess && dev == device && !may_be_captured(s) ? report_slot(dev) : -1;
-    if (slot < 0)
-        return hipMemcpyAsync(got, from, size_t(words) * 4, hipMemcpyDeviceToHost, s) == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
-    uint32_t* const at = report_page[dev].load(std::memory_order_acquire) + slot * REPORT_WORDS;
-    uint32_t number = report_number.fetch_add(1, std::memory_order_relaxed) + 1;
-    if (number == 0) number = report_number.fetch_add(1, std::memory_order_relaxed) + 1;       // (what a page begins with)
-    hipLaunchKernelGGL(k_report, dim3(1), dim3(REPORT_WORDS), 0, s, from, words, at, number);
-    // (a stream with long work in front of it is left to the runtime, which gives the processor away)
-    if (hipGetLastError() != hipSuccess || !(report_wait(at + REPORT_WORDS - 1, number) || hipStreamSynchronize(s) == hipSuccess))
-        return false;                      // (the slot stays taken: its kernel may still run)
-    std::memcpy(got, at, size_t(words) * 4);
-    report_taken[dev].fetch_and(~(1u << slot), std::memory_order_release);
-    return true;
-}
-
 // The first `words` words at the handle's status word; notes the status for later calls.
 static int read_status(csr5_handle_t h, uint32_t* got, int words) {
-    if (!read_words(h->device, h->conv_stream, h->status, got, words)) return CSR5_EHIP;
+    if (hipMemcpyAsync(got, h->status, size_t(words) * 4, hipMemcpyDeviceToHost, h->conv_stream) != hipSuccess) return CSR5_EHIP;
+    if (hipStreamSynchronize(h->conv_stream) != hipSuccess) return CSR5_EHIP;
     h->status_host.store(int32_t(got[0] & 0x7fffffffu), std::memory_order_relaxed);
     return CSR5_OK;
 }
@@ -3544,6 +3471,14 @@ static uint64_t use_latest(int dev, uint64_t use) {       // returns the one bef
     return before;
 }
 
+// A graph is replayed at any time, in turn with anything.  (An error is a capture elsewhere that forbids the question.)
+static bool may_be_captured(hipStream_t s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // before: what use_latest returned
 static bool keep_product(csr5_handle_t h, uint32_t call, uint64_t before, hipStream_t s) {
     if (!h->near.load(std::memory_order_relaxed)) return false;
@@ -3565,6 +3500,11 @@ static void* far_alloc(size_t bytes) {
     (void)hipGetLastError();
     return nullptr;
 }
+template <typename T>
+static bool far_read(T* to, const T* from, int count, hipStream_t s) {
+    return hipGetLastError() == hipSuccess && hipMemcpyAsync(to, from, count * sizeof(T), hipMemcpyDeviceToHost, s) == hipSuccess &&
+           hipStreamSynchronize(s) == hipSuccess;
+}
 // Whether the plan is made; what was launched for it may still run if it is not.
 template <int SIGMA, typename VT>
 static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double far_share) {
@@ -3584,7 +3524,7 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double fa
     const uint32_t* const tile_ptr = static_cast<const uint32_t*>(h->tile_ptr);
     uint32_t got[2];
     hipLaunchKernelGGL((k_far_sample<SIGMA, VT>), dim3(1), dim3(SCAN_THREADS), 0, s, f, tile_ptr, h->col_idx, h->status + FAR_ANSWER_AT);
-    if (hipGetLastError() != hipSuccess || !read_words(h->device, s, h->status + FAR_ANSWER_AT, got, 2) || got[1] * 100 < got[0] * FAR_LINES_PERCENT) return false;
+    if (!far_read(got, h->status + FAR_ANSWER_AT, 2, s) || got[1] * 100 < got[0] * FAR_LINES_PERCENT) return false;
     const size_t counts_bytes = align256(size_t(f.groups) * f.blocks * 2), starts_bytes = align256(size_t(f.groups) * f.blocks * 4), sums_bytes = align256(size_t(f.segments) * f.blocks * 4);
     const size_t range_bytes = align256(size_t(f.chunks) * (f.blocks + 1) * 4), base_bytes = align256((size_t(f.groups) + 1) * 4);
     plan.tables = far_alloc(counts_bytes + starts_bytes + sums_bytes + range_bytes + base_bytes + 256);
@@ -3601,8 +3541,8 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double fa
     hipLaunchKernelGGL(k_far_bases, dim3(uint32_t(f.chunks + 1)), dim3(SCAN_THREADS), 0, s, f, sums, range, base, totals);
     hipLaunchKernelGGL(k_far_starts, dim3(uint32_t(f.segments)), dim3(FAR_THREADS), 0, s, f, counts, sums, starts);
     uint32_t total[FAR_MAX_CHUNKS + 1], most = 0;
-    static_assert(sizeof(total) <= 256 && FAR_MAX_CHUNKS + 1 < REPORT_WORDS, "totals");
-    if (hipGetLastError() != hipSuccess || !read_words(h->device, s, totals, total, f.chunks + 1)) return false;
+    static_assert(sizeof(total) <= 256, "totals");
+    if (!far_read(total, totals, f.chunks + 1, s)) return false;
     plan.first[0] = 0;
     for (int c = 0; c < f.chunks; c++) {
         plan.first[c + 1] = plan.first[c] + total[c];

@@ -68,6 +68,20 @@ int main(void) {
     assert r.stdout.split() == ["64", "48"]
 
 
+def test_device_memory_is_all_that_the_library_allocates(lib):
+    """A conversion with a caller's workspace, csr5_status and the SpMV allocate nothing; what allocates for itself takes
+    device memory with hipMalloc.  So the library asks the runtime for no other kind of memory."""
+    import shutil
+    import subprocess
+    if not shutil.which("nm"):
+        pytest.skip("no nm")
+    r = subprocess.run(["nm", "-D", "--undefined-only", B.LIB_PATH], capture_output=True, text=True, stdin=subprocess.DEVNULL, timeout=60)
+    assert r.returncode == 0, r.stderr
+    names = {line.split()[-1].split("@")[0] for line in r.stdout.splitlines()}
+    taken = {n for n in names if n.startswith("hip") and re.search("Malloc|Alloc|HostRegister", n)}
+    assert taken == {"hipMalloc"}, taken
+
+
 def test_sigma_rule_matches_paper_shape(lib):
     # The library's rule is the four-way map of Section 3.2 with its own constants.
     # Recover them from its behaviour on a matrix large enough that the

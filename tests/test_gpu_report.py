@@ -1,5 +1,7 @@
-"""What a conversion that is waited for learns from the device: many threads at a time, more than there are places for
-it, each on a stream of its own and with a matrix of its own, good ones and bad ones; a conversion behind long work."""
+"""What a conversion that is waited for learns from the device: many threads at a time, each on a stream of its own and
+with a matrix of its own, good ones and bad ones; a conversion behind long work; the verdict after an error that the
+caller's own HIP call left behind."""
+import ctypes
 import threading
 
 import numpy as np
@@ -55,7 +57,7 @@ def test_many_threads():
 
 
 def test_behind_long_work():
-    """Longer than the host looks for the report by itself."""
+    """Milliseconds of products that the conversion waits for."""
     m, n, row_ptr, col = _matrix(0)
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
@@ -76,4 +78,19 @@ def test_behind_long_work():
         B.csr5_spmv_ex(h, x, y, stream=stream)
         stream.synchronize()
         assert np.array_equal(y.cpu().numpy(), np.diff(row_ptr).astype(np.float64))
+        B.csr5_free(h)
+
+
+def test_status_beside_an_error_of_the_caller():
+    """A call of the program's own that failed on this thread (a device that does not exist) is not the library's error."""
+    m, n, row_ptr, col = _matrix(0)
+    rp, c, v = (torch.from_numpy(t).cuda() for t in (row_ptr, col, np.ones(col.size)))
+    h = B.csr5_convert_ex(m, n, col.size, rp, c, v)
+    hip = ctypes.CDLL(B.LIB_PATH)                                # (the HIP runtime that the library is linked to)
+    try:
+        for _ in range(40):
+            assert hip.hipSetDevice(1 << 20) != 0
+            assert B.csr5_status(h) & 3 == 0
+    finally:
+        hip.hipGetLastError()
         B.csr5_free(h)
