@@ -122,7 +122,7 @@ size_t csr5_workspace_bytes(int32_t m, int32_t nnz, int32_t sigma);
  *
  * For a matrix with many columns anywhere in a large x (see csr5_spmv) a conversion that blocks and
  * allocates for itself also allocates 8 bytes per such entry, 6 bytes per 8192 entries of the matrix and
- * 128 KiB of x, and four buffers for the values of x, of up to 256 MiB each (more where they are more
+ * 128 KiB of x, and a buffer for the values of x, of up to 256 MiB (more where they are more
  * than 8 GiB), if that is no more than an eighth of the memory that is free.
  *
  * csr5_convert picks sigma itself, allocates with hipMalloc, runs on the default
@@ -183,7 +183,9 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * these gathered into a buffer by a kernel of its own before the tile kernel: two
  * kernels, and a third for the sums where the band has it; larger matrices in
  * several such pairs.  The lists for it are made by the conversion, which takes about twice
- * as long, and pay for that within 8 products.
+ * as long, and pay for that within 8 products.  Such a handle's products take turns on the device,
+ * whatever their streams and however many are in flight.  One that is captured, and may be replayed beside
+ * others, uses no buffer: it is the SpMV that the matrix has without it.
  * Which of these, and whether rows without nonzeros need
  * their zeros written, is in the conversion's status word: the library launches
  * only what the matrix needs once the host has seen that word (csr5_convert and

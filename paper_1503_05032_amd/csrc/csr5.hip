@@ -10,6 +10,7 @@
 
 #include <atomic>
 #include <cstdint>
+#include <mutex>
 #include <new>
 #include <type_traits>
 
@@ -1376,7 +1377,7 @@ struct FlagWord {
 // 40^3 stencil 6.82 -> 6.38, 100^3 stencil 60.9 -> 59.6, single precision 45.3 ->
 // 44.2, 20 000 rows with dense ones 7.2 -> 6.85; matrices bound by their gathers
 // 0-1 %.
-constexpr int DPP_SHIFT_DOWN = 0x100, DPP_SHIFT_UP = 0x110, DPP_ROTATE = 0x120;
+constexpr int DPP_SHIFT_DOWN = 0x100, DPP_ROTATE = 0x120;
 template <int CTRL>
 __device__ __forceinline__ float from_row(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
@@ -2206,7 +2207,8 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 // us, single precision 1020 -> 470, 51 M 422 -> 256, 34 M 253 -> 171; rows of 0-20 columns out of 4 M
 // 690 -> 268, 582 -> 181.  Of the 691, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 545
 // the second: 175 for the lists and the buffer, 70 for the stores of y, 45 for the window.
-// The buffer is a handle's (one for each of its CARRY_SLOTS), of FAR_BUFFER_BYTES at most; a matrix
+// The buffer is a handle's, of FAR_BUFFER_BYTES at most; the handle's products take turns (launch_far), and a captured
+// one, which may be replayed beside any other, goes without (68 M entries 335.3 us, with the event between products 338.1).  A matrix
 // with more such entries goes through it in chunks of workgroups (136 M entries in 1, 2, 4, 8 chunks 717,
 // 709, 717, 789; 34 M in 1, 2, 4 187, 196, 219: a drained chip between any two kernels).
 // Tried: the buffer read past the caches (nt) 709 -> 808; written so 709 -> 712, single precision 472 ->
@@ -3137,15 +3139,17 @@ hipError_t launch_window(const Geom& g, int m, int n, int nnz, const int32_t* ro
 // What a handle keeps for k_far_gather and FORM_FAR
 struct FarPlan {
     void* tables;                          // hipMalloc'ed: base, range, and what the conversion counted
-    void* lists;                           // hipMalloc'ed: src, place, cols, CARRY_SLOTS buffers; NULL: no plan
+    void* lists;                           // hipMalloc'ed: src, place, cols, the buffer; NULL: no plan
     FarShape shape;
     const uint32_t* base;
     const uint32_t* range;                 // per chunk: where the blocks' lists begin
     const uint32_t* src;
     const uint16_t* place;
     const uint16_t* cols;                  // in its block, of the buffer's entries
-    char* values;
-    size_t values_bytes;                   // of one buffer
+    char* values;                          // the buffer
+    size_t values_bytes;
+    std::mutex turn;                       // held while a product is enqueued: they go through the buffer one after the other,
+    hipEvent_t done;                       // whatever their streams; behind the latest one's kernels
     int pieces;                            // workgroups per block
     uint32_t first[FAR_MAX_CHUNKS + 1];    // of a chunk, in cols
 };
@@ -3166,15 +3170,17 @@ inline bool far_pays(int64_t nnz, double far_share) {
     return FAR_COST + FAR_COST_PER_M * 1e-6 * double(nnz) <= FAR_PAYBACK * FAR_GAIN_PER_M * 1e-6 * double(nnz) * far_share;
 }
 
+// The caller holds plan.turn.
 template <int SIGMA, typename VT>
-hipError_t launch_far(const FarPlan& plan, int turn, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
+hipError_t launch_far(const FarPlan& plan, const Geom& g, int m, int n, int nnz, const int32_t* row_ptr, const uint32_t* tile_ptr, const uint32_t* tile_desc,
                       const int32_t* eop, const int32_t* eo, const int32_t* col_idx, const VT* val, const VT* x, VT* y, VT* carry,
                       uint64_t* meet, uint32_t* arrived, const uint32_t* tile_head, bool zero_rows, hipStream_t s) {
     constexpr int WAVES = WINDOW_WAVES, K = window_tiles(SIGMA);
     static_assert(WAVES * K * SIGMA * OMEGA == FAR_ENTRIES && WAVES * OMEGA == FAR_THREADS, "a workgroup's entries");
     const FarShape& f = plan.shape;
-    VT* const values = reinterpret_cast<VT*>(plan.values + size_t(turn) * plan.values_bytes);
-    for (int c = 0; c < f.chunks; c++) {
+    VT* const values = reinterpret_cast<VT*>(plan.values);
+    hipError_t e = hipStreamWaitEvent(s, plan.done, 0);
+    for (int c = 0; c < f.chunks && e == hipSuccess; c++) {
         hipLaunchKernelGGL(k_far_gather<VT>, dim3(uint32_t(f.blocks * plan.pieces)), dim3(FAR_GATHER_THREADS), 0, s, n, plan.pieces,
                            plan.range + size_t(c) * (f.blocks + 1), plan.cols + plan.first[c], x, values);
         const int first = far_chunk_segment(f, c) * FAR_SEGMENT, last = c + 1 < f.chunks ? far_chunk_segment(f, c + 1) * FAR_SEGMENT : f.groups;
@@ -3182,10 +3188,9 @@ hipError_t launch_far(const FarPlan& plan, int turn, const Geom& g, int m, int n
         hipLaunchKernelGGL((f.window_bytes ? k_spmv_staged<SIGMA, WAVES, K, FORM_FAR, VT> : k_spmv_staged<SIGMA, WAVES, K, FORM_ALL, VT>), dim3(uint32_t(last - first) + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc,
                            uint32_t(f.groups), has_tail, zero_rows ? 1u : 0u, f.window_bytes, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet,
                            arrived, tile_head, f.slope, FarEntries{first, last - first, plan.base, plan.src, plan.place, values, int(plan.values_bytes)});
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        e = hipGetLastError();
     }
-    return hipSuccess;
+    return e;
 }
 
 template <int SIGMA, bool BACK, typename VT>
@@ -3492,7 +3497,9 @@ static bool keep_back(int64_t nnz, size_t value_bytes) { return entry_bytes(nnz,
 static void far_release(csr5_handle_t h) {
     if (h->far.tables) (void)hipFree(h->far.tables);
     if (h->far.lists) (void)hipFree(h->far.lists);
+    if (h->far.done) (void)hipEventDestroy(h->far.done);
     h->far.tables = h->far.lists = nullptr;
+    h->far.done = nullptr;
 }
 static void* far_alloc(size_t bytes) {
     void* p = nullptr;
@@ -3551,9 +3558,13 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double fa
     const uint32_t all = total[f.chunks];
     const size_t src_bytes = align256(size_t(all) * 4), place_bytes = align256(size_t(all) * 2), cols_bytes = align256(size_t(plan.first[f.chunks]) * 2);
     plan.values_bytes = align256(size_t(most) * sizeof(VT));
-    const size_t bytes = src_bytes + place_bytes + cols_bytes + CARRY_SLOTS * plan.values_bytes;
+    const size_t bytes = src_bytes + place_bytes + cols_bytes + plan.values_bytes;
     size_t free_bytes = 0, device_bytes = 0;          // not where it would take what the program may want itself
     if (plan.values_bytes > size_t(1) << 30 || hipMemGetInfo(&free_bytes, &device_bytes) != hipSuccess || bytes > free_bytes / 8) return false;
+    if (hipEventCreateWithFlags(&plan.done, hipEventDisableTiming) != hipSuccess) {
+        plan.done = nullptr;
+        return false;
+    }
     plan.lists = far_alloc(bytes);
     if (!plan.lists) return false;
     at = static_cast<char*>(plan.lists);
@@ -3646,6 +3657,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
     h->staged = 0;
     h->window = h->pairs = false;
     h->far.tables = h->far.lists = nullptr;
+    h->far.done = nullptr;
     h->order = nullptr;
     h->order_second = h->order_len = 0;
     h->conv_stream = s;
@@ -3823,6 +3835,10 @@ int csr5_convert(int32_t m, int32_t n, int32_t nnz, const int32_t* row_ptr, int3
 // the fix-up.
 constexpr int LAUNCH_TILES = 1, LAUNCH_FIXUP = 2, LAUNCH_BOTH = 3;
 
+// Whether a product on the stream has far entries' x gathered into the handle's buffer.  Not one that is captured: its replays
+// cannot be ordered with the handle's other products.
+static bool gathered(csr5_handle_t h, hipStream_t s) { return h->far.lists && !may_be_captured(s); }
+
 template <typename VT, typename IT>
 static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, int which, void* carry_mem) {
     using tp_t = typename Index<IT>::tp_t;
@@ -3879,13 +3895,16 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
         }
     }
     // a window of x in LDS: one launch where the handle's slot has what that wants, otherwise two
-    bool window = false, window_one = false;
+    bool window = false, window_one = false, in_turn = false;
+    std::unique_lock<std::mutex> far_turn(h->far.turn, std::defer_lock);
     if constexpr (std::is_same<IT, int32_t>::value) {
-        const bool far = h->far.lists && !carry_mem;
+        const bool far = !carry_mem && gathered(h, s);
+        in_turn = far && (which & LAUNCH_TILES);
+        if (in_turn) far_turn.lock();
         window = h->window || far;
         window_one = window && h->span && !carry_mem;
-        if (far && (which & LAUNCH_TILES)) {
-#define FARRED(S) e = launch_far<S, VT>(h->far, int(turn), h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
+        if (in_turn) {
+#define FARRED(S) e = launch_far<S, VT>(h->far, h->g, h->m, h->n, int(h->nnz), row_ptr, tile_ptr, h->tile_desc, eop, h->eo, h->col_idx,            \
                                       static_cast<const VT*>(h->val), x, y, carry, window_one ? meet : nullptr, arrived, h->tile_head, zero_rows, s)
             if (h->g.sigma == RULE_R) FARRED(RULE_R);
             else FARRED(RULE_SIGMA_SMALL);
@@ -3911,7 +3930,10 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
 #undef X
 #undef ARGS
     }
-    if (e != hipSuccess) return CSR5_EHIP;
+    if (e != hipSuccess) {
+        if (in_turn) (void)hipStreamSynchronize(s);       // what was launched may use the buffer
+        return CSR5_EHIP;
+    }
     if ((which & LAUNCH_FIXUP) && (window ? !window_one : carries && !one) && h->g.p > 0) {
         int ntiles = h->g.p;                                  // one thread per tile
         size_t nb = (size_t(ntiles) + 255) / 256;
@@ -3919,6 +3941,8 @@ static int spmv_launch_it(csr5_handle_t h, const VT* x, VT* y, hipStream_t s, in
                            h->m, ntiles, tile_ptr, carry, y, h->status);
         if (hipGetLastError() != hipSuccess) return CSR5_EHIP;
     }
+    // (where the event cannot be recorded, the next product could not be made to wait: this one does)
+    if (in_turn && hipEventRecord(h->far.done, s) != hipSuccess && hipStreamSynchronize(s) != hipSuccess) return CSR5_EHIP;
     return CSR5_OK;
 }
 
@@ -4130,10 +4154,11 @@ int csr5_get_shape(csr5_handle_t h, int32_t* m, int32_t* n) {
 
 int csr5_get_form(csr5_handle_t h, void* hip_stream, int32_t* kernel, int32_t* wave_tiles, int32_t* plain) {
     if (!h || !h->in_csr5_order) return CSR5_EINVAL;
-    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (h->far.lists ? CSR5_KERNEL_GATHERED : (h->window ? CSR5_KERNEL_WINDOW : (h->pairs ? CSR5_KERNEL_PAIRS : CSR5_KERNEL_TILES)));
-    if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window || h->far.lists ? window_tiles(h->g.sigma) : 1);
+    const bool far = gathered(h, static_cast<hipStream_t>(hip_stream));
+    if (kernel) *kernel = h->staged ? CSR5_KERNEL_PARTS : (far ? CSR5_KERNEL_GATHERED : (h->window ? CSR5_KERNEL_WINDOW : (h->pairs ? CSR5_KERNEL_PAIRS : CSR5_KERNEL_TILES)));
+    if (wave_tiles) *wave_tiles = h->staged ? h->staged : (h->window || far ? window_tiles(h->g.sigma) : 1);
     if (plain)
-        *plain = !h->staged && !h->window && !h->far.lists && rule_sigma(h->g.sigma) &&
+        *plain = !h->staged && !h->window && !far && rule_sigma(h->g.sigma) &&
                  keep_product(h, h->carry_turn.load(std::memory_order_relaxed), latest(h->device), static_cast<hipStream_t>(hip_stream));
     return CSR5_OK;
 }
