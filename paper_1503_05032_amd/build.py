@@ -9,7 +9,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = [os.path.join(PKG, "csrc", "csr5.hip")]
-HEADERS = [os.path.join(PKG, "csrc", "row_share.h")]
+HEADERS = [os.path.join(PKG, "csrc", name) for name in ("row_share.h", "far_lists.h")]
 INC = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "libcsr5.so")
 

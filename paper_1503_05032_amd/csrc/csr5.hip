@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "csr5.h"
+#include "far_lists.h"
 #include "row_share.h"
 
 namespace {
@@ -2221,17 +2222,19 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 // sorts its entries by block in LDS and writes them to their places (k_far_place).  The order of
 // a workgroup's entries in a block is any; the sums do not depend on it.
 // ----------------------------------------------------------------------------
-constexpr int FAR_THREADS = 512, FAR_ENTRIES = 8192, FAR_PLACE_BITS = 13, FAR_AHEAD = 10, FAR_AHEAD_ALL = 16;
-constexpr int FAR_BLOCK_BYTES = 128 << 10, FAR_MAX_BLOCKS = 1024, FAR_SEGMENT = 64, FAR_MAX_CHUNKS = 32, FAR_PAD = 16;
-constexpr int64_t FAR_BUFFER_BYTES = 256 << 20;
+constexpr int FAR_THREADS = 512, FAR_PLACE_BITS = 13, FAR_AHEAD = 10, FAR_AHEAD_ALL = 16;
 template <typename VT> constexpr int far_block_shift() { return sizeof(VT) == 8 ? 14 : 15; }
 
 struct FarShape {
-    int pc, n, groups, blocks, segments, chunks;      // workgroups, blocks of x, FAR_SEGMENTs of workgroups, chunks of segments
+    int pc, n, groups, blocks, segments;              // workgroups, blocks of x, FAR_SEGMENTs of workgroups
     int window_bytes;                                 // 0: all entries go through the buffer
     float slope;
 };
-constexpr int far_chunk_segment(const FarShape& f, int chunk) { return int(int64_t(f.segments) * chunk / f.chunks); }
+// What the counts say: how many entries, and of each chunk how long its list is and which segment it ends before
+struct FarCounted {
+    uint32_t total, list[FAR_MAX_CHUNKS];
+    int32_t end[FAR_MAX_CHUNKS];
+};
 
 // Calls take(column, place) for the entries of a workgroup's tiles outside its window
 template <int SIGMA, typename VT, typename F>
@@ -2272,11 +2275,17 @@ k_far_count(const FarShape f, const uint32_t* __restrict__ tile_ptr, const int32
     if (threadIdx.x == 0) base[group] = all;
 }
 
-// sums over FAR_SEGMENT workgroups
-__global__ void __launch_bounds__(FAR_THREADS)
-k_far_segments(const FarShape f, const uint16_t* __restrict__ counts, uint32_t* __restrict__ sums) {
+// Sums over FAR_SEGMENT workgroups.  The last workgroup: where each group's list begins.
+__global__ void __launch_bounds__(SCAN_THREADS)
+k_far_segments(const FarShape f, const uint16_t* __restrict__ counts, uint32_t* __restrict__ sums, uint32_t* __restrict__ base, FarCounted* __restrict__ counted) {
+    if (int(blockIdx.x) == f.segments) {
+        uint32_t carry = 0;
+        for (int64_t at = 0; at < f.groups; at += SCAN_CHUNK) carry += scan_chunk<uint32_t>(base, at, f.groups, carry);
+        if (threadIdx.x == 0) base[f.groups] = counted->total = carry;
+        return;
+    }
     const int g0 = blockIdx.x * FAR_SEGMENT, g1 = g0 + FAR_SEGMENT < f.groups ? g0 + FAR_SEGMENT : f.groups;
-    for (int b = threadIdx.x; b < f.blocks; b += FAR_THREADS) {
+    for (int b = threadIdx.x; b < f.blocks; b += SCAN_THREADS) {
         uint32_t s = 0;
 #pragma unroll 16
         for (int g = g0; g < g1; g++) s += counts[size_t(g) * f.blocks + b];
@@ -2284,20 +2293,17 @@ k_far_segments(const FarShape f, const uint16_t* __restrict__ counts, uint32_t* 
     }
 }
 
-// Workgroup k < chunks: in the chunk's list, by block of x, where each segment's share begins (in place of its sum), and where each
-// block's does.  The last workgroup: where each group's list begins.
+// A workgroup per chunk: in the chunk's list, by block of x, where each segment's share begins (in place of its sum), and where each
+// block's does.
 __global__ void __launch_bounds__(SCAN_THREADS)
-k_far_bases(const FarShape f, uint32_t* __restrict__ sums, uint32_t* __restrict__ range, uint32_t* __restrict__ base, uint32_t* __restrict__ totals) {
+k_far_bases(const FarShape f, int value_bytes, uint32_t* __restrict__ sums, uint32_t* __restrict__ range, const uint32_t* __restrict__ base, FarCounted* __restrict__ counted) {
     static_assert(FAR_MAX_BLOCKS == SCAN_THREADS, "a thread per block");
-    if (int(blockIdx.x) == f.chunks) {
-        uint32_t carry = 0;
-        for (int64_t at = 0; at < f.groups; at += SCAN_CHUNK) carry += scan_chunk<uint32_t>(base, at, f.groups, carry);
-        if (threadIdx.x == 0) base[f.groups] = totals[f.chunks] = carry;
-        return;
-    }
+    const uint32_t total = counted->total;
+    const int chunk = blockIdx.x, chunks = far_chunks(total, value_bytes);
+    if (chunk >= chunks) return;
     __shared__ uint32_t wave_sum[SCAN_THREADS / OMEGA];
     const int lane = lane_id(), wave = threadIdx.x / OMEGA, b = threadIdx.x;
-    const int s0 = far_chunk_segment(f, blockIdx.x), s1 = far_chunk_segment(f, blockIdx.x + 1);
+    const int s0 = far_chunk_segment(base, f.segments, total, chunks, chunk), s1 = far_chunk_segment(base, f.segments, total, chunks, chunk + 1);
     uint32_t all = 0;
     if (b < f.blocks) {
 #pragma unroll 16
@@ -2315,9 +2321,12 @@ k_far_bases(const FarShape f, uint32_t* __restrict__ sums, uint32_t* __restrict_
     uint32_t before = 0;
     for (int w = 0; w < wave; w++) before += wave_sum[w];
     uint32_t at = before + incl - all;
-    uint32_t* const my_range = range + size_t(blockIdx.x) * (f.blocks + 1);
+    uint32_t* const my_range = range + size_t(chunk) * (f.blocks + 1);
     if (b < f.blocks) my_range[b] = at;
-    if (b == f.blocks - 1) my_range[f.blocks] = totals[blockIdx.x] = at + all;
+    if (b == f.blocks - 1) {
+        my_range[f.blocks] = counted->list[chunk] = at + all;
+        counted->end[chunk] = s1;
+    }
     if (b < f.blocks) {
 #pragma unroll 16
         for (int s = s0; s < s1; s++) {
@@ -2345,7 +2354,7 @@ k_far_starts(const FarShape f, const uint16_t* __restrict__ counts, const uint32
 template <int SIGMA, typename VT>
 __global__ void __launch_bounds__(FAR_THREADS)
 k_far_place(const FarShape f, const uint32_t* __restrict__ tile_ptr, const int32_t* __restrict__ col_idx, const uint16_t* __restrict__ counts,
-            const uint32_t* __restrict__ starts, const uint32_t* __restrict__ range, const uint32_t* __restrict__ base, uint32_t* __restrict__ src,
+            const uint32_t* __restrict__ starts, const FarCounted* __restrict__ counted, const uint32_t* __restrict__ base, uint32_t* __restrict__ src,
             uint16_t* __restrict__ place, uint16_t* __restrict__ cols) {
     __shared__ uint32_t next[FAR_MAX_BLOCKS], from[FAR_MAX_BLOCKS], entry[FAR_ENTRIES], wave_sum[FAR_THREADS / OMEGA];
     __shared__ uint16_t block_of[FAR_ENTRIES];
@@ -2353,9 +2362,8 @@ k_far_place(const FarShape f, const uint32_t* __restrict__ tile_ptr, const int32
     static_assert(FAR_PLACE_BITS + SHIFT <= 32 && (1 << FAR_PLACE_BITS) == FAR_ENTRIES, "place and column in a word");
     const int group = int(xcd_order(blockIdx.x, uint32_t(f.groups), 0)), segment = group / FAR_SEGMENT;
     const int lane = lane_id(), wave = threadIdx.x / OMEGA;
-    int chunk = 0;
     size_t first = 0;                                     // of the chunk's columns
-    while (far_chunk_segment(f, chunk + 1) <= segment) first += range[size_t(chunk++) * (f.blocks + 1) + f.blocks];
+    for (int chunk = 0; counted->end[chunk] <= segment; chunk++) first += counted->list[chunk];
     uint32_t n[EACH], at[EACH], s = 0;
 #pragma unroll
     for (int u = 0; u < EACH; u++) {
@@ -2411,10 +2419,9 @@ k_far_gather(int n, int pieces, const uint32_t* __restrict__ range, const uint16
     __shared__ __align__(16) char xs[FAR_BLOCK_BYTES];
     const int block = blockIdx.x / pieces, piece = blockIdx.x % pieces;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / OMEGA);
-    const uint32_t lo = range[block], hi = range[block + 1];
-    const uint32_t share = ((hi - lo) / uint32_t(pieces) + FAR_PAD) / FAR_PAD * FAR_PAD;
-    const uint32_t begin = lo + share * uint32_t(piece), end = begin + share < hi ? begin + share : hi;
-    if (begin >= end) return;
+    const FarPiece mine(range[block], range[block + 1], piece, pieces);
+    if (mine.empty()) return;
+    const uint32_t begin = mine.begin, end = mine.end;
     const auto list = tile_buffer(cols + begin, int((end - begin) * 2));
     uint32_t c[FAR_GATHER_AHEAD];
     const auto ask = [&](uint32_t k0) {
@@ -3151,7 +3158,9 @@ struct FarPlan {
     std::mutex turn;                       // held while a product is enqueued: they go through the buffer one after the other,
     hipEvent_t done;                       // whatever their streams; behind the latest one's kernels
     int pieces;                            // workgroups per block
-    uint32_t first[FAR_MAX_CHUNKS + 1];    // of a chunk, in cols
+    int chunks;
+    size_t first[FAR_MAX_CHUNKS + 1];      // of a chunk, in cols
+    int end[FAR_MAX_CHUNKS];               // the segment that it ends before
 };
 // In how many products the plan has to come back, in what it costs a conversion and csr5_free (us per million
 // entries, and in any case: allocation and release, and what waits for them) and gives a product (us per million entries further
@@ -3180,15 +3189,16 @@ hipError_t launch_far(const FarPlan& plan, const Geom& g, int m, int n, int nnz,
     const FarShape& f = plan.shape;
     VT* const values = reinterpret_cast<VT*>(plan.values);
     hipError_t e = hipStreamWaitEvent(s, plan.done, 0);
-    for (int c = 0; c < f.chunks && e == hipSuccess; c++) {
+    for (int c = 0, first = 0; c < plan.chunks && e == hipSuccess; c++) {
         hipLaunchKernelGGL(k_far_gather<VT>, dim3(uint32_t(f.blocks * plan.pieces)), dim3(FAR_GATHER_THREADS), 0, s, n, plan.pieces,
                            plan.range + size_t(c) * (f.blocks + 1), plan.cols + plan.first[c], x, values);
-        const int first = far_chunk_segment(f, c) * FAR_SEGMENT, last = c + 1 < f.chunks ? far_chunk_segment(f, c + 1) * FAR_SEGMENT : f.groups;
+        const int last = c + 1 < plan.chunks ? plan.end[c] * FAR_SEGMENT : f.groups;
         const uint32_t has_tail = c == 0 && g.p > g.pc ? 1u : 0u;
         hipLaunchKernelGGL((f.window_bytes ? k_spmv_staged<SIGMA, WAVES, K, FORM_FAR, VT> : k_spmv_staged<SIGMA, WAVES, K, FORM_ALL, VT>), dim3(uint32_t(last - first) + has_tail), dim3(WAVES * OMEGA), 0, s, m, n, nnz, g.pc,
                            uint32_t(f.groups), has_tail, zero_rows ? 1u : 0u, f.window_bytes, 1, row_ptr, tile_ptr, tile_desc, eop, eo, col_idx, val, x, y, carry, meet,
                            arrived, tile_head, f.slope, FarEntries{first, last - first, plan.base, plan.src, plan.place, values, int(plan.values_bytes)});
         e = hipGetLastError();
+        first = last;
     }
     return e;
 }
@@ -3514,53 +3524,53 @@ static bool far_read(T* to, const T* from, int count, hipStream_t s) {
 }
 // Whether the plan is made; what was launched for it may still run if it is not.
 template <int SIGMA, typename VT>
-static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double far_share) {
+static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes) {
     FarPlan& plan = h->far;
     FarShape& f = plan.shape;
-    const int64_t x_bytes = int64_t(h->n) * int64_t(sizeof(VT)), want_chunks = int64_t(double(h->nnz) * far_share * sizeof(VT)) / FAR_BUFFER_BYTES + 1;
+    const int64_t x_bytes = int64_t(h->n) * int64_t(sizeof(VT));
     constexpr int tiles = FAR_ENTRIES / (SIGMA * OMEGA);
     f.pc = h->g.pc;
     f.n = h->n;
     f.groups = (h->g.pc + tiles - 1) / tiles;
     f.blocks = int((x_bytes + FAR_BLOCK_BYTES - 1) / FAR_BLOCK_BYTES);
     f.segments = (f.groups + FAR_SEGMENT - 1) / FAR_SEGMENT;
-    f.chunks = int(want_chunks < f.segments ? want_chunks : f.segments);
-    if (f.chunks > FAR_MAX_CHUNKS) f.chunks = FAR_MAX_CHUNKS;
     f.window_bytes = window_bytes;
     f.slope = float(h->n) / float(h->m);
     const uint32_t* const tile_ptr = static_cast<const uint32_t*>(h->tile_ptr);
     uint32_t got[2];
     hipLaunchKernelGGL((k_far_sample<SIGMA, VT>), dim3(1), dim3(SCAN_THREADS), 0, s, f, tile_ptr, h->col_idx, h->status + FAR_ANSWER_AT);
     if (!far_read(got, h->status + FAR_ANSWER_AT, 2, s) || got[1] * 100 < got[0] * FAR_LINES_PERCENT) return false;
+    const int most_chunks = far_chunks(uint32_t(h->nnz), sizeof(VT));
     const size_t counts_bytes = align256(size_t(f.groups) * f.blocks * 2), starts_bytes = align256(size_t(f.groups) * f.blocks * 4), sums_bytes = align256(size_t(f.segments) * f.blocks * 4);
-    const size_t range_bytes = align256(size_t(f.chunks) * (f.blocks + 1) * 4), base_bytes = align256((size_t(f.groups) + 1) * 4);
-    plan.tables = far_alloc(counts_bytes + starts_bytes + sums_bytes + range_bytes + base_bytes + 256);
+    const size_t range_bytes = align256(size_t(most_chunks) * (f.blocks + 1) * 4), base_bytes = align256((size_t(f.groups) + 1) * 4), counted_bytes = align256(sizeof(FarCounted));
+    plan.tables = far_alloc(counts_bytes + starts_bytes + sums_bytes + range_bytes + base_bytes + counted_bytes);
     if (!plan.tables) return false;
     char* at = static_cast<char*>(plan.tables);
-    uint32_t* const totals = reinterpret_cast<uint32_t*>(at);
-    uint32_t* const base = reinterpret_cast<uint32_t*>(at += 256);
+    FarCounted* const counted = reinterpret_cast<FarCounted*>(at);
+    uint32_t* const base = reinterpret_cast<uint32_t*>(at += counted_bytes);
     uint32_t* const range = reinterpret_cast<uint32_t*>(at += base_bytes);
     uint32_t* const sums = reinterpret_cast<uint32_t*>(at += range_bytes);
     uint32_t* const starts = reinterpret_cast<uint32_t*>(at += sums_bytes);
     uint16_t* const counts = reinterpret_cast<uint16_t*>(at += starts_bytes);
     hipLaunchKernelGGL((k_far_count<SIGMA, VT>), dim3(uint32_t(f.groups)), dim3(FAR_THREADS), 0, s, f, tile_ptr, h->col_idx, counts, base);
-    hipLaunchKernelGGL(k_far_segments, dim3(uint32_t(f.segments)), dim3(FAR_THREADS), 0, s, f, counts, sums);
-    hipLaunchKernelGGL(k_far_bases, dim3(uint32_t(f.chunks + 1)), dim3(SCAN_THREADS), 0, s, f, sums, range, base, totals);
+    hipLaunchKernelGGL(k_far_segments, dim3(uint32_t(f.segments + 1)), dim3(SCAN_THREADS), 0, s, f, counts, sums, base, counted);
+    hipLaunchKernelGGL(k_far_bases, dim3(uint32_t(most_chunks)), dim3(SCAN_THREADS), 0, s, f, int(sizeof(VT)), sums, range, base, counted);
     hipLaunchKernelGGL(k_far_starts, dim3(uint32_t(f.segments)), dim3(FAR_THREADS), 0, s, f, counts, sums, starts);
-    uint32_t total[FAR_MAX_CHUNKS + 1], most = 0;
-    static_assert(sizeof(total) <= 256, "totals");
-    if (!far_read(total, totals, f.chunks + 1, s)) return false;
+    FarCounted c;
+    if (!far_read(&c, counted, 1, s)) return false;
+    plan.chunks = far_chunks(c.total, sizeof(VT));
     plan.first[0] = 0;
-    for (int c = 0; c < f.chunks; c++) {
-        plan.first[c + 1] = plan.first[c] + total[c];
-        if (total[c] > most) most = total[c];
+    uint32_t most = 0;
+    for (int k = 0; k < plan.chunks; k++) {
+        plan.first[k + 1] = plan.first[k] + c.list[k];
+        plan.end[k] = c.end[k];
+        if (c.list[k] > most) most = c.list[k];
     }
-    const uint32_t all = total[f.chunks];
-    const size_t src_bytes = align256(size_t(all) * 4), place_bytes = align256(size_t(all) * 2), cols_bytes = align256(size_t(plan.first[f.chunks]) * 2);
+    const size_t src_bytes = align256(size_t(c.total) * 4), place_bytes = align256(size_t(c.total) * 2), cols_bytes = align256(plan.first[plan.chunks] * 2);
     plan.values_bytes = align256(size_t(most) * sizeof(VT));
     const size_t bytes = src_bytes + place_bytes + cols_bytes + plan.values_bytes;
     size_t free_bytes = 0, device_bytes = 0;          // not where it would take what the program may want itself
-    if (plan.values_bytes > size_t(1) << 30 || hipMemGetInfo(&free_bytes, &device_bytes) != hipSuccess || bytes > free_bytes / 8) return false;
+    if (plan.values_bytes > size_t(FAR_BUFFER_BYTES) || hipMemGetInfo(&free_bytes, &device_bytes) != hipSuccess || bytes > free_bytes / 8) return false;
     if (hipEventCreateWithFlags(&plan.done, hipEventDisableTiming) != hipSuccess) {
         plan.done = nullptr;
         return false;
@@ -3578,7 +3588,7 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double fa
     plan.place = place;
     plan.cols = cols;
     plan.pieces = STAGE_CUS / f.blocks > 1 ? STAGE_CUS / f.blocks : 1;
-    hipLaunchKernelGGL((k_far_place<SIGMA, VT>), dim3(uint32_t(f.groups)), dim3(FAR_THREADS), 0, s, f, tile_ptr, h->col_idx, counts, starts, range, base, src, place, cols);
+    hipLaunchKernelGGL((k_far_place<SIGMA, VT>), dim3(uint32_t(f.groups)), dim3(FAR_THREADS), 0, s, f, tile_ptr, h->col_idx, counts, starts, counted, base, src, place, cols);
     return hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
 }
 // near, far, spread: of `samples` entries, see WindowJob
@@ -3588,8 +3598,7 @@ static void far_plan(csr5_handle_t h, hipStream_t s, uint32_t samples, uint32_t 
     if (x_bytes > int64_t(FAR_BLOCK_BYTES) * FAR_MAX_BLOCKS || spread * 100 < samples / (2 * OMEGA) * FAR_SPREAD_PERCENT ||
         !far_pays(h->nnz, double(far) / samples)) return;
     const int window = near * 100 >= samples * FAR_WINDOW_PERCENT ? WINDOW_BYTES : 0;
-    const double share = window ? double(samples - near) / samples : 1.0;
-    if (h->g.sigma == RULE_R ? far_make<RULE_R, VT>(h, s, window, share) : far_make<RULE_SIGMA_SMALL, VT>(h, s, window, share)) return;
+    if (h->g.sigma == RULE_R ? far_make<RULE_R, VT>(h, s, window) : far_make<RULE_SIGMA_SMALL, VT>(h, s, window)) return;
     (void)hipGetLastError();
     (void)hipStreamSynchronize(s);         // before the memory goes
     far_release(h);

@@ -17,9 +17,10 @@ pytestmark = pytest.mark.gpu
 BLOCK = 128 * 1024 // 8        # entries of x in a block
 
 
-def _far(m, n, lo, hi, near, uneven=False, seed=0):
+def _far(m, n, lo, hi, near, uneven=False, seed=0, banded_from=1.0):
     """Rows of lo to hi entries, a share `near` of them within +-4000 columns of the diagonal, the others anywhere;
-    uneven: a tenth of the rows empty, one in the middle and the last one long."""
+    uneven: a tenth of the rows empty, one in the middle and the last one long; banded_from: from that share of the rows on
+    all are near."""
     g = torch.Generator(device="cuda:0")
     g.manual_seed(seed)
     lens = torch.randint(lo, hi + 1, (m,), generator=g, device="cuda:0")
@@ -29,7 +30,7 @@ def _far(m, n, lo, hi, near, uneven=False, seed=0):
     rows = torch.repeat_interleave(torch.arange(m, device="cuda:0"), lens)
     col = torch.randint(0, n, rows.shape, generator=g, device="cuda:0")
     band = (rows * n // m + torch.randint(-4000, 4001, rows.shape, generator=g, device="cuda:0")).clamp_(0, n - 1)
-    col = torch.where(torch.rand(rows.shape, generator=g, device="cuda:0") < near, band, col)
+    col = torch.where((torch.rand(rows.shape, generator=g, device="cuda:0") < near) | (rows >= banded_from * m), band, col)
     col[0], col[-1] = 0, n - 1
     col = (torch.sort(rows * n + col).values - rows * n).int()                  # (columns may repeat)
     row_ptr = torch.zeros(m + 1, dtype=torch.int64, device="cuda:0")
@@ -105,6 +106,28 @@ def test_against_sums_in_double_precision(m, n, lo, hi, near, sigma, single):
         y.fill_(float("nan"))
         (B.csr5s_spmv_ex if single else B.csr5_spmv_ex)(h, x, y)
         assert bool(((y.double() - want).abs() <= rel * scale + tiny).all()), call
+    B.csr5_free(h)
+
+
+def test_far_entries_in_a_part_of_the_rows():
+    """64 M far entries among the first four fifths of the rows, in two chunks: the buffer is no larger than what it may be."""
+    a = _far(5_000_000, 4_000_001, 15, 25, 0.2, seed=8, banded_from=0.8)
+    d = DeviceCsr(a)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    h = B.csr5_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, d.val)
+    held = before - torch.cuda.mem_get_info()[0]
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
+    far, blocks = 0.64 * a.nnz, -(-a.n // BLOCK)
+    assert held <= B.csr5_workspace_bytes(a.m, a.nnz) + 8 * far * 1.01 + 6 * (a.nnz / 8192) * blocks * 1.05 + (256 << 20) + (16 << 20), held
+    B.csr5_spmv_ex(h, d.x, d.y)
+    first = d.y.clone()
+    B.csr5_to_csr(h)
+    products = d.val * d.x[d.col_idx.long()]
+    want = torch.segment_reduce(products, "sum", offsets=d.row_ptr.long(), initial=0)
+    scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)
+    assert bool(((first - want).abs() <= 1e-12 * scale + 1e-300).all())
     B.csr5_free(h)
 
 
