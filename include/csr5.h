@@ -121,9 +121,9 @@ size_t csr5_workspace_bytes(int32_t m, int32_t nnz, int32_t sigma);
  *               empty_offset with its per-tile start array.
  *
  * For a matrix with many columns anywhere in a large x (see csr5_spmv) a conversion that blocks and
- * allocates for itself also allocates 8 bytes per such entry, 6 bytes per 8192 entries of the matrix and
- * 128 KiB of x, and a buffer for the values of x, of up to 256 MiB, if that is no more than an
- * eighth of the memory that is free.
+ * allocates for itself also allocates 8 bytes per such entry and a buffer for the values of x, of up to
+ * 256 MiB, which the handle keeps, and, until it returns, 6 bytes per 8192 entries of the matrix and 128 KiB of x;
+ * if all of that is no more than an eighth of the memory that is free.
  *
  * csr5_convert picks sigma itself, allocates with hipMalloc, runs on the default
  * stream and waits for the conversion's device-side checks of the input

@@ -3145,8 +3145,8 @@ hipError_t launch_window(const Geom& g, int m, int n, int nnz, const int32_t* ro
 
 // What a handle keeps for k_far_gather and FORM_FAR
 struct FarPlan {
-    void* tables;                          // hipMalloc'ed: base, range, and what the conversion counted
-    void* lists;                           // hipMalloc'ed: src, place, cols, the buffer; NULL: no plan
+    void* tables;                          // hipMalloc'ed: what the conversion counts; released before it returns
+    void* lists;                           // hipMalloc'ed: base, range, src, place, cols, the buffer; NULL: no plan
     FarShape shape;
     const uint32_t* base;
     const uint32_t* range;                 // per chunk: where the blocks' lists begin
@@ -3524,7 +3524,7 @@ static bool far_read(T* to, const T* from, int count, hipStream_t s) {
 }
 // Whether the plan is made; what was launched for it may still run if it is not.
 template <int SIGMA, typename VT>
-static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes) {
+static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes, double far_share) {
     FarPlan& plan = h->far;
     FarShape& f = plan.shape;
     const int64_t x_bytes = int64_t(h->n) * int64_t(sizeof(VT));
@@ -3543,7 +3543,12 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes) {
     const int most_chunks = far_chunks(uint32_t(h->nnz), sizeof(VT));
     const size_t counts_bytes = align256(size_t(f.groups) * f.blocks * 2), starts_bytes = align256(size_t(f.groups) * f.blocks * 4), sums_bytes = align256(size_t(f.segments) * f.blocks * 4);
     const size_t range_bytes = align256(size_t(most_chunks) * (f.blocks + 1) * 4), base_bytes = align256((size_t(f.groups) + 1) * 4), counted_bytes = align256(sizeof(FarCounted));
-    plan.tables = far_alloc(counts_bytes + starts_bytes + sums_bytes + range_bytes + base_bytes + counted_bytes);
+    const size_t tables_bytes = counts_bytes + starts_bytes + sums_bytes + range_bytes + base_bytes + counted_bytes;
+    // not where it would take what the program may want itself: by what the sample says first, and by the counts
+    size_t free_bytes = 0, device_bytes = 0;
+    const double want = double(h->nnz) * far_share, want_buffer = want * sizeof(VT) < double(FAR_BUFFER_BYTES) ? want * sizeof(VT) : double(FAR_BUFFER_BYTES);
+    if (hipMemGetInfo(&free_bytes, &device_bytes) != hipSuccess || tables_bytes + size_t(want * 8 + want_buffer) > free_bytes / 8) return false;
+    plan.tables = far_alloc(tables_bytes);
     if (!plan.tables) return false;
     char* at = static_cast<char*>(plan.tables);
     FarCounted* const counted = reinterpret_cast<FarCounted*>(at);
@@ -3568,9 +3573,8 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes) {
     }
     const size_t src_bytes = align256(size_t(c.total) * 4), place_bytes = align256(size_t(c.total) * 2), cols_bytes = align256(plan.first[plan.chunks] * 2);
     plan.values_bytes = align256(size_t(most) * sizeof(VT));
-    const size_t bytes = src_bytes + place_bytes + cols_bytes + plan.values_bytes;
-    size_t free_bytes = 0, device_bytes = 0;          // not where it would take what the program may want itself
-    if (plan.values_bytes > size_t(FAR_BUFFER_BYTES) || hipMemGetInfo(&free_bytes, &device_bytes) != hipSuccess || bytes > free_bytes / 8) return false;
+    const size_t bytes = base_bytes + range_bytes + src_bytes + place_bytes + cols_bytes + plan.values_bytes;
+    if (plan.values_bytes > size_t(FAR_BUFFER_BYTES) || tables_bytes + bytes > free_bytes / 8) return false;
     if (hipEventCreateWithFlags(&plan.done, hipEventDisableTiming) != hipSuccess) {
         plan.done = nullptr;
         return false;
@@ -3578,18 +3582,22 @@ static bool far_make(csr5_handle_t h, hipStream_t s, int window_bytes) {
     plan.lists = far_alloc(bytes);
     if (!plan.lists) return false;
     at = static_cast<char*>(plan.lists);
-    uint32_t* const src = reinterpret_cast<uint32_t*>(at);
+    plan.base = reinterpret_cast<uint32_t*>(at);
+    plan.range = reinterpret_cast<uint32_t*>(at += base_bytes);
+    uint32_t* const src = reinterpret_cast<uint32_t*>(at += range_bytes);
     uint16_t* const place = reinterpret_cast<uint16_t*>(at += src_bytes);
     uint16_t* const cols = reinterpret_cast<uint16_t*>(at += place_bytes);
     plan.values = at + cols_bytes;
-    plan.base = base;
-    plan.range = range;
     plan.src = src;
     plan.place = place;
     plan.cols = cols;
     plan.pieces = STAGE_CUS / f.blocks > 1 ? STAGE_CUS / f.blocks : 1;
     hipLaunchKernelGGL((k_far_place<SIGMA, VT>), dim3(uint32_t(f.groups)), dim3(FAR_THREADS), 0, s, f, tile_ptr, h->col_idx, counts, starts, counted, base, src, place, cols);
-    return hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
+    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(plan.lists, base, base_bytes + range_bytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess) return false;
+    (void)hipFree(plan.tables);
+    plan.tables = nullptr;
+    return true;
 }
 // near, far, spread: of `samples` entries, see WindowJob
 template <typename VT>
@@ -3598,7 +3606,8 @@ static void far_plan(csr5_handle_t h, hipStream_t s, uint32_t samples, uint32_t 
     if (x_bytes > int64_t(FAR_BLOCK_BYTES) * FAR_MAX_BLOCKS || spread * 100 < samples / (2 * OMEGA) * FAR_SPREAD_PERCENT ||
         !far_pays(h->nnz, double(far) / samples)) return;
     const int window = near * 100 >= samples * FAR_WINDOW_PERCENT ? WINDOW_BYTES : 0;
-    if (h->g.sigma == RULE_R ? far_make<RULE_R, VT>(h, s, window) : far_make<RULE_SIGMA_SMALL, VT>(h, s, window)) return;
+    const double share = window ? double(samples - near) / samples : 1.0;
+    if (h->g.sigma == RULE_R ? far_make<RULE_R, VT>(h, s, window, share) : far_make<RULE_SIGMA_SMALL, VT>(h, s, window, share)) return;
     (void)hipGetLastError();
     (void)hipStreamSynchronize(s);         // before the memory goes
     far_release(h);

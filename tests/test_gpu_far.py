@@ -119,8 +119,8 @@ def test_far_entries_in_a_part_of_the_rows():
     h = B.csr5_convert_ex(a.m, a.n, a.nnz, d.row_ptr, d.col_idx, d.val)
     held = before - torch.cuda.mem_get_info()[0]
     assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
-    far, blocks = 0.64 * a.nnz, -(-a.n // BLOCK)
-    assert held <= B.csr5_workspace_bytes(a.m, a.nnz) + 8 * far * 1.01 + 6 * (a.nnz / 8192) * blocks * 1.05 + (256 << 20) + (16 << 20), held
+    # workspace, lists and buffer, and not the 20 MB that the conversion counts in (the driver hands out 2 MB at a time)
+    assert held <= B.csr5_workspace_bytes(a.m, a.nnz) + 8 * 0.64 * a.nnz * 1.01 + (256 << 20) + (8 << 20), held
     B.csr5_spmv_ex(h, d.x, d.y)
     first = d.y.clone()
     B.csr5_to_csr(h)
@@ -129,6 +129,51 @@ def test_far_entries_in_a_part_of_the_rows():
     scale = torch.segment_reduce(products.abs(), "sum", offsets=d.row_ptr.long(), initial=0)
     assert bool(((first - want).abs() <= 1e-12 * scale + 1e-300).all())
     B.csr5_free(h)
+
+
+def test_left_alone_where_memory_is_short():
+    """Lists and buffer of 190 MB, 1.2 GB free: more than an eighth of it.  Nothing beyond the workspace is held."""
+    a = _far(600_000, 200 * BLOCK, 15, 25, 0.0, seed=2)
+    d = DeviceCsr(a)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    fill = []
+    for _ in range(2):                             # (what is free after a large allocation is more than was left)
+        fill.append(torch.empty(torch.cuda.mem_get_info()[0] - (1200 << 20), dtype=torch.uint8, device="cuda:0"))
+    before = torch.cuda.mem_get_info()[0]
+    assert before <= 1250 << 20, before
+    for _ in range(3):
+        h = convert(d, use_workspace=False)
+        held = before - torch.cuda.mem_get_info()[0]
+        assert B.csr5_get_form(h)["kernel"] != B.CSR5_KERNEL_GATHERED
+        assert held <= B.csr5_workspace_bytes(a.m, a.nnz) + (8 << 20), held
+        check_spmv(d, h, "short")
+        B.csr5_to_csr(h)
+        B.csr5_free(h)
+    del fill
+    torch.cuda.empty_cache()
+    h = convert(d, use_workspace=False)
+    assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
+    check_spmv(d, h, "enough")
+    B.csr5_free(h)
+
+
+def test_release_with_a_product_in_flight():
+    """csr5_free waits for the device before the buffer goes: the product that was enqueued is whole."""
+    a = _far(600_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=6)
+    d = DeviceCsr(a)
+    stream, col, val = torch.cuda.Stream(), d.col_idx.clone(), d.val.clone()
+    for _ in range(3):
+        d.col_idx.copy_(col)
+        d.val.copy_(val)
+        d.y.fill_(float("nan"))
+        h = convert(d, use_workspace=False)
+        assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
+        for _ in range(3):
+            B.csr5_spmv_ex(h, d.x, d.y, stream=stream)
+        B.csr5_free(h)
+        y, (want, s) = d.y.cpu().numpy(), oracle.csr_spmv(a.m, a.row_ptr, a.col_idx, a.val, a.x)
+        assert np.all(np.abs(y - want) <= 1e-12 * s + 1e-300)
 
 
 def test_products_in_flight_on_four_streams_and_other_vectors():
