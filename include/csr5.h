@@ -179,11 +179,12 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * 32768 tiles (csr5_get_form tells).
  * After csr5_convert, or a csr5_convert_ex (csr5s_convert_ex) that blocks and allocates for
  * itself, at the automatic sigma or 8 or 16, a matrix many of whose columns are anywhere in an x
- * larger than the L2s (some 10 million such entries and more, x of up to 128 MiB) has the x of
+ * larger than the L2s (some 15 million such entries and more, x of up to 128 MiB) has the x of
  * these gathered into a buffer by a kernel of its own before the tile kernel: two
  * kernels, and a third for the sums where the band has it; larger matrices in
  * several such pairs.  The lists for it are made by the conversion, which takes about twice
- * as long, and pay for that within 8 products.  Such a handle's products take turns on the device,
+ * as long with its release (0.5 ms and 3 us per million entries more) and comes back after 1.4 to 4 products: a program that
+ * converts for fewer, for instance anew for every product, brings a workspace and pays nothing.  Such a handle's products take turns on the device,
  * whatever their streams and however many are in flight.  One that is captured, and may be replayed beside
  * others, uses no buffer: it is the SpMV that the matrix has without it.
  * Which of these, and whether rows without nonzeros need

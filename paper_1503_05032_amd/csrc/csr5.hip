@@ -3163,12 +3163,13 @@ struct FarPlan {
     int end[FAR_MAX_CHUNKS];               // the segment that it ends before
 };
 // In how many products the plan has to come back, in what it costs a conversion and csr5_free (us per million
-// entries, and in any case: allocation and release, and what waits for them) and gives a product (us per million entries further
-// from their window than an L2 reaches).  Conversion and free longer by, product before -> after: mixed in double precision
-// 25.6 M entries 634, 177 -> 134 (not taken); 34 M 639, 263 -> 173; 51 M 780, 422 -> 261; 136 M 1458, 1211 -> 710; single precision 34 M 658,
-// 176 -> 126 (not taken); 68 M 881, 469 -> 236; random columns out of 1 M, 15 M entries 422, 160 -> 114 (not taken), out of 4 M, 40 M
-// entries 575, 690 -> 326.
-constexpr double FAR_PAYBACK = 8, FAR_COST = 400, FAR_COST_PER_M = 8, FAR_GAIN_PER_M = 8.5;
+// entries, and in any case: allocation, release and waits, most of it the release of more than 64 MB) and gives a product (us per million
+// entries further from their window than an L2 reaches).  Conversion and free longer by, product before -> after, hence back after so many
+// products: mixed in double precision 34 M entries 510, 254 -> 170, 6 (not taken); 51 M 560, 408 -> 246, 3.5; 68 M 640, 568 -> 333, 2.7;
+// 136 M 880, 1184 -> 688, 1.8; single precision 51 M 570, 315 -> 184, 4.4; 68 M 620, 455 -> 235, 2.8; 136 M 850, 1027 -> 463, 1.5; random
+// columns out of 2 M, 30 M entries 560, 438 -> 190, 2.2; out of 4 M, 40 M 580, 682 -> 257, 1.4; single precision 585, 564 -> 166, 1.5.
+// How many products follow is not known here; whoever makes fewer brings a workspace.
+constexpr double FAR_PAYBACK = 4, FAR_COST = 450, FAR_COST_PER_M = 3.2, FAR_GAIN_PER_M = 8.5;
 // Lines, of 100 entries far away (random columns 95-99, power-law ones 23-32; columns that all together are on fewer lines are in
 // the caches), and tiles that spread them, of 100 (random 85-100; power-law columns and rows as long as several tiles 17).
 constexpr uint32_t FAR_LINES_PERCENT = 85, FAR_SPREAD_PERCENT = 75;

@@ -40,16 +40,16 @@ def _far(m, n, lo, hi, near, uneven=False, seed=0, banded_from=1.0):
                   x=rng.uniform(-1, 1, n), name=f"far{m}x{n}")
 
 
-@pytest.mark.parametrize("m,n,lo,hi,near,sigma,uneven", [
-    (600_000, 200 * BLOCK, 15, 25, 0.0, 0, False),             # whole blocks, no window, height 8
-    (600_001, 200 * BLOCK + 1, 15, 25, 0.0, 0, True),
-    (400_000, 300 * BLOCK - 1, 60, 100, 0.5, 16, True),       # a window; height 16, one kernel for the sums
-    (5_000_000, 200 * BLOCK + 17, 1, 6, 0.1, 0, True),        # tall
-    (30_001, 8_000_001, 600, 800, 0.45, 16, True),             # wide, rows longer than half a tile, a window
-    (900_000, 250 * BLOCK + 5, 30, 40, 0.45, 8, True),        # a window; more than 32768 tiles: a kernel more
-    (900_000, 250 * BLOCK + 5, 18, 26, 0.15, 8, True),        # the same without
-    (700_000, 1024 * BLOCK, 15, 25, 0.0, 0, False)])           # the largest x
-def test_parity(m, n, lo, hi, near, sigma, uneven):
+@pytest.mark.parametrize("m,n,lo,hi,near,sigma,uneven,one", [
+    (820_000, 600 * BLOCK, 15, 25, 0.0, 8, False, True),       # whole blocks, no window, height 8
+    (1_100_001, 200 * BLOCK + 1, 15, 25, 0.0, 0, True, True),
+    (440_000, 300 * BLOCK - 1, 60, 100, 0.4, 16, True, True), # a window; height 16, one kernel for the sums
+    (7_500_000, 200 * BLOCK + 17, 1, 6, 0.1, 0, True, True),  # tall
+    (50_001, 8_000_001, 600, 800, 0.4, 16, True, True),        # wide, rows longer than half a tile, a window
+    (1_300_000, 250 * BLOCK + 5, 30, 40, 0.45, 8, True, False),       # a window; more than 32768 tiles: a kernel more
+    (1_300_000, 250 * BLOCK + 5, 18, 26, 0.15, 8, True, False),       # the same without
+    (900_000, 1024 * BLOCK, 15, 25, 0.0, 0, False, True)])     # the largest x
+def test_parity(m, n, lo, hi, near, sigma, uneven, one):
     a = _far(m, n, lo, hi, near, uneven, seed=m % 97)
     print("far", m, n, lo, hi, near, sigma, uneven, a.nnz, flush=True)
     d = DeviceCsr(a)
@@ -57,8 +57,7 @@ def test_parity(m, n, lo, hi, near, sigma, uneven):
     check_format(d, h, a.name)
     info, first = B.csr5_get_info(h), None
     assert B.csr5_get_form(h) == {"kernel": B.CSR5_KERNEL_GATHERED, "wave_tiles": 2 if info["sigma"] == 8 else 1, "plain": 0}
-    one = info["p"] <= 32768
-    assert one == (sigma != 8), info["p"]
+    assert one == (info["p"] <= 32768) and info["sigma"] == (sigma or 16), info
     whole_tiles = info["p_complete"] * 64 * info["sigma"]
     fixed = int(np.searchsorted(a.row_ptr, whole_tiles, side="right")) - 1      # rows in the incomplete tile are added in any order
     for call in range(6):                          # every one of the handle's buffers
@@ -85,7 +84,7 @@ def test_parity(m, n, lo, hi, near, sigma, uneven):
 
 
 @pytest.mark.parametrize("m,n,lo,hi,near,sigma,single", [
-    (700_000, 2 * 260 * BLOCK + 1, 15, 25, 0.0, 0, True), (700_000, 2 * 260 * BLOCK - 1, 30, 50, 0.45, 16, True),
+    (1_100_000, 2 * 260 * BLOCK + 1, 15, 25, 0.0, 0, True), (1_100_000, 2 * 260 * BLOCK - 1, 30, 50, 0.45, 16, True),
     (3_000_000, 4_000_001, 25, 35, 0.45, 0, False),            # 45 M entries through the buffer, in two chunks
     (3_000_000, 4_000_001, 10, 20, 0.1, 0, False),             # 37 M entries through the buffer, in two chunks
     (3_000_000, 6_000_001, 20, 30, 0.05, 0, True)])             # 68 M, two chunks
@@ -132,8 +131,8 @@ def test_far_entries_in_a_part_of_the_rows():
 
 
 def test_left_alone_where_memory_is_short():
-    """Lists and buffer of 190 MB, 1.2 GB free: more than an eighth of it.  Nothing beyond the workspace is held."""
-    a = _far(600_000, 200 * BLOCK, 15, 25, 0.0, seed=2)
+    """Lists and buffer of 350 MB, 1.2 GB free: more than an eighth of it.  Nothing beyond the workspace is held."""
+    a = _far(1_100_000, 200 * BLOCK, 15, 25, 0.0, seed=2)
     d = DeviceCsr(a)
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
@@ -160,7 +159,7 @@ def test_left_alone_where_memory_is_short():
 
 def test_release_with_a_product_in_flight():
     """csr5_free waits for the device before the buffer goes: the product that was enqueued is whole."""
-    a = _far(600_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=6)
+    a = _far(1_100_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=6)
     d = DeviceCsr(a)
     stream, col, val = torch.cuda.Stream(), d.col_idx.clone(), d.val.clone()
     for _ in range(3):
@@ -177,7 +176,7 @@ def test_release_with_a_product_in_flight():
 
 
 def test_products_in_flight_on_four_streams_and_other_vectors():
-    a = _far(600_001, 200 * BLOCK + 1, 45, 55, 0.45, True, seed=3)
+    a = _far(700_001, 200 * BLOCK + 1, 45, 55, 0.36, True, seed=3)
     d = DeviceCsr(a)
     h = convert(d, use_workspace=False)
     assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
@@ -200,7 +199,7 @@ def test_products_in_flight_on_four_streams_and_other_vectors():
 
 
 def test_graph_replays():
-    a = _far(600_001, 200 * BLOCK + 1, 25, 35, 0.2, True, seed=9)
+    a = _far(900_001, 200 * BLOCK + 1, 25, 35, 0.2, True, seed=9)
     d = DeviceCsr(a)
     h = convert(d, use_workspace=False)
     assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
@@ -227,7 +226,7 @@ def test_graph_replays():
 def test_more_products_in_flight_than_buffers_and_replays_beside_them():
     """Twelve products of one handle on six streams, each with an x of its own, and two graphs that are replayed beside
     them: no row is longer than a tile, so neither a product nor a replay needs anything of the handle to itself."""
-    a = _far(600_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=6)
+    a = _far(1_100_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=6)
     d = DeviceCsr(a)
     h = convert(d, use_workspace=False)
     assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
@@ -271,7 +270,7 @@ def test_more_products_in_flight_than_buffers_and_replays_beside_them():
 
 
 def test_nan_and_infinities_of_x_reach_their_rows_only():
-    a = _far(600_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=4)
+    a = _far(1_100_001, 200 * BLOCK + 1, 15, 25, 0.1, seed=4)
     d = DeviceCsr(a)
     h = convert(d, use_workspace=False)
     assert B.csr5_get_form(h)["kernel"] == B.CSR5_KERNEL_GATHERED
@@ -287,11 +286,12 @@ def test_nan_and_infinities_of_x_reach_their_rows_only():
     B.csr5_free(h)
 
 
-@pytest.mark.parametrize("n,how", [(200 * BLOCK, "workspace"), (200 * BLOCK, "not waited for"), (200 * BLOCK, "two kernels"),
-                                   (200_000, "small x"), (1024 * BLOCK + 1, "largest x")])
-def test_left_alone(n, how):
-    """What a conversion that enqueues only, brings its memory or fixes the form gets, and x that caches hold or that has too many blocks."""
-    a = _far(600_000, n, 15, 25, 0.0, seed=2)
+@pytest.mark.parametrize("m,n,how", [(1_100_000, 200 * BLOCK, "workspace"), (1_100_000, 200 * BLOCK, "not waited for"), (1_100_000, 200 * BLOCK, "two kernels"),
+                                     (1_100_000, 200_000, "small x"), (1_100_000, 1024 * BLOCK + 1, "largest x"), (600_000, 200 * BLOCK, "few entries")])
+def test_left_alone(m, n, how):
+    """What a conversion that enqueues only, brings its memory or fixes the form gets, x that caches hold or that has too many
+    blocks, and entries that would not pay for the lists in four products."""
+    a = _far(m, n, 15, 25, 0.0, seed=2)
     d = DeviceCsr(a)
     flags = {"not waited for": B.CSR5_FLAG_NO_HOST_CHECK, "two kernels": B.CSR5_FLAG_AUX_TWO_KERNELS}.get(how, B.CSR5_FLAG_NONE)
     h = convert(d, use_workspace=how == "workspace", flags=flags)
@@ -305,7 +305,7 @@ def test_columns_that_few_lines_hold_are_left_alone():
     g = np.random.default_rng(7)
     for kind in ("power law", "band", "long rows"):
         n = 200 * BLOCK
-        m, length = (5000, 2400) if kind == "long rows" else (600_000, 20)
+        m, length = (9000, 2400) if kind == "long rows" else (1_100_000, 20)
         rows = np.repeat(np.arange(m, dtype=np.int64), length)
         if kind == "power law":
             col = g.permutation(n)[np.minimum(g.zipf(1.5, rows.size) - 1, n - 1)]
