@@ -311,7 +311,10 @@ int csr5_get_shape(csr5_handle_t h, int32_t *m, int32_t *n);
  *                 CSR5_KERNEL_GATHERED the same, or no part of x, with the other entries' x gathered
  *                                    into a buffer by a kernel before it
  *                 CSR5_KERNEL_PAIRS  the tile kernel in its one-kernel form for single precision, with
- *                                    neighbouring columns gathered two at a time
+ *                                    neighbouring columns gathered two at a time: runs of columns, after
+ *                                    a conversion that blocks, at sigma 8 or 16 and 6400 complete tiles and
+ *                                    more, x of 80 KiB to 1 GiB
+ *                 On a stream that is being captured CSR5_KERNEL_GATHERED is never the answer.
  *   wave_tiles    tiles of a wavefront (1 for CSR5_KERNEL_TILES)
  *   plain         1: col_idx, val and the descriptors would be read with plain loads, 0: with
  *                 non-temporal ones (a hint to the caches, the result is the same)

@@ -1695,7 +1695,7 @@ __device__ __forceinline__ uint32_t walk_columns(typename FlagWord<SIGMA>::type 
 // Tried: three and four entries at a time (44.3, 45.4 on the 100^3 stencil: more registers, and 12 and 16
 // bytes a lane to bring back); pairs at any place, not only from even lanes: the same; in double precision
 // (16 bytes) 60.3 -> 71.7; either way in one kernel, decided per tile: 44.0 (98 registers instead of 79).
-constexpr size_t PAIR_MAX_X_BYTES = 0x7fffff00, PAIR_NOWHERE = 0x7ffffff0;       // outside of any x
+constexpr int PAIR_NOWHERE = 0x7ffffff0;                          // outside of any x
 constexpr int DPP_QUAD_EVEN = 0xa0;                               // lanes 0, 0, 2, 2 of every four
 template <int COUNT>
 __device__ __forceinline__ void gather_pairs(const float* x, int x_bytes, const int32_t* c, float* xv) {
@@ -1707,7 +1707,7 @@ __device__ __forceinline__ void gather_pairs(const float* x, int x_bytes, const 
     for (int k = 0; k < COUNT; k++) {
         // (in this form: the difference of the two came out with its sign changed)
         second[k] = __builtin_amdgcn_update_dpp(0, c[k], DPP_QUAD_EVEN, 0xf, 0xf, true) + 1 == c[k];
-        got[k] = __builtin_bit_cast(pair_t, __builtin_amdgcn_raw_buffer_load_b64(xbuf, second[k] ? int(PAIR_NOWHERE) : c[k] * 4, 0, 0));
+        got[k] = __builtin_bit_cast(pair_t, __builtin_amdgcn_raw_buffer_load_b64(xbuf, second[k] ? PAIR_NOWHERE : c[k] * 4, 0, 0));
     }
 #pragma unroll
     for (int k = 0; k < COUNT; k++) {
@@ -3013,10 +3013,11 @@ k_stream_floor(int m, int pc, int sigma, int W, uint32_t nb_tiles, uint32_t xcd_
 // Whether the entries' x is gathered in pairs (gather_pairs), by a sample of neighbouring entries: of 100 of them, how many are
 // one column on (blocks of 2 to 8 columns 50-87, 27-point stencil 67, 9-point 67, 5-point 40, all of which gain; 7-point 29, which
 // gains 2 %; a star of 25 32, which loses 3 %), and how many a line of x and more (those 60-13; tridiagonal and five
-// diagonals 0, which lose 5-7 %).
+// diagonals 0, which lose 5-7 %).  The sample is the window form's, so that matrices without it (window_fits: fewer than
+// WINDOW_MIN_TILES tiles, other heights, an x below 80 KB or above WINDOW_MAX_X_BYTES) keep the gathers one by one.
 constexpr uint32_t PAIR_NEXT_PERCENT = 36, PAIR_AWAY_PERCENT = 12;
-inline bool pairs_pay(int n, uint32_t sampled, uint32_t next, uint32_t away) {
-    return sampled && size_t(n) * sizeof(float) <= PAIR_MAX_X_BYTES && next * 100 >= sampled * PAIR_NEXT_PERCENT && away * 100 >= sampled * PAIR_AWAY_PERCENT;
+inline bool pairs_pay(uint32_t sampled, uint32_t next, uint32_t away) {
+    return sampled && next * 100 >= sampled * PAIR_NEXT_PERCENT && away * 100 >= sampled * PAIR_AWAY_PERCENT;
 }
 
 template <int SIGMA, typename VT, typename IT, int MODE>
@@ -3111,12 +3112,14 @@ hipError_t launch_staged(const Geom& g, int m, int n, int nnz, const int32_t* ro
 //  * Tiles: below WINDOW_MIN_TILES of them some CUs have two workgroups and most have one
 //    (mixed, 2.5 M entries 17.6 -> 18.0, 3.1 M 20.8 -> 21.3, 3.9 M 26.0 -> 22.9).
 constexpr int WINDOW_WAVES = 8, WINDOW_MIN_TILES = 6400;
+constexpr int64_t WINDOW_MAX_X_BYTES = 1 << 30;
+static_assert(WINDOW_MAX_X_BYTES <= PAIR_NOWHERE, "gather_pairs");
 constexpr uint32_t WINDOW_NEAR_PERCENT = 50, WINDOW_LINES_PERCENT = 70;
 static_assert((WINDOW_WAVES & (WINDOW_WAVES - 1)) == 0, "window_sampled");
 constexpr int window_tiles(int sigma) { return sigma == RULE_SIGMA_SMALL ? 2 : 1; }       // per wavefront
 inline bool window_fits(const Geom& g, int n, size_t value_bytes) {
     const int64_t x_bytes = int64_t(n) * int64_t(value_bytes);
-    return rule_sigma(g.sigma) && g.pc >= WINDOW_MIN_TILES && x_bytes >= WINDOW_BYTES && x_bytes <= (1 << 30);
+    return rule_sigma(g.sigma) && g.pc >= WINDOW_MIN_TILES && x_bytes >= WINDOW_BYTES && x_bytes <= WINDOW_MAX_X_BYTES;
 }
 inline bool window_pays(uint32_t samples, uint32_t near, uint32_t lines) {
     return near * 100 >= samples * WINDOW_NEAR_PERCENT && lines * 100 >= near * WINDOW_LINES_PERCENT;
@@ -3171,7 +3174,9 @@ struct FarPlan {
 // How many products follow is not known here; whoever makes fewer brings a workspace.
 constexpr double FAR_PAYBACK = 4, FAR_COST = 450, FAR_COST_PER_M = 3.2, FAR_GAIN_PER_M = 8.5;
 // Lines, of 100 entries far away (random columns 95-99, power-law ones 23-32; columns that all together are on fewer lines are in
-// the caches), and tiles that spread them, of 100 (random 85-100; power-law columns and rows as long as several tiles 17).
+// the caches), and tiles that spread them, of 100 (random 85-100; power-law columns and rows as long as several tiles 17).  Random
+// ones over an x of 8 MB do not reach that: tiles at its ends have no 4 MB to spread over (2 M columns in single precision are
+// left alone at 292 us a product, with the buffer 154).
 constexpr uint32_t FAR_LINES_PERCENT = 85, FAR_SPREAD_PERCENT = 75;
 // Near ones, of 100, for the window and the columns to be loaded.  48 M entries, a share near the diagonal, with the window
 // and without: 0.1 356, 306 us; 0.3 326, 320; 0.4 269, 326; single precision 253, 205; 223, 204; 194, 203.
@@ -3802,7 +3807,7 @@ static int convert_impl(int32_t m, int32_t n, IT nnz, const IT* row_ptr, int32_t
                 far_plan<VT>(h, s, samples, near, got[WINDOW_ANSWER_AT + 1] >> 16, got[WINDOW_ANSWER_AT + 1] & 0xffffu);
             // (the instantiation with the look-behind only)
             h->pairs = rc == CSR5_OK && sizeof(VT) == 4 && h->last_col && !(got[0] & STATUS_NEEDS_CARRY) && !h->staged && !h->window && !h->far.lists &&
-                       pairs_pay(n, samples / 2, got[WINDOW_ANSWER_AT + 2] >> 16, got[WINDOW_ANSWER_AT + 2] & 0xffffu);
+                       pairs_pay(samples / 2, got[WINDOW_ANSWER_AT + 2] >> 16, got[WINDOW_ANSWER_AT + 2] & 0xffffu);
         }
         if (rc == CSR5_OK && (got[0] & BAD_BITS)) {
             (void)csr5_to_csr(h, hip_stream);

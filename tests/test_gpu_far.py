@@ -105,6 +105,11 @@ def test_against_sums_in_double_precision(m, n, lo, hi, near, sigma, single):
         y.fill_(float("nan"))
         (B.csr5s_spmv_ex if single else B.csr5_spmv_ex)(h, x, y)
         assert bool(((y.double() - want).abs() <= rel * scale + tiny).all()), call
+    odd = torch.empty(a.n + 1, dtype=x.dtype, device="cuda:0")                  # x at an address that is no multiple of 16
+    odd[1:] = x
+    y.fill_(float("nan"))
+    (B.csr5s_spmv_ex if single else B.csr5_spmv_ex)(h, odd[1:], y)
+    assert bool(((y.double() - want).abs() <= rel * scale + tiny).all()), "odd"
     B.csr5_free(h)
 
 
