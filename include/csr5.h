@@ -183,7 +183,7 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * these gathered into a buffer by a kernel of its own before the tile kernel: two
  * kernels, and a third for the sums where the band has it; larger matrices in
  * several such pairs.  The lists for it are made by the conversion, which takes about twice
- * as long with its release (0.5 ms and 3 us per million entries more) and comes back after 1.4 to 4 products: a program that
+ * as long with its release (0.5 ms and 3 us per million entries more) and comes back after 1.3 to 4 products: a program that
  * converts for fewer, for instance anew for every product, brings a workspace and pays nothing.  Such a handle's products take turns on the device,
  * whatever their streams and however many are in flight.  One that is captured, and may be replayed beside
  * others, uses no buffer: it is the SpMV that the matrix has without it.
@@ -200,7 +200,9 @@ int csr5_convert_ex(int32_t m, int32_t n, int32_t nnz, const int32_t *row_ptr, i
  * bits may differ between runs.  The one-kernel forms add in a fixed order, and so
  * does the second kernel of a matrix that is taken by column where it would be one
  * kernel otherwise.  The handle holds four auxiliary arrays, taken in turn by successive calls: up to four SpMVs on ONE handle may be in flight at
- * the same time (on different streams); a fifth must be ordered after the first.
+ * the same time (on different streams); a fifth must be ordered after the first.  A call that is captured keeps the
+ * array that it took: its replays are ordered with the handle's other calls by the caller, unless the SpMV
+ * needs no such array (the first of the two ways above).
  */
 int csr5_spmv(csr5_handle_t h, const double *x, double *y);
 int csr5_spmv_ex(csr5_handle_t h, const double *x, double *y, void *hip_stream);

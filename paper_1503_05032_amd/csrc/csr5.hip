@@ -2204,9 +2204,9 @@ __device__ __forceinline__ void to_lds_4(__amdgpu_buffer_rsrc_t r, char* lds, in
 //     the diagonal have taken theirs from the window there; from LDS every lane picks its own.
 // Where few entries are near the diagonal all of them go that way, and the tile kernel reads no columns
 // (FORM_ALL).  22 to 40 bytes an entry instead of 128 and more.  Whole SpMV, before -> after:
-// mixed (four fifths of the rows within +-5000 columns, the others anywhere) 136 M entries 1185 -> 691
-// us, single precision 1020 -> 470, 51 M 422 -> 256, 34 M 253 -> 171; rows of 0-20 columns out of 4 M
-// 690 -> 268, 582 -> 181.  Of the 691, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 545
+// mixed (four fifths of the rows within +-5000 columns, the others anywhere) 136 M entries 1187 -> 688
+// us, single precision 1020 -> 464, 51 M 405 -> 247; rows of 0-20 columns out of 4 M
+// 682 -> 258, 554 -> 167.  Of the 688, 147 are the first kernel (0.66 GB, 4.5 TB/s: stores), 540
 // the second: 175 for the lists and the buffer, 70 for the stores of y, 45 for the window.
 // The buffer is a handle's, of FAR_BUFFER_BYTES at most; the handle's products take turns (launch_far), and a captured
 // one, which may be replayed beside any other, goes without (68 M entries 335.3 us, with the event between products 338.1).  A matrix
@@ -3168,9 +3168,10 @@ struct FarPlan {
 // In how many products the plan has to come back, in what it costs a conversion and csr5_free (us per million
 // entries, and in any case: allocation, release and waits, most of it the release of more than 64 MB) and gives a product (us per million
 // entries further from their window than an L2 reaches).  Conversion and free longer by, product before -> after, hence back after so many
-// products: mixed in double precision 34 M entries 510, 254 -> 170, 6 (not taken); 51 M 560, 408 -> 246, 3.5; 68 M 640, 568 -> 333, 2.7;
-// 136 M 880, 1184 -> 688, 1.8; single precision 51 M 570, 315 -> 184, 4.4; 68 M 620, 455 -> 235, 2.8; 136 M 850, 1027 -> 463, 1.5; random
-// columns out of 2 M, 30 M entries 560, 438 -> 190, 2.2; out of 4 M, 40 M 580, 682 -> 257, 1.4; single precision 585, 564 -> 166, 1.5.
+// products: mixed in double precision 34 M entries 540, 253 -> 170, 6.5 (not taken); 51 M 573, 405 -> 247, 3.6; 68 M 617, 556 -> 332, 2.8;
+// 136 M 778, 1187 -> 688, 1.6; single precision 51 M 570, 313 -> 184, 4.4 (not taken); 68 M 614, 451 -> 234, 2.8; 136 M 764, 1020 -> 464, 1.4;
+// random columns out of 3.3 M, 18 M entries 486, 297 -> 123, 2.8; out of 2 M, 30 M 531, 430 -> 191, 2.2; out of 4 M, 40 M 561, 682 -> 258, 1.3;
+// single precision 555, 554 -> 167, 1.4.
 // How many products follow is not known here; whoever makes fewer brings a workspace.
 constexpr double FAR_PAYBACK = 4, FAR_COST = 450, FAR_COST_PER_M = 3.2, FAR_GAIN_PER_M = 8.5;
 // Lines, of 100 entries far away (random columns 95-99, power-law ones 23-32; columns that all together are on fewer lines are in
