@@ -143,7 +143,7 @@ def test_left_alone_where_memory_is_short():
     torch.cuda.empty_cache()
     fill = []
     for _ in range(2):                             # (what is free after a large allocation is more than was left)
-        fill.append(torch.empty(torch.cuda.mem_get_info()[0] - (1200 << 20), dtype=torch.uint8, device="cuda:0"))
+        fill.append(torch.empty(max(torch.cuda.mem_get_info()[0] - (1200 << 20), 1 << 20), dtype=torch.uint8, device="cuda:0"))
     before = torch.cuda.mem_get_info()[0]
     assert before <= 1250 << 20, before
     for _ in range(3):
